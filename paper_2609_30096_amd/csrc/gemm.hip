@@ -2,13 +2,14 @@
 //
 // A is the activation matrix [M tokens, K] and W a linear weight [N, K]
 // (both K-contiguous).  The bfloat16 kernel runs on CDNA4 matrix cores
-// (v_mfma_f32_32x32x16_bf16) with the weight tile as the MFMA "A" operand and
+// (v_mfma_f32_16x16x32_bf16) with the weight tile as the MFMA "A" operand and
 // the token tile as the "B" operand, so each lane's accumulators hold one
-// token and runs of four consecutive output features; the epilogue then
-// writes 8- or 16-byte vectors.  Epilogues fuse the bias, the tanh GELU of
-// the MLP, and the adaLN gate with the float32 residual update; one variant
-// stores the output transposed per batch (V^T for attention) through LDS.
+// token and runs of consecutive output features; the epilogue then writes
+// 16-byte vectors.  Epilogues fuse the bias, the tanh GELU of the MLP, and the
+// adaLN gate with the float32 residual update; one variant swaps the operands
+// and stores the output transposed per batch (V^T for attention).
 #include <cstdlib>
+#include <type_traits>
 
 #include "common.h"
 #include "kernels.h"
@@ -236,23 +237,31 @@ __global__ __launch_bounds__(256) void gemm_bf16_kernel(const bf16_t* __restrict
 // One workgroup per CU loops over the 256 x 256 output tiles p, p + G, p + 2G,
 // ... (p the XCD-remapped block index, G the grid), so the copy pipeline runs
 // on from one tile into the next and a tile's epilogue overlaps the loads of
-// the next tile's first slab.
+// the next tile's first slabs.  Four waves in a 2 x 2 grid own 128 x 128 each as
+// 8 x 8 blocks of v_mfma_f32_16x16x32_bf16.
 //
 // K-slabs of 64 (128-byte rows) travel global -> LDS through a 2-slot ring
 // with buffer_load ... lds (16 bytes per lane, lane-contiguous in LDS); a
-// buffer resource per tile makes rows past M read as zero.  A slab's barrier
-// sits before its last 16-deep step: by then every wave holds that step's
-// fragments and the next slab has landed, so the last step's MFMAs run while
-// the next slab's first fragments are read, and the slot just released is
-// refilled.  The 16 loads a wave issues for slab g + 1 go out one per two
-// MFMAs during the last step of slab g - 1 and the first step of slab g, in
-// program order (sched_barrier), so the load unit never holds a wave's MFMA
-// stream for long and each slab has two steps to land; the fragments of the
-// next step are read one per MFMA the same way.  LDS rows carry a 32-byte-granular XOR
-// swizzle applied on the global side: lane pairs keep contiguous 32-byte
-// pieces of a row, which the load path coalesces better than a 16-byte
-// permutation, at the cost of 2-way bank conflicts on fragment reads.
-__device__ __forceinline__ int lds_swz32(int row) { return ((row & 7) ^ ((row >> 3) & 1)) & ~1; }
+// buffer resource per tile makes rows past M read as zero.  A slab is two
+// 32-deep steps of 64 MFMAs.  The fragments of a step are read one per MFMA
+// during the step before it, into the other half of a register double buffer,
+// so a slab's last reads are over a third of the way into it: its one barrier
+// sits there, after which the slot is refilled with slab g + 2 (one copy per
+// PK_DPM MFMAs, in program order; 3 or 4 stalls the wave behind the load unit,
+// 2-8% slower) while two thirds of slab g are still to be multiplied.  LDS rows carry a
+// 32-byte-granular XOR swizzle applied on the global side: no bank conflicts on
+// the 16-row fragment reads, and lane pairs keep contiguous 32-byte pieces of a
+// row, which the load path coalesces better than a 16-byte permutation (3% slower).
+//
+// The 16x16x32 shape moves half the accumulator bytes of 32x32x16 per FLOP, and
+// the chip's clock under matrix work is set by its power: a stream of it holds
+// 2040-2060 TFLOP/s on N(0,1) operands where 32x32x16 holds 1830, and this
+// kernel ran 7-9% faster with it at every Wan projection (14B q/k 5.02 -> 4.57
+// ms, 1378 -> 1505 TFLOP/s; 1.3B q/k 0.541 -> 0.493).  What bounds it now
+// (s_memtime copy, 14B q/k): 2470 of the 2048 cycles per slab the MFMAs need,
+// 140 of the excess the copies' issue waiting on L2 misses, 10 k cycles of
+// output stores per tile (220 k).
+__device__ __forceinline__ int lds_swz16(int row) { return ((row & 7) ^ ((row >> 3) & 1)) & ~1; }
 
 typedef __attribute__((address_space(3))) void* lds_ptr_t;
 
@@ -266,183 +275,148 @@ __device__ __forceinline__ void wait_vmcnt() {
 
 __device__ __forceinline__ void wait_lgkm0() { __builtin_amdgcn_s_waitcnt((15 << 0) | (3 << 14) | (7 << 4) | (0 << 8)); }
 
-// Epilogue of a tile with bfloat16 output (bias, bias + GELU).  Every bias
-// value is loaded before the first store (a load issued after a store would
-// wait for it), and lanes l and l + 32, which hold features +0..3 and +4..7
-// of the same token, trade halves with permlane32_swap so that each lane
-// stores 16 contiguous bytes.
-template <int EPI, int FI, int TI>
-__device__ __forceinline__ void epilogue_bf16(const EpiArgs& e, const f32x16 (&acc)[FI][TI], int64_t M,
-                                              int64_t m_base, int n_base, int fhalf) {
-  const bf16_t* __restrict__ bias_p = (const bf16_t*)e.bias;
-  u32x2 bias[FI][4];
+constexpr int PK_F = 8;     // 16-row fragments per wave and operand
+constexpr int PK_RS = 2;    // MFMAs per fragment read
+constexpr int PK_BAR = 40;  // the slab's barrier follows MFMA 40 of its first step
+constexpr int PK_DPM = 5;   // MFMAs per copy
+
+// The MFMA "A" operand's rows (features; tokens in the transposed-output
+// kernel) sit permuted in LDS, within every 32 rows: row 16 h + 4 q + j holds
+// row 8 q + 4 h + j.  A lane's accumulators of the fragment pair 2 p, 2 p + 1
+// (rows 4 q + j of each) are then 8 consecutive rows 32 p + 8 q + 0..7: whole
+// 16-byte bf16 stores without a lane exchange.
+//
+// Epilogue of a tile with bfloat16 output (bias, bias + GELU): the lane holds
+// tokens m_base + 16 y and features n_base + 32 p + 0..7.  Every bias value is
+// loaded before the first store (a load issued after a store would wait for
+// it).  Token blocks outermost: the 64-byte pieces of a token row's 128-byte
+// line are stored back to back, so the L2 holds whole lines when it writes
+// them back (feature blocks outermost left lines half written long enough to be
+// evicted and written twice: 20% more HBM writes).
+template <int EPI>
+__device__ __forceinline__ void epilogue_bf16(const EpiArgs& e, const f32x4 (&acc)[PK_F][PK_F], int64_t M,
+                                              int64_t m_base, int n_base) {
+  const bf16_t* __restrict__ bias_p = (const bf16_t*)e.bias + n_base;
+  u32x2 bias[PK_F / 2][2];
 #pragma unroll
-  for (int fi = 0; fi < FI; ++fi)
+  for (int p = 0; p < PK_F / 2; ++p)
 #pragma unroll
-    for (int g = 0; g < 4; ++g) bias[fi][g] = *(const u32x2*)(bias_p + n_base + fi * 32 + 8 * g);
-  // Token blocks outermost: the two 32-feature blocks that share a token
-  // row's 128-byte line are stored back to back, so the L2 holds whole lines
-  // when it writes them back (feature blocks outermost left lines half
-  // written long enough to be evicted and written twice: 20% more HBM writes).
+    for (int h = 0; h < 2; ++h) bias[p][h] = *(const u32x2*)(bias_p + 32 * p + 4 * h);
 #pragma unroll
-  for (int ti = 0; ti < TI; ++ti) {
+  for (int y = 0; y < PK_F; ++y) {
+    const int64_t m = m_base + y * 16;
+    bf16_t* __restrict__ orow = (bf16_t*)e.out + m * e.ldo + n_base;
 #pragma unroll
-    for (int fi = 0; fi < FI; ++fi) {
-      const int64_t m = m_base + ti * 32;
-      u32x2 pk[4];
+    for (int p = 0; p < PK_F / 2; ++p) {
+      u32x4 pk;
 #pragma unroll
-      for (int g = 0; g < 4; ++g) {
-        const u32x2 bv = bias[fi][g];
+      for (int h = 0; h < 2; ++h) {
+        const u32x2 bv = bias[p][h];
+        const f32x4& c = acc[2 * p + h][y];
         float v[4];
-        v[0] = acc[fi][ti][4 * g + 0] + __uint_as_float(bv[0] << 16);
-        v[1] = acc[fi][ti][4 * g + 1] + __uint_as_float(bv[0] & 0xffff0000u);
-        v[2] = acc[fi][ti][4 * g + 2] + __uint_as_float(bv[1] << 16);
-        v[3] = acc[fi][ti][4 * g + 3] + __uint_as_float(bv[1] & 0xffff0000u);
+        v[0] = c[0] + __uint_as_float(bv[0] << 16);
+        v[1] = c[1] + __uint_as_float(bv[0] & 0xffff0000u);
+        v[2] = c[2] + __uint_as_float(bv[1] << 16);
+        v[3] = c[3] + __uint_as_float(bv[1] & 0xffff0000u);
         if constexpr (EPI == TRACK_EPI_BIAS_GELU) {
 #pragma unroll
           for (int j = 0; j < 4; ++j) v[j] = gelu_tanh(v[j]);
         }
-        pk[g][0] = pack_bf2(v[0], v[1]);
-        pk[g][1] = pack_bf2(v[2], v[3]);
+        pk[2 * h] = pack_bf2(v[0], v[1]);
+        pk[2 * h + 1] = pack_bf2(v[2], v[3]);
       }
-      bf16_t* __restrict__ orow = (bf16_t*)e.out + m * e.ldo + n_base - 4 * fhalf + fi * 32;
-#pragma unroll
-      for (int gp = 0; gp < 2; ++gp) {
-        // lanes < 32 keep group 2gp (own +0..3, partner's +4..7), lanes >= 32
-        // group 2gp + 1 (partner's +0..3, own +4..7)
-        const auto s0 = __builtin_amdgcn_permlane32_swap(pk[2 * gp][0], pk[2 * gp + 1][0], false, false);
-        const auto s1 = __builtin_amdgcn_permlane32_swap(pk[2 * gp][1], pk[2 * gp + 1][1], false, false);
-        const u32x4 q = {s0[0], s1[0], s0[1], s1[1]};
-        if (m < M) *(u32x4*)(orow + 8 * (2 * gp + fhalf)) = q;
-      }
+      if (m < M) *(u32x4*)(orow + 32 * p) = pk;
     }
   }
 }
 
 // Epilogue of a tile with float32 output (gated residual, residual, plain).
-// The bias, gate and residual values of feature block fi + 1 are loaded
-// before the stores of block fi are issued, so no load waits behind a store
-// of the same tile.
-template <int EPI, int FI, int TI>
-__device__ __forceinline__ void epilogue_f32(const EpiArgs& e, const f32x16 (&acc)[FI][TI], int64_t M,
+// The bias and gate values are loaded first, and the residual rows of token
+// block y + 1 before the stores of block y are issued, so no load waits behind
+// a store of the same tile.
+template <int EPI>
+__device__ __forceinline__ void epilogue_f32(const EpiArgs& e, const f32x4 (&acc)[PK_F][PK_F], int64_t M,
                                              int64_t m_base, int n_base) {
   constexpr bool RES = EPI == TRACK_EPI_GATE_RESID || EPI == TRACK_EPI_RESID;
   constexpr bool GATE = EPI == TRACK_EPI_GATE_RESID;
-  const bf16_t* __restrict__ bias_p = (const bf16_t*)e.bias;
-  float* __restrict__ out = (float*)e.out;
-  struct Block {
-    u32x2 bias[4];
-    f32x4 gate[4];
-    f32x4 x[TI][4];
-  };
-  auto load = [&](int fi, Block& bl) {
+  const bf16_t* __restrict__ bias_p = (const bf16_t*)e.bias + n_base;
+  float* __restrict__ out = (float*)e.out + n_base;
+  u32x2 bias[PK_F];
+  f32x4 gate[PK_F];
+  f32x4 x[2][PK_F];
+  auto load = [&](int y) {
+    const int64_t m = m_base + y * 16;
 #pragma unroll
-    for (int g = 0; g < 4; ++g) {
-      bl.bias[g] = *(const u32x2*)(bias_p + n_base + fi * 32 + 8 * g);
-      if constexpr (GATE) bl.gate[g] = *(const f32x4*)(e.gate + n_base + fi * 32 + 8 * g);
-    }
+    for (int f = 0; f < PK_F; ++f)
+      x[y & 1][f] = m < M ? *(const f32x4*)(out + m * e.ldo + 32 * (f >> 1) + 4 * (f & 1)) : f32x4{0, 0, 0, 0};
+  };
+#pragma unroll
+  for (int f = 0; f < PK_F; ++f) {
+    bias[f] = *(const u32x2*)(bias_p + 32 * (f >> 1) + 4 * (f & 1));
+    if constexpr (GATE) gate[f] = *(const f32x4*)(e.gate + n_base + 32 * (f >> 1) + 4 * (f & 1));
+  }
+  if constexpr (RES) load(0);
+#pragma unroll
+  for (int y = 0; y < PK_F; ++y) {
     if constexpr (RES) {
-#pragma unroll
-      for (int ti = 0; ti < TI; ++ti) {
-        const int64_t m = m_base + ti * 32;
-#pragma unroll
-        for (int g = 0; g < 4; ++g)
-          bl.x[ti][g] = m < M ? *(const f32x4*)(out + m * e.ldo + n_base + fi * 32 + 8 * g) : f32x4{0, 0, 0, 0};
-      }
+      if (y + 1 < PK_F) load(y + 1);
     }
-  };
-  Block bl[2];
-  load(0, bl[0]);
-#pragma unroll
-  for (int fi = 0; fi < FI; ++fi) {
-    if (fi + 1 < FI) load(fi + 1, bl[(fi + 1) & 1]);
     __builtin_amdgcn_sched_barrier(0);  // keep those loads ahead of this block's stores
-    const Block& c = bl[fi & 1];
+    const int64_t m = m_base + y * 16;
 #pragma unroll
-    for (int ti = 0; ti < TI; ++ti) {
-      const int64_t m = m_base + ti * 32;
+    for (int f = 0; f < PK_F; ++f) {
+      const u32x2 bv = bias[f];
+      const f32x4& c = acc[f][y];
+      f32x4 v;
+      v[0] = c[0] + __uint_as_float(bv[0] << 16);
+      v[1] = c[1] + __uint_as_float(bv[0] & 0xffff0000u);
+      v[2] = c[2] + __uint_as_float(bv[1] << 16);
+      v[3] = c[3] + __uint_as_float(bv[1] & 0xffff0000u);
+      if constexpr (GATE) {
 #pragma unroll
-      for (int g = 0; g < 4; ++g) {
-        const u32x2 bv = c.bias[g];
-        f32x4 v;
-        v[0] = acc[fi][ti][4 * g + 0] + __uint_as_float(bv[0] << 16);
-        v[1] = acc[fi][ti][4 * g + 1] + __uint_as_float(bv[0] & 0xffff0000u);
-        v[2] = acc[fi][ti][4 * g + 2] + __uint_as_float(bv[1] << 16);
-        v[3] = acc[fi][ti][4 * g + 3] + __uint_as_float(bv[1] & 0xffff0000u);
-        if constexpr (GATE) {
+        for (int j = 0; j < 4; ++j) v[j] = fmaf(gate[f][j], v[j], x[y & 1][f][j]);
+      } else if constexpr (RES) {
 #pragma unroll
-          for (int j = 0; j < 4; ++j) v[j] = fmaf(c.gate[g][j], v[j], c.x[ti][g][j]);
-        } else if constexpr (RES) {
-#pragma unroll
-          for (int j = 0; j < 4; ++j) v[j] = c.x[ti][g][j] + v[j];
-        }
-        if (m < M) *(f32x4*)(out + m * e.ldo + n_base + fi * 32 + 8 * g) = v;
+        for (int j = 0; j < 4; ++j) v[j] = x[y & 1][f][j] + v[j];
       }
+      if (m < M) *(f32x4*)(out + m * e.ldo + 32 * (f >> 1) + 4 * (f & 1)) = v;
     }
   }
 }
 
-// Epilogue of the transposed-output GEMM: out^T per batch.
-// Each wave stages one 32-feature block of its 128 x 128 sub-tile at a time
-// ([feature][128 tokens] bf16, 8 KB of LDS beside the copy ring), then reads
-// back rows of 8 consecutive tokens and stores them as 16-byte vectors.
-// Requires L % 8 == 0, so that 8 tokens starting at a multiple of 8 share a
-// batch, L >= 128 and ldv % 8 == 0.
-template <int FI, int TI>
-__device__ __forceinline__ void epilogue_vt(const EpiArgs& e, const f32x16 (&acc)[FI][TI], int64_t M, int64_t tok0,
-                                            int feat0, int jq, int fhalf, uint8_t* stage) {
-  // lane-derived offsets are recomputed here rather than hoisted out of the
-  // tile loop (kept live across the main loop they would spill)
-  int lane = jq + 32 * fhalf;
-  asm volatile("" : "+v"(lane));
-  jq = lane & 31;
-  fhalf = lane >> 5;
-  const bf16_t* __restrict__ bias_p = (const bf16_t*)e.bias + feat0 + 4 * fhalf;
+// Epilogue of the transposed-output GEMM: out^T per batch.  Tokens are the
+// MFMA "A" operand here, so the lane holds feature feat + 16 y and 8
+// consecutive tokens tok0 + 32 p + 8 q + 0..7: one 16-byte store along the
+// output row.  Requires L % 8 == 0, so that 8 tokens starting at a multiple of
+// 8 share a batch, L >= 128 and ldv % 8 == 0.
+__device__ __forceinline__ void epilogue_vt(const EpiArgs& e, const f32x4 (&acc)[PK_F][PK_F], int64_t M, int64_t tok0,
+                                            int q, int feat) {
   // batch and position of the wave's first token; its 128 tokens cross at
   // most one batch boundary (L >= 128)
   const int64_t mg0 = e.m_off + tok0;
   const int64_t b0 = mg0 / e.L;
   const int64_t l0 = mg0 - b0 * e.L;
   bf16_t* __restrict__ vt = (bf16_t*)e.vt;
-  u32x2 bias[2][4];
+  const bf16_t* __restrict__ bias_p = (const bf16_t*)e.bias + feat;
+  float bias[PK_F];
 #pragma unroll
-  for (int g = 0; g < 4; ++g) bias[0][g] = *(const u32x2*)(bias_p + 8 * g);
+  for (int y = 0; y < PK_F; ++y) bias[y] = bf2f(bias_p[16 * y]);
 #pragma unroll
-  for (int fi = 0; fi < FI; ++fi) {
-    // the next block's bias is loaded before this block's stores
-    if (fi + 1 < FI) {
+  for (int y = 0; y < PK_F; ++y) {
 #pragma unroll
-      for (int g = 0; g < 4; ++g) bias[(fi + 1) & 1][g] = *(const u32x2*)(bias_p + (fi + 1) * 32 + 8 * g);
-    }
-    __builtin_amdgcn_sched_barrier(0);
-#pragma unroll
-    for (int ti = 0; ti < TI; ++ti)
-#pragma unroll
-      for (int g = 0; g < 4; ++g) {
-        const u32x2 bv = bias[fi & 1][g];
-#pragma unroll
-        for (int j = 0; j < 4; j += 2) {
-          const float b_lo = __uint_as_float(bv[j / 2] << 16), b_hi = __uint_as_float(bv[j / 2] & 0xffff0000u);
-          const uint32_t h = pack_bf2(acc[fi][ti][4 * g + j] + b_lo, acc[fi][ti][4 * g + j + 1] + b_hi);
-          uint8_t* p = stage + (8 * g + 4 * fhalf + j) * 256 + (ti * 32 + jq) * 2;
-          *(uint16_t*)p = (uint16_t)(h & 0xffffu);
-          *(uint16_t*)(p + 256) = (uint16_t)(h >> 16);
-        }
-      }
-    // 32 rows x 16 chunks of 8 tokens; LDS operations of a wave complete in order
-#pragma unroll
-    for (int i = 0; i < 8; ++i) {
-      const int id = i * 64 + lane;
-      const int row = id >> 4, ch = id & 15;
-      const u32x4 v = *(const u32x4*)(stage + row * 256 + ch * 16);
-      if (tok0 + ch * 8 < M) {
-        int64_t l = l0 + ch * 8, b = b0;
+    for (int p = 0; p < PK_F / 2; ++p) {
+      const f32x4 &c0 = acc[2 * p][y], &c1 = acc[2 * p + 1][y];
+      const float bv = bias[y];
+      const u32x4 pk = {pack_bf2(c0[0] + bv, c0[1] + bv), pack_bf2(c0[2] + bv, c0[3] + bv),
+                        pack_bf2(c1[0] + bv, c1[1] + bv), pack_bf2(c1[2] + bv, c1[3] + bv)};
+      const int t = 32 * p + 8 * q;
+      if (tok0 + t < M) {
+        int64_t l = l0 + t, b = b0;
         if (l >= e.L) {
           l -= e.L;
           ++b;
         }
-        const int n = feat0 + fi * 32 + row;
-        *(u32x4*)(vt + (b * e.nv + n) * e.ldv + l) = v;
+        *(u32x4*)(vt + (b * e.nv + feat + 16 * y) * e.ldv + l) = pk;
       }
     }
   }
@@ -453,17 +427,12 @@ __global__ __launch_bounds__(256) void gemm_bf16_persist_kernel(const bf16_t* __
                                                                 const bf16_t* __restrict__ W, int64_t M, int N,
                                                                 int K, EpiArgs e, int ntiles, int GB) {
   constexpr int BM = 256, BN = 256, BK = 64, NWV = 4;
-  constexpr int WM = 128, WN = 128, TI = 4, FI = 4;
-  constexpr int ROWB = BK * 2, CPR = ROWB / 16;      // 128-byte LDS rows, 8 chunks
-  constexpr int STAGE_BYTES = (BM + BN) * ROWB;       // 64 KB per slot
-  constexpr int LOADS = (BM + BN) * ROWB / (NWV * 64 * 16);  // 16 per wave per slab
-  constexpr int ROWS_PER_LOAD = 1024 / ROWB;          // 8 rows per wave-wide load
-  constexpr int ALOADS = BM / ROWS_PER_LOAD / NWV;    // 8 of them cover A
-  constexpr int KS = BK / 16;                         // 16-deep MFMA steps per slab
-  constexpr int DPM = 2;                              // MFMAs per DMA load
-  static_assert(LOADS * DPM <= KS * 16, "the loads fit in the slab");
-  // the copy ring, then (transposed epilogue only) 8 KB of staging per wave
-  __shared__ __attribute__((aligned(1024))) uint8_t smem[2 * STAGE_BYTES + (EPI == EPI_BIAS_VT ? NWV * 8192 : 0)];
+  constexpr int ROWB = BK * 2;                               // 128-byte LDS rows, 8 chunks of 16 bytes
+  constexpr int STAGE_BYTES = (BM + BN) * ROWB;              // 64 KB per slot: A tile, then W tile
+  constexpr int LOADS = (BM + BN) / 8 / NWV;                 // 16 per wave and slab
+  constexpr int F = PK_F;
+  constexpr bool VT = EPI == EPI_BIAS_VT;
+  __shared__ __attribute__((aligned(1024))) uint8_t smem[2 * STAGE_BYTES];
 
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -481,15 +450,15 @@ __global__ __launch_bounds__(256) void gemm_bf16_persist_kernel(const bf16_t* __
     n0 = (in_band / gsz) * BN;
   };
 
-  // Load i of a wave covers rows rb(i) .. rb(i) + 7 of the A tile (i < ALOADS)
-  // or of the W tile: lane -> row rb(i) + lane / 8, fetching the global
-  // chunk that the swizzle puts at LDS chunk lane % 8.  rb(i) is a multiple
-  // of 8 whose bit 3 is the wave's, so the swizzle is the same for every load.
-  const int lrow = lane / CPR;
-  const int lcol = ((lane % CPR) ^ lds_swz32(wave * ROWS_PER_LOAD + lrow)) * 8;
-  const uint32_t voffA = (uint32_t)((lrow * lda + lcol) * 2);
-  const uint32_t voffW = (uint32_t)((lrow * (int64_t)K + lcol) * 2);
-  auto rb = [&](int i) { return (i < ALOADS ? i : i - ALOADS) * NWV * ROWS_PER_LOAD + wave * ROWS_PER_LOAD; };
+  // Load i of a wave fills the 8 LDS rows 32 (i % 8) + 8 wave .. + 7 of the A
+  // tile (i < 8) or of the W tile, lane -> row + lane / 8, fetching the global
+  // chunk that the swizzle puts at LDS chunk lane % 8.
+  const int lrow = lane >> 3;
+  const int lcol = ((lane & 7) ^ lds_swz16(wave * 8 + lrow)) * 8;
+  const int plain_row = wave * 8 + lrow;
+  const int perm_row = 8 * (2 * (wave & 1) + (lrow >> 2)) + 4 * (wave >> 1) + (lrow & 3);
+  const uint32_t voffA = (uint32_t)(((VT ? perm_row : plain_row) * lda + lcol) * 2);
+  const uint32_t voffW = (uint32_t)(((VT ? plain_row : perm_row) * (int64_t)K + lcol) * 2);
   __amdgpu_buffer_rsrc_t rsA, rsW;
   auto set_src = [&](int T) {
     int64_t m0;
@@ -506,12 +475,21 @@ __global__ __launch_bounds__(256) void gemm_bf16_persist_kernel(const bf16_t* __
   // column offset (less than a row) is scalar, so a row past M lies beyond
   // the resource's size whatever the scalar part, and an in-range row's
   // address stays inside that row.
+  uint32_t voA[LOADS / 2];
+  // formed anew for every tile (the lane offset is made opaque), so that they
+  // are not kept, and spilled, across the epilogue
+  auto set_vo = [&]() {
+    uint32_t v = voffA;
+    asm volatile("" : "+v"(v));
+#pragma unroll
+    for (int i = 0; i < LOADS / 2; ++i) voA[i] = v + (uint32_t)(i * 32 * lda * 2);
+  };
   auto issue_one = [&](int i) {
-    lds_ptr_t d = (lds_ptr_t)(smem + ld_slot * STAGE_BYTES + (i < ALOADS ? 0 : BM * ROWB) + rb(i) * ROWB);
-    if (i < ALOADS)
-      __builtin_amdgcn_raw_ptr_buffer_load_lds(rsA, d, 16, voffA + (uint32_t)(rb(i) * lda * 2), ld_kt * BK * 2, 0, 0);
+    lds_ptr_t d = (lds_ptr_t)(smem + ld_slot * STAGE_BYTES + (i * 32 + wave * 8) * ROWB);
+    if (i < LOADS / 2)
+      __builtin_amdgcn_raw_ptr_buffer_load_lds(rsA, d, 16, voA[i], ld_kt * BK * 2, 0, 0);
     else
-      __builtin_amdgcn_raw_ptr_buffer_load_lds(rsW, d, 16, voffW, (int)((rb(i) * (int64_t)K + ld_kt * BK) * 2), 0, 0);
+      __builtin_amdgcn_raw_ptr_buffer_load_lds(rsW, d, 16, voffW, (int)(((i - LOADS / 2) * 32 * (int64_t)K + ld_kt * BK) * 2), 0, 0);
   };
   // After the last slab of the last tile the loads keep re-fetching that tile
   // (in bounds, into a slot nobody reads again).
@@ -525,108 +503,84 @@ __global__ __launch_bounds__(256) void gemm_bf16_persist_kernel(const bf16_t* __
       }
     }
   };
-  f32x16 acc[FI][TI];
-#pragma unroll
-  for (int fi = 0; fi < FI; ++fi)
-#pragma unroll
-    for (int ti = 0; ti < TI; ++ti)
-#pragma unroll
-      for (int r = 0; r < 16; ++r) acc[fi][ti][r] = 0.0f;
 
-  const int frow = lane & 31, fhalf = lane >> 5;
-  // fragment idx of 16-deep step kk: 0..3 the W rows (MFMA A operand),
-  // 4..7 the token rows (B operand)
-  auto read_frag = [&](const uint8_t* base, int kk, int idx) -> bf16x8 {
-    const int ch = kk * 2 + fhalf;
-    const int row = idx < FI ? BM + wn * WN + idx * 32 + frow : wm * WM + (idx - FI) * 32 + frow;
-    return __builtin_bit_cast(bf16x8, *(const u32x4*)(base + row * ROWB + ((ch ^ lds_swz32(row)) << 4)));
-  };
-  bf16x8 fw[2][FI], fa[2][TI];
-  // MFMAs of 16-deep step kk (fragments in buffer kk & 1); with rd, before
-  // MFMA j < 8 fragment j of step nk of the slab at nbase is read into the
-  // other buffer; with lo >= 0, DMA loads lo .. lo + 7 follow every second
-  // MFMA.
-  auto step = [&](int kk, const uint8_t* nbase, int nk, int lo, bool rd) {
-    const bf16x8* w_ = fw[kk & 1];
-    const bf16x8* a_ = fa[kk & 1];
-    bf16x8* nw = fw[(kk + 1) & 1];
-    bf16x8* na = fa[(kk + 1) & 1];
+  // LDS byte offsets of the lane's fragments, 32-deep step 0 of slot 0: lane ->
+  // row lane % 16, chunk lane / 16 (step 1: chunk + 4, an XOR of 64 bytes
+  // either way; fragment f: + 2048 f)
+  const int frow = lane & 15, q = lane >> 4;
+  const uint32_t foff = (uint32_t)(frow * ROWB + ((q ^ lds_swz16(frow)) << 4));
+  const uint32_t offA = (uint32_t)(wm * 128 * ROWB) + foff, offW = (uint32_t)((BM + wn * 128) * ROWB) + foff;
+  uint32_t xo = VT ? offA : offW, yo = VT ? offW : offA;  // MFMA "A" and "B" operand
+  auto frag = [&](uint32_t o, int f) { return __builtin_bit_cast(bf16x8, *(const u32x4*)(smem + o + f * 16 * ROWB)); };
+
+  f32x4 acc[F][F];
+  bf16x8 fx[2][F], fy[2][F];
+  // MFMAs j0 .. j1 of a step, with the reads of the next step's fragments (one
+  // per PK_RS MFMAs from MFMA 0 on) and, with load0 >= 0, the copies from load0 on
+  auto mfmas = [&](int kk, int j0, int j1, bool zero, uint32_t nx, uint32_t ny, int load0, int dpm) {
+    bf16x8 *rx = fx[kk ^ 1], *ry = fy[kk ^ 1];
 #pragma unroll
-    for (int j = 0; j < 16; ++j) {
-      if (rd && j < FI + TI) {
-        if (j < FI) nw[j] = read_frag(nbase, nk, j);
-        else na[j - FI] = read_frag(nbase, nk, j);
+    for (int j = j0; j < j1; ++j) {
+      if (j % PK_RS == 0 && j / PK_RS < 2 * F) {
+        const int r = j / PK_RS;
+        if (r < F) ry[r] = frag(ny, r);
+        else rx[r - F] = frag(nx, r - F);
       }
-      acc[j / TI][j % TI] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(w_[j / TI], a_[j % TI], acc[j / TI][j % TI], 0, 0, 0);
-      if (lo >= 0 && j % DPM == 0) issue_one(lo + j / DPM);
+      const int x = j / F, y = j % F;
+      acc[x][y] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(fx[kk][x], fy[kk][y], zero ? f32x4{0, 0, 0, 0} : acc[x][y], 0, 0, 0);
+      if (load0 >= 0 && (j - j0) % dpm == 0 && load0 + (j - j0) / dpm < LOADS) issue_one(load0 + (j - j0) / dpm);
       __builtin_amdgcn_sched_barrier(0);
     }
   };
-  static_assert(KS == 4 && LOADS == 16 && DPM == 2, "the slab schedule below assumes 4 steps and 16 loads");
-
-  // prologue: slab 0, then the first half of slab 1's loads and slab 0's
-  // first fragments
-#pragma unroll
-  for (int i = 0; i < LOADS; ++i) issue_one(i);
-  advance_ld();
-  wait_vmcnt<0>();
-  __builtin_amdgcn_s_barrier();
-#pragma unroll
-  for (int i = 0; i < LOADS / 2; ++i) issue_one(i);
-#pragma unroll
-  for (int f = 0; f < FI + TI; ++f) {
-    if (f < FI) fw[0][f] = read_frag(smem, 0, f);
-    else fa[0][f - FI] = read_frag(smem, 0, f);
-  }
-
-  const int my_tiles = (ntiles - p + G - 1) / G;
-  int slot = 0;
-  // slab body; rd: read the next slab's first fragments during the last
-  // step (not at a tile's last slab, where they would stay live through the
-  // epilogue and push it into spilling)
-  auto slab = [&](bool rd) {
-    const uint8_t* base = smem + slot * STAGE_BYTES;
-    const uint8_t* nbase = smem + (slot ^ 1) * STAGE_BYTES;
-    step(0, base, 1, LOADS / 2, true);  // second half of slab g + 1's loads
-    advance_ld();
-    step(1, base, 2, -1, true);
-    step(2, base, 3, -1, true);
+  constexpr int L0 = (64 - PK_BAR + PK_DPM - 1) / PK_DPM;  // loads issued during step 0
+  static_assert(PK_BAR > PK_RS * (2 * F - 1) && PK_BAR <= 64 && L0 + (64 + PK_DPM - 1) / PK_DPM >= LOADS, "slab schedule");
+  auto slab = [&](auto first_tag) {
+    constexpr bool FIRST = decltype(first_tag)::value;
+    mfmas(0, 0, PK_BAR, FIRST, xo ^ 64, yo ^ 64, -1, 1);
     // slab g + 1 has landed for this wave (and, at a tile's first slab, the
-    // previous epilogue's stores are complete); after the barrier for every
-    // wave, and every wave holds its step-3 fragments of slab g
+    // previous epilogue's stores are complete) and the wave holds all of slab
+    // g's fragments; after the barrier both hold for every wave
     wait_vmcnt<0>();
     wait_lgkm0();
     __builtin_amdgcn_s_barrier();
     __builtin_amdgcn_sched_barrier(0);
-    step(3, nbase, 0, 0, rd);  // first half of slab g + 2's loads, into slab g's slot
-    slot ^= 1;
+    mfmas(0, PK_BAR, 64, FIRST, xo ^ 64, yo ^ 64, 0, PK_DPM);  // slab g + 2 into slab g's slot
+    xo ^= STAGE_BYTES;
+    yo ^= STAGE_BYTES;
+    mfmas(1, 0, 64, false, xo, yo, L0, PK_DPM);
+    advance_ld();
   };
+
+  // prologue: slabs 0 and 1, slab 0's first fragments
+  set_vo();
+#pragma unroll
+  for (int i = 0; i < LOADS; ++i) issue_one(i);
+  advance_ld();
+#pragma unroll
+  for (int i = 0; i < LOADS; ++i) issue_one(i);
+  advance_ld();
+  wait_vmcnt<LOADS>();
+  __builtin_amdgcn_s_barrier();
+#pragma unroll
+  for (int f = 0; f < F; ++f) {
+    fx[0][f] = frag(xo, f);
+    fy[0][f] = frag(yo, f);
+  }
+
+  const int my_tiles = (ntiles - p + G - 1) / G;
   for (int t = 0; t < my_tiles; ++t) {
-    for (int kt = 0; kt + 1 < KT; ++kt) slab(true);
-    slab(false);
+    set_vo();
+    slab(std::true_type{});
+    for (int kt = 1; kt < KT; ++kt) slab(std::false_type{});
     int64_t cm0;
     int cn0;
     tile_mn(p + t * G, cm0, cn0);
-    if constexpr (EPI == EPI_BIAS_VT) {
-      epilogue_vt<FI, TI>(e, acc, M, cm0 + wm * WM, cn0 + wn * WN, frow, fhalf, smem + 2 * STAGE_BYTES + wave * 8192);
-    } else if constexpr (EPI == TRACK_EPI_BIAS || EPI == TRACK_EPI_BIAS_GELU)
-      epilogue_bf16<EPI, FI, TI>(e, acc, M, cm0 + wm * WM + frow, cn0 + wn * WN + 4 * fhalf, fhalf);
+    if constexpr (VT)
+      epilogue_vt(e, acc, M, cm0 + wm * 128, q, cn0 + wn * 128 + frow);
+    else if constexpr (EPI == TRACK_EPI_BIAS || EPI == TRACK_EPI_BIAS_GELU)
+      epilogue_bf16<EPI>(e, acc, M, cm0 + wm * 128 + frow, cn0 + wn * 128 + 8 * q);
     else
-      epilogue_f32<EPI, FI, TI>(e, acc, M, cm0 + wm * WM + frow, cn0 + wn * WN + 4 * fhalf);
-#pragma unroll
-    for (int fi = 0; fi < FI; ++fi)
-#pragma unroll
-      for (int ti = 0; ti < TI; ++ti)
-#pragma unroll
-        for (int r = 0; r < 16; ++r) acc[fi][ti][r] = 0.0f;
-    // the next tile's first fragments (its first slab landed before the
-    // last barrier)
-    const uint8_t* nb = smem + slot * STAGE_BYTES;
-#pragma unroll
-    for (int f = 0; f < FI + TI; ++f) {
-      if (f < FI) fw[0][f] = read_frag(nb, 0, f);
-      else fa[0][f - FI] = read_frag(nb, 0, f);
-    }
+      epilogue_f32<EPI>(e, acc, M, cm0 + wm * 128 + frow, cn0 + wn * 128 + 8 * q);
   }
   // the last copies must land before the workgroup's LDS is released
   wait_vmcnt<0>();
