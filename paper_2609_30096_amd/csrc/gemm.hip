@@ -8,6 +8,7 @@
 // 16-byte vectors.  Epilogues fuse the bias, the tanh GELU of the MLP, and the
 // adaLN gate with the float32 residual update; one variant swaps the operands
 // and stores the output transposed per batch (V^T for attention).
+#include <algorithm>
 #include <cstdlib>
 #include <type_traits>
 
@@ -115,17 +116,18 @@ __device__ __forceinline__ void epilogue(const EpiArgs& e, const f32x16 (&acc)[F
 // reads are conflict free whether LDS serves 8 or 16 lanes per cycle.
 __device__ __forceinline__ int lds_swz(int row) { return (row & 7) ^ ((row >> 3) & 1); }
 
-// Block tile BM tokens x BN features x 64 (K); four waves in a 2 x 2 grid,
-// each owning (BM/2) x (BN/2) as 32 x 32 MFMA blocks.  Tiles are staged
+// Any leading dimension (64-bit addresses).  Block tile BM tokens x BN features
+// x 64 (K); four waves in a 2 x 2 grid, each owning (BM/2) x (BN/2) as 32 x 32
+// MFMA blocks.  Tiles are staged
 // through LDS, double buffered, rows of 64 bf16 (128 B) with the 16-byte
 // chunk index XOR-swizzled (lds_swz) so that the 32-row fragment reads are
 // bank-conflict free.  Global loads of the next K-slab are issued before
 // the MFMAs of the current one.
-template <int BM, int BN, int EPI>
+template <int EPI>
 __global__ __launch_bounds__(256) void gemm_bf16_kernel(const bf16_t* __restrict__ A, int64_t lda,
                                                         const bf16_t* __restrict__ W, int64_t M, int N, int K,
                                                         EpiArgs e) {
-  constexpr int BK = 64;
+  constexpr int BM = 128, BN = 64, BK = 64;
   constexpr int WM = BM / 2, WN = BN / 2;
   constexpr int TI = WM / 32, FI = WN / 32;
   constexpr int AC = BM / 32;  // 16-byte chunks per thread for the A tile (BM * 8 / 256)
@@ -281,7 +283,7 @@ constexpr int PK_BAR = 40;  // the slab's barrier follows MFMA 40 of its first s
 constexpr int PK_DPM = 5;   // MFMAs per copy
 
 // The MFMA "A" operand's rows (features; tokens in the transposed-output
-// kernel) sit permuted in LDS, within every 32 rows: row 16 h + 4 q + j holds
+// kernels) sit permuted in LDS, within every 32 rows: row 16 h + 4 q + j holds
 // row 8 q + 4 h + j.  A lane's accumulators of the fragment pair 2 p, 2 p + 1
 // (rows 4 q + j of each) are then 8 consecutive rows 32 p + 8 q + 0..7: whole
 // 16-byte bf16 stores without a lane exchange.
@@ -293,25 +295,23 @@ constexpr int PK_DPM = 5;   // MFMAs per copy
 // line are stored back to back, so the L2 holds whole lines when it writes
 // them back (feature blocks outermost left lines half written long enough to be
 // evicted and written twice: 20% more HBM writes).
-template <int EPI>
-__device__ __forceinline__ void epilogue_bf16(const EpiArgs& e, const f32x4 (&acc)[PK_F][PK_F], int64_t M,
+template <int EPI, int XF, int YF>
+__device__ __forceinline__ void epilogue_bf16(const EpiArgs& e, const f32x4 (&acc)[XF][YF], int64_t M,
                                               int64_t m_base, int n_base) {
   const bf16_t* __restrict__ bias_p = (const bf16_t*)e.bias + n_base;
-  u32x2 bias[PK_F / 2][2];
+  u32x2 bias[XF];
 #pragma unroll
-  for (int p = 0; p < PK_F / 2; ++p)
+  for (int f = 0; f < XF; ++f) bias[f] = *(const u32x2*)(bias_p + 32 * (f >> 1) + 4 * (f & 1));
 #pragma unroll
-    for (int h = 0; h < 2; ++h) bias[p][h] = *(const u32x2*)(bias_p + 32 * p + 4 * h);
-#pragma unroll
-  for (int y = 0; y < PK_F; ++y) {
+  for (int y = 0; y < YF; ++y) {
     const int64_t m = m_base + y * 16;
     bf16_t* __restrict__ orow = (bf16_t*)e.out + m * e.ldo + n_base;
 #pragma unroll
-    for (int p = 0; p < PK_F / 2; ++p) {
+    for (int p = 0; p < XF / 2; ++p) {
       u32x4 pk;
 #pragma unroll
       for (int h = 0; h < 2; ++h) {
-        const u32x2 bv = bias[p][h];
+        const u32x2 bv = bias[2 * p + h];
         const f32x4& c = acc[2 * p + h][y];
         float v[4];
         v[0] = c[0] + __uint_as_float(bv[0] << 16);
@@ -334,37 +334,39 @@ __device__ __forceinline__ void epilogue_bf16(const EpiArgs& e, const f32x4 (&ac
 // The bias and gate values are loaded first, and the residual rows of token
 // block y + 1 before the stores of block y are issued, so no load waits behind
 // a store of the same tile.
-template <int EPI>
-__device__ __forceinline__ void epilogue_f32(const EpiArgs& e, const f32x4 (&acc)[PK_F][PK_F], int64_t M,
+template <int XF>
+__device__ __forceinline__ void load_resid(const EpiArgs& e, int64_t M, int64_t m, int n_base, f32x4 (&x)[XF]) {
+  const float* __restrict__ out = (const float*)e.out + n_base;
+#pragma unroll
+  for (int f = 0; f < XF; ++f)
+    x[f] = m < M ? *(const f32x4*)(out + m * e.ldo + 32 * (f >> 1) + 4 * (f & 1)) : f32x4{0, 0, 0, 0};
+}
+
+template <int EPI, int XF, int YF>
+__device__ __forceinline__ void epilogue_f32(const EpiArgs& e, const f32x4 (&acc)[XF][YF], int64_t M,
                                              int64_t m_base, int n_base) {
   constexpr bool RES = EPI == TRACK_EPI_GATE_RESID || EPI == TRACK_EPI_RESID;
   constexpr bool GATE = EPI == TRACK_EPI_GATE_RESID;
   const bf16_t* __restrict__ bias_p = (const bf16_t*)e.bias + n_base;
   float* __restrict__ out = (float*)e.out + n_base;
-  u32x2 bias[PK_F];
-  f32x4 gate[PK_F];
-  f32x4 x[2][PK_F];
-  auto load = [&](int y) {
-    const int64_t m = m_base + y * 16;
+  u32x2 bias[XF];
+  f32x4 gate[XF];
+  f32x4 x[2][XF];
 #pragma unroll
-    for (int f = 0; f < PK_F; ++f)
-      x[y & 1][f] = m < M ? *(const f32x4*)(out + m * e.ldo + 32 * (f >> 1) + 4 * (f & 1)) : f32x4{0, 0, 0, 0};
-  };
-#pragma unroll
-  for (int f = 0; f < PK_F; ++f) {
+  for (int f = 0; f < XF; ++f) {
     bias[f] = *(const u32x2*)(bias_p + 32 * (f >> 1) + 4 * (f & 1));
     if constexpr (GATE) gate[f] = *(const f32x4*)(e.gate + n_base + 32 * (f >> 1) + 4 * (f & 1));
   }
-  if constexpr (RES) load(0);
+  if constexpr (RES) load_resid<XF>(e, M, m_base, n_base, x[0]);
 #pragma unroll
-  for (int y = 0; y < PK_F; ++y) {
+  for (int y = 0; y < YF; ++y) {
     if constexpr (RES) {
-      if (y + 1 < PK_F) load(y + 1);
+      if (y + 1 < YF) load_resid<XF>(e, M, m_base + (y + 1) * 16, n_base, x[(y + 1) & 1]);
     }
     __builtin_amdgcn_sched_barrier(0);  // keep those loads ahead of this block's stores
     const int64_t m = m_base + y * 16;
 #pragma unroll
-    for (int f = 0; f < PK_F; ++f) {
+    for (int f = 0; f < XF; ++f) {
       const u32x2 bv = bias[f];
       const f32x4& c = acc[f][y];
       f32x4 v;
@@ -388,23 +390,24 @@ __device__ __forceinline__ void epilogue_f32(const EpiArgs& e, const f32x4 (&acc
 // MFMA "A" operand here, so the lane holds feature feat + 16 y and 8
 // consecutive tokens tok0 + 32 p + 8 q + 0..7: one 16-byte store along the
 // output row.  Requires L % 8 == 0, so that 8 tokens starting at a multiple of
-// 8 share a batch, L >= 128 and ldv % 8 == 0.
-__device__ __forceinline__ void epilogue_vt(const EpiArgs& e, const f32x4 (&acc)[PK_F][PK_F], int64_t M, int64_t tok0,
+// 8 share a batch, L >= 128 (the wave's at most 128 tokens then cross at most
+// one batch boundary) and ldv % 8 == 0.
+template <int XF, int YF>
+__device__ __forceinline__ void epilogue_vt(const EpiArgs& e, const f32x4 (&acc)[XF][YF], int64_t M, int64_t tok0,
                                             int q, int feat) {
-  // batch and position of the wave's first token; its 128 tokens cross at
-  // most one batch boundary (L >= 128)
+  static_assert(XF <= 8, "a wave's tokens cross at most one batch boundary");
   const int64_t mg0 = e.m_off + tok0;
   const int64_t b0 = mg0 / e.L;
   const int64_t l0 = mg0 - b0 * e.L;
   bf16_t* __restrict__ vt = (bf16_t*)e.vt;
   const bf16_t* __restrict__ bias_p = (const bf16_t*)e.bias + feat;
-  float bias[PK_F];
+  float bias[YF];
 #pragma unroll
-  for (int y = 0; y < PK_F; ++y) bias[y] = bf2f(bias_p[16 * y]);
+  for (int y = 0; y < YF; ++y) bias[y] = bf2f(bias_p[16 * y]);
 #pragma unroll
-  for (int y = 0; y < PK_F; ++y) {
+  for (int y = 0; y < YF; ++y) {
 #pragma unroll
-    for (int p = 0; p < PK_F / 2; ++p) {
+    for (int p = 0; p < XF / 2; ++p) {
       const f32x4 &c0 = acc[2 * p][y], &c1 = acc[2 * p + 1][y];
       const float bv = bias[y];
       const u32x4 pk = {pack_bf2(c0[0] + bv, c0[1] + bv), pack_bf2(c0[2] + bv, c0[3] + bv),
@@ -420,6 +423,19 @@ __device__ __forceinline__ void epilogue_vt(const EpiArgs& e, const f32x4 (&acc)
       }
     }
   }
+}
+
+// The tile epilogue of `EPI`: tokens tok0 .. and features feat0 .. are the
+// wave's, frow = lane % 16, q = lane / 16.
+template <int EPI, int XF, int YF>
+__device__ __forceinline__ void tile_epilogue(const EpiArgs& e, const f32x4 (&acc)[XF][YF], int64_t M, int64_t tok0,
+                                              int feat0, int frow, int q) {
+  if constexpr (EPI == EPI_BIAS_VT)
+    epilogue_vt<XF, YF>(e, acc, M, tok0, q, feat0 + frow);
+  else if constexpr (EPI == TRACK_EPI_BIAS || EPI == TRACK_EPI_BIAS_GELU)
+    epilogue_bf16<EPI, XF, YF>(e, acc, M, tok0 + frow, feat0 + 8 * q);
+  else
+    epilogue_f32<EPI, XF, YF>(e, acc, M, tok0 + frow, feat0 + 8 * q);
 }
 
 template <int EPI>
@@ -575,15 +591,145 @@ __global__ __launch_bounds__(256) void gemm_bf16_persist_kernel(const bf16_t* __
     int64_t cm0;
     int cn0;
     tile_mn(p + t * G, cm0, cn0);
-    if constexpr (VT)
-      epilogue_vt(e, acc, M, cm0 + wm * 128, q, cn0 + wn * 128 + frow);
-    else if constexpr (EPI == TRACK_EPI_BIAS || EPI == TRACK_EPI_BIAS_GELU)
-      epilogue_bf16<EPI>(e, acc, M, cm0 + wm * 128 + frow, cn0 + wn * 128 + 8 * q);
-    else
-      epilogue_f32<EPI>(e, acc, M, cm0 + wm * 128 + frow, cn0 + wn * 128 + 8 * q);
+    tile_epilogue<EPI, F, F>(e, acc, M, cm0 + wm * 128, cn0 + wn * 128, frow, q);
   }
   // the last copies must land before the workgroup's LDS is released
   wait_vmcnt<0>();
+}
+
+// ------------------------------------------------------------------ bf16 MFMA kernel, one tile per workgroup
+// The same slab schedule for every shape whose 256 x 256 tiles would leave CUs
+// idle: X rows x Y rows of 32 XF x 32 YF (X the MFMA "A" operand: features, or
+// tokens in the transposed-output form), four waves in a 2 x 2 grid of
+// 16 XF x 16 YF, NS ring slots.  Slab g + NS is copied into slab g's slot after
+// the slab's barrier, so NS - 1 slabs are in flight while one is multiplied.
+// Copies past the last slab go through an empty buffer resource (they fetch
+// nothing; the counts the waits rely on stay the same).
+template <int XF, int YF, int NS, int EPI>
+__global__ __launch_bounds__(256) void gemm_bf16_tile_kernel(const bf16_t* __restrict__ A, int64_t lda,
+                                                             const bf16_t* __restrict__ W, int64_t M, int N, int K,
+                                                             EpiArgs e, int GB) {
+  constexpr bool VT = EPI == EPI_BIAS_VT;
+  constexpr int BX = 32 * XF, BY = 32 * YF, BM = VT ? BX : BY, BN = VT ? BY : BX;
+  constexpr int BK = 64, ROWB = 128, NWV = 4;
+  constexpr int STAGE_BYTES = (BX + BY) * ROWB;
+  constexpr int LOADS = XF + YF;  // per wave and slab
+  constexpr int NM = XF * YF;     // MFMAs per 32-deep step
+  __shared__ __attribute__((aligned(1024))) uint8_t smem[NS * STAGE_BYTES];
+
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int wx = wave & 1, wy = wave >> 1;
+  // tile order: XCD-aware remap, then bands of GB M-tiles swept across N
+  const int num_tm = (int)((M + BM - 1) / BM), num_tn = N / BN;
+  const int p = xcd_remap(blockIdx.x, gridDim.x);
+  const int band = p / (GB * num_tn);
+  const int gsz = min(num_tm - band * GB, GB);
+  const int in_band = p - band * GB * num_tn;
+  const int64_t m0 = (int64_t)(band * GB + in_band % gsz) * BM;
+  const int n0 = (in_band / gsz) * BN;
+
+  const int lrow = lane >> 3;
+  const int lcol = ((lane & 7) ^ lds_swz16(wave * 8 + lrow)) * 8;
+  const int plain_row = wave * 8 + lrow;
+  const int perm_row = 8 * (2 * (wave & 1) + (lrow >> 2)) + 4 * (wave >> 1) + (lrow & 3);
+  // the host keeps BM * lda * 2 and BN * K * 2 below 2^31; rows past M lie
+  // beyond the resource through their vector offset
+  const int64_t arows = M - m0 < BM ? M - m0 : BM;
+  const bf16_t *xp = VT ? A + m0 * lda : W + (int64_t)n0 * K, *yp = VT ? W + (int64_t)n0 * K : A + m0 * lda;
+  const int64_t ldx = VT ? lda : K, ldy = VT ? K : lda;
+  const int xbytes = (int)((VT ? arows * lda : (int64_t)BN * K) * 2), ybytes = (int)((VT ? (int64_t)BN * K : arows * lda) * 2);
+  uint32_t vox[XF], voy[YF];
+#pragma unroll
+  for (int i = 0; i < XF; ++i) vox[i] = (uint32_t)(((i * 32 + perm_row) * ldx + lcol) * 2);
+#pragma unroll
+  for (int i = 0; i < YF; ++i) voy[i] = (uint32_t)(((i * 32 + plain_row) * ldy + lcol) * 2);
+  const int KT = K / BK;
+  int ld_kt = 0, ld_off = wave * 8 * ROWB;  // slab and LDS offset of the next copy
+  __amdgpu_buffer_rsrc_t rx, ry;
+  auto set_rsrc = [&]() {
+    rx = __builtin_amdgcn_make_buffer_rsrc((void*)xp, (short)0, ld_kt < KT ? xbytes : 0, 0x00020000);
+    ry = __builtin_amdgcn_make_buffer_rsrc((void*)yp, (short)0, ld_kt < KT ? ybytes : 0, 0x00020000);
+  };
+  // (plain types only: the builtin is not accepted with type-dependent arguments)
+  uint8_t* const ring = smem;
+  auto copy16 = [&](__amdgpu_buffer_rsrc_t r, int dst, uint32_t voff) {
+    __builtin_amdgcn_raw_ptr_buffer_load_lds(r, (lds_ptr_t)(ring + dst), 16, voff, ld_kt * 128, 0, 0);
+  };
+  auto issue_one = [&](int i) {
+    if (i < XF) copy16(rx, ld_off + i * 32 * ROWB, vox[i < XF ? i : 0]);
+    else copy16(ry, ld_off + i * 32 * ROWB, voy[i < XF ? 0 : i - XF]);
+  };
+  auto advance_ld = [&]() {
+    ++ld_kt;
+    ld_off += STAGE_BYTES;
+    if (ld_off >= NS * STAGE_BYTES) ld_off -= NS * STAGE_BYTES;
+    set_rsrc();
+  };
+
+  const int frow = lane & 15, q = lane >> 4;
+  const uint32_t foff = (uint32_t)(frow * ROWB + ((q ^ lds_swz16(frow)) << 4));
+  const uint32_t xo = (uint32_t)(wx * 16 * XF * ROWB) + foff, yo = (uint32_t)((BX + wy * 16 * YF) * ROWB) + foff;
+  uint32_t rd = 0;  // ring offset of the slab being read
+  auto frag = [&](uint32_t o, int f) { return __builtin_bit_cast(bf16x8, *(const u32x4*)(smem + o + f * 16 * ROWB)); };
+
+  f32x4 acc[XF][YF];
+#pragma unroll
+  for (int x = 0; x < XF; ++x)
+#pragma unroll
+    for (int y = 0; y < YF; ++y) acc[x][y] = f32x4{0, 0, 0, 0};
+  bf16x8 fx[2][XF], fy[2][YF];
+  // fragment reads r0 .. r1 (y first) of a step into buffer b
+  auto reads = [&](int b, uint32_t nx, uint32_t ny, int r0, int r1) {
+#pragma unroll
+    for (int r = r0; r < r1; ++r) {
+      if (r < YF) fy[b][r < YF ? r : 0] = frag(ny, r);
+      else fx[b][r < YF ? 0 : r - YF] = frag(nx, r - YF);
+    }
+  };
+  // MFMAs j0 .. j1 of step kk, with reads (from r0 on) or copies (from c0 on) spread over them
+  auto mfmas = [&](int kk, int j0, int j1, int r0, uint32_t nx, uint32_t ny, int c0, int c1) {
+#pragma unroll
+    for (int j = j0; j < j1; ++j) {
+      const int a = j - j0, n = j1 - j0;
+      if (r0 >= 0) reads(kk ^ 1, nx, ny, r0 + a * (LOADS - r0) / n, r0 + (a + 1) * (LOADS - r0) / n);
+      acc[j / YF][j % YF] =
+          __builtin_amdgcn_mfma_f32_16x16x32_bf16(fx[kk][j / YF], fy[kk][j % YF], acc[j / YF][j % YF], 0, 0, 0);
+#pragma unroll
+      for (int c = c0 + a * (c1 - c0) / n; c < c0 + (a + 1) * (c1 - c0) / n; ++c) issue_one(c);
+      __builtin_amdgcn_sched_barrier(0);
+    }
+  };
+
+#pragma unroll
+  for (int s = 0; s < NS; ++s) {
+    set_rsrc();
+#pragma unroll
+    for (int i = 0; i < LOADS; ++i) issue_one(i);
+    advance_ld();
+  }
+  wait_vmcnt<(NS - 1) * LOADS>();
+  __builtin_amdgcn_s_barrier();
+  reads(0, xo, yo, 0, LOADS);
+  constexpr int HALF = NM / 2;  // the barrier's place: step 0's second half covers the wait of a partner
+  for (int kt = 0; kt < KT; ++kt) {
+    // every fragment of the slab's second step read by the middle of its first
+    mfmas(0, 0, HALF, 0, rd + (xo ^ 64), rd + (yo ^ 64), 0, 0);
+    // slab kt + 1 has landed for this wave and the wave holds all of slab kt's
+    // fragments; after the barrier both hold for every wave
+    wait_vmcnt<(NS - 2) * LOADS>();
+    wait_lgkm0();
+    __builtin_amdgcn_s_barrier();
+    __builtin_amdgcn_sched_barrier(0);
+    mfmas(0, HALF, NM, -1, 0, 0, 0, LOADS / 3);  // slab kt + NS into slab kt's slot
+    rd += STAGE_BYTES;
+    if (rd >= NS * STAGE_BYTES) rd -= NS * STAGE_BYTES;
+    mfmas(1, 0, NM, 0, rd + xo, rd + yo, LOADS / 3, LOADS);
+    advance_ld();
+  }
+  wait_vmcnt<0>();  // the last copies must land before the workgroup's LDS is released
+  tile_epilogue<EPI, XF, YF>(e, acc, M, m0 + (VT ? wx * 16 * XF : wy * 16 * YF),
+                             n0 + (VT ? wy * 16 * YF : wx * 16 * XF), frow, q);
 }
 
 // ------------------------------------------------------------------ float32 kernel
@@ -640,29 +786,20 @@ __global__ __launch_bounds__(256) void gemm_f32_kernel(const float* __restrict__
 }
 
 // ------------------------------------------------------------------ launchers
-template <int BM, int BN>
-static void launch_bf16_cfg(int epi, const bf16_t* A, int64_t lda, const bf16_t* W, int64_t M, int N, int K,
-                            const EpiArgs& e, hipStream_t s) {
-  const int tiles = (int)((M + BM - 1) / BM) * (N / BN);
-  dim3 grid(tiles), block(256);
-  switch (epi) {
-    case TRACK_EPI_BIAS: gemm_bf16_kernel<BM, BN, TRACK_EPI_BIAS><<<grid, block, 0, s>>>(A, lda, W, M, N, K, e); break;
-    case TRACK_EPI_BIAS_GELU: gemm_bf16_kernel<BM, BN, TRACK_EPI_BIAS_GELU><<<grid, block, 0, s>>>(A, lda, W, M, N, K, e); break;
-    case TRACK_EPI_GATE_RESID: gemm_bf16_kernel<BM, BN, TRACK_EPI_GATE_RESID><<<grid, block, 0, s>>>(A, lda, W, M, N, K, e); break;
-    case TRACK_EPI_RESID: gemm_bf16_kernel<BM, BN, TRACK_EPI_RESID><<<grid, block, 0, s>>>(A, lda, W, M, N, K, e); break;
-    default: gemm_bf16_kernel<BM, BN, TRACK_EPI_BIAS_F32><<<grid, block, 0, s>>>(A, lda, W, M, N, K, e); break;
-  }
-}
+// The register-staged kernel, for leading dimensions whose tiles a buffer
+// resource cannot address (BUF_LD and up).
+constexpr int64_t BUF_LD = (int64_t)1 << 22;
 
-// Kernel override for tuning and test runs (TRACK_GEMM_CFG, read at every
-// call): 0 automatic, 1 256x256, 2 128x128, 3 256x128 (register-staged
-// kernel), 4 the persistent kernel for every shape it supports (N % 256 == 0)
-// whatever the tile count; shapes the forced kernel does not take use the
-// automatic choice.
-static int gemm_config() {
-  const char* v = getenv("TRACK_GEMM_CFG");
-  const int c = v ? atoi(v) : 0;
-  return (c >= 0 && c <= 4) ? c : 0;
+static void launch_bf16_big_ld(int epi, const bf16_t* A, int64_t lda, const bf16_t* W, int64_t M, int N, int K,
+                               const EpiArgs& e, hipStream_t s) {
+  dim3 grid((unsigned)((M + 127) / 128) * (unsigned)(N / 64)), block(256);
+  switch (epi) {
+    case TRACK_EPI_BIAS: gemm_bf16_kernel<TRACK_EPI_BIAS><<<grid, block, 0, s>>>(A, lda, W, M, N, K, e); break;
+    case TRACK_EPI_BIAS_GELU: gemm_bf16_kernel<TRACK_EPI_BIAS_GELU><<<grid, block, 0, s>>>(A, lda, W, M, N, K, e); break;
+    case TRACK_EPI_GATE_RESID: gemm_bf16_kernel<TRACK_EPI_GATE_RESID><<<grid, block, 0, s>>>(A, lda, W, M, N, K, e); break;
+    case TRACK_EPI_RESID: gemm_bf16_kernel<TRACK_EPI_RESID><<<grid, block, 0, s>>>(A, lda, W, M, N, K, e); break;
+    default: gemm_bf16_kernel<TRACK_EPI_BIAS_F32><<<grid, block, 0, s>>>(A, lda, W, M, N, K, e); break;
+  }
 }
 
 // Compute units of the current device (the persistent grid size).
@@ -676,6 +813,85 @@ int device_cus() {
     cus[dev] = n;
   }
   return cus[dev];
+}
+
+// The tile kernels (X rows, Y rows in units of 32, ring slots, workgroups a CU
+// holds by their LDS); entry 0 is the persistent 256 x 256 kernel.  Ties go to
+// the earlier entry, so the deeper ring of two equal tiles comes first.
+struct TileCfg {
+  int xf, yf, slots, resident;
+  bool vt;  // compiled with the transposed output (X the tokens there, Y the features)
+};
+static const TileCfg kTiles[] = {{8, 8, 2, 1, true},  {8, 4, 3, 1, false}, {4, 8, 3, 1, true},  {4, 5, 4, 1, false},
+                                 {4, 5, 2, 2, false}, {4, 4, 4, 1, true},  {4, 3, 4, 1, false}, {4, 2, 3, 2, false},
+                                 {2, 4, 3, 2, true},  {2, 2, 4, 2, true},  {2, 1, 4, 3, false}};
+constexpr int NTILES = sizeof(kTiles) / sizeof(kTiles[0]);
+
+// Kernel override for tests (TRACK_GEMM_CFG, read at every call): 4 the
+// persistent kernel, 10 + i entry i of kTiles, for every shape it supports;
+// anything else, and shapes the forced kernel does not take, automatic.
+static int gemm_config() {
+  const char* v = getenv("TRACK_GEMM_CFG");
+  const int c = v ? atoi(v) : 0;
+  return c == 4 ? 0 : (c >= 10 && c < 10 + NTILES ? c - 10 : -1);
+}
+
+// The tile for a shape, by an estimate of its time.  A slab of a BM x BN tile
+// takes at least BM BN / 64 + 70 ns on a CU (its MFMAs at 2 GHz, and the
+// barrier, fragment and copy latency of one workgroup), and (BM + BN) 1.47 ns of
+// the CU's share of the L2 (16 TB/s over the chip); workgroups that share a CU
+// overlap the first but add up in the second.  Tiles run in rounds of what the
+// 256 CUs hold; the last round holds what is left.  Fitted over 75 shapes (M
+// 130 - 9000, N 64 - 13824, K 64 - 13824), every tile timed at each: the pick is
+// within 1% of the fastest tile on average and 13% at worst, where the largest tile
+// for all that fill half the chip, and 128 x 128 for the rest, were 1.1 to 4.5 times
+// slower (1.3B, 3120 rows: FFN2 154.7 -> 76.3 us, O 35.8 -> 22.8, q/k 51.3 ->
+// 29.7, FFN1 111 -> 79; text K/V of 1024 rows 22.9 -> 14.1; 14B, 130 rows: O 61 -> 19).
+static int pick_tile(int64_t M, int64_t N, int64_t K, bool vt, int force) {
+  const int cus = device_cus();
+  int best = -1;
+  double best_t = 0.0;
+  for (int i = 0; i < NTILES; ++i) {
+    const TileCfg& c = kTiles[i];
+    if (vt && !c.vt) continue;
+    const int64_t bm = 32 * (vt ? c.xf : c.yf), bn = 32 * (vt ? c.yf : c.xf);
+    if (N % bn) continue;
+    if (i == force) return i;
+    const int64_t tiles = (M + bm - 1) / bm * (N / bn);
+    const int64_t round = (int64_t)c.resident * cus, full = tiles / round, rem = tiles % round;
+    const double l2 = 1.47 * (double)(bm + bn), one = (double)(bm * bn) / 64.0 + 70.0;
+    double t = (double)full * std::max(c.resident * l2, one);
+    if (rem) t += std::max((double)((rem + cus - 1) / cus) * l2, one);
+    t = t * (double)(K / 64) + 500.0 * (double)(full + (rem != 0));
+    if (best < 0 || t < best_t) {
+      best = i;
+      best_t = t;
+    }
+  }
+  return best;
+}
+
+template <int XF, int YF, int NS, bool VT>
+static void launch_tile(int epi, const bf16_t* A, int64_t lda, const bf16_t* W, int64_t M, int N, int K,
+                        const EpiArgs& e, hipStream_t s) {
+  const int bm = 32 * (epi == EPI_BIAS_VT ? XF : YF), bn = 32 * (epi == EPI_BIAS_VT ? YF : XF);
+  dim3 grid((unsigned)((M + bm - 1) / bm) * (unsigned)(N / bn)), block(256);
+  constexpr int GB = 8;  // height of the bands of M-tiles swept across N
+#define TRACK_TK(E) gemm_bf16_tile_kernel<XF, YF, NS, E><<<grid, block, 0, s>>>(A, lda, W, M, N, K, e, GB)
+  if constexpr (VT) {
+    if (epi == EPI_BIAS_VT) {
+      TRACK_TK(EPI_BIAS_VT);
+      return;
+    }
+  }
+  switch (epi) {
+    case TRACK_EPI_BIAS: TRACK_TK(TRACK_EPI_BIAS); break;
+    case TRACK_EPI_BIAS_GELU: TRACK_TK(TRACK_EPI_BIAS_GELU); break;
+    case TRACK_EPI_GATE_RESID: TRACK_TK(TRACK_EPI_GATE_RESID); break;
+    case TRACK_EPI_RESID: TRACK_TK(TRACK_EPI_RESID); break;
+    default: TRACK_TK(TRACK_EPI_BIAS_F32); break;
+  }
+#undef TRACK_TK
 }
 
 // The persistent kernel addresses A through a buffer resource whose size
@@ -707,6 +923,23 @@ static void launch_bf16_persist(int epi, const bf16_t* A, int64_t lda, const bf1
       default: TRACK_PK(TRACK_EPI_BIAS_F32); break;
     }
 #undef TRACK_PK
+  }
+}
+
+static void launch_bf16(int tile, int epi, const bf16_t* A, int64_t lda, const bf16_t* W, int64_t M, int N, int K,
+                        const EpiArgs& e, int out_elem, hipStream_t s) {
+  switch (tile) {
+    case 0: launch_bf16_persist(epi, A, lda, W, M, N, K, e, out_elem, s); break;
+    case 1: launch_tile<8, 4, 3, false>(epi, A, lda, W, M, N, K, e, s); break;
+    case 2: launch_tile<4, 8, 3, true>(epi, A, lda, W, M, N, K, e, s); break;
+    case 3: launch_tile<4, 5, 4, false>(epi, A, lda, W, M, N, K, e, s); break;
+    case 4: launch_tile<4, 5, 2, false>(epi, A, lda, W, M, N, K, e, s); break;
+    case 5: launch_tile<4, 4, 4, true>(epi, A, lda, W, M, N, K, e, s); break;
+    case 6: launch_tile<4, 3, 4, false>(epi, A, lda, W, M, N, K, e, s); break;
+    case 7: launch_tile<4, 2, 3, false>(epi, A, lda, W, M, N, K, e, s); break;
+    case 8: launch_tile<2, 4, 3, true>(epi, A, lda, W, M, N, K, e, s); break;
+    case 9: launch_tile<2, 2, 4, true>(epi, A, lda, W, M, N, K, e, s); break;
+    default: launch_tile<2, 1, 4, false>(epi, A, lda, W, M, N, K, e, s); break;
   }
 }
 
@@ -742,24 +975,11 @@ track_status linear(int dtype, int epi, int64_t M, int64_t N, int64_t K, const v
   const bf16_t* a = (const bf16_t*)A;
   const bf16_t* w = (const bf16_t*)W;
   const int n = (int)N, k = (int)K;
-  const int64_t big = ((M + 255) / 256) * (N / 256);
-  const int force = gemm_config();
   const int out_elem = (epi == TRACK_EPI_BIAS || epi == TRACK_EPI_BIAS_GELU) ? 2 : 4;
-  if (force == 1 && N % 256 == 0)
-    launch_bf16_cfg<256, 256>(epi, a, lda, w, M, n, k, e, s);
-  else if (force == 2 && N % 128 == 0)
-    launch_bf16_cfg<128, 128>(epi, a, lda, w, M, n, k, e, s);
-  else if (force == 3 && N % 128 == 0)
-    launch_bf16_cfg<256, 128>(epi, a, lda, w, M, n, k, e, s);
-  // the persistent kernel for at least two tiles per CU, or, with a long K
-  // (the 14B-width text K/V projection: 160 tiles, K 5120, 0.11 against
-  // 0.17 ms), at least half a tile per CU
-  else if (N % 256 == 0 && (big >= 512 || (big >= 128 && K >= 4096) || force == 4) && lda < ((int64_t)1 << 22))
-    launch_bf16_persist(epi, a, lda, w, M, n, k, e, out_elem, s);
-  else if (N % 128 == 0)
-    launch_bf16_cfg<128, 128>(epi, a, lda, w, M, n, k, e, s);
+  if (lda >= BUF_LD || K >= BUF_LD)
+    launch_bf16_big_ld(epi, a, lda, w, M, n, k, e, s);
   else
-    launch_bf16_cfg<128, 64>(epi, a, lda, w, M, n, k, e, s);
+    launch_bf16(pick_tile(M, N, K, false, gemm_config()), epi, a, lda, w, M, n, k, e, out_elem, s);
   TRACK_LAUNCH_CHECK();
   return TRACK_OK;
 }
@@ -782,7 +1002,8 @@ track_status linear_vt(int64_t M, int64_t N, int64_t K, const void* A, int64_t l
   e.m_off = 0;
   e.nv = (int)N;
   ProfScope prof(TRACK_PROF_GEMM, s);
-  launch_bf16_persist(EPI_BIAS_VT, (const bf16_t*)A, lda, (const bf16_t*)W, M, (int)N, (int)K, e, 2, s);
+  launch_bf16(K < BUF_LD ? pick_tile(M, N, K, true, gemm_config()) : 0, EPI_BIAS_VT, (const bf16_t*)A, lda,
+              (const bf16_t*)W, M, (int)N, (int)K, e, 2, s);
   TRACK_LAUNCH_CHECK();
   return TRACK_OK;
 }

@@ -483,6 +483,51 @@ def test_linear_persistent_row_blocks(epi):
     np.testing.assert_allclose(got, ref, rtol=0, atol=8 * tol * (np.abs(ref).max() + 1))
 
 
+@pytest.mark.parametrize("M,N,K", [(1, 256, 64), (33, 512, 128), (161, 256, 192), (1000, 768, 1088), (257, 64, 320)])
+def test_linear_tiles_agree(M, N, K, monkeypatch):
+    """Every tile kernel (TRACK_GEMM_CFG = 10 + entry) at one slab, fewer slabs
+    than its ring holds and more, on ragged M-tiles: all sum each output over K
+    in the same order, so the tile choice changes no bit, and the automatic
+    choice agrees with the oracle.  Forced tiles that do not divide N fall back."""
+    say(f"linear tiles M={M} N={N} K={K}")
+    A = normal((8600, M, K), (M, K), 1.0, True)
+    W = normal((8601, N, K), (N, K), 0.05, True)
+    b = normal((8602, N), (N,), 0.1, True)
+    gate = normal((8603, N), (N,), 1.0)
+    resid = normal((8604, M, N), (M, N), 1.0)
+    for epi in EPIS:
+        monkeypatch.delenv("TRACK_GEMM_CFG", raising=False)
+        auto = _run_linear(BF16, epi, A, W, b, gate, resid)
+        tol = 1e-5 if epi in (track.EPI_GATE_RESID, track.EPI_RESID, track.EPI_BIAS_F32) else 4e-3
+        ref = _linear_ref(epi, A, W, b, gate, resid)
+        assert rel_l2(auto, ref) < tol, (epi, rel_l2(auto, ref))
+        for i in range(11):
+            monkeypatch.setenv("TRACK_GEMM_CFG", str(10 + i))
+            assert np.array_equal(_run_linear(BF16, epi, A, W, b, gate, resid), auto), (epi, i)
+
+
+@pytest.mark.parametrize("B,L,N,K", [(1, 128, 256, 64), (3, 136, 512, 128), (2, 1000, 256, 704)])
+def test_linear_vt_tiles_agree(B, L, N, K, monkeypatch):
+    """The transposed-output tiles: same bits as the persistent kernel, columns past L untouched."""
+    import torch
+    say(f"linear_vt tiles B={B} L={L} N={N} K={K}")
+    M, ldv = B * L, L + 24
+    A = dev(normal((8610, M, K), (M, K), 1.0, True), BF16)
+    W = normal((8611, N, K), (N, K), 0.05, True)
+    b = normal((8612, N), (N,), 0.1, True)
+    outs = []
+    for cfg in [0, 4] + list(range(10, 21)):
+        monkeypatch.setenv("TRACK_GEMM_CFG", str(cfg))
+        vt = torch.full((B * N, ldv), 7.0, dtype=torch.bfloat16, device="cuda")
+        track.op_linear_vt(A, dev(W, BF16), dev(b, BF16), L, vt, ldv)
+        outs.append(host(vt))
+        assert np.array_equal(outs[-1], outs[0]), cfg
+    v = outs[0].reshape(B, N, ldv)
+    assert np.all(v[:, :, L:] == 7.0)
+    ref = dit.linear(host(A).astype(np.float64), W, b)
+    assert rel_l2(v[:, :, :L].transpose(0, 2, 1).reshape(M, N), ref) < 4e-3
+
+
 @pytest.mark.parametrize("B,L,N,K,ldv", [(2, 1000, 512, 320, 1008), (3, 136, 256, 64, 136),
                                           (2, 32760, 1536, 1536, 32768), (2, 70000, 256, 8192, 70000)])
 def test_linear_vt(B, L, N, K, ldv):
