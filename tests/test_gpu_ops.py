@@ -201,6 +201,33 @@ def test_attention_f32(dh, Lq, Lk):
     assert rel_l2(got, ref) < 1e-5, rel_l2(got, ref)
 
 
+# float32 attention rounds each product and sum at 2^-24; over dh 128 and these keys the errors add to
+# a few 1e-7, and 2e-6 (a sequential float32 chain's level) bounds them
+@pytest.mark.parametrize("dh", [32, 64, 128])
+@pytest.mark.parametrize("B,H,Lq,Lk", [(1, 1, 1, 1), (1, 3, 16, 15), (2, 1, 17, 16), (1, 2, 33, 65), (2, 2, 48, 130),
+                                       (2, 8, 1030, 33)])
+@pytest.mark.parametrize("pad", [0, 1])
+def test_attention_f32_forms(dh, B, H, Lq, Lk, pad):
+    """One query block per workgroup with the keys over its waves (the small cases) and a query block per wave
+    (the last), with 16-byte aligned rows (pad 0) and rows of any alignment (pad 1); V^T's padding holds NaN,
+    which no output may see."""
+    say(f"attention f32 dh={dh} B={B} H={H} Lq={Lq} Lk={Lk} pad={pad}")
+    import torch
+    w, key = H * dh, 6300 + dh + Lq + Lk
+    q, k, v = (normal((key, i), (B * n, w)) for i, n in ((1, Lq), (2, Lk), (3, Lk)))
+    ldv = (Lk + 3) // 4 * 4 + pad
+    vt = vt_layout(v, B, Lk, H, dh, ldv)
+    vt[..., Lk:] = np.nan
+    tq, tk, out = (torch.full((B * n, w + pad), float("nan"), device="cuda") for n in (Lq, Lk, Lq))
+    tq[:, :w], tk[:, :w] = dev(q), dev(k)
+    track.op_attention(track.DTYPE_F32, B, H, dh, Lq, Lk, tq, w + pad, tk, w + pad, dev(vt), ldv, out, w + pad)
+    got = host(out)[:, :w].reshape(B, Lq, H, dh)
+    ref = np.stack([dit.attention(q.reshape(B, Lq, H, dh)[b].astype(np.float64),
+                                  k.reshape(B, Lk, H, dh)[b].astype(np.float64),
+                                  v.reshape(B, Lk, H, dh)[b].astype(np.float64)) for b in range(B)])
+    assert rel_l2(got, ref) < 2e-6, rel_l2(got, ref)
+
+
 def test_attention_errors_and_empty():
     import torch
     z = torch.zeros(64, 128, dtype=torch.bfloat16, device="cuda")
