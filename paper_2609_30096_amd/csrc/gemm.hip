@@ -785,6 +785,78 @@ __global__ __launch_bounds__(256) void gemm_f32_kernel(const float* __restrict__
   }
 }
 
+// Few-tile float32 GEMM on v_mfma_f32_16x16x4_f32 (float32 products and sums): a
+// workgroup owns 16 T x 16 T outputs and its four waves share K, every fourth
+// 16-deep chunk each, joined through LDS.  The small float32 models' products (128
+// rows, K 128 - 512) are a latency chain: here one global load and K / 64 short
+// steps, where the LDS tiles above took a load, two barriers and a store per 16 of
+// K on a handful of CUs.  K-index i of chunk kc is k = 16 kc + 4 (lane / 16) + i, so
+// every lane loads 16 bytes.  Needs K % 4 == 0 and 16-byte aligned rows.
+template <int EPI, int T>
+__global__ __launch_bounds__(256) void gemm_f32_small_kernel(const float* __restrict__ A, int64_t lda,
+                                                             const float* __restrict__ W, int64_t M, int N, int K,
+                                                             EpiArgs e) {
+  __shared__ f32x4 red[4][T * T][64];
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  const int j = lane & 15, g = lane >> 4;
+  const int64_t m0 = (int64_t)blockIdx.y * 16 * T;
+  const int n0 = blockIdx.x * 16 * T;
+  const float *ap[T], *wp[T];
+#pragma unroll
+  for (int t = 0; t < T; ++t) {
+    const int64_t m = m0 + 16 * t + j;
+    const int n = n0 + 16 * t + j;
+    ap[t] = A + (m < M ? m : M - 1) * lda + 4 * g;
+    wp[t] = W + (int64_t)(n < N ? n : N - 1) * K + 4 * g;
+  }
+  f32x4 acc[T][T];  // features 4 g + r of block x, token j of block y
+#pragma unroll
+  for (int x = 0; x < T; ++x)
+#pragma unroll
+    for (int y = 0; y < T; ++y) acc[x][y] = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
+  const int chunks = (K + 15) / 16;
+  constexpr int U = 4 / T;  // chunks whose loads are issued together
+  for (int kc = wave; kc < chunks; kc += 4 * U) {
+    f32x4 a[U][T], w[U][T];
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      const int k0 = 16 * (kc + 4 * u);
+      const bool in = k0 + 4 * g < K;
+#pragma unroll
+      for (int t = 0; t < T; ++t) {
+        a[u][t] = in ? *(const f32x4*)(ap[t] + k0) : f32x4{0.0f, 0.0f, 0.0f, 0.0f};
+        w[u][t] = in ? *(const f32x4*)(wp[t] + k0) : f32x4{0.0f, 0.0f, 0.0f, 0.0f};
+      }
+    }
+#pragma unroll
+    for (int u = 0; u < U; ++u)
+#pragma unroll
+      for (int i = 0; i < 4; ++i)
+#pragma unroll
+        for (int x = 0; x < T; ++x)
+#pragma unroll
+          for (int y = 0; y < T; ++y)
+            acc[x][y] = __builtin_amdgcn_mfma_f32_16x16x4f32(w[u][x][i], a[u][y][i], acc[x][y], 0, 0, 0);
+  }
+#pragma unroll
+  for (int x = 0; x < T; ++x)
+#pragma unroll
+    for (int y = 0; y < T; ++y) red[wave][x * T + y][lane] = acc[x][y];
+  __syncthreads();
+  // thread -> token threadIdx / 16, feature threadIdx % 16 of each 16 x 16 block
+  const int tm = threadIdx.x >> 4, tn = threadIdx.x & 15, src = (tn >> 2) * 16 + tm, r = tn & 3;
+#pragma unroll
+  for (int x = 0; x < T; ++x)
+#pragma unroll
+    for (int y = 0; y < T; ++y) {
+      const int64_t m = m0 + 16 * y + tm;
+      const int n = n0 + 16 * x + tn;
+      if (m < M && n < N)
+        epi_store1<EPI, float>(e, m, n, (red[0][x * T + y][src][r] + red[1][x * T + y][src][r]) +
+                                            (red[2][x * T + y][src][r] + red[3][x * T + y][src][r]));
+    }
+}
+
 // ------------------------------------------------------------------ launchers
 // The register-staged kernel, for leading dimensions whose tiles a buffer
 // resource cannot address (BUF_LD and up).
@@ -943,6 +1015,30 @@ static void launch_bf16(int tile, int epi, const bf16_t* A, int64_t lda, const b
   }
 }
 
+static void launch_f32(int epi, const float* A, int64_t lda, const float* W, int64_t M, int N, int K,
+                       const EpiArgs& e, hipStream_t s) {
+  const int64_t t16 = ((M + 15) / 16) * ((N + 15) / 16);
+  const bool aligned = K % 4 == 0 && lda % 4 == 0 && (((uintptr_t)A | (uintptr_t)W) & 15) == 0;
+  const int64_t cus = device_cus();
+  const int t = !aligned || t16 > 32 * cus ? 0 : (t16 > 4 * cus ? 2 : 1);
+  dim3 block(256), grid = t ? dim3((unsigned)((N + 16 * t - 1) / (16 * t)), (unsigned)((M + 16 * t - 1) / (16 * t)))
+                            : dim3((unsigned)((N + 63) / 64), (unsigned)((M + 63) / 64));
+#define TRACK_F32(E)                                                                     \
+  do {                                                                                   \
+    if (t == 1) gemm_f32_small_kernel<E, 1><<<grid, block, 0, s>>>(A, lda, W, M, N, K, e); \
+    else if (t == 2) gemm_f32_small_kernel<E, 2><<<grid, block, 0, s>>>(A, lda, W, M, N, K, e); \
+    else gemm_f32_kernel<E><<<grid, block, 0, s>>>(A, lda, W, M, N, K, e);               \
+  } while (0)
+  switch (epi) {
+    case TRACK_EPI_BIAS: TRACK_F32(TRACK_EPI_BIAS); break;
+    case TRACK_EPI_BIAS_GELU: TRACK_F32(TRACK_EPI_BIAS_GELU); break;
+    case TRACK_EPI_GATE_RESID: TRACK_F32(TRACK_EPI_GATE_RESID); break;
+    case TRACK_EPI_RESID: TRACK_F32(TRACK_EPI_RESID); break;
+    default: TRACK_F32(TRACK_EPI_BIAS_F32); break;
+  }
+#undef TRACK_F32
+}
+
 track_status linear(int dtype, int epi, int64_t M, int64_t N, int64_t K, const void* A, int64_t lda, const void* W,
                     const void* bias, const float* gate, void* out, int64_t ldo, hipStream_t s) {
   if (M <= 0 || N <= 0 || K <= 0) return fail(TRACK_E_SHAPE, "linear: empty shape M=%lld N=%lld K=%lld", (long long)M, (long long)N, (long long)K);
@@ -954,16 +1050,7 @@ track_status linear(int dtype, int epi, int64_t M, int64_t N, int64_t K, const v
   EpiArgs e{bias, gate, out, ldo};
   ProfScope prof(TRACK_PROF_GEMM, s);
   if (dtype == TRACK_DTYPE_F32) {
-    dim3 grid((unsigned)((N + 63) / 64), (unsigned)((M + 63) / 64)), block(256);
-    const float* a = (const float*)A;
-    const float* w = (const float*)W;
-    switch (epi) {
-      case TRACK_EPI_BIAS: gemm_f32_kernel<TRACK_EPI_BIAS><<<grid, block, 0, s>>>(a, lda, w, M, (int)N, (int)K, e); break;
-      case TRACK_EPI_BIAS_GELU: gemm_f32_kernel<TRACK_EPI_BIAS_GELU><<<grid, block, 0, s>>>(a, lda, w, M, (int)N, (int)K, e); break;
-      case TRACK_EPI_GATE_RESID: gemm_f32_kernel<TRACK_EPI_GATE_RESID><<<grid, block, 0, s>>>(a, lda, w, M, (int)N, (int)K, e); break;
-      case TRACK_EPI_RESID: gemm_f32_kernel<TRACK_EPI_RESID><<<grid, block, 0, s>>>(a, lda, w, M, (int)N, (int)K, e); break;
-      default: gemm_f32_kernel<TRACK_EPI_BIAS_F32><<<grid, block, 0, s>>>(a, lda, w, M, (int)N, (int)K, e); break;
-    }
+    launch_f32(epi, (const float*)A, lda, (const float*)W, M, (int)N, (int)K, e, s);
     TRACK_LAUNCH_CHECK();
     return TRACK_OK;
   }

@@ -73,6 +73,22 @@ def test_linear_small(dtype, epi, M, N, K):
     np.testing.assert_allclose(got, ref, rtol=0, atol=8 * tol * (np.abs(ref).max() + 1))
 
 
+# float32: sums of K terms in other orders differ by a few 1e-7 (K up to 640 here)
+@pytest.mark.parametrize("epi", EPIS)
+@pytest.mark.parametrize("M,N,K", [(1, 1, 4), (16, 17, 20), (33, 31, 64), (130, 100, 260), (700, 900, 68), (50, 40, 30)])
+def test_linear_f32_few_tiles(epi, M, N, K):
+    """The K-sharing kernel at one and two 16 x 16 blocks a side, with ragged M, N and K, and (K 30) the
+    kernel it leaves to rows that are not 16-byte aligned."""
+    say(f"linear f32 few tiles epi={epi} M={M} N={N} K={K}")
+    key = 5300 + M + N + K
+    A, W, b = normal((key, 1), (M, K)), normal((key, 2), (N, K), 0.05), normal((key, 3), (N,), 0.1)
+    gate = normal((key, 4), (N,)) if epi == track.EPI_GATE_RESID else None
+    resid = normal((key, 5), (M, N)) if epi in (track.EPI_GATE_RESID, track.EPI_RESID) else None
+    got = _run_linear(F32, epi, A, W, b, gate, resid)
+    ref = _linear_ref(epi, *(None if x is None else x.astype(np.float64) for x in (A, W, b, gate, resid)))
+    assert rel_l2(got, ref) < 2e-6, rel_l2(got, ref)
+
+
 def test_linear_rejects_bad_shapes():
     import torch
     A = torch.zeros(10, 60, dtype=torch.bfloat16, device="cuda")
