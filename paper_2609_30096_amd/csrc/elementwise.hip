@@ -183,25 +183,28 @@ __host__ __device__ __forceinline__ void rope_widths(int dh, int n[3]) {
   n[0] = dh - 2 * n[1];
 }
 
-__global__ void rope_tables_kernel(int dh, int E0, int E1, int E2, float* cos_t, float* sin_t) {
+// One thread per entry: a float64 pow, cos and sin each, a chain long enough
+// that a single workgroup took 25 us over the 2186 entries of a 21 x 30 x 52 grid.
+__global__ __launch_bounds__(64) void rope_tables_kernel(int dh, int E0, int E1, int E2, float* cos_t, float* sin_t) {
   int n[3];
   rope_widths(dh, n);
-  const int E[3] = {E0, E1, E2};
-  int off = 0;
-  for (int a = 0; a < 3; ++a) {
-    const int half = n[a] / 2;
-    for (int i = threadIdx.x; i < E[a] * half; i += blockDim.x) {
-      const int pos = i / half, p = i % half;
-      const double ang = (double)pos * pow(10000.0, -2.0 * (double)p / (double)n[a]);
-      cos_t[off + i] = (float)cos(ang);
-      sin_t[off + i] = (float)sin(ang);
-    }
-    off += E[a] * half;
-  }
+  const int h0 = n[0] / 2, h1 = n[1] / 2, c0 = E0 * h0, c1 = c0 + E1 * h1, c2 = c1 + E2 * h1;
+  const int e = blockIdx.x * 64 + threadIdx.x;
+  if (e >= c2) return;
+  const int a = e < c0 ? 0 : (e < c1 ? 1 : 2);
+  const int i = e - (a == 0 ? 0 : (a == 1 ? c0 : c1)), half = a == 0 ? h0 : h1;
+  const int pos = i / half, p = i % half;
+  const double ang = (double)pos * pow(10000.0, -2.0 * (double)p / (double)n[a]);
+  cos_t[e] = (float)cos(ang);
+  sin_t[e] = (float)sin(ang);
 }
 
 track_status rope_tables(int head_dim, Grid3 g, float* cos_t, float* sin_t, hipStream_t s) {
-  rope_tables_kernel<<<1, 256, 0, s>>>(head_dim, g.f, g.h, g.w, cos_t, sin_t);
+  int n[3];
+  rope_widths(head_dim, n);
+  const int64_t count = (int64_t)g.f * (n[0] / 2) + ((int64_t)g.h + g.w) * (n[1] / 2);
+  if (count == 0) return TRACK_OK;
+  rope_tables_kernel<<<cdiv(count, 64), 64, 0, s>>>(head_dim, g.f, g.h, g.w, cos_t, sin_t);
   TRACK_LAUNCH_CHECK();
   return TRACK_OK;
 }
@@ -476,7 +479,8 @@ __global__ __launch_bounds__(256) void rmsnorm_rope_kernel(int64_t rows, int d, 
       }
     }
   }
-  row_sums<WPR, RPB>(sq, red);
+  // the rows' positions and, where a lane's are the same in every chunk, its
+  // rotation angles: fetched while the rows are on their way
   int n[3];
   rope_widths(dh, n);
   const int h0 = n[0] / 2, h1 = n[1] / 2, h2 = n[2] / 2;
@@ -485,6 +489,50 @@ __global__ __launch_bounds__(256) void rmsnorm_rope_kernel(int64_t rows, int d, 
   // elements sit at the same offset of their head in every chunk, so its
   // rotation angles are loaded once per row instead of once per chunk.
   const bool lane_fixed = cos_t && ((E * CS) % dh) == 0;
+  int pos[RPB][3];
+  float cf[RPB][E / 2], sf[RPB][E / 2];
+  auto table_index = [&](const int (&ps)[3], int p) {  // p: pair index within the head
+    if (p < h0) return ps[0] * h0 + p;
+    if (p < h0 + h1) return off1 + ps[1] * h1 + (p - h0);
+    return off2 + ps[2] * h2 + (p - h0 - h1);
+  };
+#pragma unroll
+  for (int r = 0; r < RPB; ++r) {
+    const int64_t row = g2 ? (row0 + r) >> 1 : row0 + r;
+    pos[r][0] = pos[r][1] = pos[r][2] = 0;
+    if (r & 1 && g2) {  // the k segment of the same row (row0 is even)
+#pragma unroll
+      for (int a = 0; a < 3; ++a) pos[r][a] = pos[r - 1][a];
+    } else if (cos_t) {
+      if (((row | L) >> 31) == 0) {  // (a 64-bit division is some 100 instructions)
+        const uint32_t l = (uint32_t)row % (uint32_t)L, lw = l / (uint32_t)Gw;
+        pos[r][2] = (int)(l - lw * Gw);
+        pos[r][1] = (int)(lw % (uint32_t)Gh);
+        pos[r][0] = (int)(lw / (uint32_t)Gh);
+      } else {
+        const int64_t l = row % L;
+        pos[r][2] = (int)(l % Gw);
+        pos[r][1] = (int)((l / Gw) % Gh);
+        pos[r][0] = (int)(l / ((int64_t)Gw * Gh));
+      }
+    }
+#pragma unroll
+    for (int pr = 0; pr < E / 2; ++pr) {
+      if (r & 1 && g2) {
+        cf[r][pr] = cf[r - 1][pr];
+        sf[r][pr] = sf[r - 1][pr];
+      } else {
+        cf[r][pr] = 1.0f;
+        sf[r][pr] = 0.0f;
+        if (lane_fixed) {
+          const int idx = table_index(pos[r], ((E * t) % dh) / 2 + pr);
+          cf[r][pr] = cos_t[idx];
+          sf[r][pr] = sin_t[idx];
+        }
+      }
+    }
+  }
+  row_sums<WPR, RPB>(sq, red);
 #pragma unroll
   for (int r = 0; r < RPB; ++r) {
     const int64_t vrow = row0 + r;
@@ -493,32 +541,6 @@ __global__ __launch_bounds__(256) void rmsnorm_rope_kernel(int64_t rows, int d, 
     const int seg = g2 ? (int)(vrow & 1) : 0;
     const T* gs = seg ? g2 : g;
     const float rstd = (1.0f / sqrtf(sq[r] / (float)d + 1e-6f)) * (seg ? 1.0f : qscale);
-    int pos[3] = {0, 0, 0};
-    if (cos_t) {
-      const int64_t l = row % L;
-      pos[2] = (int)(l % Gw);
-      pos[1] = (int)((l / Gw) % Gh);
-      pos[0] = (int)(l / ((int64_t)Gw * Gh));
-    }
-    auto table_index = [&](int p) {  // p: pair index within the head
-      if (p < h0) return pos[0] * h0 + p;
-      if (p < h0 + h1) return off1 + pos[1] * h1 + (p - h0);
-      return off2 + pos[2] * h2 + (p - h0 - h1);
-    };
-    float cf[E / 2], sf[E / 2];
-#pragma unroll
-    for (int pr = 0; pr < E / 2; ++pr) {
-      cf[pr] = 1.0f;
-      sf[pr] = 0.0f;
-    }
-    if (lane_fixed) {
-#pragma unroll
-      for (int pr = 0; pr < E / 2; ++pr) {
-        const int idx = table_index(((E * t) % dh) / 2 + pr);
-        cf[pr] = cos_t[idx];
-        sf[pr] = sin_t[idx];
-      }
-    }
     T* xr = buf + row * ld + col0 + (int64_t)seg * d;
 #pragma unroll
     for (int i = 0; i < NC; ++i) {
@@ -532,9 +554,9 @@ __global__ __launch_bounds__(256) void rmsnorm_rope_kernel(int64_t rows, int d, 
         if (cos_t) {
 #pragma unroll
           for (int pr = 0; pr < E / 2; ++pr) {
-            float c = cf[pr], s = sf[pr];
+            float c = cf[r][pr], s = sf[r][pr];
             if (!lane_fixed) {
-              const int idx = table_index(((E * ch) % dh) / 2 + pr);
+              const int idx = table_index(pos[r], ((E * ch) % dh) / 2 + pr);
               c = cos_t[idx];
               s = sin_t[idx];
             }
