@@ -115,7 +115,9 @@ __device__ __forceinline__ bf16x8 att_sum_selector(int lane) {
 // The row sum of the lane's query (l % 32) from the accumulated selector products.
 __device__ __forceinline__ float att_row_sum(att_f32x4 ls, int lane) {
   const int q = lane & 31;
-  const float a = __shfl(ls[0], q & 15), b = __shfl(ls[1], q & 15);
+  const int src = (q & 15) << 2;
+  const float a = __int_as_float(__builtin_amdgcn_ds_bpermute(src, __float_as_int(ls[0])));
+  const float b = __int_as_float(__builtin_amdgcn_ds_bpermute(src, __float_as_int(ls[1])));
   return q < 16 ? a : b;
 }
 
@@ -150,12 +152,17 @@ __device__ __forceinline__ void att_tile(const uint8_t* kb, const bf16x8 (&qf)[A
       s[sb] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(kf[kc & 1][sb], qf[kc], s[sb], 0, 0, 0);
   }
   float mx = -INFINITY;
+  // valid keys from this half-wave's first on (opaque, so that the comparisons are
+  // formed here rather than kept across the tiles)
+  int lim = Lk - key0 - 8 * hf;
+  if constexpr (MASK) asm volatile("" : "+v"(lim));
 #pragma unroll
   for (int sb = 0; sb < NSB; ++sb)
 #pragma unroll
     for (int r = 0; r < 16; ++r) {
       if constexpr (MASK) {
-        if (key0 + key_of_row(32 * sb + 8 * (r >> 2) + 4 * hf + (r & 3)) >= Lk) s[sb][r] = -INFINITY;
+        // row 32 sb + 8 (r / 4) + 4 hf + r % 4 of the tile: its key_of_row less 8 hf
+        if (32 * sb + 16 * (r >> 3) + 4 * ((r >> 2) & 1) + (r & 3) >= lim) s[sb][r] = -INFINITY;
       }
       mx = fmaxf(mx, s[sb][r]);
     }
@@ -370,6 +377,15 @@ __global__ __launch_bounds__(512) void flash_attn_bf16_kernel(const bf16_t* __re
 // LDS reads instead of a global load.  Every wave reads back only the Q rows
 // that it copied itself, so those copies need no barrier.  ntiles must be
 // even: a tile's ring slot is then its index within the item modulo 2.
+//
+// All workgroups finish their items together, and the burst of output stores
+// (16 MB over the chip) takes longer than a tile.  vmcnt counts loads and stores
+// alike, in order, so a copy issued behind the stores would make the next item's
+// first tile wait for them.  The next item's first two tiles are therefore
+// copied (and its Q registers read) before the stores are issued, and its first
+// tile waits only for what precedes them; the Q copies, as many bytes again, are
+// spread over an item's last tiles.  2 x 12 heads, 32760 queries: 240.9 -> 229.7 us at 512
+// keys (0.90 PFLOP/s; 8 tiles of 1.75 us and 4.5 us at the item's ends), 187 -> 161 at 226.
 template <int KIND, bool QLOG2>
 __global__ __launch_bounds__(512) void flash_attn_items_kernel(const bf16_t* __restrict__ q, int64_t ldq,
                                                                const bf16_t* __restrict__ k, int64_t ldk,
@@ -435,9 +451,10 @@ __global__ __launch_bounds__(512) void flash_attn_items_kernel(const bf16_t* __r
       __builtin_amdgcn_raw_ptr_buffer_load_lds(rsV, (att_lds_ptr_t)(smem + S * SLOT + K_BYTES + wave * 2048 + i * 1024),
                                                16, voffg[i] + (uint32_t)(key0 * 2), 0, 0, 0);
   };
-  // this wave's 32 Q rows of item it into LDS (rows past Lq read as zero)
-  auto issue_q = [&](int it) {
-    if (it >= nitems) return;
+  // pieces i0 .. i1 - 1 (of 8) of this wave's 32 Q rows of item it into LDS (rows
+  // past Lq read as zero)
+  auto issue_q = [&](int it, int i0, int i1) {
+    if (it >= nitems || i0 >= i1) return;
     int qb, h, b;
     split(it, qb, h, b);
     const int r0 = qb * BQ + wave * 32;
@@ -445,13 +462,12 @@ __global__ __launch_bounds__(512) void flash_attn_items_kernel(const bf16_t* __r
     const __amdgpu_buffer_rsrc_t rsQ =
         __builtin_amdgcn_make_buffer_rsrc((void*)(q + ((int64_t)b * Lq + r0) * ldq + (int64_t)h * D), (short)0,
                                           (int)(uint32_t)(nrows * ldq * 2), 0x00020000);
-    // copy i (0..7) fills LDS rows 4 i .. 4 i + 3 of the wave's 32 (1 KB);
+    // piece i fills LDS rows 4 i .. 4 i + 3 of the wave's 32 (1 KB);
     // unit u of row r sits at u ^ (r & 15).  The lane index is made opaque so
     // that these offsets are formed here, not kept live across the tiles.
     int ln = lane;
     asm volatile("" : "+v"(ln));
-#pragma unroll
-    for (int i = 0; i < 8; ++i) {
+    for (int i = i0; i < i1; ++i) {
       const int r = 4 * i + (ln >> 4);
       const uint32_t off = (uint32_t)((r * ldq + ((ln & 15) ^ (r & 15)) * 8) * 2);
       __builtin_amdgcn_raw_ptr_buffer_load_lds(rsQ, (att_lds_ptr_t)(qs + wave * 32 * QROW + i * 1024), 16, off, 0, 0, 0);
@@ -483,53 +499,84 @@ __global__ __launch_bounds__(512) void flash_attn_items_kernel(const bf16_t* __r
   };
   using S0 = std::integral_constant<int, 0>;
   using S1 = std::integral_constant<int, 1>;
-  // tile t of item it in slot S, the copy of the tile after it in flight
-  auto tile = [&](int it, int t, auto slot_tag, auto mask_tag) {
+  // 16-byte output stores of an item per wave.  They go through a buffer resource
+  // (rows past Lq are dropped there, not masked), so every wave issues as many.
+  constexpr int NST = D / 16;
+  // Q pieces per tile: the 8 pieces over the item's last tiles, away from the stores
+  const int qper = ntiles > 8 ? 1 : (ntiles > 4 ? 2 : (ntiles > 2 ? 4 : 8));
+  auto store_item = [&](int it) {
+    int qb, h, b;
+    split(it, qb, h, b);
+    const int r0 = qb * BQ + wave * 32;
+    const int nrows = __builtin_amdgcn_readfirstlane(max(0, min(32, Lq - r0)));
+    const __amdgpu_buffer_rsrc_t rsO =
+        __builtin_amdgcn_make_buffer_rsrc((void*)(out + ((int64_t)b * Lq + r0) * ldo + (int64_t)h * D), (short)0,
+                                          (int)(uint32_t)(nrows * ldo * 2), 0x00020000);
+    // the lane index, formed here so that neither it nor the offset is spilled
+    // across the tiles (a reload would wait for the copies just issued)
+    int ln;
+    asm volatile("v_mbcnt_lo_u32_b32 %0, -1, 0\n\tv_mbcnt_hi_u32_b32 %0, -1, %0" : "=v"(ln));
+    const float inv = 1.0f / att_row_sum(lsum, ln);
+    const uint32_t off = (uint32_t)(((ln & 31) * ldo + 8 * (ln >> 5)) * 2);
+#pragma unroll
+    for (int db = 0; db < D / 32; ++db)
+#pragma unroll
+      for (int rg = 0; rg < 4; rg += 2) {
+        // a lane holds 4 of the 8 channels of groups rg and rg + 1 and its
+        // half-wave partner the other 4: exchanged, each has one whole group
+        const uint32_t a0 = pack_bf2(o[db][4 * rg + 0] * inv, o[db][4 * rg + 1] * inv);
+        const uint32_t a1 = pack_bf2(o[db][4 * rg + 2] * inv, o[db][4 * rg + 3] * inv);
+        const uint32_t b0 = pack_bf2(o[db][4 * rg + 4] * inv, o[db][4 * rg + 5] * inv);
+        const uint32_t b1 = pack_bf2(o[db][4 * rg + 6] * inv, o[db][4 * rg + 7] * inv);
+        const auto x = __builtin_amdgcn_permlane32_swap(a0, b0, false, false);
+        const auto y = __builtin_amdgcn_permlane32_swap(a1, b1, false, false);
+        __builtin_amdgcn_raw_buffer_store_b128(u32x4{(uint32_t)x[0], (uint32_t)y[0], (uint32_t)x[1], (uint32_t)y[1]},
+                                               rsO, off + (uint32_t)((db * 32 + 8 * rg) * 2), 0, 0);
+      }
+  };
+  // tile t of item it in slot S, the copy of the tile after it in flight (the
+  // first tile's successor is under way already, before the last item's stores)
+  auto tile = [&](int it, int t, auto slot_tag, auto mask_tag, bool stores_behind) {
     constexpr int S = decltype(slot_tag)::value;
-    if (t + 1 < ntiles) issue(it, t + 1, std::integral_constant<int, 1 - S>{});
-    else issue(it + G, 0, std::integral_constant<int, 1 - S>{});
+    if (t > 0) {
+      if (t + 1 < ntiles) issue(it, t + 1, std::integral_constant<int, 1 - S>{});
+      else issue(it + G, 0, std::integral_constant<int, 1 - S>{});
+      const int i1 = 8 - (ntiles - 1 - t) * qper;  // the last tiles copy the next item's Q
+      issue_q(it + G, max(0, i1 - qper), min(i1, 8));
+    }
     att_tile<decltype(mask_tag)::value, QLOG2>(smem + S * SLOT, qf, kfo, vfo, o, m_i, thr, zref, lsum, sel, t * BKV, Lk, hf,
                                                scale_log2);
-    att_wait_vmcnt<0>();
+    if (stores_behind) att_wait_vmcnt<NST>();
+    else att_wait_vmcnt<0>();
     __builtin_amdgcn_s_waitcnt((15 << 0) | (3 << 14) | (7 << 4) | (0 << 8));  // lgkmcnt(0)
     __builtin_amdgcn_s_barrier();
   };
+  // the Q of item it to registers, the item's second tile on its way
+  auto begin = [&](int it) {
+    if (it >= nitems) return;
+    read_q();
+    issue(it, 1, S1{});
+    __builtin_amdgcn_sched_barrier(0);
+  };
 
   int it = blockIdx.x;
-  issue_q(it);
+  issue_q(it, 0, 8);
   issue(it, 0, S0{});
   att_wait_vmcnt<0>();
   __builtin_amdgcn_s_barrier();
-  for (; it < nitems; it += G) {
-    read_q();
-    issue_q(it + G);
+  begin(it);
+  for (bool first = true; it < nitems; it += G, first = false) {
     reset();
     int t = 0;
     for (; t + 2 < ntiles; t += 2) {
-      tile(it, t, S0{}, std::false_type{});
-      tile(it, t + 1, S1{}, std::false_type{});
+      tile(it, t, S0{}, std::false_type{}, t == 0 && !first);
+      tile(it, t + 1, S1{}, std::false_type{}, false);
     }
-    tile(it, t, S0{}, std::false_type{});
-    if (Lk % BKV) tile(it, t + 1, S1{}, std::true_type{});
-    else tile(it, t + 1, S1{}, std::false_type{});
-
-    int qb, h, b;
-    split(it, qb, h, b);
-    const float inv = 1.0f / att_row_sum(lsum, lane);
-    const int qi = qb * BQ + wave * 32 + jq;
-    if (qi < Lq) {
-      bf16_t* op = out + ((int64_t)b * Lq + qi) * ldo + (int64_t)h * D;
-#pragma unroll
-      for (int db = 0; db < D / 32; ++db)
-#pragma unroll
-        for (int rg = 0; rg < 4; ++rg) {
-          const int c0 = db * 32 + 8 * rg + 4 * hf;
-          u32x2 pk;
-          pk[0] = pack_bf2(o[db][4 * rg + 0] * inv, o[db][4 * rg + 1] * inv);
-          pk[1] = pack_bf2(o[db][4 * rg + 2] * inv, o[db][4 * rg + 3] * inv);
-          *(u32x2*)(op + c0) = pk;
-        }
-    }
+    tile(it, t, S0{}, std::false_type{}, t == 0 && !first);
+    if (Lk % BKV) tile(it, t + 1, S1{}, std::true_type{}, false);
+    else tile(it, t + 1, S1{}, std::false_type{}, false);
+    begin(it + G);
+    store_item(it);
   }
   att_wait_vmcnt<0>();
 }
@@ -735,7 +782,8 @@ track_status attention(int dtype, int B, int H, int head_dim, int64_t Lq, int64_
     // give identical bits; the tests compare them)
     const char* items_env = getenv("TRACK_ATTN_ITEMS");
     const bool items_ok = !(items_env && items_env[0] == '0');
-    if (items_ok && ntiles % 2 == 0 && ntiles <= ATT_ITEMS_MAX_TILES) {
+    // (the items kernel addresses 32 output rows through a 32-bit buffer size)
+    if (items_ok && ntiles % 2 == 0 && ntiles <= ATT_ITEMS_MAX_TILES && ldo < ((int64_t)1 << 25)) {
       // short key sequence: one workgroup per CU over all (query block, head, batch) items
       const int64_t nitems = (int64_t)grid.x * H * B;
       if (nitems > INT32_MAX) return fail(TRACK_E_SHAPE, "attention: too many query blocks");
