@@ -121,12 +121,15 @@ __device__ __forceinline__ float att_row_sum(att_f32x4 ls, int lane) {
   return q < 16 ? a : b;
 }
 
-template <bool MASK, bool QLOG2>
+// NSB 32-key blocks of the tile (1: the half that kfo and vfo point at).  With
+// SAFE a row whose logits so far are all -inf (a wave of a split sequence can begin
+// with such a tile) takes reference 0 instead of -inf.
+template <bool MASK, bool QLOG2, int NSB = ATT_NSB, bool SAFE = false>
 __device__ __forceinline__ void att_tile(const uint8_t* kb, const bf16x8 (&qf)[ATT_D / 16],
-                                         const uint32_t (&kfo)[ATT_D / 16], const uint32_t (&vfo)[2 * ATT_NSB],
+                                         const uint32_t (&kfo)[ATT_D / 16], const uint32_t (&vfo)[2 * NSB],
                                          f32x16 (&o)[ATT_D / 32], float& m_i, float& thr, bool& zref, att_f32x4& lsum,
                                          const bf16x8& sel, int key0, int Lk, int hf, float scale_log2) {
-  constexpr int D = ATT_D, NSB = ATT_NSB;
+  constexpr int D = ATT_D;
   typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
   const uint8_t* vb = kb + ATT_K_BYTES;
   f32x16 s[NSB];
@@ -170,7 +173,7 @@ __device__ __forceinline__ void att_tile(const uint8_t* kb, const bf16x8 (&qf)[A
   if (__ballot(mt > thr)) {
     float mn = fmaxf(m_i, mt);
     if (mn >= ATT_MLO && mn <= ATT_TAU) mn = 0.0f;
-    const float alpha = __builtin_amdgcn_exp2f(m_i - mn);
+    const float alpha = SAFE && mn == -INFINITY ? 1.0f : __builtin_amdgcn_exp2f(m_i - mn);
     m_i = mn;
     thr = mn + ATT_TAU;
     zref = !__ballot(mn != 0.0f);
@@ -184,7 +187,7 @@ __device__ __forceinline__ void att_tile(const uint8_t* kb, const bf16x8 (&qf)[A
   }
   // probabilities exp2(s - m) (QLOG2; the shift only where some row of the
   // wave has a nonzero reference, a wave-uniform branch), or exp2(s c - m)
-  const float nm = -m_i;
+  const float nm = SAFE && m_i == -INFINITY ? 0.0f : -m_i;
   bf16x8 pf[2 * NSB];
   auto probs = [&](auto shift_tag) {
 #pragma unroll
@@ -363,6 +366,156 @@ __global__ __launch_bounds__(512) void flash_attn_bf16_kernel(const bf16_t* __re
         pk[1] = pack_bf2(o[db][4 * rg + 2] * inv, o[db][4 * rg + 3] * inv);
         *(u32x2*)(op + c0) = pk;
       }
+  }
+}
+
+// Split attention, for shapes whose 256-query blocks leave most CUs idle.  A
+// workgroup's 8 waves are 8 / KS groups of 32 queries times KS shares of the keys:
+// fewer queries per workgroup, so KS times the workgroups, each with 1 / KS of the
+// steps.  A ring slot holds 128 keys (two of the tiles above); with KS = 2 a wave takes
+// one tile of it, with KS = 4 one 32-key half of one.  The shares' sums meet through
+// LDS at the end: 16 KB of float32 O a wave, in the ring's space.  3 heads, 1000 x 1000:
+// 28.4 us with 1 share, 21.0 with 2, 15.9 with 4; 8 heads, 3001 x 3001: 67.0 / 57.4 / 88.6.
+template <int KS, bool QLOG2>
+__global__ __launch_bounds__(512) void flash_attn_split_kernel(const bf16_t* __restrict__ q, int64_t ldq,
+                                                               const bf16_t* __restrict__ k, int64_t ldk,
+                                                               const bf16_t* __restrict__ vt, int64_t ldv,
+                                                               bf16_t* __restrict__ out, int64_t ldo, int H, int Lq,
+                                                               int Lk, float scale_log2) {
+  static_assert(KS == 2 || KS == 4, "key shares");
+  constexpr int D = ATT_D, NSB = KS == 2 ? 2 : 1, STEP = 2 * ATT_BKV, NK = 32 * NSB;
+  constexpr int STEP_BYTES = 2 * ATT_SLOT;
+  __shared__ __attribute__((aligned(1024))) uint8_t smem[2 * STEP_BYTES];
+  __shared__ float sm[8][32], sl[8][32];
+
+  const int tid = threadIdx.x;
+  const int lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int ks = wave % KS, qw = wave / KS;
+  const int jq = lane & 31;
+  const int hf = lane >> 5;
+  const int h = blockIdx.y;
+  const int b = blockIdx.z;
+  const int q0 = blockIdx.x * (256 / KS) + qw * 32;
+
+  const bf16_t* kbase = k + (int64_t)b * Lk * ldk + (int64_t)h * D;
+  const bf16_t* vbase = vt + ((int64_t)b * H + h) * D * ldv;
+  bf16x8 qf[D / 16];
+  {
+    const int qi = min(q0 + jq, Lq - 1);
+    const bf16_t* qp = q + (int64_t)b * Lq * ldq + (int64_t)h * D + (int64_t)qi * ldq + hf * 8;
+#pragma unroll
+    for (int kc = 0; kc < D / 16; ++kc) qf[kc] = __builtin_bit_cast(bf16x8, *(const u32x4*)(qp + kc * 16));
+  }
+  uint32_t koffg[2], voffg[2];
+#pragma unroll
+  for (int i = 0; i < 2; ++i) {
+    const int row = 8 * wave + 4 * i + (lane >> 4);
+    koffg[i] = (uint32_t)((key_of_row(row) * ldk + ((lane & 15) ^ (row & 15)) * 8) * 2);
+    const int vr = 16 * wave + 8 * i + (lane >> 3);
+    voffg[i] = (uint32_t)((vr * ldv + ((lane & 7) ^ att_vswz(vr)) * 8) * 2);
+  }
+  const __amdgpu_buffer_rsrc_t rsV =
+      __builtin_amdgcn_make_buffer_rsrc((void*)vbase, (short)0, (int)(uint32_t)(D * ldv * 2), 0x00020000);
+  int slot = 0;  // byte offset of the slot copied into next
+  auto issue = [&](int step) {
+#pragma unroll
+    for (int t = 0; t < 2; ++t) {
+      const int key0 = step * STEP + t * ATT_BKV;
+      // K rows key0 .. Lk - 1 of this head; a tile past Lk reads zeros (and the
+      // last V^T tile again), which no wave uses
+      const int rows = max(0, Lk - key0);
+      const __amdgpu_buffer_rsrc_t rsK = __builtin_amdgcn_make_buffer_rsrc(
+          (void*)(kbase + (int64_t)min(key0, Lk) * ldk), (short)0, (int)(uint32_t)(rows * ldk * 2), 0x00020000);
+      uint8_t* const dst = smem + slot + t * ATT_SLOT + wave * 2048;
+#pragma unroll
+      for (int i = 0; i < 2; ++i)
+        __builtin_amdgcn_raw_ptr_buffer_load_lds(rsK, (att_lds_ptr_t)(dst + i * 1024), 16, koffg[i], 0, 0, 0);
+#pragma unroll
+      for (int i = 0; i < 2; ++i)
+        __builtin_amdgcn_raw_ptr_buffer_load_lds(rsV, (att_lds_ptr_t)(dst + ATT_K_BYTES + i * 1024), 16,
+                                                 voffg[i] + (uint32_t)(min(key0, (Lk - 1) & ~(ATT_BKV - 1)) * 2), 0, 0, 0);
+    }
+    slot ^= STEP_BYTES;
+  };
+
+  // the lane's fragment offsets in the wave's share of slot 0
+  const int share = (KS == 2 ? ks : ks >> 1) * ATT_SLOT, half = KS == 2 ? 0 : ks & 1;
+  uint32_t kfo[D / 16], vfo[2 * NSB];
+#pragma unroll
+  for (int kc = 0; kc < D / 16; ++kc) kfo[kc] = share + half * 8192 + jq * 256 + (((kc * 2 + hf) ^ (jq & 15)) << 4);
+#pragma unroll
+  for (int c = 0; c < 2 * NSB; ++c) vfo[c] = share + jq * ATT_VROW + (((4 * half + 2 * c + hf) ^ att_vswz(jq)) << 4);
+
+  f32x16 o[D / 32];
+#pragma unroll
+  for (int db = 0; db < D / 32; ++db)
+#pragma unroll
+    for (int r = 0; r < 16; ++r) o[db][r] = 0.0f;
+  float m_i = -INFINITY, thr = -INFINITY;
+  bool zref = false;
+  att_f32x4 lsum = {0.0f, 0.0f, 0.0f, 0.0f};
+  const bf16x8 sel = att_sum_selector(lane);
+
+  issue(0);
+  att_wait_vmcnt<0>();
+  __builtin_amdgcn_s_barrier();
+  const int nsteps = (Lk + STEP - 1) / STEP;
+  int key0 = ks * NK;  // the wave's first key of the step
+  for (int step = 0; step < nsteps; ++step, key0 += STEP) {
+    if (step + 1 < nsteps) issue(step + 1);
+    if (key0 + NK <= Lk)
+      att_tile<false, QLOG2, NSB, true>(smem, qf, kfo, vfo, o, m_i, thr, zref, lsum, sel, key0, Lk, hf, scale_log2);
+    else if (key0 < Lk)
+      att_tile<true, QLOG2, NSB, true>(smem, qf, kfo, vfo, o, m_i, thr, zref, lsum, sel, key0, Lk, hf, scale_log2);
+#pragma unroll
+    for (int kc = 0; kc < D / 16; ++kc) kfo[kc] ^= STEP_BYTES;
+#pragma unroll
+    for (int c = 0; c < 2 * NSB; ++c) vfo[c] ^= STEP_BYTES;
+    att_wait_vmcnt<0>();
+    __builtin_amdgcn_s_waitcnt((15 << 0) | (3 << 14) | (7 << 4) | (0 << 8));  // lgkmcnt(0)
+    __builtin_amdgcn_s_barrier();
+  }
+
+  // join the shares: [wave][4 channel blocks][4 groups of 8 channels][lane] of float32 quads
+  f32x4* const so = (f32x4*)smem;
+#pragma unroll
+  for (int db = 0; db < D / 32; ++db)
+#pragma unroll
+    for (int rg = 0; rg < 4; ++rg)
+      so[(wave * 16 + db * 4 + rg) * 64 + lane] =
+          f32x4{o[db][4 * rg], o[db][4 * rg + 1], o[db][4 * rg + 2], o[db][4 * rg + 3]};
+  const float l = att_row_sum(lsum, lane);
+  if (hf == 0) {
+    sm[wave][jq] = m_i;
+    sl[wave][jq] = l;
+  }
+  __syncthreads();
+  float wt[KS], mx = sm[qw * KS][jq], sum = 0.0f;
+#pragma unroll
+  for (int i = 1; i < KS; ++i) mx = fmaxf(mx, sm[qw * KS + i][jq]);
+#pragma unroll
+  for (int i = 0; i < KS; ++i) {
+    const float mi = sm[qw * KS + i][jq];
+    wt[i] = mi == -INFINITY ? 0.0f : __builtin_amdgcn_exp2f(mi - mx);  // a share without keys
+    sum = fmaf(wt[i], sl[qw * KS + i][jq], sum);
+  }
+  const float inv = 1.0f / sum;
+  const int qi = q0 + jq;
+  if (qi >= Lq) return;
+  bf16_t* op = out + ((int64_t)b * Lq + qi) * ldo + (int64_t)h * D + 4 * hf;
+  // this wave's channels of the group's queries
+#pragma unroll
+  for (int i = 0; i < 16 / KS; ++i) {
+    const int cg = ks * (16 / KS) + i;  // 8-channel group
+    f32x4 v = {0.0f, 0.0f, 0.0f, 0.0f};
+#pragma unroll
+    for (int w = 0; w < KS; ++w) {
+      const f32x4 u = so[((qw * KS + w) * 16 + cg) * 64 + lane];
+#pragma unroll
+      for (int r = 0; r < 4; ++r) v[r] = fmaf(wt[w], u[r], v[r]);
+    }
+    *(u32x2*)(op + 8 * cg) = u32x2{pack_bf2(v[0] * inv, v[1] * inv), pack_bf2(v[2] * inv, v[3] * inv)};
   }
 }
 
@@ -750,6 +903,32 @@ __global__ __launch_bounds__(256) void attn_f32_kernel(const float* __restrict__
   }
 }
 
+// Key shares per query block (1, 2 or 4), by an estimate of the time: rounds of
+// workgroups over the CUs, times steps of a workgroup and its fixed cost.  The constants
+// are fits to all three at 19 shapes (1 - 5000 queries, 1 - 40 heads): a step is a 64-key
+// tile with 1 share (1.55 us), 128 keys with 2 (2.2: the copies of 64 KB) or 4 (1.72: half
+// the work per wave).  A shape that fills the chip keeps one share: 2 x 12 heads, 1560 x
+// 1560: 44 us, 72 with 2, 79 with 4.
+// TRACK_ATTN_SPLIT = 1, 2 or 4 (read at every call) forces one, for tests.
+static int pick_split(int64_t Lq, int64_t Lk, int64_t heads) {
+  const char* v = getenv("TRACK_ATTN_SPLIT");
+  if (v && (v[0] == '1' || v[0] == '2' || v[0] == '4')) return v[0] - '0';
+  const int64_t cus = device_cus();
+  const double step_us[3] = {1.55, 2.2, 1.72}, fixed_us[3] = {5.5, 8.5, 6.0};
+  int best = 1;
+  double best_t = 0.0;
+  for (int i = 0; i < 3; ++i) {
+    const int ks = 1 << i, per = i == 0 ? 64 : 128;
+    const int64_t wgs = (Lq * ks + 255) / 256 * heads, rounds = (wgs + cus - 1) / cus;
+    const double t = (double)rounds * ((double)((Lk + per - 1) / per) * step_us[i] + fixed_us[i]);
+    if (i == 0 || t < best_t) {
+      best = ks;
+      best_t = t;
+    }
+  }
+  return best;
+}
+
 float attn_log2_scale(int head_dim) { return (float)(1.4426950408889634 / sqrt((double)head_dim)); }
 
 track_status attention(int dtype, int B, int H, int head_dim, int64_t Lq, int64_t Lk, const void* q, int64_t ldq,
@@ -782,6 +961,23 @@ track_status attention(int dtype, int B, int H, int head_dim, int64_t Lq, int64_
     // give identical bits; the tests compare them)
     const char* items_env = getenv("TRACK_ATTN_ITEMS");
     const bool items_ok = !(items_env && items_env[0] == '0');
+    // (either setting leaves the sequence unsplit)
+    const int ksplit = items_env ? 1 : pick_split(Lq, Lk, (int64_t)H * B);
+    if (ksplit > 1) {
+      dim3 sgrid((unsigned)((Lq * ksplit + 255) / 256), H, B);
+#define TRACK_ATT_SPLIT(KS, QL) \
+  flash_attn_split_kernel<KS, QL><<<sgrid, 512, 0, s>>>(qq, ldq, kk, ldk, vv, ldv, oo, ldo, H, (int)Lq, (int)Lk, scale_log2)
+      if (ksplit == 2) {
+        if (q_log2) TRACK_ATT_SPLIT(2, true);
+        else TRACK_ATT_SPLIT(2, false);
+      } else {
+        if (q_log2) TRACK_ATT_SPLIT(4, true);
+        else TRACK_ATT_SPLIT(4, false);
+      }
+#undef TRACK_ATT_SPLIT
+      TRACK_LAUNCH_CHECK();
+      return TRACK_OK;
+    }
     // (the items kernel addresses 32 output rows through a 32-bit buffer size)
     if (items_ok && ntiles % 2 == 0 && ntiles <= ATT_ITEMS_MAX_TILES && ldo < ((int64_t)1 << 25)) {
       // short key sequence: one workgroup per CU over all (query block, head, batch) items

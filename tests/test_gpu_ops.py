@@ -244,6 +244,19 @@ def test_attention_f32_forms(dh, B, H, Lq, Lk, pad):
     assert rel_l2(got, ref) < 2e-6, rel_l2(got, ref)
 
 
+@pytest.mark.parametrize("q_log2", [False, True])
+@pytest.mark.parametrize("B,H,Lq,Lk", [(1, 1, 1, 1), (1, 2, 31, 32), (2, 1, 64, 33), (1, 2, 65, 128), (2, 2, 129, 129),
+                                       (1, 1, 257, 385), (1, 2, 100, 1000)])
+def test_attention_bf16_split_shares(B, H, Lq, Lk, q_log2, monkeypatch):
+    """1, 2 and 4 key shares per query block (TRACK_ATTN_SPLIT), shares without a key among them: each against
+    the oracle, within the rounding of P and the output to bfloat16 (1e-2, as for the unsplit kernel)."""
+    for ks in ("1", "2", "4"):
+        say(f"attention bf16 split={ks} B={B} H={H} Lq={Lq} Lk={Lk} q_log2={q_log2}")
+        monkeypatch.setenv("TRACK_ATTN_SPLIT", ks)
+        got, ref = _attn_case(BF16, B, H, 128, Lq, Lk, 6400 + Lq + Lk, q_log2=q_log2)
+        assert rel_l2(got, ref) < 1e-2, (ks, rel_l2(got, ref))
+
+
 def test_attention_errors_and_empty():
     import torch
     z = torch.zeros(64, 128, dtype=torch.bfloat16, device="cuda")
