@@ -8,15 +8,19 @@
 // over (H, W).  Band membership is decided in integer arithmetic.
 //
 // Passes (all on the caller's stream):
-//   band_tables   twiddles exp(-2 pi i m / n) for the three axes (fp64 -> fp32)
-//   band_row      per latent row: Y[h, k_w] = sum_w d[h, w] tw_W[k_w w]
-//   band_col      per (slice, 32 columns): X[k_h, k_w] = sum_h Y[h, k_w] tw_H[k_h h],
-//                 |X|^2 / (H W) accumulated per band (fp64), one partial per block
-//   band_temporal per (c, h, w): the F-point DFT, |X|^2 / F per band, partials
+//   band_temporal the F-point DFTs of 256 (c, h, w) series a block; the common
+//                 layout also leaves d itself, one 2 x 2 patch of a channel per 16
+//                 bytes in (frame, channel, token) order
+//   band_spatial  64 columns k_w of one (c, f) slice's 2D DFT a block, from that (the
+//                 velocities interleave a token's channels: each slice read straight
+//                 from them takes 16 of every 256 bytes)
+//   each leaves a block's three band energies (fp64) as a partial
 //   band_finish   partials summed in a fixed order -> 6 energies (and scores)
-// The work is a few GFLOP per call against multi-second denoiser steps, so the
-// kernels favour simplicity over peak throughput; all reads of the velocities
-// are 16 B contiguous (the 2x2 patch of one channel) or coalesced.
+// The DFTs are products with the axis' cosine and sine matrices on
+// v_mfma_f32_16x16x4_f32 (float32 products and sums), whose entries are looked up
+// in LDS tables exp(-2 pi i m / n) (fp64 -> fp32) at (k x) mod n.  The input is
+// real, so k_w (temporal: k_f) runs to n / 2 only, the rest being the conjugates
+// at -k, and row k_h and row H - k_h come from the same four products.
 #include <math.h>
 
 #include "common.h"
@@ -27,9 +31,11 @@ namespace track {
 namespace {
 
 constexpr int BAND_THREADS = 256;
-constexpr int BAND_COLS = 32;     // spatial columns per band_col block
-constexpr int BAND_MAX_W = 1024;  // row kernel LDS bound
-constexpr int BAND_MAX_H = 256;   // column kernel LDS bound
+constexpr int BAND_COLS = 64;     // columns k_w per spatial block, 16 a wave
+constexpr int BAND_XCH = 128;     // latent columns staged at a time
+constexpr int BAND_XLD = BAND_XCH + 4;  // LDS row stride: 4 mod 8 floats, so 16 rows' 16-byte reads hit all banks
+constexpr int BAND_MAX_W = 1024;  // twiddle table bound
+constexpr int BAND_MAX_H = 256;   // LDS bound of a staged chunk, and the accumulators of 16 row blocks
 constexpr int BAND_MAX_F = 64;    // temporal kernel LDS bound
 
 inline unsigned blocks_for(int64_t n, int64_t per) { return (unsigned)((n + per - 1) / per); }
@@ -97,91 +103,236 @@ __device__ __forceinline__ void block_sum3(double a0, double a1, double a2, doub
   }
 }
 
-__global__ void band_tables_kernel(int W, int H, int F, float2* __restrict__ tw) {
-  const int i = blockIdx.x * blockDim.x + threadIdx.x;
-  if (i >= W + H + F) return;
-  const int n = i < W ? W : (i < W + H ? H : F);
-  const int m = i < W ? i : (i < W + H ? i - W : i - W - H);
+__device__ __forceinline__ float2 twiddle(int m, int n) {
   double sn, cs;
   sincospi(2.0 * m / n, &sn, &cs);
-  tw[i] = make_float2((float)cs, (float)-sn);
+  return make_float2((float)cs, (float)-sn);
 }
 
-__global__ __launch_bounds__(BAND_THREADS) void band_row_kernel(BandShape s, int B, float w, const float* __restrict__ vL,
-                                                               const float* __restrict__ vS, int64_t n,
-                                                               const float2* __restrict__ twW, float2* __restrict__ Y) {
-  __shared__ float drow[BAND_MAX_W];
-  __shared__ float2 tw[BAND_MAX_W];
-  const int h = blockIdx.x;
-  const int sl = blockIdx.y;  // slice c * F + f
-  const int c = sl / s.F, f = sl % s.F;
-  for (int x = threadIdx.x; x < s.W; x += BAND_THREADS) {
-    drow[x] = guided_diff(vL, vS, n, B, w, tok_offset(s, c, f, h, x));
-    tw[x] = twW[x];
+__device__ __forceinline__ void fill_twiddles(float2* __restrict__ tw, int n) {
+  for (int m = threadIdx.x; m < n; m += BAND_THREADS) tw[m] = twiddle(m, n);
+}
+
+// n over the energy of the float32 table of length n (one wave): the entries'
+// rounding scales every energy by its inverse on average, the largest error of the
+// transforms (9e-9 of the energies at 21 x 60 x 104, against 2e-9 with it taken out).
+__device__ __forceinline__ double table_correction(int n, int lane) {
+  double e = 0.0;
+  for (int m = lane; m < n; m += 64) {
+    const float2 t = twiddle(m, n);
+    e += (double)t.x * t.x + (double)t.y * t.y;
   }
-  __syncthreads();
-  float2* yrow = Y + ((int64_t)sl * s.H + h) * s.W;
-  for (int kw = threadIdx.x; kw < s.W; kw += BAND_THREADS) {
-    float re = 0.0f, im = 0.0f;
-    int m = 0;  // kw * x mod W
-    for (int x = 0; x < s.W; ++x) {
-      const float2 t = tw[m];
-      re = fmaf(drow[x], t.x, re);
-      im = fmaf(drow[x], t.y, im);
-      m += kw;
-      if (m >= s.W) m -= s.W;
+  return n / wave_sum_d(e);
+}
+
+// (a + b) mod n for a, b < n
+__device__ __forceinline__ uint32_t add_mod(uint32_t a, uint32_t b, uint32_t n) { return min(a + b, a + b - n); }
+
+__device__ __forceinline__ f32x4 guided_diff4(const float* __restrict__ vL, const float* __restrict__ vS, int64_t n,
+                                              int B, float w, int64_t o) {
+  const f32x4 cL = *(const f32x4*)(vL + o), cS = *(const f32x4*)(vS + o);
+  f32x4 d;
+  if (B == 2) {
+    const f32x4 uL = *(const f32x4*)(vL + n + o), uS = *(const f32x4*)(vS + n + o);
+#pragma unroll
+    for (int j = 0; j < 4; ++j) d[j] = fmaf(w, cS[j] - uS[j], uS[j]) - fmaf(w, cL[j] - uL[j], uL[j]);
+  } else {
+#pragma unroll
+    for (int j = 0; j < 4; ++j) d[j] = cS[j] - cL[j];
+  }
+  return d;
+}
+
+__device__ __forceinline__ void add_band(double (&acc)[3], int b, double e) {
+  acc[0] += b == 0 ? e : 0.0;
+  acc[1] += b == 1 ? e : 0.0;
+  acc[2] += b == 2 ? e : 0.0;
+}
+
+// Spatial block: slice (c, f), columns k_w = 64 kg .. + 63, 16 a wave.  The slice
+// (up to BAND_XCH columns at a time, rows and columns padded with zeros) is staged
+// in LDS as the MFMA "A" operand; a wave's row DFTs for all rows stay in its
+// accumulators (lane: column k_w, rows 16 b + 4 g + r), which are the "B" operand of
+// the column DFT as they are.  Slices are numbered frame by frame over the XCDs, so
+// that those of one frame are read through one L2.
+template <int HB>
+__global__ __launch_bounds__(BAND_THREADS) void band_spatial_kernel(BandShape s, int B, float w,
+                                                                    const float* __restrict__ vL,
+                                                                    const float* __restrict__ vS, int64_t n,
+                                                                    const f32x4* __restrict__ diff, int kwg,
+                                                                    double* __restrict__ part) {
+  __shared__ __attribute__((aligned(16))) float sd[16 * HB][BAND_XLD];
+  __shared__ float2 twW[BAND_MAX_W], twH[BAND_MAX_H];
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  const int jq = lane & 15, g = lane >> 4;
+  const int id = xcd_remap(blockIdx.x, gridDim.x);
+  const int f = id / (s.C * kwg), c = id / kwg % s.C, kg = id % kwg;
+  fill_twiddles(twW, s.W);
+  fill_twiddles(twH, s.H);
+  const uint32_t W = s.W, H = s.H;
+  const int kw0 = (kg * 4 + wave) * 16, kw = kw0 + jq;
+  const bool live = kw0 <= s.W / 2;  // wave-uniform
+  f32x4 yr[HB], yi[HB];
+#pragma unroll
+  for (int b = 0; b < HB; ++b) yr[b] = yi[b] = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
+  const uint32_t step16 = (16u * kw) % W;
+  for (int x0 = 0; x0 < s.W; x0 += BAND_XCH) {
+    const int xc = min(BAND_XCH, (s.W - x0 + 15) & ~15);
+    if (x0) __syncthreads();
+    if (diff) {  // a token's 2 x 2 patch per 16 bytes
+      const int nx = xc >> 1, np = 8 * HB * nx;
+      const f32x4* src = diff + ((int64_t)f * s.C + c) * s.Hp * s.Wp;
+      constexpr int U = 4;  // pieces a thread loads before it stores them
+      for (int i0 = threadIdx.x; i0 < np; i0 += U * BAND_THREADS) {
+        f32x4 d[U];
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+          const int i = i0 + u * BAND_THREADS, hp = i / nx, wp = (x0 >> 1) + i - hp * nx;
+          d[u] = hp < s.Hp && wp < s.Wp ? src[hp * s.Wp + wp] : f32x4{0.0f, 0.0f, 0.0f, 0.0f};
+        }
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+          const int i = i0 + u * BAND_THREADS, hp = i / nx, xl = i - hp * nx;
+          if (i >= np) continue;
+          *(float2*)&sd[2 * hp][2 * xl] = make_float2(d[u][0], d[u][1]);
+          *(float2*)&sd[2 * hp + 1][2 * xl] = make_float2(d[u][2], d[u][3]);
+        }
+      }
+    } else {
+      for (int i = threadIdx.x; i < 16 * HB * xc; i += BAND_THREADS) {
+        const int h = i / xc, x = i - h * xc;
+        sd[h][x] = h < s.H && x0 + x < s.W ? guided_diff(vL, vS, n, B, w, tok_offset(s, c, f, h, x0 + x)) : 0.0f;
+      }
     }
-    yrow[kw] = make_float2(re, im);
+    __syncthreads();
+    if (live) {
+      uint32_t m[4];
+#pragma unroll
+      for (int i = 0; i < 4; ++i) m[i] = ((uint32_t)kw * (uint32_t)(x0 + 4 * g + i)) % W;
+      for (int xk = 0; xk < xc; xk += 16) {
+        float2 t[4];
+        f32x4 a[HB];
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+          t[i] = twW[m[i]];
+          m[i] = add_mod(m[i], step16, W);
+        }
+#pragma unroll
+        for (int b = 0; b < HB; ++b) a[b] = *(const f32x4*)&sd[16 * b + jq][xk + 4 * g];
+#pragma unroll
+        for (int i = 0; i < 4; ++i)
+#pragma unroll
+          for (int b = 0; b < HB; ++b) {
+            yr[b] = __builtin_amdgcn_mfma_f32_16x16x4f32(a[b][i], t[i].x, yr[b], 0, 0, 0);
+            yi[b] = __builtin_amdgcn_mfma_f32_16x16x4f32(a[b][i], t[i].y, yi[b], 0, 0, 0);
+          }
+      }
+    }
   }
-}
-
-__global__ __launch_bounds__(BAND_THREADS) void band_col_kernel(BandShape s, const float2* __restrict__ Y,
-                                                               const float2* __restrict__ twH,
-                                                               double* __restrict__ part) {
-  __shared__ float2 ytile[BAND_MAX_H][BAND_COLS];
-  __shared__ float2 tw[BAND_MAX_H];
-  const int sl = blockIdx.y;
-  const int kw0 = blockIdx.x * BAND_COLS;
-  for (int i = threadIdx.x; i < s.H * BAND_COLS; i += BAND_THREADS) {
-    const int h = i / BAND_COLS, j = i % BAND_COLS;
-    ytile[h][j] = kw0 + j < s.W ? Y[((int64_t)sl * s.H + h) * s.W + kw0 + j] : make_float2(0.0f, 0.0f);
-  }
-  for (int i = threadIdx.x; i < s.H; i += BAND_THREADS) tw[i] = twH[i];
-  __syncthreads();
-  const double norm = 1.0 / ((double)s.H * s.W);
   double acc[3] = {0.0, 0.0, 0.0};
-  for (int i = threadIdx.x; i < s.H * BAND_COLS; i += BAND_THREADS) {
-    const int kh = i / BAND_COLS, j = i % BAND_COLS;
-    const int kw = kw0 + j;
-    if (kw >= s.W) continue;
-    float re = 0.0f, im = 0.0f;
-    int m = 0;  // kh * h mod H
-    for (int h = 0; h < s.H; ++h) {
-      const float2 y = ytile[h][j], t = tw[m];
-      re = fmaf(y.x, t.x, fmaf(-y.y, t.y, re));
-      im = fmaf(y.x, t.y, fmaf(y.y, t.x, im));
-      m += kh;
-      if (m >= s.H) m -= s.H;
+  const double norm = (kw == 0 || 2 * kw == s.W ? 1.0 : 2.0) / ((double)s.H * s.W);
+  for (int kh0 = 0; live && kh0 <= s.H / 2; kh0 += 16) {
+    const uint32_t kh = kh0 + jq, steph = (16u * kh) % H;
+    uint32_t m[4];
+#pragma unroll
+    for (int r = 0; r < 4; ++r) m[r] = (kh * (uint32_t)(4 * g + r)) % H;
+    f32x4 p = {0.0f, 0.0f, 0.0f, 0.0f}, q = p, u = p, v = p;  // sums of yr tx, yi ty, yr ty, yi tx
+#pragma unroll
+    for (int b = 0; b < HB; ++b)
+#pragma unroll
+      for (int r = 0; r < 4; ++r) {
+        const float2 t = twH[m[r]];
+        m[r] = add_mod(m[r], steph, H);
+        p = __builtin_amdgcn_mfma_f32_16x16x4f32(t.x, yr[b][r], p, 0, 0, 0);
+        q = __builtin_amdgcn_mfma_f32_16x16x4f32(t.y, yi[b][r], q, 0, 0, 0);
+        u = __builtin_amdgcn_mfma_f32_16x16x4f32(t.y, yr[b][r], u, 0, 0, 0);
+        v = __builtin_amdgcn_mfma_f32_16x16x4f32(t.x, yi[b][r], v, 0, 0, 0);
+      }
+#pragma unroll
+    for (int r = 0; r < 4; ++r) {
+      const int k = kh0 + 4 * g + r;
+      if (k > s.H / 2 || kw > s.W / 2) continue;
+      const double re = (double)(p[r] - q[r]), im = (double)(u[r] + v[r]);
+      const double re2 = (double)(p[r] + q[r]), im2 = (double)(v[r] - u[r]);  // row H - k
+      const double e = re * re + im * im, e2 = k == 0 || 2 * k == s.H ? 0.0 : re2 * re2 + im2 * im2;
+      add_band(acc, spatial_band(k, kw, s.H, s.W), (e + e2) * norm);
     }
-    const double e = ((double)re * re + (double)im * im) * norm;
-    const int b = spatial_band(kh, kw, s.H, s.W);
-    acc[0] += b == 0 ? e : 0.0;
-    acc[1] += b == 1 ? e : 0.0;
-    acc[2] += b == 2 ? e : 0.0;
   }
-  block_sum3(acc[0], acc[1], acc[2], part + 3 * ((int64_t)blockIdx.y * gridDim.x + blockIdx.x));
+  block_sum3(acc[0], acc[1], acc[2], part + 3 * (int64_t)blockIdx.x);
 }
 
-// One thread per (c, h, w) series, numbered in the token order of one frame
+// Temporal block (patch_t 1: a frame's series are contiguous): 64 series a wave,
+// lane jq the four from 4 jq on, "B" operands of four MFMAs as they are loaded.  With
+// `diff` (patch 1 x 2 x 2) those four, one channel of one token, go there too.
+__global__ __launch_bounds__(BAND_THREADS) void band_temporal_rows_kernel(BandShape s, int B, float w,
+                                                                          const float* __restrict__ vL,
+                                                                          const float* __restrict__ vS, int64_t n,
+                                                                          f32x4* __restrict__ diff,
+                                                                          double* __restrict__ part) {
+  __shared__ float2 tw[BAND_MAX_F];
+  fill_twiddles(tw, s.F);
+  __syncthreads();
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  const int jq = lane & 15, g = lane >> 4;
+  const int64_t total = (int64_t)s.Hp * s.Wp * s.P;  // series, a multiple of 4
+  const int64_t i0 = ((int64_t)xcd_remap(blockIdx.x, gridDim.x) * 4 + wave) * 64 + 4 * jq;
+  const bool in = i0 < total;
+  const int64_t base = in ? i0 : 0;
+  const uint32_t F = s.F;
+  // the piece's place in frame 0, and the pieces of a frame
+  const int64_t T = (int64_t)s.Hp * s.Wp, frame = s.C * T;
+  const uint32_t b32 = (uint32_t)base, P = s.P;  // (a latent holds at most 2^31 values)
+  f32x4* const dst = diff + (int64_t)(b32 % P / 4) * T + b32 / P;
+  double acc[3] = {0.0, 0.0, 0.0};
+  for (int kf0 = 0; kf0 <= s.F / 2; kf0 += 16) {
+    const uint32_t kf = kf0 + jq, step4 = (4u * kf) % F;
+    uint32_t m = (kf * (uint32_t)g) % F;
+    f32x4 re[4], im[4];
+#pragma unroll
+    for (int i = 0; i < 4; ++i) re[i] = im[i] = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
+    constexpr int U = 3;  // steps of 4 frames whose loads are issued together
+    for (int f0 = 0; f0 < s.F; f0 += 4 * U) {
+      f32x4 d[U];
+#pragma unroll
+      for (int u = 0; u < U; ++u)
+        d[u] = guided_diff4(vL, vS, n, B, w, (int64_t)min(f0 + 4 * u + g, s.F - 1) * total + base);
+#pragma unroll
+      for (int u = 0; u < U; ++u) {
+        const bool live = in && f0 + 4 * u + g < s.F;
+        if (live && diff && kf0 == 0) dst[(f0 + 4 * u + g) * frame] = d[u];
+        const float2 t = tw[m];
+        m = add_mod(m, step4, F);
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+          const float v = live ? d[u][i] : 0.0f;
+          re[i] = __builtin_amdgcn_mfma_f32_16x16x4f32(t.x, v, re[i], 0, 0, 0);
+          im[i] = __builtin_amdgcn_mfma_f32_16x16x4f32(t.y, v, im[i], 0, 0, 0);
+        }
+      }
+    }
+#pragma unroll
+    for (int r = 0; r < 4; ++r) {
+      const int k = kf0 + 4 * g + r;
+      if (k > s.F / 2) continue;
+      double e = 0.0;
+#pragma unroll
+      for (int i = 0; i < 4; ++i) e += (double)re[i][r] * re[i][r] + (double)im[i][r] * im[i][r];
+      add_band(acc, axis_band(k, s.F), e * ((k == 0 || 2 * k == s.F ? 1.0 : 2.0) / s.F));
+    }
+  }
+  block_sum3(acc[0], acc[1], acc[2], part + 3 * (int64_t)blockIdx.x);
+}
+
+// Temporal energies of the other layouts (patch_t > 1, or velocities that are not
+// 16-byte aligned).  One thread per (c, h, w) series, numbered in the token order of one frame
 // group so that neighbouring threads read neighbouring floats.
 __global__ __launch_bounds__(BAND_THREADS) void band_temporal_kernel(BandShape s, int B, float w,
                                                                     const float* __restrict__ vL,
                                                                     const float* __restrict__ vS, int64_t n,
-                                                                    const float2* __restrict__ twF,
                                                                     double* __restrict__ part) {
   __shared__ float ser[BAND_MAX_F][BAND_THREADS];
   __shared__ float2 tw[BAND_MAX_F];
-  for (int i = threadIdx.x; i < s.F; i += BAND_THREADS) tw[i] = twF[i];
+  fill_twiddles(tw, s.F);
   const int64_t i = (int64_t)blockIdx.x * BAND_THREADS + threadIdx.x;
   const int Q = s.C * s.ph * s.pw;
   const int64_t total = (int64_t)s.Hp * s.Wp * Q;
@@ -221,34 +372,36 @@ __global__ __launch_bounds__(BAND_THREADS) void band_temporal_kernel(BandShape s
   block_sum3(acc[0], acc[1], acc[2], part + 3 * (int64_t)blockIdx.x);
 }
 
-// Sums the partials in a fixed order.  energy[0..2] spatial, [3..5] temporal.
+// Sums the partials in a fixed order, one wave per quantity (the eighth: the
+// tables' correction factors).  energy[0..2]
+// spatial, [3..5] temporal.
 // With step partials (pairs (sum d^2, sum p_L^2) of the calibration step
 // kernel) it also writes score[b] = sqrt(energy[b]) / max(||p_L||, eps).
-__global__ __launch_bounds__(BAND_THREADS) void band_finish_kernel(int ns, const double* __restrict__ part_s, int nt,
-                                                                  const double* __restrict__ part_t, int nstep,
-                                                                  const double* __restrict__ step_part, double eps,
-                                                                  double* __restrict__ energy,
-                                                                  double* __restrict__ score) {
-  __shared__ double tot[7];
-  for (int q = 0; q < 7; ++q) {
-    const double* p = q < 3 ? part_s + q : (q < 6 ? part_t + (q - 3) : step_part + 1);
-    const int cnt = q < 3 ? ns : (q < 6 ? nt : nstep);
-    const int stride = q < 6 ? 3 : 2;
-    double a = 0.0;
-    if (q < 6 || step_part)
-      for (int i = threadIdx.x; i < cnt; i += BAND_THREADS) a += p[(int64_t)i * stride];
-    __shared__ double red[BAND_THREADS / 64];
-    a = wave_sum_d(a);
-    if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = a;
-    __syncthreads();
-    if (threadIdx.x == 0) {
-      double s = 0.0;
-      for (int i = 0; i < BAND_THREADS / 64; ++i) s += red[i];
-      tot[q] = s;
+__global__ __launch_bounds__(512) void band_finish_kernel(int ns, const double* __restrict__ part_s, int nt,
+                                                          const double* __restrict__ part_t, int nstep,
+                                                          const double* __restrict__ step_part, double eps,
+                                                          int F, int H, int W, double* __restrict__ energy,
+                                                          double* __restrict__ score) {
+  __shared__ double tot[8], corr[2];
+  const int q = threadIdx.x >> 6, lane = threadIdx.x & 63;
+  const double* p = q < 3 ? part_s + q : (q < 6 ? part_t + (q - 3) : step_part + 1);
+  const int cnt = q < 3 ? ns : (q < 6 ? nt : (q == 6 && step_part ? nstep : 0));
+  const int stride = q < 6 ? 3 : 2;
+  double a = 0.0;
+#pragma unroll 4
+  for (int i = lane; i < cnt; i += 64) a += p[(int64_t)i * stride];
+  a = wave_sum_d(a);
+  if (lane == 0) tot[q] = a;
+  if (q == 7) {
+    const double cw = table_correction(W, lane), ch = table_correction(H, lane), cf = table_correction(F, lane);
+    if (lane == 0) {
+      corr[0] = cw * ch;
+      corr[1] = cf;
     }
-    __syncthreads();
   }
+  __syncthreads();
   if (threadIdx.x < 6) {
+    tot[threadIdx.x] *= corr[threadIdx.x / 3];
     energy[threadIdx.x] = tot[threadIdx.x];
     if (step_part && score) {
       const double dn = sqrt(tot[6]);
@@ -258,9 +411,12 @@ __global__ __launch_bounds__(BAND_THREADS) void band_finish_kernel(int ns, const
 }
 
 struct BandLayout {
-  size_t Y, tw, part_s, part_t, energy, total;
-  int col_blocks, ns, nt;
+  size_t diff, part_s, part_t, energy, total;
+  int kwg, ns, nt;
 };
+
+// Layouts whose d goes through the workspace (where the velocities are aligned).
+bool planar(const BandShape& s) { return s.pt == 1 && s.ph == 2 && s.pw == 2; }
 
 BandLayout band_layout(const BandShape& s) {
   BandLayout b{};
@@ -270,11 +426,10 @@ BandLayout band_layout(const BandShape& s) {
     off = align_256(off + bytes);
     return o;
   };
-  b.col_blocks = (s.W + BAND_COLS - 1) / BAND_COLS;
-  b.ns = b.col_blocks * s.C * s.F;
+  b.kwg = s.W / 2 / BAND_COLS + 1;
+  b.ns = b.kwg * s.C * s.F;
   b.nt = (int)(((int64_t)s.Hp * s.Wp * s.C * s.ph * s.pw + BAND_THREADS - 1) / BAND_THREADS);
-  b.Y = take((size_t)s.C * s.F * s.H * s.W * sizeof(float2));
-  b.tw = take((size_t)(s.W + s.H + s.F) * sizeof(float2));
+  b.diff = take(planar(s) ? (size_t)s.C * s.F * s.H * s.W * sizeof(float) : 0);
   b.part_s = take((size_t)b.ns * 3 * 8);
   b.part_t = take((size_t)b.nt * 3 * 8);
   b.energy = take(6 * 8);
@@ -320,22 +475,29 @@ track_status band_scores(int C, int F, int H, int W, int pt, int ph, int pw, int
   const BandShape s = make_shape(C, F, H, W, pt, ph, pw);
   const BandLayout L = band_layout(s);
   uint8_t* base = (uint8_t*)ws;
-  float2* Y = (float2*)(base + L.Y);
-  float2* tw = (float2*)(base + L.tw);
   double* part_s = (double*)(base + L.part_s);
   double* part_t = (double*)(base + L.part_t);
   double* energy = energy_dev ? energy_dev : (double*)(base + L.energy);
   const int64_t n = (int64_t)C * F * H * W;  // floats per branch
   ProfScope prof(TRACK_PROF_STEP, st);
-  band_tables_kernel<<<blocks_for(W + H + F, 256), 256, 0, st>>>(W, H, F, tw);
+  const bool aligned = (((uintptr_t)vel_L | (uintptr_t)vel_S) & 15) == 0 && n % 4 == 0 && s.P % 4 == 0;
+  f32x4* const diff = aligned && planar(s) ? (f32x4*)(base + L.diff) : nullptr;
+  if (aligned && pt == 1)
+    band_temporal_rows_kernel<<<L.nt, BAND_THREADS, 0, st>>>(s, B, w, vel_L, vel_S, n, diff, part_t);
+  else
+    band_temporal_kernel<<<L.nt, BAND_THREADS, 0, st>>>(s, B, w, vel_L, vel_S, n, part_t);
   TRACK_LAUNCH_CHECK();
-  band_row_kernel<<<dim3(H, C * F), BAND_THREADS, 0, st>>>(s, B, w, vel_L, vel_S, n, tw, Y);
+#define TRACK_BAND(HB) \
+  band_spatial_kernel<HB><<<L.ns, BAND_THREADS, 0, st>>>(s, B, w, vel_L, vel_S, n, diff, L.kwg, part_s)
+  const int hb = (H + 15) / 16;
+  if (hb <= 2) TRACK_BAND(2);
+  else if (hb <= 4) TRACK_BAND(4);
+  else if (hb <= 6) TRACK_BAND(6);
+  else if (hb <= 8) TRACK_BAND(8);
+  else TRACK_BAND(16);
+#undef TRACK_BAND
   TRACK_LAUNCH_CHECK();
-  band_col_kernel<<<dim3(L.col_blocks, C * F), BAND_THREADS, 0, st>>>(s, Y, tw + W, part_s);
-  TRACK_LAUNCH_CHECK();
-  band_temporal_kernel<<<L.nt, BAND_THREADS, 0, st>>>(s, B, w, vel_L, vel_S, n, tw + W + H, part_t);
-  TRACK_LAUNCH_CHECK();
-  band_finish_kernel<<<1, BAND_THREADS, 0, st>>>(L.ns, part_s, L.nt, part_t, (int)n_step_partials, step_partial, eps,
+  band_finish_kernel<<<1, 512, 0, st>>>(L.ns, part_s, L.nt, part_t, (int)n_step_partials, step_partial, eps, F, H, W,
                                                 energy, score_dev);
   TRACK_LAUNCH_CHECK();
   return TRACK_OK;

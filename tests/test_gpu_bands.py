@@ -52,6 +52,43 @@ def test_band_energy_matches_oracle(C, F, H, W, patch, B):
     np.testing.assert_array_equal(got, again)
 
 
+@pytest.mark.parametrize("C,F,H,W,patch,offset", [
+    (1, 1, 1, 1, (1, 1, 1), 0),
+    (2, 3, 34, 258, (1, 2, 2), 0),    # three column groups, three staged chunks
+    (1, 33, 98, 6, (1, 2, 2), 0),     # k_f beyond one block of 16, k_h beyond 48
+    (1, 64, 256, 4, (1, 2, 2), 0),    # the largest F and H
+    (1, 2, 2, 1024, (1, 2, 2), 0),    # the largest W
+    (3, 5, 17, 33, (1, 1, 1), 0),     # odd sizes, element-wise staging
+    (4, 5, 12, 20, (1, 2, 2), 1),     # velocities that are not 16-byte aligned
+])
+def test_band_energy_block_edges(C, F, H, W, patch, offset):
+    """Tolerance: float32 DFT sums of up to 1024 terms and the float32 table entries, a few 1e-7 of the energy,
+    and the float32 guided predictions, each off by at most 2^-23 of itself and its inputs (summed by
+    Cauchy-Schwarz)."""
+    import torch
+    from paper_2609_30096_amd import track
+    say(f"band energy edges C={C} F={F} H={H} W={W} patch={patch} offset={offset}")
+    shape = synth.LatentShape(C, F, H, W, 16)
+    L, P, B, w = shape.tokens(patch), C * math.prod(patch), 2, 5.0
+    key = 7100 + C + F + H + W
+    vL = normal((key, 1), (B, L, P))
+    vS = vL + 0.3 * normal((key, 2), (B, L, P))
+
+    def shifted(v):
+        t = torch.empty(v.size + offset, device="cuda")
+        t[offset:] = dev(v).reshape(-1)
+        return t[offset:]
+
+    ws = torch.empty(track.band_workspace_bytes(shape, patch), dtype=torch.uint8, device="cuda")
+    got = track.op_band_energy(shape, B, w, shifted(vL), shifted(vS), ws, patch)
+    d_tok = _guided(vS.astype(np.float64), B, w) - _guided(vL.astype(np.float64), B, w)
+    sp, tp = bands.band_energies(dit.unpatchify(d_tok, C, F, H, W, patch))
+    ref = np.concatenate([sp, tp])
+    tot = float(sp.sum())
+    size = (2 * w + 1) * (np.linalg.norm(vL) + np.linalg.norm(vS))
+    assert np.all(np.abs(got - ref) <= 2e-6 * tot + 2 * np.sqrt(tot) * 2.0 ** -23 * size), (got, ref)
+
+
 def test_band_energy_argument_checks():
     import torch
     from paper_2609_30096_amd import track
