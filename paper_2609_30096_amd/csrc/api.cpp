@@ -267,7 +267,8 @@ track_status track_dit_forward(track_model mh, const track_latent_shape* shape, 
     TRY(patchify(x_t, xtok, c.in_ch, shape->frames, shape->height, shape->width, c.patch_t, c.patch_h, c.patch_w, s));
   }
   const void* ctx[2] = {cond, uncond};
-  TRY(forward(m, *shape, B, xtok, t, ctx, vel, s));
+  TRY(prepare(m, *shape, B, ctx, s));
+  TRY(forward(m, *shape, B, xtok, t, vel, s));
   TRY(guide_unpatchify(vel, B, guidance_scale, p_out, c.in_ch, shape->frames, shape->height, shape->width, c.patch_t,
                        c.patch_h, c.patch_w, s));
   return TRACK_OK;
@@ -316,10 +317,12 @@ static track_status calibrate_impl(track_model lh, track_model sh, const track_l
       ProfScope prof(TRACK_PROF_OTHER, s);
       TRY(patchify(x_T[j], xtok, c.in_ch, shape->frames, shape->height, shape->width, c.patch_t, c.patch_h, c.patch_w, s));
     }
+    TRY(prepare(L, *shape, B, ctx, s));
+    TRY(prepare(S, *shape, B, ctx, s));
     for (int k = 0; k < N; ++k) {
       const double t = 1000.0 * sig[k];
-      TRY(forward(L, *shape, B, xtok, t, ctx, velL, s));
-      TRY(forward(S, *shape, B, xtok, t, ctx, velS, s));
+      TRY(forward(L, *shape, B, xtok, t, velL, s));
+      TRY(forward(S, *shape, B, xtok, t, velS, s));
       // the band kernels read the velocities, which the update leaves intact
       TRY(sched.advance(k, B, w, velL, velS, xtok, partial, scfg->eps, rdev + k, s));
       if (bands)
@@ -498,10 +501,19 @@ track_status track_sample(track_model lh, track_model sh, const uint8_t* use_sma
     ProfScope prof(TRACK_PROF_OTHER, s);
     TRY(patchify(x_T, xtok, c.in_ch, shape->frames, shape->height, shape->width, c.patch_t, c.patch_h, c.patch_w, s));
   }
+  // each model's text keys and values are formed at its first step (at every change
+  // of model where the two share workspace memory)
+  bool have_ctx[2] = {false, false};
+  const bool shared_ws =
+      any_small && L.ws < sh->m.ws + sh->m.ws_bytes && sh->m.ws < L.ws + L.ws_bytes;
   for (int i = 0; i < N; ++i) {
     const Model& m = use_small[i] ? sh->m : L;
     float* vel = wsp<float>(m, ws_layout(m, *shape, B).vel);
-    TRY(forward(m, *shape, B, xtok, 1000.0 * sig[i], ctx, vel, s));
+    if (shared_ws && i > 0 && (use_small[i] != 0) != (use_small[i - 1] != 0)) have_ctx[0] = have_ctx[1] = false;
+    bool& ready = have_ctx[use_small[i] != 0];
+    if (!ready) TRY(prepare(m, *shape, B, ctx, s));
+    ready = true;
+    TRY(forward(m, *shape, B, xtok, 1000.0 * sig[i], vel, s));
     // UniPC's history is one sequence whichever model produced each entry
     TRY(sched.advance(i, B, w, vel, nullptr, xtok, nullptr, 0.0, nullptr, s));
     TRY(report_progress(s, -1, i, N));

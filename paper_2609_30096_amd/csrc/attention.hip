@@ -533,7 +533,8 @@ __global__ __launch_bounds__(512) void flash_attn_split_kernel(const bf16_t* __r
 //
 // All workgroups finish their items together, and the burst of output stores
 // (16 MB over the chip) takes longer than a tile.  vmcnt counts loads and stores
-// alike, in order, so a copy issued behind the stores would make the next item's
+// alike, in issue order (the compiler's own waits rely on it), so a copy issued
+// behind the stores would make the next item's
 // first tile wait for them.  The next item's first two tiles are therefore
 // copied (and its Q registers read) before the stores are issued, and its first
 // tile waits only for what precedes them; the Q copies, as many bytes again, are
@@ -764,7 +765,7 @@ __device__ __forceinline__ f32x4 att_load4(const float* __restrict__ p) {
   else return f32x4{p[0], p[1], p[2], p[3]};
 }
 
-template <int D, int KS, bool VEC>
+template <int D, int KS, bool VEC, bool VROWS>
 __global__ __launch_bounds__(256) void attn_f32_kernel(const float* __restrict__ q, int64_t ldq,
                                                        const float* __restrict__ k, int64_t ldk,
                                                        const float* __restrict__ vt, int64_t ldv,
@@ -782,7 +783,8 @@ __global__ __launch_bounds__(256) void attn_f32_kernel(const float* __restrict__
   const int64_t qi = q0 + jq;
   const float* qp = q + ((int64_t)b * Lq + (qi < Lq ? qi : Lq - 1)) * ldq + (int64_t)h * D + 4 * g;
   const float* kb = k + (int64_t)b * Lk * ldk + (int64_t)h * D + 4 * g;
-  const float* vb = vt + (((int64_t)b * H + h) * D + jq) * ldv + 4 * g;
+  const float* vb = VROWS ? vt + ((int64_t)b * Lk + 4 * g) * ldv + (int64_t)h * D + jq
+                          : vt + (((int64_t)b * H + h) * D + jq) * ldv + 4 * g;
   f32x4 qf[C], kf[C], vf[C], o[C];
   // K row key0 + jq (the last key again past the end) and the V^T columns
   // key0 + 4 g + 0..3, zero past the end
@@ -792,7 +794,15 @@ __global__ __launch_bounds__(256) void attn_f32_kernel(const float* __restrict__
     for (int c = 0; c < C; ++c) d[c] = att_load4<VEC>(p + 16 * c);
   };
   auto load_v = [&](int64_t key0, f32x4 (&d)[C]) {
-    if (key0 + 16 <= Lk) {
+    if constexpr (VROWS) {
+#pragma unroll
+      for (int j = 0; j < 4; ++j) {
+        const bool in = key0 + 4 * g + j < Lk;
+        const float* p = vb + (in ? key0 + j : -4 * g) * ldv;
+#pragma unroll
+        for (int c = 0; c < C; ++c) d[c][j] = in ? p[16 * c] : 0.0f;
+      }
+    } else if (key0 + 16 <= Lk) {
 #pragma unroll
       for (int c = 0; c < C; ++c) d[c] = att_load4<VEC>(vb + 16 * c * ldv + key0);
     } else {
@@ -931,6 +941,41 @@ static int pick_split(int64_t Lq, int64_t Lk, int64_t heads) {
 
 float attn_log2_scale(int head_dim) { return (float)(1.4426950408889634 / sqrt((double)head_dim)); }
 
+static track_status attention_f32(int B, int H, int head_dim, int64_t Lq, int64_t Lk, const float* q, int64_t ldq,
+                                  const float* k, int64_t ldk, const float* v, int64_t ldv, float* out, int64_t ldo,
+                                  bool vrows, hipStream_t s) {
+  const float scale_log2 = attn_log2_scale(head_dim);
+  const int64_t nqb = (Lq + 15) / 16;
+  // four waves a query block until the blocks alone give every SIMD a wave
+  const bool split = nqb * H * B < 4 * (int64_t)device_cus();
+  const bool vec = ((ldq | ldk | ldv | ldo) & 3) == 0 &&
+                   (((uintptr_t)q | (uintptr_t)k | (uintptr_t)v | (uintptr_t)out) & 15) == 0;
+  dim3 grid((unsigned)(split ? nqb : (nqb + 3) / 4), H, B);
+#define TRACK_ATT_F32_K(DH, KS, VEC, VR) \
+  attn_f32_kernel<DH, KS, VEC, VR><<<grid, 256, 0, s>>>(q, ldq, k, ldk, v, ldv, out, ldo, H, Lq, Lk, scale_log2)
+#define TRACK_ATT_F32(DH)                                     \
+  do {                                                        \
+    if (vrows && split && vec) TRACK_ATT_F32_K(DH, 4, true, true); \
+    else if (vrows && split) TRACK_ATT_F32_K(DH, 4, false, true);  \
+    else if (vrows && vec) TRACK_ATT_F32_K(DH, 1, true, true);     \
+    else if (vrows) TRACK_ATT_F32_K(DH, 1, false, true);           \
+    else if (split && vec) TRACK_ATT_F32_K(DH, 4, true, false);    \
+    else if (split) TRACK_ATT_F32_K(DH, 4, false, false);          \
+    else if (vec) TRACK_ATT_F32_K(DH, 1, true, false);             \
+    else TRACK_ATT_F32_K(DH, 1, false, false);                     \
+  } while (0)
+  switch (head_dim) {
+    case 32: TRACK_ATT_F32(32); break;
+    case 64: TRACK_ATT_F32(64); break;
+    case 128: TRACK_ATT_F32(128); break;
+    default: return fail(TRACK_E_UNSUPPORTED, "attention: float32 path supports head_dim 32, 64, 128 (got %d)", head_dim);
+  }
+#undef TRACK_ATT_F32
+#undef TRACK_ATT_F32_K
+  TRACK_LAUNCH_CHECK();
+  return TRACK_OK;
+}
+
 track_status attention(int dtype, int B, int H, int head_dim, int64_t Lq, int64_t Lk, const void* q, int64_t ldq,
                        const void* k, int64_t ldk, const void* vt, int64_t ldv, void* out, int64_t ldo,
                        hipStream_t s, int prof_kind, bool q_log2) {
@@ -1011,33 +1056,18 @@ track_status attention(int dtype, int B, int H, int head_dim, int64_t Lq, int64_
     return TRACK_OK;
   }
   if (dtype != TRACK_DTYPE_F32) return fail(TRACK_E_INVALID, "attention: bad dtype %d", dtype);
-  const float scale_log2 = attn_log2_scale(head_dim);
-  const int64_t nqb = (Lq + 15) / 16;
-  // four waves a query block until the blocks alone give every SIMD a wave
-  const bool split = nqb * H * B < 4 * (int64_t)device_cus();
-  const bool vec = ((ldq | ldk | ldv | ldo) & 3) == 0 &&
-                   (((uintptr_t)q | (uintptr_t)k | (uintptr_t)vt | (uintptr_t)out) & 15) == 0;
-  dim3 grid((unsigned)(split ? nqb : (nqb + 3) / 4), H, B);
-#define TRACK_ATT_F32_K(DH, KS, VEC)                                                                               \
-  attn_f32_kernel<DH, KS, VEC><<<grid, 256, 0, s>>>((const float*)q, ldq, (const float*)k, ldk, (const float*)vt, \
-                                                    ldv, (float*)out, ldo, H, Lq, Lk, scale_log2)
-#define TRACK_ATT_F32(DH)                         \
-  do {                                            \
-    if (split && vec) TRACK_ATT_F32_K(DH, 4, true); \
-    else if (split) TRACK_ATT_F32_K(DH, 4, false);  \
-    else if (vec) TRACK_ATT_F32_K(DH, 1, true);     \
-    else TRACK_ATT_F32_K(DH, 1, false);             \
-  } while (0)
-  switch (head_dim) {
-    case 32: TRACK_ATT_F32(32); break;
-    case 64: TRACK_ATT_F32(64); break;
-    case 128: TRACK_ATT_F32(128); break;
-    default: return fail(TRACK_E_UNSUPPORTED, "attention: float32 path supports head_dim 32, 64, 128 (got %d)", head_dim);
-  }
-#undef TRACK_ATT_F32
-#undef TRACK_ATT_F32_K
-  TRACK_LAUNCH_CHECK();
-  return TRACK_OK;
+  return attention_f32(B, H, head_dim, Lq, Lk, (const float*)q, ldq, (const float*)k, ldk, (const float*)vt, ldv,
+                       (float*)out, ldo, false, s);
+}
+
+track_status attention_f32_vrows(int B, int H, int head_dim, int64_t Lq, int64_t Lk, const float* q, int64_t ldq,
+                                 const float* k, int64_t ldk, const float* v, int64_t ldv, float* out, int64_t ldo,
+                                 hipStream_t s, int prof_kind) {
+  const int64_t width = (int64_t)H * head_dim;
+  if (B < 1 || H < 1 || Lq < 1 || Lk < 1 || ldq < width || ldk < width || ldv < width || ldo < width)
+    return fail(TRACK_E_SHAPE, "attention_f32_vrows: bad sizes");
+  ProfScope prof(prof_kind, s);
+  return attention_f32(B, H, head_dim, Lq, Lk, q, ldq, k, ldk, v, ldv, out, ldo, true, s);
 }
 
 }  // namespace track

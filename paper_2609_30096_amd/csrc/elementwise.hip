@@ -141,37 +141,28 @@ track_status gemv(int dtype, int N, int K, const void* W, const void* b, const f
 }
 
 template <typename T>
-__global__ void mod_tables_kernel(int blocks, int n6, const float* __restrict__ m, const T* __restrict__ Tb,
-                                  int64_t stride, float* __restrict__ mods) {
-  const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (i >= (int64_t)blocks * n6) return;
-  const int blk = (int)(i / n6), j = (int)(i % n6);
-  mods[i] = m[j] + ldf(Tb + blk * stride + j);
+__global__ void mod_tables_kernel(int blocks, int d, const float* __restrict__ m, const T* __restrict__ Tb,
+                                  int64_t stride, float* __restrict__ mods, const float* __restrict__ e,
+                                  const T* __restrict__ Th, float* __restrict__ hmod) {
+  const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x, n = (int64_t)blocks * 6 * d;
+  if (i < n) {
+    const int blk = (int)(i / (6 * d)), j = (int)(i % (6 * d));
+    mods[i] = m[j] + ldf(Tb + blk * stride + j);
+  } else if (i < n + 2 * d) {
+    const int j = (int)(i - n);
+    hmod[j] = ldf(Th + j) + e[j % d];
+  }
 }
 
 track_status mod_tables(int dtype, int blocks, int d, const float* m, const void* Tbase, int64_t stride_elems,
-                        float* mods, hipStream_t s) {
-  const int64_t n = (int64_t)blocks * 6 * d;
-  if (n == 0) return TRACK_OK;
+                        float* mods, const float* e, const void* Thead, float* hmod, hipStream_t s) {
+  const int64_t n = ((int64_t)blocks * 6 + 2) * d;
   if (dtype == TRACK_DTYPE_BF16)
-    mod_tables_kernel<bf16_t><<<cdiv(n, 256), 256, 0, s>>>(blocks, 6 * d, m, (const bf16_t*)Tbase, stride_elems, mods);
+    mod_tables_kernel<bf16_t><<<cdiv(n, 256), 256, 0, s>>>(blocks, d, m, (const bf16_t*)Tbase, stride_elems, mods, e,
+                                                           (const bf16_t*)Thead, hmod);
   else
-    mod_tables_kernel<float><<<cdiv(n, 256), 256, 0, s>>>(blocks, 6 * d, m, (const float*)Tbase, stride_elems, mods);
-  TRACK_LAUNCH_CHECK();
-  return TRACK_OK;
-}
-
-template <typename T>
-__global__ void head_mod_kernel(int d, const float* __restrict__ e, const T* __restrict__ Tt, float* __restrict__ out) {
-  const int i = blockIdx.x * blockDim.x + threadIdx.x;
-  if (i < 2 * d) out[i] = ldf(Tt + i) + e[i % d];
-}
-
-track_status head_mod(int dtype, int d, const float* e, const void* T, float* out, hipStream_t s) {
-  if (dtype == TRACK_DTYPE_BF16)
-    head_mod_kernel<bf16_t><<<cdiv(2 * d, 256), 256, 0, s>>>(d, e, (const bf16_t*)T, out);
-  else
-    head_mod_kernel<float><<<cdiv(2 * d, 256), 256, 0, s>>>(d, e, (const float*)T, out);
+    mod_tables_kernel<float><<<cdiv(n, 256), 256, 0, s>>>(blocks, d, m, (const float*)Tbase, stride_elems, mods, e,
+                                                          (const float*)Thead, hmod);
   TRACK_LAUNCH_CHECK();
   return TRACK_OK;
 }
@@ -447,7 +438,8 @@ __global__ __launch_bounds__(256) void rmsnorm_rope_kernel(int64_t rows, int d, 
                                                            const T* __restrict__ g2,
                                                            const float* __restrict__ cos_t,
                                                            const float* __restrict__ sin_t, int Gf, int Gh, int Gw,
-                                                           int64_t L, float qscale) {
+                                                           int64_t L, float qscale, uint32_t gain_rows,
+                                                           int64_t gain_stride) {
   static_assert(WPR == 1 || WPR == 4, "RPB rows per wave, or per workgroup");
   typedef typename RawOf<T, E>::type Raw;
   __shared__ float red[4 * RPB];
@@ -540,6 +532,7 @@ __global__ __launch_bounds__(256) void rmsnorm_rope_kernel(int64_t rows, int d, 
     const int64_t row = g2 ? vrow >> 1 : vrow;
     const int seg = g2 ? (int)(vrow & 1) : 0;
     const T* gs = seg ? g2 : g;
+    if (gain_rows) gs += (uint32_t)row / gain_rows * gain_stride;
     const float rstd = (1.0f / sqrtf(sq[r] / (float)d + 1e-6f)) * (seg ? 1.0f : qscale);
     T* xr = buf + row * ld + col0 + (int64_t)seg * d;
 #pragma unroll
@@ -583,6 +576,8 @@ struct RmsArgs {
   int64_t L;
   hipStream_t s;
   float qscale;
+  uint32_t gain_rows;
+  int64_t gain_stride;
 };
 static thread_local RmsArgs g_rms;
 
@@ -598,16 +593,16 @@ struct RmsLaunchW {
       if constexpr (E == 8) {
         rmsnorm_rope_kernel<bf16_t, 8, NC, WPR, RPB><<<grid, 256, 0, a.s>>>(
             vrows, d, a.head_dim, (bf16_t*)a.buf, a.ld, a.col0, (const bf16_t*)a.g, (const bf16_t*)a.g2, a.cos_t,
-            a.sin_t, a.grid.f, a.grid.h, a.grid.w, a.L, a.qscale);
+            a.sin_t, a.grid.f, a.grid.h, a.grid.w, a.L, a.qscale, a.gain_rows, a.gain_stride);
       } else {
         if (a.dtype == TRACK_DTYPE_BF16)
           rmsnorm_rope_kernel<bf16_t, 4, NC, WPR, RPB><<<grid, 256, 0, a.s>>>(
               vrows, d, a.head_dim, (bf16_t*)a.buf, a.ld, a.col0, (const bf16_t*)a.g, (const bf16_t*)a.g2, a.cos_t,
-              a.sin_t, a.grid.f, a.grid.h, a.grid.w, a.L, a.qscale);
+              a.sin_t, a.grid.f, a.grid.h, a.grid.w, a.L, a.qscale, a.gain_rows, a.gain_stride);
         else
           rmsnorm_rope_kernel<float, 4, NC, WPR, RPB><<<grid, 256, 0, a.s>>>(
               vrows, d, a.head_dim, (float*)a.buf, a.ld, a.col0, (const float*)a.g, (const float*)a.g2, a.cos_t,
-              a.sin_t, a.grid.f, a.grid.h, a.grid.w, a.L, a.qscale);
+              a.sin_t, a.grid.f, a.grid.h, a.grid.w, a.L, a.qscale, a.gain_rows, a.gain_stride);
       }
     }
   };
@@ -615,18 +610,19 @@ struct RmsLaunchW {
 
 track_status rmsnorm_rope(int dtype, int64_t rows, int heads, int head_dim, void* buf, int64_t ld, int64_t col0,
                           const void* g, const void* g2, const float* cos_t, const float* sin_t, Grid3 grid, int64_t L,
-                          hipStream_t s, float qscale) {
+                          hipStream_t s, float qscale, int64_t gain_rows, int64_t gain_stride) {
   const int d = heads * head_dim;
   if (g2 && ld < col0 + 2 * (int64_t)d) return fail(TRACK_E_SHAPE, "rmsnorm_rope: two segments need ld >= col0 + 2d");
   if (head_dim % 4 || d > 256 * NORM_MAXC) return fail(TRACK_E_UNSUPPORTED, "rmsnorm_rope: width %d unsupported", d);
   if (cos_t && (int64_t)grid.f * grid.h * grid.w != L) return fail(TRACK_E_SHAPE, "rmsnorm_rope: grid != L");
   if (rows <= 0) return TRACK_OK;
+  if (gain_rows && rows > INT32_MAX) return fail(TRACK_E_UNSUPPORTED, "rmsnorm_rope: too many rows for gain groups");
   ProfScope prof(TRACK_PROF_NORM, s);
-  g_rms = RmsArgs{dtype, rows, heads, head_dim, buf, ld, col0, g, g2, cos_t, sin_t, grid, L > 0 ? L : 1, s, qscale};
+  g_rms = RmsArgs{dtype, rows, heads, head_dim, buf, ld, col0, g, g2, cos_t, sin_t, grid, L > 0 ? L : 1, s, qscale, (uint32_t)gain_rows, gain_stride};
   // bfloat16 rows move in 16-byte chunks of 8 elements when the width allows
   // (a chunk must not straddle two heads: head_dim % 8 == 0)
   const bool wide_chunks = dtype == TRACK_DTYPE_BF16 && head_dim % 8 == 0 &&
-                           ((uintptr_t)buf & 15) == 0 && ((uintptr_t)g & 15) == 0 && (!g2 || ((uintptr_t)g2 & 15) == 0) &&
+                           ((uintptr_t)buf & 15) == 0 && ((uintptr_t)g & 15) == 0 && gain_stride % 8 == 0 && (!g2 || ((uintptr_t)g2 & 15) == 0) &&
                            ld % 8 == 0 && col0 % 8 == 0;
   if (wide_chunks) {
     if (d > NORM_WIDE)

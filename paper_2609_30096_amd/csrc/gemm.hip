@@ -27,6 +27,8 @@ struct EpiArgs {
   void* vt = nullptr;
   int64_t ldv = 0, L = 1, m_off = 0;
   int nv = 0;  // N
+  // products of a batch (blockIdx.z): element strides of W and bias (one stride), and of out
+  int64_t zw = 0, zo = 0;
 };
 
 // Persistent-kernel epilogue that writes the output transposed per batch
@@ -609,6 +611,11 @@ template <int XF, int YF, int NS, int EPI>
 __global__ __launch_bounds__(256) void gemm_bf16_tile_kernel(const bf16_t* __restrict__ A, int64_t lda,
                                                              const bf16_t* __restrict__ W, int64_t M, int N, int K,
                                                              EpiArgs e, int GB) {
+  if constexpr (EPI == TRACK_EPI_BIAS) {
+    W += blockIdx.z * e.zw;
+    e.bias = (const bf16_t*)e.bias + blockIdx.z * e.zw;
+    e.out = (bf16_t*)e.out + blockIdx.z * e.zo;
+  }
   constexpr bool VT = EPI == EPI_BIAS_VT;
   constexpr int BX = 32 * XF, BY = 32 * YF, BM = VT ? BX : BY, BN = VT ? BY : BX;
   constexpr int BK = 64, ROWB = 128, NWV = 4;
@@ -792,10 +799,38 @@ __global__ __launch_bounds__(256) void gemm_f32_kernel(const float* __restrict__
 // steps, where the LDS tiles above took a load, two barriers and a store per 16 of
 // K on a handful of CUs.  K-index i of chunk kc is k = 16 kc + 4 (lane / 16) + i, so
 // every lane loads 16 bytes.  Needs K % 4 == 0 and 16-byte aligned rows.
-template <int EPI, int T>
+//
+// With LN the rows of A are LayerNorm inputs: a wave's share of its rows (K up to
+// SF_LN_K) stays in registers, the rows' means and centred square sums are joined over
+// the lanes and (LDS) the waves, and the normalised, modulated values go straight into the
+// products, in place of a launch that writes them and another that reads them.
+constexpr int SF_LN_CH = 8, SF_LN_K = 4 * 16 * SF_LN_CH;
+
+// Sums over a row's four 16-lane groups and the four waves, for T rows a lane.
+template <int T>
+__device__ __forceinline__ void small_row_sums(float (&v)[T], float (*red)[16 * T], int wave, int j, int g) {
+#pragma unroll
+  for (int t = 0; t < T; ++t) {
+    v[t] += __shfl_xor(v[t], 16);
+    v[t] += __shfl_xor(v[t], 32);
+    if (g == 0) red[wave][16 * t + j] = v[t];
+  }
+  __syncthreads();
+#pragma unroll
+  for (int t = 0; t < T; ++t)
+    v[t] = (red[0][16 * t + j] + red[1][16 * t + j]) + (red[2][16 * t + j] + red[3][16 * t + j]);
+}
+
+template <int EPI, int T, bool LN>
 __global__ __launch_bounds__(256) void gemm_f32_small_kernel(const float* __restrict__ A, int64_t lda,
                                                              const float* __restrict__ W, int64_t M, int N, int K,
-                                                             EpiArgs e) {
+                                                             EpiArgs e, const float* __restrict__ ln_scale,
+                                                             const float* __restrict__ ln_shift) {
+  if constexpr (EPI == TRACK_EPI_BIAS) {
+    W += blockIdx.z * e.zw;
+    e.bias = (const float*)e.bias + blockIdx.z * e.zw;
+    e.out = (float*)e.out + blockIdx.z * e.zo;
+  }
   __shared__ f32x4 red[4][T * T][64];
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   const int j = lane & 15, g = lane >> 4;
@@ -815,28 +850,89 @@ __global__ __launch_bounds__(256) void gemm_f32_small_kernel(const float* __rest
 #pragma unroll
     for (int y = 0; y < T; ++y) acc[x][y] = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
   const int chunks = (K + 15) / 16;
-  constexpr int U = 4 / T;  // chunks whose loads are issued together
-  for (int kc = wave; kc < chunks; kc += 4 * U) {
-    f32x4 a[U][T], w[U][T];
+  const f32x4 zero = {0.0f, 0.0f, 0.0f, 0.0f};
+  if constexpr (LN) {
+    __shared__ float rs[2][4][16 * T];
+    f32x4 a[SF_LN_CH][T];
+    float sum[T], sq[T];
 #pragma unroll
-    for (int u = 0; u < U; ++u) {
-      const int k0 = 16 * (kc + 4 * u);
-      const bool in = k0 + 4 * g < K;
+    for (int t = 0; t < T; ++t) sum[t] = sq[t] = 0.0f;
 #pragma unroll
-      for (int t = 0; t < T; ++t) {
-        a[u][t] = in ? *(const f32x4*)(ap[t] + k0) : f32x4{0.0f, 0.0f, 0.0f, 0.0f};
-        w[u][t] = in ? *(const f32x4*)(wp[t] + k0) : f32x4{0.0f, 0.0f, 0.0f, 0.0f};
-      }
+    for (int u = 0; u < SF_LN_CH; ++u) {
+      const int k0 = 16 * (wave + 4 * u);
+#pragma unroll
+      for (int t = 0; t < T; ++t) a[u][t] = k0 + 4 * g < K ? *(const f32x4*)(ap[t] + k0) : zero;
     }
 #pragma unroll
-    for (int u = 0; u < U; ++u)
+    for (int u = 0; u < SF_LN_CH; ++u)
 #pragma unroll
-      for (int i = 0; i < 4; ++i)
+      for (int t = 0; t < T; ++t) sum[t] += (a[u][t][0] + a[u][t][1]) + (a[u][t][2] + a[u][t][3]);
+    small_row_sums<T>(sum, rs[0], wave, j, g);
+#pragma unroll
+    for (int u = 0; u < SF_LN_CH; ++u)
+#pragma unroll
+      for (int t = 0; t < T; ++t) {
+        if (16 * (wave + 4 * u) + 4 * g >= K) continue;
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+          a[u][t][i] -= sum[t] / (float)K;
+          sq[t] = fmaf(a[u][t][i], a[u][t][i], sq[t]);
+        }
+      }
+    small_row_sums<T>(sq, rs[1], wave, j, g);
+#pragma unroll
+    for (int t = 0; t < T; ++t) sq[t] = 1.0f / sqrtf(sq[t] / (float)K + 1e-6f);
+#pragma unroll
+    for (int u = 0; u < SF_LN_CH; ++u) {
+      const int k0 = 16 * (wave + 4 * u);
+      if (k0 >= K) break;  // wave-uniform
+      const bool in = k0 + 4 * g < K;
+      f32x4 w[T], sc = zero, sh = zero;
+      if (ln_scale && in) {
+        sc = *(const f32x4*)(ln_scale + k0 + 4 * g);
+        sh = *(const f32x4*)(ln_shift + k0 + 4 * g);
+      }
+#pragma unroll
+      for (int t = 0; t < T; ++t) w[t] = in ? *(const f32x4*)(wp[t] + k0) : zero;
+#pragma unroll
+      for (int i = 0; i < 4; ++i) {
+        float v[T];
+#pragma unroll
+        for (int t = 0; t < T; ++t) {
+          v[t] = a[u][t][i] * sq[t];
+          if (ln_scale) v[t] = fmaf(v[t], 1.0f + sc[i], sh[i]);
+        }
 #pragma unroll
         for (int x = 0; x < T; ++x)
 #pragma unroll
           for (int y = 0; y < T; ++y)
-            acc[x][y] = __builtin_amdgcn_mfma_f32_16x16x4f32(w[u][x][i], a[u][y][i], acc[x][y], 0, 0, 0);
+            acc[x][y] = __builtin_amdgcn_mfma_f32_16x16x4f32(w[x][i], v[y], acc[x][y], 0, 0, 0);
+      }
+    }
+  } else {
+    constexpr int U = 4 / T;  // chunks whose loads are issued together
+    for (int kc = wave; kc < chunks; kc += 4 * U) {
+      f32x4 a[U][T], w[U][T];
+#pragma unroll
+      for (int u = 0; u < U; ++u) {
+        const int k0 = 16 * (kc + 4 * u);
+        const bool in = k0 + 4 * g < K;
+#pragma unroll
+        for (int t = 0; t < T; ++t) {
+          a[u][t] = in ? *(const f32x4*)(ap[t] + k0) : zero;
+          w[u][t] = in ? *(const f32x4*)(wp[t] + k0) : zero;
+        }
+      }
+#pragma unroll
+      for (int u = 0; u < U; ++u)
+#pragma unroll
+        for (int i = 0; i < 4; ++i)
+#pragma unroll
+          for (int x = 0; x < T; ++x)
+#pragma unroll
+            for (int y = 0; y < T; ++y)
+              acc[x][y] = __builtin_amdgcn_mfma_f32_16x16x4f32(w[u][x][i], a[u][y][i], acc[x][y], 0, 0, 0);
+    }
   }
 #pragma unroll
   for (int x = 0; x < T; ++x)
@@ -919,17 +1015,18 @@ static int gemm_config() {
 // for all that fill half the chip, and 128 x 128 for the rest, were 1.1 to 4.5 times
 // slower (1.3B, 3120 rows: FFN2 154.7 -> 76.3 us, O 35.8 -> 22.8, q/k 51.3 ->
 // 29.7, FFN1 111 -> 79; text K/V of 1024 rows 22.9 -> 14.1; 14B, 130 rows: O 61 -> 19).
-static int pick_tile(int64_t M, int64_t N, int64_t K, bool vt, int force) {
+// A batch of nb products (not for the persistent kernel) counts all their tiles.
+static int pick_tile(int64_t M, int64_t N, int64_t K, bool vt, int force, int64_t nb = 1) {
   const int cus = device_cus();
   int best = -1;
   double best_t = 0.0;
   for (int i = 0; i < NTILES; ++i) {
     const TileCfg& c = kTiles[i];
-    if (vt && !c.vt) continue;
+    if ((vt && !c.vt) || (nb > 1 && i == 0)) continue;
     const int64_t bm = 32 * (vt ? c.xf : c.yf), bn = 32 * (vt ? c.yf : c.xf);
     if (N % bn) continue;
     if (i == force) return i;
-    const int64_t tiles = (M + bm - 1) / bm * (N / bn);
+    const int64_t tiles = (M + bm - 1) / bm * (N / bn) * nb;
     const int64_t round = (int64_t)c.resident * cus, full = tiles / round, rem = tiles % round;
     const double l2 = 1.47 * (double)(bm + bn), one = (double)(bm * bn) / 64.0 + 70.0;
     double t = (double)full * std::max(c.resident * l2, one);
@@ -945,9 +1042,9 @@ static int pick_tile(int64_t M, int64_t N, int64_t K, bool vt, int force) {
 
 template <int XF, int YF, int NS, bool VT>
 static void launch_tile(int epi, const bf16_t* A, int64_t lda, const bf16_t* W, int64_t M, int N, int K,
-                        const EpiArgs& e, hipStream_t s) {
+                        const EpiArgs& e, hipStream_t s, int nb) {
   const int bm = 32 * (epi == EPI_BIAS_VT ? XF : YF), bn = 32 * (epi == EPI_BIAS_VT ? YF : XF);
-  dim3 grid((unsigned)((M + bm - 1) / bm) * (unsigned)(N / bn)), block(256);
+  dim3 grid((unsigned)((M + bm - 1) / bm) * (unsigned)(N / bn), 1, (unsigned)nb), block(256);
   constexpr int GB = 8;  // height of the bands of M-tiles swept across N
 #define TRACK_TK(E) gemm_bf16_tile_kernel<XF, YF, NS, E><<<grid, block, 0, s>>>(A, lda, W, M, N, K, e, GB)
   if constexpr (VT) {
@@ -999,35 +1096,43 @@ static void launch_bf16_persist(int epi, const bf16_t* A, int64_t lda, const bf1
 }
 
 static void launch_bf16(int tile, int epi, const bf16_t* A, int64_t lda, const bf16_t* W, int64_t M, int N, int K,
-                        const EpiArgs& e, int out_elem, hipStream_t s) {
+                        const EpiArgs& e, int out_elem, hipStream_t s, int nb = 1) {
   switch (tile) {
     case 0: launch_bf16_persist(epi, A, lda, W, M, N, K, e, out_elem, s); break;
-    case 1: launch_tile<8, 4, 3, false>(epi, A, lda, W, M, N, K, e, s); break;
-    case 2: launch_tile<4, 8, 3, true>(epi, A, lda, W, M, N, K, e, s); break;
-    case 3: launch_tile<4, 5, 4, false>(epi, A, lda, W, M, N, K, e, s); break;
-    case 4: launch_tile<4, 5, 2, false>(epi, A, lda, W, M, N, K, e, s); break;
-    case 5: launch_tile<4, 4, 4, true>(epi, A, lda, W, M, N, K, e, s); break;
-    case 6: launch_tile<4, 3, 4, false>(epi, A, lda, W, M, N, K, e, s); break;
-    case 7: launch_tile<4, 2, 3, false>(epi, A, lda, W, M, N, K, e, s); break;
-    case 8: launch_tile<2, 4, 3, true>(epi, A, lda, W, M, N, K, e, s); break;
-    case 9: launch_tile<2, 2, 4, true>(epi, A, lda, W, M, N, K, e, s); break;
-    default: launch_tile<2, 1, 4, false>(epi, A, lda, W, M, N, K, e, s); break;
+    case 1: launch_tile<8, 4, 3, false>(epi, A, lda, W, M, N, K, e, s, nb); break;
+    case 2: launch_tile<4, 8, 3, true>(epi, A, lda, W, M, N, K, e, s, nb); break;
+    case 3: launch_tile<4, 5, 4, false>(epi, A, lda, W, M, N, K, e, s, nb); break;
+    case 4: launch_tile<4, 5, 2, false>(epi, A, lda, W, M, N, K, e, s, nb); break;
+    case 5: launch_tile<4, 4, 4, true>(epi, A, lda, W, M, N, K, e, s, nb); break;
+    case 6: launch_tile<4, 3, 4, false>(epi, A, lda, W, M, N, K, e, s, nb); break;
+    case 7: launch_tile<4, 2, 3, false>(epi, A, lda, W, M, N, K, e, s, nb); break;
+    case 8: launch_tile<2, 4, 3, true>(epi, A, lda, W, M, N, K, e, s, nb); break;
+    case 9: launch_tile<2, 2, 4, true>(epi, A, lda, W, M, N, K, e, s, nb); break;
+    default: launch_tile<2, 1, 4, false>(epi, A, lda, W, M, N, K, e, s, nb); break;
   }
 }
 
-static void launch_f32(int epi, const float* A, int64_t lda, const float* W, int64_t M, int N, int K,
-                       const EpiArgs& e, hipStream_t s) {
-  const int64_t t16 = ((M + 15) / 16) * ((N + 15) / 16);
-  const bool aligned = K % 4 == 0 && lda % 4 == 0 && (((uintptr_t)A | (uintptr_t)W) & 15) == 0;
-  const int64_t cus = device_cus();
-  const int t = !aligned || t16 > 32 * cus ? 0 : (t16 > 4 * cus ? 2 : 1);
-  dim3 block(256), grid = t ? dim3((unsigned)((N + 16 * t - 1) / (16 * t)), (unsigned)((M + 16 * t - 1) / (16 * t)))
-                            : dim3((unsigned)((N + 63) / 64), (unsigned)((M + 63) / 64));
-#define TRACK_F32(E)                                                                     \
-  do {                                                                                   \
-    if (t == 1) gemm_f32_small_kernel<E, 1><<<grid, block, 0, s>>>(A, lda, W, M, N, K, e); \
-    else if (t == 2) gemm_f32_small_kernel<E, 2><<<grid, block, 0, s>>>(A, lda, W, M, N, K, e); \
-    else gemm_f32_kernel<E><<<grid, block, 0, s>>>(A, lda, W, M, N, K, e);               \
+// Blocks a side of the few-tile kernel's workgroup (0: the LDS-tiled kernel takes
+// the shape): one until the 16 x 16 blocks fill the chip four times over.
+static int f32_small_blocks(int64_t M, int64_t N, int64_t K, const void* A, int64_t lda, const void* W, int64_t nb) {
+  const int64_t t16 = ((M + 15) / 16) * ((N + 15) / 16) * nb, cus = device_cus();
+  if (K % 4 || lda % 4 || (((uintptr_t)A | (uintptr_t)W) & 15) || t16 > 32 * cus) return 0;
+  return t16 > 4 * cus ? 2 : 1;
+}
+
+// ln: the rows of A are LayerNorm inputs (few-tile kernel only, t > 0)
+static void launch_f32(int t, int epi, const float* A, int64_t lda, const float* W, int64_t M, int N, int K,
+                       const EpiArgs& e, int nb, bool ln, const float* scale, const float* shift, hipStream_t s) {
+  const int b = t ? 16 * t : 64;
+  dim3 block(256), grid((unsigned)((N + b - 1) / b), (unsigned)((M + b - 1) / b), (unsigned)nb);
+#define TRACK_F32_S(E, T, LN) gemm_f32_small_kernel<E, T, LN><<<grid, block, 0, s>>>(A, lda, W, M, N, K, e, scale, shift)
+#define TRACK_F32(E)                                                \
+  do {                                                              \
+    if (t == 1 && ln) TRACK_F32_S(E, 1, true);                      \
+    else if (t == 2 && ln) TRACK_F32_S(E, 2, true);                 \
+    else if (t == 1) TRACK_F32_S(E, 1, false);                      \
+    else if (t == 2) TRACK_F32_S(E, 2, false);                      \
+    else gemm_f32_kernel<E><<<grid, block, 0, s>>>(A, lda, W, M, N, K, e); \
   } while (0)
   switch (epi) {
     case TRACK_EPI_BIAS: TRACK_F32(TRACK_EPI_BIAS); break;
@@ -1037,6 +1142,7 @@ static void launch_f32(int epi, const float* A, int64_t lda, const float* W, int
     default: TRACK_F32(TRACK_EPI_BIAS_F32); break;
   }
 #undef TRACK_F32
+#undef TRACK_F32_S
 }
 
 track_status linear(int dtype, int epi, int64_t M, int64_t N, int64_t K, const void* A, int64_t lda, const void* W,
@@ -1050,7 +1156,8 @@ track_status linear(int dtype, int epi, int64_t M, int64_t N, int64_t K, const v
   EpiArgs e{bias, gate, out, ldo};
   ProfScope prof(TRACK_PROF_GEMM, s);
   if (dtype == TRACK_DTYPE_F32) {
-    launch_f32(epi, (const float*)A, lda, (const float*)W, M, (int)N, (int)K, e, s);
+    launch_f32(f32_small_blocks(M, N, K, A, lda, W, 1), epi, (const float*)A, lda, (const float*)W, M, (int)N, (int)K, e,
+               1, false, nullptr, nullptr, s);
     TRACK_LAUNCH_CHECK();
     return TRACK_OK;
   }
@@ -1067,6 +1174,59 @@ track_status linear(int dtype, int epi, int64_t M, int64_t N, int64_t K, const v
     launch_bf16_big_ld(epi, a, lda, w, M, n, k, e, s);
   else
     launch_bf16(pick_tile(M, N, K, false, gemm_config()), epi, a, lda, w, M, n, k, e, out_elem, s);
+  TRACK_LAUNCH_CHECK();
+  return TRACK_OK;
+}
+
+track_status linear_batch(int dtype, int nb, int64_t M, int64_t N, int64_t K, const void* A, int64_t lda, const void* W,
+                          const void* bias, int64_t wstride, void* out, int64_t ldo, int64_t ostride, hipStream_t s) {
+  const size_t es = dtype == TRACK_DTYPE_BF16 ? 2 : 4;
+  const bool bf = dtype == TRACK_DTYPE_BF16;
+  const int t = bf ? 0 : f32_small_blocks(M, N, K, A, lda, W, nb);
+  // one launch on the kernels that take a batch, within their alignment needs
+  const bool batch = nb > 1 && nb < 65536 && M > 0 && N > 0 && K > 0 && A && W && bias && out && lda >= K && ldo >= N &&
+                     N <= (1 << 30) && K <= (1 << 30) &&
+                     (bf ? K % 64 == 0 && N % 64 == 0 && lda % 8 == 0 && ldo % 4 == 0 && wstride % 8 == 0 &&
+                               ostride % 8 == 0 && (((uintptr_t)A | (uintptr_t)W | (uintptr_t)out) & 15) == 0 &&
+                               ((uintptr_t)bias & 7) == 0 && lda < BUF_LD && K < BUF_LD
+                         : t > 0 && wstride % 4 == 0);
+  if (!batch) {
+    for (int i = 0; i < nb; ++i) {
+      const track_status st =
+          linear(dtype, TRACK_EPI_BIAS, M, N, K, A, lda, (const uint8_t*)W + i * wstride * es,
+                 (const uint8_t*)bias + i * wstride * es, nullptr, (uint8_t*)out + i * ostride * es, ldo, s);
+      if (st != TRACK_OK) return st;
+    }
+    return TRACK_OK;
+  }
+  EpiArgs e{bias, nullptr, out, ldo};
+  e.zw = wstride;
+  e.zo = ostride;
+  ProfScope prof(TRACK_PROF_GEMM, s);
+  if (bf)
+    launch_bf16(pick_tile(M, N, K, false, -1, nb), TRACK_EPI_BIAS, (const bf16_t*)A, lda, (const bf16_t*)W, M, (int)N,
+                (int)K, e, 2, s, nb);
+  else
+    launch_f32(t, TRACK_EPI_BIAS, (const float*)A, lda, (const float*)W, M, (int)N, (int)K, e, nb, false, nullptr,
+               nullptr, s);
+  TRACK_LAUNCH_CHECK();
+  return TRACK_OK;
+}
+
+track_status layernorm_linear(int dtype, int epi, int64_t M, int64_t N, int64_t K, const float* X, const float* scale,
+                              const float* shift, void* Y, const void* W, const void* bias, const float* gate,
+                              void* out, int64_t ldo, hipStream_t s) {
+  const int t = dtype == TRACK_DTYPE_F32 && K <= SF_LN_K && M > 0 && N > 0 && ldo >= N && N <= (1 << 30) && bias && out &&
+                        (epi != TRACK_EPI_GATE_RESID || gate) && (((uintptr_t)scale | (uintptr_t)shift) & 15) == 0
+                    ? f32_small_blocks(M, N, K, X, K, W, 1)
+                    : 0;
+  if (!t) {
+    const track_status st = layernorm(dtype, M, (int)K, X, scale, shift, Y, s);
+    if (st != TRACK_OK) return st;
+    return linear(dtype, epi, M, N, K, Y, K, W, bias, gate, out, ldo, s);
+  }
+  ProfScope prof(TRACK_PROF_GEMM, s);
+  launch_f32(t, epi, X, K, (const float*)W, M, (int)N, (int)K, EpiArgs{bias, gate, out, ldo}, 1, true, scale, shift, s);
   TRACK_LAUNCH_CHECK();
   return TRACK_OK;
 }

@@ -14,6 +14,16 @@ namespace track {
 // gemm.hip
 track_status linear(int dtype, int epi, int64_t M, int64_t N, int64_t K, const void* A, int64_t lda, const void* W,
                     const void* bias, const float* gate, void* out, int64_t ldo, hipStream_t s);
+// `nb` products over one A: W, bias and out advance by wstride, wstride_b and
+// ostride elements from one to the next (bias epilogue only).
+track_status linear_batch(int dtype, int nb, int64_t M, int64_t N, int64_t K, const void* A, int64_t lda, const void* W,
+                          const void* bias, int64_t wstride, void* out, int64_t ldo, int64_t ostride, hipStream_t s);
+// linear() on the modulated LayerNorm of float32 rows X [M, K] (scale and shift
+// both null: plain LayerNorm).  One launch where the float32 kernel that holds its
+// rows applies; otherwise layernorm() into Y, then linear().
+track_status layernorm_linear(int dtype, int epi, int64_t M, int64_t N, int64_t K, const float* X, const float* scale,
+                              const float* shift, void* Y, const void* W, const void* bias, const float* gate,
+                              void* out, int64_t ldo, hipStream_t s);
 // A W^T + bias (bfloat16) written transposed per batch of L rows:
 // vt[((m / L) * N + n) * ldv + m % L].
 track_status linear_vt(int64_t M, int64_t N, int64_t K, const void* A, int64_t lda, const void* W, const void* bias,
@@ -29,6 +39,11 @@ track_status zero_cols_bf16(void* p, int64_t rows, int64_t ld, int64_t c0, int64
 track_status attention(int dtype, int B, int H, int head_dim, int64_t Lq, int64_t Lk, const void* q, int64_t ldq,
                        const void* k, int64_t ldk, const void* vt, int64_t ldv, void* out, int64_t ldo,
                        hipStream_t s, int prof_kind, bool q_log2 = false);
+// attention() in float32 with V in rows of stride ldv (key j of head h at
+// v[(b Lk + j) ldv + h head_dim]) in place of V^T.
+track_status attention_f32_vrows(int B, int H, int head_dim, int64_t Lq, int64_t Lk, const float* q, int64_t ldq,
+                                 const float* k, int64_t ldk, const float* v, int64_t ldv, float* out, int64_t ldo,
+                                 hipStream_t s, int prof_kind);
 // The softmax scale in log2 units, log2(e) / sqrt(head_dim).
 float attn_log2_scale(int head_dim);
 
@@ -45,11 +60,10 @@ track_status sinusoid(double t, int dim, float* out, hipStream_t s);
 // if y_silu != NULL it also receives SiLU(y).
 track_status gemv(int dtype, int N, int K, const void* W, const void* b, const float* x, float* y, float* y_silu,
                   int post_silu, hipStream_t s);
-// mods[blk, 6, d] = m[6, d] + T_blk[6, d]; T_blk at Tbase + blk * stride_elems (weight dtype)
+// mods[blk, 6, d] = m[6, d] + T_blk[6, d], T_blk at Tbase + blk * stride_elems (weight
+// dtype), and hmod[2, d] = Thead[2, d] + e[d]
 track_status mod_tables(int dtype, int blocks, int d, const float* m, const void* Tbase, int64_t stride_elems,
-                        float* mods, hipStream_t s);
-// out[2, d] = T[2, d] + e[d]
-track_status head_mod(int dtype, int d, const float* e, const void* T, float* out, hipStream_t s);
+                        float* mods, const float* e, const void* Thead, float* hmod, hipStream_t s);
 // cos/sin tables in float64 cast to float32: for axis a with section width n_a
 // and extent E_a, table[a][pos][i] for i < n_a / 2.
 track_status rope_tables(int head_dim, Grid3 g, float* cos_t, float* sin_t, hipStream_t s);
@@ -57,9 +71,10 @@ track_status layernorm(int dtype, int64_t rows, int d, const float* x, const flo
                        hipStream_t s);
 // g2 != nullptr: two adjacent segments per row (col0 with gain g, col0 + d with g2) in one launch.
 // qscale multiplies the first segment's output (before its one rounding).
+// gain_rows > 0: rows [i gain_rows, (i + 1) gain_rows) take the gains at g + i gain_stride (elements).
 track_status rmsnorm_rope(int dtype, int64_t rows, int heads, int head_dim, void* buf, int64_t ld, int64_t col0,
                           const void* g, const void* g2, const float* cos_t, const float* sin_t, Grid3 grid, int64_t L,
-                          hipStream_t s, float qscale = 1.0f);
+                          hipStream_t s, float qscale = 1.0f, int64_t gain_rows = 0, int64_t gain_stride = 0);
 // vt[(b*H + h)*head_dim + c][key] = src[(b*Lk + key)*ld + col0 + h*head_dim + c]; zeros for Lk <= key < ldv
 track_status v_transpose(int dtype, int B, int H, int head_dim, int64_t Lk, const void* src, int64_t ld, int64_t col0,
                          void* vt, int64_t ldv, hipStream_t s);

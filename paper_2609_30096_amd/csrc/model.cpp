@@ -143,13 +143,14 @@ WsLayout ws_layout(const Model& m, const track_latent_shape& s, int B) {
   w.ctx = take((size_t)B * w.Lc * c.text_dim * es);
   w.th = take((size_t)B * w.Lc * d * es);
   w.temb = take((size_t)B * w.Lc * d * es);
-  w.kvc = take((size_t)B * w.Lc * 2 * d * es);
-  w.vct = take((size_t)B * c.heads * c.head_dim * w.Lcpad * es);
+  // text keys and values of all blocks (V transposed too for the bfloat16 attention)
+  w.kvc = take((size_t)c.blocks * B * w.Lc * 2 * d * es);
+  w.vct = take(c.dtype == TRACK_DTYPE_BF16 ? (size_t)c.blocks * B * d * w.Lcpad * es : 0);
   w.tok = take((size_t)w.L * w.P * es);
   w.X = take((size_t)B * w.L * d * 4);
   w.Y = take((size_t)B * w.L * d * es);
   w.QKV = take((size_t)B * w.L * 3 * d * es);
-  w.Vt = take((size_t)B * c.heads * c.head_dim * w.Lpad * es);
+  w.Vt = take(c.dtype == TRACK_DTYPE_BF16 ? (size_t)B * d * w.Lpad * es : 0);
   w.AO = take((size_t)B * w.L * d * es);
   w.Hf = take((size_t)B * w.L * c.ffn_dim * es);
   w.vel = take((size_t)B * w.L * w.P * 4);
@@ -175,8 +176,62 @@ WsLayout ws_layout(const Model& m, const track_latent_shape& s, int B) {
     if (st_ != TRACK_OK) return st_;    \
   } while (0)
 
+// Elements between a tensor of one block and the same tensor of the next.
+static int64_t block_stride(const Model& m) {
+  return m.cfg.blocks > 1 ? (int64_t)(m.specs[T_NGLOBAL + B_NBLOCK].offset - m.specs[T_NGLOBAL].offset) /
+                                (int64_t)dtype_size(m.cfg.dtype)
+                          : 0;
+}
+
+// bfloat16, whole 8-token groups, at least 128 tokens and a width the 256-wide
+// tiles divide: the V projection writes V^T for attention straight from its
+// epilogue, all but the padding columns [L, Lpad).
+static bool v_from_gemm(const Model& m, const WsLayout& w) {
+  return m.cfg.dtype == TRACK_DTYPE_BF16 && w.L % 8 == 0 && w.L >= 128 && m.cfg.dim % 256 == 0 &&
+         m.cfg.dim < ((int64_t)1 << 22);
+}
+
+// The RoPE tables, V^T's zero padding, the text MLP and every block's text keys and
+// values (projection, key RMSNorm, bfloat16: V^T): none depends on the latent or the
+// timestep, so a sampling loop runs this once per set of contexts, and the blocks'
+// products are one launch instead of one per block, each too small to fill the chip.
+track_status prepare(const Model& m, const track_latent_shape& s, int B, const void* const* ctx, hipStream_t st) {
+  const auto& c = m.cfg;
+  const int dt = c.dtype;
+  const size_t es = dtype_size(dt);
+  const WsLayout w = ws_layout(m, s, B);
+  if (!m.ws || m.ws_bytes < w.total) return fail(TRACK_E_NOMEM, "workspace of %zu bytes needed, %zu attached", w.total, m.ws_bytes);
+  const int64_t d = c.dim, Lc = w.Lc, H = c.heads, dh = c.head_dim;
+  uint8_t* ctxb = wsp<uint8_t>(m, w.ctx);
+  void* th = wsp<void>(m, w.th);
+  void* temb = wsp<void>(m, w.temb);
+  uint8_t* kvc = wsp<uint8_t>(m, w.kvc);
+  {
+    ProfScope prof(TRACK_PROF_OTHER, st);
+    TRY(rope_tables(c.head_dim, w.grid, wsp<float>(m, w.rope_cos), wsp<float>(m, w.rope_sin), st));
+    // (nothing else writes these columns)
+    if (v_from_gemm(m, w)) TRY(zero_cols_bf16(wsp<void>(m, w.Vt), B * d, w.Lpad, w.L, w.Lpad, st));
+    // text context of each branch, contiguous
+    const size_t cbytes = (size_t)Lc * c.text_dim * es;
+    for (int b = 0; b < B; ++b) TRACK_HIP(hipMemcpyAsync(ctxb + b * cbytes, ctx[b], cbytes, hipMemcpyDeviceToDevice, st));
+  }
+  TRY(linear(dt, TRACK_EPI_BIAS_GELU, B * Lc, d, c.text_dim, ctxb, c.text_dim, gW(m, T_TEXT_W1), gW(m, T_TEXT_B1), nullptr, th, d, st));
+  TRY(linear(dt, TRACK_EPI_BIAS, B * Lc, d, d, th, d, gW(m, T_TEXT_W2), gW(m, T_TEXT_B2), nullptr, temb, d, st));
+  if (c.blocks == 0) return TRACK_OK;
+  const int64_t stride = block_stride(m);
+  TRY(linear_batch(dt, c.blocks, B * Lc, 2 * d, d, temb, d, bW(m, 0, B_CKV_W), bW(m, 0, B_CKV_B), stride, kvc, 2 * d,
+                   B * Lc * 2 * d, st));
+  TRY(rmsnorm_rope(dt, c.blocks * B * Lc, (int)H, (int)dh, kvc, 2 * d, 0, bW(m, 0, B_NORM_CK), nullptr, nullptr, nullptr,
+                   w.grid, Lc, st, 1.0f, B * Lc, stride));
+  if (dt == TRACK_DTYPE_BF16) {
+    ProfScope prof(TRACK_PROF_NORM, st);
+    TRY(v_transpose(dt, c.blocks * B, (int)H, (int)dh, Lc, kvc, 2 * d, d, wsp<void>(m, w.vct), w.Lcpad, st));
+  }
+  return TRACK_OK;
+}
+
 track_status forward(const Model& m, const track_latent_shape& s, int B, const float* x_tok, double t,
-                     const void* const* ctx, float* vel, hipStream_t st) {
+                     float* vel, hipStream_t st) {
   const auto& c = m.cfg;
   const int dt = c.dtype;
   const size_t es = dtype_size(dt);
@@ -193,11 +248,8 @@ track_status forward(const Model& m, const track_latent_shape& s, int B, const f
   float* hmod = wsp<float>(m, w.hmod);
   float* rcos = wsp<float>(m, w.rope_cos);
   float* rsin = wsp<float>(m, w.rope_sin);
-  uint8_t* ctxb = wsp<uint8_t>(m, w.ctx);
-  void* th = wsp<void>(m, w.th);
-  void* temb = wsp<void>(m, w.temb);
-  uint8_t* kvc = wsp<uint8_t>(m, w.kvc);
-  void* vct = wsp<void>(m, w.vct);
+  const uint8_t* kvc = wsp<uint8_t>(m, w.kvc);
+  const uint8_t* vct = wsp<uint8_t>(m, w.vct);
   float* X = wsp<float>(m, w.X);
   void* Y = wsp<void>(m, w.Y);
   uint8_t* QKV = wsp<uint8_t>(m, w.QKV);
@@ -212,16 +264,8 @@ track_status forward(const Model& m, const track_latent_shape& s, int B, const f
     TRY(gemv(dt, (int)d, c.freq_dim, gW(m, T_TIME_W1), gW(m, T_TIME_B1), sinb, hb, nullptr, 1, st));
     TRY(gemv(dt, (int)d, (int)d, gW(m, T_TIME_W2), gW(m, T_TIME_B2), hb, eb, seb, 0, st));
     TRY(gemv(dt, (int)(6 * d), (int)d, gW(m, T_MOD_W), gW(m, T_MOD_B), seb, mb, nullptr, 0, st));
-    const int64_t blk_stride = c.blocks > 1 ? (int64_t)(m.specs[T_NGLOBAL + B_NBLOCK].offset - m.specs[T_NGLOBAL].offset) / (int64_t)es : 0;
-    if (c.blocks > 0) TRY(mod_tables(dt, c.blocks, (int)d, mb, bW(m, 0, B_MOD), blk_stride, mods, st));
-    TRY(head_mod(dt, (int)d, eb, hW(m, H_MOD), hmod, st));
-    TRY(rope_tables(c.head_dim, w.grid, rcos, rsin, st));
-    // text context of each branch, contiguous
-    const size_t cbytes = (size_t)Lc * c.text_dim * es;
-    for (int b = 0; b < B; ++b) TRACK_HIP(hipMemcpyAsync(ctxb + b * cbytes, ctx[b], cbytes, hipMemcpyDeviceToDevice, st));
+    TRY(mod_tables(dt, c.blocks, (int)d, mb, bW(m, 0, B_MOD), block_stride(m), mods, eb, hW(m, H_MOD), hmod, st));
   }
-  TRY(linear(dt, TRACK_EPI_BIAS_GELU, B * Lc, d, c.text_dim, ctxb, c.text_dim, gW(m, T_TEXT_W1), gW(m, T_TEXT_B1), nullptr, th, d, st));
-  TRY(linear(dt, TRACK_EPI_BIAS, B * Lc, d, d, th, d, gW(m, T_TEXT_W2), gW(m, T_TEXT_B2), nullptr, temb, d, st));
 
   // patch embedding (identical for every branch)
   const void* tokA = x_tok;
@@ -233,64 +277,61 @@ track_status forward(const Model& m, const track_latent_shape& s, int B, const f
   TRY(linear(dt, TRACK_EPI_BIAS_F32, L, d, P, tokA, P, gW(m, T_PATCH_W), gW(m, T_PATCH_B), nullptr, X, d, st));
   for (int b = 1; b < B; ++b) TRACK_HIP(hipMemcpyAsync(X + b * L * d, X, (size_t)L * d * 4, hipMemcpyDeviceToDevice, st));
 
-  // bfloat16, whole 8-token groups, at least 128 tokens and a width the
-  // 256-wide tiles divide: the V projection writes V^T for attention straight
-  // from its epilogue, so V^T's padding columns [L, Lpad) are zeroed once
-  // here (nothing else writes them during the forward)
-  const bool vt_epi = dt == TRACK_DTYPE_BF16 && L % 8 == 0 && L >= 128 && d % 256 == 0 && d < ((int64_t)1 << 22);
+  const bool vt_epi = v_from_gemm(m, w);
   // bfloat16: the q RMSNorms write q times the softmax scale log2(e) / sqrt(dh)
   // (folded into their one rounding), the input the attention kernel takes
   const bool q_log2 = dt == TRACK_DTYPE_BF16;
   const float qscale = q_log2 ? attn_log2_scale((int)dh) : 1.0f;
-  if (vt_epi) {
-    ProfScope prof(TRACK_PROF_NORM, st);
-    TRY(zero_cols_bf16(Vt, B * d, w.Lpad, L, w.Lpad, st));
-  }
   for (int blk = 0; blk < c.blocks; ++blk) {
     const float* md = mods + (int64_t)blk * 6 * d;
     const float *sh1 = md, *sc1 = md + d, *g1 = md + 2 * d, *sh2 = md + 3 * d, *sc2 = md + 4 * d, *g2 = md + 5 * d;
+    const uint8_t* kb = kvc + (size_t)blk * B * Lc * 2 * d * es;
     // self-attention sub-block
-    TRY(layernorm(dt, rows, (int)d, X, sc1, sh1, Y, st));
     if (vt_epi) {
       // q and k to QKV (columns 0 .. 2d), v straight to V^T
+      TRY(layernorm(dt, rows, (int)d, X, sc1, sh1, Y, st));
       TRY(linear(dt, TRACK_EPI_BIAS, rows, 2 * d, d, Y, d, bW(m, blk, B_QKV_W), bW(m, blk, B_QKV_B), nullptr, QKV, 3 * d,
                  st));
       TRY(linear_vt(rows, d, d, Y, d, (const uint8_t*)bW(m, blk, B_QKV_W) + 2 * d * d * es,
                     (const uint8_t*)bW(m, blk, B_QKV_B) + 2 * d * es, L, Vt, w.Lpad, st));
     } else {
-      TRY(linear(dt, TRACK_EPI_BIAS, rows, 3 * d, d, Y, d, bW(m, blk, B_QKV_W), bW(m, blk, B_QKV_B), nullptr, QKV, 3 * d, st));
-      ProfScope prof(TRACK_PROF_NORM, st);
-      TRY(v_transpose(dt, B, (int)H, (int)dh, L, QKV, 3 * d, 2 * d, Vt, w.Lpad, st));
+      TRY(layernorm_linear(dt, TRACK_EPI_BIAS, rows, 3 * d, d, X, sc1, sh1, Y, bW(m, blk, B_QKV_W), bW(m, blk, B_QKV_B),
+                           nullptr, QKV, 3 * d, st));
+      if (dt == TRACK_DTYPE_BF16) {
+        ProfScope prof(TRACK_PROF_NORM, st);
+        TRY(v_transpose(dt, B, (int)H, (int)dh, L, QKV, 3 * d, 2 * d, Vt, w.Lpad, st));
+      }
     }
     // q and k of each row in one pass
     TRY(rmsnorm_rope(dt, rows, (int)H, (int)dh, QKV, 3 * d, 0, bW(m, blk, B_NORM_Q), bW(m, blk, B_NORM_K), rcos, rsin,
                      w.grid, L, st, qscale));
-    TRY(attention(dt, B, (int)H, (int)dh, L, L, QKV, 3 * d, QKV + d * es, 3 * d, Vt, w.Lpad, AO, d, st, TRACK_PROF_ATTN_SELF,
-                  q_log2));
+    if (dt == TRACK_DTYPE_BF16)
+      TRY(attention(dt, B, (int)H, (int)dh, L, L, QKV, 3 * d, QKV + d * es, 3 * d, Vt, w.Lpad, AO, d, st,
+                    TRACK_PROF_ATTN_SELF, q_log2));
+    else
+      TRY(attention_f32_vrows(B, (int)H, (int)dh, L, L, (const float*)QKV, 3 * d, (const float*)QKV + d, 3 * d,
+                              (const float*)QKV + 2 * d, 3 * d, (float*)AO, d, st, TRACK_PROF_ATTN_SELF));
     TRY(linear(dt, TRACK_EPI_GATE_RESID, rows, d, d, AO, d, bW(m, blk, B_O_W), bW(m, blk, B_O_B), g1, X, d, st));
     // cross-attention sub-block
-    TRY(layernorm(dt, rows, (int)d, X, nullptr, nullptr, Y, st));
-    TRY(linear(dt, TRACK_EPI_BIAS, rows, d, d, Y, d, bW(m, blk, B_CQ_W), bW(m, blk, B_CQ_B), nullptr, QKV, d, st));
+    TRY(layernorm_linear(dt, TRACK_EPI_BIAS, rows, d, d, X, nullptr, nullptr, Y, bW(m, blk, B_CQ_W), bW(m, blk, B_CQ_B),
+                         nullptr, QKV, d, st));
     TRY(rmsnorm_rope(dt, rows, (int)H, (int)dh, QKV, d, 0, bW(m, blk, B_NORM_CQ), nullptr, nullptr, nullptr, w.grid, L,
                      st, qscale));
-    TRY(linear(dt, TRACK_EPI_BIAS, B * Lc, 2 * d, d, temb, d, bW(m, blk, B_CKV_W), bW(m, blk, B_CKV_B), nullptr, kvc, 2 * d, st));
-    TRY(rmsnorm_rope(dt, B * Lc, (int)H, (int)dh, kvc, 2 * d, 0, bW(m, blk, B_NORM_CK), nullptr, nullptr, nullptr, w.grid,
-                     Lc, st));
-    {
-      ProfScope prof(TRACK_PROF_NORM, st);
-      TRY(v_transpose(dt, B, (int)H, (int)dh, Lc, kvc, 2 * d, d, vct, w.Lcpad, st));
-    }
-    TRY(attention(dt, B, (int)H, (int)dh, L, Lc, QKV, d, kvc, 2 * d, vct, w.Lcpad, AO, d, st, TRACK_PROF_ATTN_CROSS,
-                  q_log2));
+    if (dt == TRACK_DTYPE_BF16)
+      TRY(attention(dt, B, (int)H, (int)dh, L, Lc, QKV, d, kb, 2 * d, vct + (size_t)blk * B * d * w.Lcpad * es, w.Lcpad,
+                    AO, d, st, TRACK_PROF_ATTN_CROSS, q_log2));
+    else
+      TRY(attention_f32_vrows(B, (int)H, (int)dh, L, Lc, (const float*)QKV, d, (const float*)kb, 2 * d,
+                              (const float*)kb + d, 2 * d, (float*)AO, d, st, TRACK_PROF_ATTN_CROSS));
     TRY(linear(dt, TRACK_EPI_RESID, rows, d, d, AO, d, bW(m, blk, B_CO_W), bW(m, blk, B_CO_B), nullptr, X, d, st));
     // MLP sub-block
-    TRY(layernorm(dt, rows, (int)d, X, sc2, sh2, Y, st));
-    TRY(linear(dt, TRACK_EPI_BIAS_GELU, rows, c.ffn_dim, d, Y, d, bW(m, blk, B_FFN1_W), bW(m, blk, B_FFN1_B), nullptr, Hf, c.ffn_dim, st));
+    TRY(layernorm_linear(dt, TRACK_EPI_BIAS_GELU, rows, c.ffn_dim, d, X, sc2, sh2, Y, bW(m, blk, B_FFN1_W),
+                         bW(m, blk, B_FFN1_B), nullptr, Hf, c.ffn_dim, st));
     TRY(linear(dt, TRACK_EPI_GATE_RESID, rows, d, c.ffn_dim, Hf, c.ffn_dim, bW(m, blk, B_FFN2_W), bW(m, blk, B_FFN2_B), g2, X, d, st));
   }
   // head
-  TRY(layernorm(dt, rows, (int)d, X, hmod + d, hmod, Y, st));
-  TRY(linear(dt, TRACK_EPI_BIAS_F32, rows, P, d, Y, d, hW(m, H_W), hW(m, H_B), nullptr, vel, P, st));
+  TRY(layernorm_linear(dt, TRACK_EPI_BIAS_F32, rows, P, d, X, hmod + d, hmod, Y, hW(m, H_W), hW(m, H_B), nullptr, vel, P,
+                       st));
   return TRACK_OK;
 }
 

@@ -52,10 +52,13 @@ struct Model {
 track_status check_shape(const Model& m, const track_latent_shape& s);
 WsLayout ws_layout(const Model& m, const track_latent_shape& s, int B);
 
-// f(x_tok, t, ctx_b) for b < B; vel [B, L, P] float32 in token layout.
-// x_tok [L, P] float32.  Uses m's workspace.
-track_status forward(const Model& m, const track_latent_shape& s, int B, const float* x_tok, double t,
-                     const void* const* ctx, float* vel, hipStream_t stream);
+// What the forward passes of one latent shape over the contexts ctx_b, b < B, share:
+// every block's text keys and values and the constant tables, into m's workspace.
+track_status prepare(const Model& m, const track_latent_shape& s, int B, const void* const* ctx, hipStream_t stream);
+// f(x_tok, t, ctx_b) for b < B, with the contexts of the last prepare() call;
+// vel [B, L, P] float32 in token layout.  x_tok [L, P] float32.  Uses m's workspace.
+track_status forward(const Model& m, const track_latent_shape& s, int B, const float* x_tok, double t, float* vel,
+                     hipStream_t stream);
 
 // Pointer into m's workspace.
 template <typename T>

@@ -489,3 +489,44 @@ def test_wan14b_one_block_full_size_sampled():
 def test_wan13b_one_block_full_size_long_unguided_sampled():
     """The step-distilled workload: 75600 tokens, no CFG (batch 1), ragged query tiles in attention."""
     _one_block_full_size_sampled(synth.WAN_1_3B, synth.SEED_SMALL, "wan 1.3B long", synth.WAN_LATENT_LONG, False)
+
+
+@pytest.mark.parametrize("heads,dh,ffn,frames,guided", [
+    (4, 32, 192, 1, True),     # 12 tokens: one 16 x 16 block of rows, ragged
+    (4, 128, 320, 3, True),    # width 512, the widest whose LayerNorm runs inside the projection
+    (5, 128, 320, 2, False),   # width 640: LayerNorm as its own launch
+    (2, 64, 200, 40, True),    # 960 rows: two blocks a side
+])
+def test_f32_forward_widths(heads, dh, ffn, frames, guided):
+    """The float32 forward over its kernel choices, within the float32 path's tolerance."""
+    say(f"f32 forward heads={heads} dh={dh} ffn={ffn} frames={frames} guided={guided}")
+    cfg = synth.DiTConfig(blocks=2, dim=heads * dh, heads=heads, head_dim=dh, ffn_dim=ffn, text_dim=72, dtype=synth.F32)
+    shape = synth.LatentShape(16, frames, 6, 8, 9)
+    p = synth.gen_params(cfg, synth.SEED_LARGE)
+    m = track.Model(cfg, track.pack_weights(cfg, p))
+    x = synth.gen_latent(shape, 0)
+    c, u = synth.gen_text(shape, cfg.text_dim, 0, synth.F32), synth.gen_null_text(shape, cfg.text_dim, synth.F32)
+    scfg = synth.SamplerConfig(steps=2, shift=3.0, guidance=5.0, use_cfg=guided)
+    got = host(track.dit_forward(m, shape, dev(x), 640.0, dev(c), dev(u) if guided else None, 5.0 if guided else 1.0))
+    ref = sampler.guided_prediction((p, cfg), x.astype(np.float64), 640.0, c, u if guided else None, scfg)
+    assert rel_l2(got, ref) < TOL_F32, rel_l2(got, ref)
+
+
+@pytest.mark.parametrize("dtype", [synth.F32, synth.BF16])
+def test_sample_with_one_workspace_for_both_models(dtype):
+    """Two models of one layout may share their workspace in sample(): each keeps to its own text keys and values
+    at every change of model, bit for bit as with workspaces of their own."""
+    import ctypes
+    say(f"sample, shared workspace, dtype={dtype}")
+    cfg = BF_LARGE if dtype == synth.BF16 else synth.TINY_LARGE
+    shape = BF_LATENT if dtype == synth.BF16 else synth.TINY_LATENT
+    pair = Pair(cfg, cfg, shape)
+    scfg = synth.SamplerConfig(steps=5, shift=3.0, guidance=5.0)
+    mask = np.array([0, 1, 1, 0, 1], bool)
+    want = host(track.sample(pair.L, pair.S, mask, shape, scfg, pair.dx[0], pair.dc[0], pair.du))
+    need = pair.L.workspace_bytes(shape, 2)
+    pair.S.workspace = pair.L.workspace
+    track._check(track.lib().track_model_set_workspace(pair.S.handle, track._ptr(pair.L.workspace),
+                                                       ctypes.c_size_t(need)))
+    got = host(track.sample(pair.L, pair.S, mask, shape, scfg, pair.dx[0], pair.dc[0], pair.du))
+    np.testing.assert_array_equal(got, want)
