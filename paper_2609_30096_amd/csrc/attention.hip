@@ -770,7 +770,7 @@ __global__ __launch_bounds__(256) void attn_f32_kernel(const float* __restrict__
                                                        const float* __restrict__ k, int64_t ldk,
                                                        const float* __restrict__ vt, int64_t ldv,
                                                        float* __restrict__ out, int64_t ldo, int H, int64_t Lq,
-                                                       int64_t Lk, float scale_log2) {
+                                                       int64_t Lk, float scale_log2, const float* __restrict__ q_gain) {
   static_assert(KS == 1 || KS == 4, "waves per query block");
   constexpr int C = D / 16;
   __shared__ f32x4 so[KS == 4 ? 4 : 1][KS == 4 ? C : 1][64];
@@ -816,6 +816,24 @@ __global__ __launch_bounds__(256) void attn_f32_kernel(const float* __restrict__
   for (int c = 0; c < C; ++c) {
     qf[c] = att_load4<VEC>(qp + 16 * c);
     o[c] = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
+  }
+  if (q_gain) {  // RMSNorm of the query rows over all heads, times the gain
+    const float* row = qp - (int64_t)h * D;
+    float sq = 0.0f;
+#pragma unroll 4
+    for (int c = 0; c < H * C; ++c) {
+      const f32x4 v = att_load4<VEC>(row + 16 * c);
+      sq = fmaf(v[0], v[0], fmaf(v[1], v[1], fmaf(v[2], v[2], fmaf(v[3], v[3], sq))));
+    }
+    sq += __shfl_xor(sq, 16);
+    sq += __shfl_xor(sq, 32);
+    const float rstd = 1.0f / sqrtf(sq / (float)(H * D) + 1e-6f);
+#pragma unroll
+    for (int c = 0; c < C; ++c) {
+      const f32x4 gn = att_load4<VEC>(q_gain + (int64_t)h * D + 16 * c + 4 * g);
+#pragma unroll
+      for (int r = 0; r < 4; ++r) qf[c][r] = qf[c][r] * rstd * gn[r];
+    }
   }
   float m = -INFINITY, l = 0.0f;  // reference max (log2 units), the lane's share of the denominator
   int64_t key0 = KS == 4 ? 16 * wave : 0;
@@ -943,16 +961,16 @@ float attn_log2_scale(int head_dim) { return (float)(1.4426950408889634 / sqrt((
 
 static track_status attention_f32(int B, int H, int head_dim, int64_t Lq, int64_t Lk, const float* q, int64_t ldq,
                                   const float* k, int64_t ldk, const float* v, int64_t ldv, float* out, int64_t ldo,
-                                  bool vrows, hipStream_t s) {
+                                  bool vrows, const float* q_gain, hipStream_t s) {
   const float scale_log2 = attn_log2_scale(head_dim);
   const int64_t nqb = (Lq + 15) / 16;
   // four waves a query block until the blocks alone give every SIMD a wave
   const bool split = nqb * H * B < 4 * (int64_t)device_cus();
   const bool vec = ((ldq | ldk | ldv | ldo) & 3) == 0 &&
-                   (((uintptr_t)q | (uintptr_t)k | (uintptr_t)v | (uintptr_t)out) & 15) == 0;
+                   (((uintptr_t)q | (uintptr_t)k | (uintptr_t)v | (uintptr_t)out | (uintptr_t)q_gain) & 15) == 0;
   dim3 grid((unsigned)(split ? nqb : (nqb + 3) / 4), H, B);
 #define TRACK_ATT_F32_K(DH, KS, VEC, VR) \
-  attn_f32_kernel<DH, KS, VEC, VR><<<grid, 256, 0, s>>>(q, ldq, k, ldk, v, ldv, out, ldo, H, Lq, Lk, scale_log2)
+  attn_f32_kernel<DH, KS, VEC, VR><<<grid, 256, 0, s>>>(q, ldq, k, ldk, v, ldv, out, ldo, H, Lq, Lk, scale_log2, q_gain)
 #define TRACK_ATT_F32(DH)                                     \
   do {                                                        \
     if (vrows && split && vec) TRACK_ATT_F32_K(DH, 4, true, true); \
@@ -1057,17 +1075,17 @@ track_status attention(int dtype, int B, int H, int head_dim, int64_t Lq, int64_
   }
   if (dtype != TRACK_DTYPE_F32) return fail(TRACK_E_INVALID, "attention: bad dtype %d", dtype);
   return attention_f32(B, H, head_dim, Lq, Lk, (const float*)q, ldq, (const float*)k, ldk, (const float*)vt, ldv,
-                       (float*)out, ldo, false, s);
+                       (float*)out, ldo, false, nullptr, s);
 }
 
 track_status attention_f32_vrows(int B, int H, int head_dim, int64_t Lq, int64_t Lk, const float* q, int64_t ldq,
                                  const float* k, int64_t ldk, const float* v, int64_t ldv, float* out, int64_t ldo,
-                                 hipStream_t s, int prof_kind) {
+                                 const float* q_gain, hipStream_t s, int prof_kind) {
   const int64_t width = (int64_t)H * head_dim;
   if (B < 1 || H < 1 || Lq < 1 || Lk < 1 || ldq < width || ldk < width || ldv < width || ldo < width)
     return fail(TRACK_E_SHAPE, "attention_f32_vrows: bad sizes");
   ProfScope prof(prof_kind, s);
-  return attention_f32(B, H, head_dim, Lq, Lk, q, ldq, k, ldk, v, ldv, out, ldo, true, s);
+  return attention_f32(B, H, head_dim, Lq, Lk, q, ldq, k, ldk, v, ldv, out, ldo, true, q_gain, s);
 }
 
 }  // namespace track

@@ -844,6 +844,23 @@ __global__ __launch_bounds__(256) void gemm_f32_small_kernel(const float* __rest
     ap[t] = A + (m < M ? m : M - 1) * lda + 4 * g;
     wp[t] = W + (int64_t)(n < N ? n : N - 1) * K + 4 * g;
   }
+  // thread -> token threadIdx / 16, feature threadIdx % 16 of each 16 x 16 block in
+  // the epilogue; what it adds there is fetched with the operands
+  const int tm = threadIdx.x >> 4, tn = threadIdx.x & 15;
+  float pre_bias[T], pre_gate[T], pre_out[T][T];
+#pragma unroll
+  for (int x = 0; x < T; ++x) {
+    const int n = min(n0 + 16 * x + tn, N - 1);
+    pre_bias[x] = ((const float*)e.bias)[n];
+    pre_gate[x] = EPI == TRACK_EPI_GATE_RESID ? e.gate[n] : 1.0f;
+#pragma unroll
+    for (int y = 0; y < T; ++y) {
+      const int64_t m = m0 + 16 * y + tm;
+      pre_out[x][y] = EPI == TRACK_EPI_GATE_RESID || EPI == TRACK_EPI_RESID
+                          ? ((const float*)e.out)[(m < M ? m : M - 1) * e.ldo + n]
+                          : 0.0f;
+    }
+  }
   f32x4 acc[T][T];  // features 4 g + r of block x, token j of block y
 #pragma unroll
   for (int x = 0; x < T; ++x)
@@ -853,7 +870,7 @@ __global__ __launch_bounds__(256) void gemm_f32_small_kernel(const float* __rest
   const f32x4 zero = {0.0f, 0.0f, 0.0f, 0.0f};
   if constexpr (LN) {
     __shared__ float rs[2][4][16 * T];
-    f32x4 a[SF_LN_CH][T];
+    f32x4 a[SF_LN_CH][T], w[SF_LN_CH][T], sc[SF_LN_CH], sh[SF_LN_CH];
     float sum[T], sq[T];
 #pragma unroll
     for (int t = 0; t < T; ++t) sum[t] = sq[t] = 0.0f;
@@ -862,6 +879,16 @@ __global__ __launch_bounds__(256) void gemm_f32_small_kernel(const float* __rest
       const int k0 = 16 * (wave + 4 * u);
 #pragma unroll
       for (int t = 0; t < T; ++t) a[u][t] = k0 + 4 * g < K ? *(const f32x4*)(ap[t] + k0) : zero;
+    }
+    // (the other operands too, so that nothing is waited for after the sums)
+#pragma unroll
+    for (int u = 0; u < SF_LN_CH; ++u) {
+      const int k0 = 16 * (wave + 4 * u);
+      const bool in = k0 + 4 * g < K;
+#pragma unroll
+      for (int t = 0; t < T; ++t) w[u][t] = in ? *(const f32x4*)(wp[t] + k0) : zero;
+      sc[u] = ln_scale && in ? *(const f32x4*)(ln_scale + k0 + 4 * g) : zero;
+      sh[u] = ln_scale && in ? *(const f32x4*)(ln_shift + k0 + 4 * g) : zero;
     }
 #pragma unroll
     for (int u = 0; u < SF_LN_CH; ++u)
@@ -886,27 +913,19 @@ __global__ __launch_bounds__(256) void gemm_f32_small_kernel(const float* __rest
     for (int u = 0; u < SF_LN_CH; ++u) {
       const int k0 = 16 * (wave + 4 * u);
       if (k0 >= K) break;  // wave-uniform
-      const bool in = k0 + 4 * g < K;
-      f32x4 w[T], sc = zero, sh = zero;
-      if (ln_scale && in) {
-        sc = *(const f32x4*)(ln_scale + k0 + 4 * g);
-        sh = *(const f32x4*)(ln_shift + k0 + 4 * g);
-      }
-#pragma unroll
-      for (int t = 0; t < T; ++t) w[t] = in ? *(const f32x4*)(wp[t] + k0) : zero;
 #pragma unroll
       for (int i = 0; i < 4; ++i) {
         float v[T];
 #pragma unroll
         for (int t = 0; t < T; ++t) {
           v[t] = a[u][t][i] * sq[t];
-          if (ln_scale) v[t] = fmaf(v[t], 1.0f + sc[i], sh[i]);
+          if (ln_scale) v[t] = fmaf(v[t], 1.0f + sc[u][i], sh[u][i]);
         }
 #pragma unroll
         for (int x = 0; x < T; ++x)
 #pragma unroll
           for (int y = 0; y < T; ++y)
-            acc[x][y] = __builtin_amdgcn_mfma_f32_16x16x4f32(w[x][i], v[y], acc[x][y], 0, 0, 0);
+            acc[x][y] = __builtin_amdgcn_mfma_f32_16x16x4f32(w[u][x][i], v[y], acc[x][y], 0, 0, 0);
       }
     }
   } else {
@@ -939,17 +958,20 @@ __global__ __launch_bounds__(256) void gemm_f32_small_kernel(const float* __rest
 #pragma unroll
     for (int y = 0; y < T; ++y) red[wave][x * T + y][lane] = acc[x][y];
   __syncthreads();
-  // thread -> token threadIdx / 16, feature threadIdx % 16 of each 16 x 16 block
-  const int tm = threadIdx.x >> 4, tn = threadIdx.x & 15, src = (tn >> 2) * 16 + tm, r = tn & 3;
+  const int src = (tn >> 2) * 16 + tm, r = tn & 3;
 #pragma unroll
   for (int x = 0; x < T; ++x)
 #pragma unroll
     for (int y = 0; y < T; ++y) {
       const int64_t m = m0 + 16 * y + tm;
       const int n = n0 + 16 * x + tn;
-      if (m < M && n < N)
-        epi_store1<EPI, float>(e, m, n, (red[0][x * T + y][src][r] + red[1][x * T + y][src][r]) +
-                                            (red[2][x * T + y][src][r] + red[3][x * T + y][src][r]));
+      if (m >= M || n >= N) continue;
+      float v = (red[0][x * T + y][src][r] + red[1][x * T + y][src][r]) +
+                (red[2][x * T + y][src][r] + red[3][x * T + y][src][r]) + pre_bias[x];
+      if constexpr (EPI == TRACK_EPI_BIAS_GELU) v = gelu_tanh(v);
+      if constexpr (EPI == TRACK_EPI_GATE_RESID) v = fmaf(pre_gate[x], v, pre_out[x][y]);
+      if constexpr (EPI == TRACK_EPI_RESID) v += pre_out[x][y];
+      ((float*)e.out)[m * e.ldo + n] = v;
     }
 }
 

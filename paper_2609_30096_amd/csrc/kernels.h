@@ -40,10 +40,11 @@ track_status attention(int dtype, int B, int H, int head_dim, int64_t Lq, int64_
                        const void* k, int64_t ldk, const void* vt, int64_t ldv, void* out, int64_t ldo,
                        hipStream_t s, int prof_kind, bool q_log2 = false);
 // attention() in float32 with V in rows of stride ldv (key j of head h at
-// v[(b Lk + j) ldv + h head_dim]) in place of V^T.
+// v[(b Lk + j) ldv + h head_dim]) in place of V^T.  With q_gain [H head_dim] the
+// rows of q are RMS-normalised and multiplied by it first.
 track_status attention_f32_vrows(int B, int H, int head_dim, int64_t Lq, int64_t Lk, const float* q, int64_t ldq,
                                  const float* k, int64_t ldk, const float* v, int64_t ldv, float* out, int64_t ldo,
-                                 hipStream_t s, int prof_kind);
+                                 const float* q_gain, hipStream_t s, int prof_kind);
 // The softmax scale in log2 units, log2(e) / sqrt(head_dim).
 float attn_log2_scale(int head_dim);
 

@@ -310,19 +310,21 @@ track_status forward(const Model& m, const track_latent_shape& s, int B, const f
                     TRACK_PROF_ATTN_SELF, q_log2));
     else
       TRY(attention_f32_vrows(B, (int)H, (int)dh, L, L, (const float*)QKV, 3 * d, (const float*)QKV + d, 3 * d,
-                              (const float*)QKV + 2 * d, 3 * d, (float*)AO, d, st, TRACK_PROF_ATTN_SELF));
+                              (const float*)QKV + 2 * d, 3 * d, (float*)AO, d, nullptr, st, TRACK_PROF_ATTN_SELF));
     TRY(linear(dt, TRACK_EPI_GATE_RESID, rows, d, d, AO, d, bW(m, blk, B_O_W), bW(m, blk, B_O_B), g1, X, d, st));
     // cross-attention sub-block
     TRY(layernorm_linear(dt, TRACK_EPI_BIAS, rows, d, d, X, nullptr, nullptr, Y, bW(m, blk, B_CQ_W), bW(m, blk, B_CQ_B),
                          nullptr, QKV, d, st));
-    TRY(rmsnorm_rope(dt, rows, (int)H, (int)dh, QKV, d, 0, bW(m, blk, B_NORM_CQ), nullptr, nullptr, nullptr, w.grid, L,
-                     st, qscale));
-    if (dt == TRACK_DTYPE_BF16)
+    if (dt == TRACK_DTYPE_BF16) {
+      TRY(rmsnorm_rope(dt, rows, (int)H, (int)dh, QKV, d, 0, bW(m, blk, B_NORM_CQ), nullptr, nullptr, nullptr, w.grid, L,
+                       st, qscale));
       TRY(attention(dt, B, (int)H, (int)dh, L, Lc, QKV, d, kb, 2 * d, vct + (size_t)blk * B * d * w.Lcpad * es, w.Lcpad,
                     AO, d, st, TRACK_PROF_ATTN_CROSS, q_log2));
-    else
+    } else {  // the float32 attention normalises its queries itself
       TRY(attention_f32_vrows(B, (int)H, (int)dh, L, Lc, (const float*)QKV, d, (const float*)kb, 2 * d,
-                              (const float*)kb + d, 2 * d, (float*)AO, d, st, TRACK_PROF_ATTN_CROSS));
+                              (const float*)kb + d, 2 * d, (float*)AO, d, (const float*)bW(m, blk, B_NORM_CQ), st,
+                              TRACK_PROF_ATTN_CROSS));
+    }
     TRY(linear(dt, TRACK_EPI_RESID, rows, d, d, AO, d, bW(m, blk, B_CO_W), bW(m, blk, B_CO_B), nullptr, X, d, st));
     // MLP sub-block
     TRY(layernorm_linear(dt, TRACK_EPI_BIAS_GELU, rows, c.ffn_dim, d, X, sc2, sh2, Y, bW(m, blk, B_FFN1_W),
