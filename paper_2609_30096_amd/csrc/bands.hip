@@ -372,17 +372,19 @@ __global__ __launch_bounds__(BAND_THREADS) void band_temporal_kernel(BandShape s
   block_sum3(acc[0], acc[1], acc[2], part + 3 * (int64_t)blockIdx.x);
 }
 
-// Sums the partials in a fixed order, one wave per quantity (the eighth: the
+// Sums the partials in a fixed order, one wave per quantity (the last three: the
 // tables' correction factors).  energy[0..2]
 // spatial, [3..5] temporal.
 // With step partials (pairs (sum d^2, sum p_L^2) of the calibration step
 // kernel) it also writes score[b] = sqrt(energy[b]) / max(||p_L||, eps).
-__global__ __launch_bounds__(512) void band_finish_kernel(int ns, const double* __restrict__ part_s, int nt,
+constexpr int BAND_FINISH_THREADS = 10 * 64;
+
+__global__ __launch_bounds__(BAND_FINISH_THREADS) void band_finish_kernel(int ns, const double* __restrict__ part_s, int nt,
                                                           const double* __restrict__ part_t, int nstep,
                                                           const double* __restrict__ step_part, double eps,
                                                           int F, int H, int W, double* __restrict__ energy,
                                                           double* __restrict__ score) {
-  __shared__ double tot[8], corr[2];
+  __shared__ double tot[7], corr[3];
   const int q = threadIdx.x >> 6, lane = threadIdx.x & 63;
   const double* p = q < 3 ? part_s + q : (q < 6 ? part_t + (q - 3) : step_part + 1);
   const int cnt = q < 3 ? ns : (q < 6 ? nt : (q == 6 && step_part ? nstep : 0));
@@ -390,18 +392,16 @@ __global__ __launch_bounds__(512) void band_finish_kernel(int ns, const double* 
   double a = 0.0;
 #pragma unroll 4
   for (int i = lane; i < cnt; i += 64) a += p[(int64_t)i * stride];
-  a = wave_sum_d(a);
-  if (lane == 0) tot[q] = a;
-  if (q == 7) {
-    const double cw = table_correction(W, lane), ch = table_correction(H, lane), cf = table_correction(F, lane);
-    if (lane == 0) {
-      corr[0] = cw * ch;
-      corr[1] = cf;
-    }
+  if (q < 7) {
+    a = wave_sum_d(a);
+    if (lane == 0) tot[q] = a;
+  } else {
+    const double c = table_correction(q == 7 ? W : (q == 8 ? H : F), lane);
+    if (lane == 0) corr[q - 7] = c;
   }
   __syncthreads();
   if (threadIdx.x < 6) {
-    tot[threadIdx.x] *= corr[threadIdx.x / 3];
+    tot[threadIdx.x] *= threadIdx.x < 3 ? corr[0] * corr[1] : corr[2];
     energy[threadIdx.x] = tot[threadIdx.x];
     if (step_part && score) {
       const double dn = sqrt(tot[6]);
@@ -459,10 +459,6 @@ size_t band_workspace_bytes(int C, int F, int H, int W, int pt, int ph, int pw) 
   return band_layout(make_shape(C, F, H, W, pt, ph, pw)).total;
 }
 
-size_t band_energy_offset(int C, int F, int H, int W, int pt, int ph, int pw) {
-  return band_layout(make_shape(C, F, H, W, pt, ph, pw)).energy;
-}
-
 track_status band_scores(int C, int F, int H, int W, int pt, int ph, int pw, int B, float w, const float* vel_L,
                          const float* vel_S, const double* step_partial, int64_t n_step_partials, double eps, void* ws,
                          double* energy_dev, double* score_dev, hipStream_t st) {
@@ -497,7 +493,7 @@ track_status band_scores(int C, int F, int H, int W, int pt, int ph, int pw, int
   else TRACK_BAND(16);
 #undef TRACK_BAND
   TRACK_LAUNCH_CHECK();
-  band_finish_kernel<<<1, 512, 0, st>>>(L.ns, part_s, L.nt, part_t, (int)n_step_partials, step_partial, eps, F, H, W,
+  band_finish_kernel<<<1, BAND_FINISH_THREADS, 0, st>>>(L.ns, part_s, L.nt, part_t, (int)n_step_partials, step_partial, eps, F, H, W,
                                                 energy, score_dev);
   TRACK_LAUNCH_CHECK();
   return TRACK_OK;
