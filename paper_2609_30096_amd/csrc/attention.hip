@@ -74,6 +74,14 @@ __device__ __forceinline__ int key_of_row(int row) {
 
 typedef __attribute__((address_space(3))) void* att_lds_ptr_t;
 
+// The lane index, computed where it is used (opaque to the compiler, which would
+// otherwise keep values derived from it live across long loops).
+__device__ __forceinline__ int att_lane() {
+  int ln;
+  asm volatile("v_mbcnt_lo_u32_b32 %0, -1, 0\n\tv_mbcnt_hi_u32_b32 %0, -1, %0" : "=v"(ln));
+  return ln;
+}
+
 template <int N>
 __device__ __forceinline__ void att_wait_vmcnt() {
   // s_waitcnt vmcnt(N) (gfx9 encoding), expcnt and lgkmcnt not waited on
@@ -538,8 +546,9 @@ __global__ __launch_bounds__(512) void flash_attn_split_kernel(const bf16_t* __r
 // first tile wait for them.  The next item's first two tiles are therefore
 // copied (and its Q registers read) before the stores are issued, and its first
 // tile waits only for what precedes them; the Q copies, as many bytes again, are
-// spread over an item's last tiles.  2 x 12 heads, 32760 queries: 240.9 -> 229.7 us at 512
-// keys (0.90 PFLOP/s; 8 tiles of 1.75 us and 4.5 us at the item's ends), 187 -> 161 at 226.
+// spread over an item's last tiles, and the outputs leave through LDS as whole 256-byte
+// rows.  2 x 12 heads, 32760 queries: 240.9 -> 227.4 us at 512 keys (0.91 PFLOP/s; 8 tiles
+// of 1.75 us and 4.3 us at the item's ends), 187 -> 161 at 226.
 template <int KIND, bool QLOG2>
 __global__ __launch_bounds__(512) void flash_attn_items_kernel(const bf16_t* __restrict__ q, int64_t ldq,
                                                                const bf16_t* __restrict__ k, int64_t ldk,
@@ -619,8 +628,7 @@ __global__ __launch_bounds__(512) void flash_attn_items_kernel(const bf16_t* __r
     // piece i fills LDS rows 4 i .. 4 i + 3 of the wave's 32 (1 KB);
     // unit u of row r sits at u ^ (r & 15).  The lane index is made opaque so
     // that these offsets are formed here, not kept live across the tiles.
-    int ln = lane;
-    asm volatile("" : "+v"(ln));
+    const int ln = att_lane();
     for (int i = i0; i < i1; ++i) {
       const int r = 4 * i + (ln >> 4);
       const uint32_t off = (uint32_t)((r * ldq + ((ln & 15) ^ (r & 15)) * 8) * 2);
@@ -668,10 +676,12 @@ __global__ __launch_bounds__(512) void flash_attn_items_kernel(const bf16_t* __r
                                           (int)(uint32_t)(nrows * ldo * 2), 0x00020000);
     // the lane index, formed here so that neither it nor the offset is spilled
     // across the tiles (a reload would wait for the copies just issued)
-    int ln;
-    asm volatile("v_mbcnt_lo_u32_b32 %0, -1, 0\n\tv_mbcnt_hi_u32_b32 %0, -1, %0" : "=v"(ln));
+    const int ln = att_lane();
     const float inv = 1.0f / att_row_sum(lsum, ln);
-    const uint32_t off = (uint32_t)(((ln & 31) * ldo + 8 * (ln >> 5)) * 2);
+    // through the wave's Q rows in LDS (free until the next Q pieces; unit u of row r
+    // at u ^ (r & 15)), so that a store covers four whole 256-byte rows
+    uint8_t* const ob = qs + wave * 32 * QROW;
+    const int orow = ln & 31;
 #pragma unroll
     for (int db = 0; db < D / 32; ++db)
 #pragma unroll
@@ -684,9 +694,15 @@ __global__ __launch_bounds__(512) void flash_attn_items_kernel(const bf16_t* __r
         const uint32_t b1 = pack_bf2(o[db][4 * rg + 6] * inv, o[db][4 * rg + 7] * inv);
         const auto x = __builtin_amdgcn_permlane32_swap(a0, b0, false, false);
         const auto y = __builtin_amdgcn_permlane32_swap(a1, b1, false, false);
-        __builtin_amdgcn_raw_buffer_store_b128(u32x4{(uint32_t)x[0], (uint32_t)y[0], (uint32_t)x[1], (uint32_t)y[1]},
-                                               rsO, off + (uint32_t)((db * 32 + 8 * rg) * 2), 0, 0);
+        *(u32x4*)(ob + orow * QROW + (((db * 4 + rg + (ln >> 5)) ^ (orow & 15)) << 4)) =
+            u32x4{(uint32_t)x[0], (uint32_t)y[0], (uint32_t)x[1], (uint32_t)y[1]};
       }
+#pragma unroll
+    for (int i = 0; i < NST; ++i) {
+      const int r = 4 * i + (ln >> 4), u = ln & 15;
+      const u32x4 v = *(const u32x4*)(ob + r * QROW + ((u ^ (r & 15)) << 4));
+      __builtin_amdgcn_raw_buffer_store_b128(v, rsO, (uint32_t)(r * ldo * 2 + u * 16), 0, 0);
+    }
   };
   // tile t of item it in slot S, the copy of the tile after it in flight (the
   // first tile's successor is under way already, before the last item's stores)
