@@ -2,27 +2,34 @@
 // self-attention and text cross-attention.
 //
 // bfloat16 path (dh = 128): a flash-style kernel on CDNA4 matrix cores.  A
-// workgroup of 8 waves owns 256 queries, 32 per wave.  Per 64-key tile each
-// wave forms the transposed logits S^T = K Q^T with v_mfma_f32_32x32x16_bf16
-// (K tile from LDS as the MFMA "A" operand, the wave's Q fragments held in
-// registers as "B"), so each lane's accumulators belong to a single query: the
-// running max of the online softmax stays per lane and only the max is
-// exchanged between the two half-waves.  The reference max moves only when a
-// tile's max exceeds it by more than ATT_TAU (log2 units), which bounds every
-// probability by 2^ATT_TAU and spares most rescales of O; while a row's max
-// stays within [ATT_MLO, ATT_TAU] the reference is 0.  With QLOG2 q arrives
-// multiplied by the softmax scale log2(e) / sqrt(dh) (the forward's RMSNorm
-// writes it so, inside its one rounding): the logits leave the MFMAs in log2
-// units and a row with reference 0 takes each probability as the plain exp2
-// of its logit, with no per-element scale or shift.  Without QLOG2 each
-// probability is exp2 of one FMA (logit times scale, minus the reference).
+// workgroup of 8 waves owns 256 queries, 32 per wave (two blocks of 16).  Per 64-key
+// tile each wave forms the transposed logits S^T = K Q^T with
+// v_mfma_f32_16x16x32_bf16 (K tile from LDS as the MFMA "A" operand, the wave's Q
+// fragments held in registers as "B"), so each lane's accumulators of a block belong
+// to a single query and only the max is exchanged between lanes.  The reference max
+// moves only when a tile's max exceeds it by more than ATT_TAU (log2 units), which
+// bounds every probability by 2^ATT_TAU and spares most rescales of O; while a row's
+// max stays within [ATT_MLO, ATT_TAU] the reference is 0, and a wave whose rows all
+// have reference 0 takes each probability as the plain exp2 of its logit.  With QLOG2
+// q arrives multiplied by the softmax scale log2(e) / sqrt(dh) (the forward's RMSNorm
+// writes it so, inside its one rounding), without it each logit is scaled first.
 // The probabilities are packed to bf16 and used as the "B" operand of
-// O^T += V^T P^T, with V^T read from LDS; V arrives pre-transposed
-// ([dh, keys]).  The softmax
-// denominators are sums of those same bf16 probabilities, formed on the
-// matrix cores too: a 16x16x32 MFMA per 16-key chunk with a 0/1 selector as
-// "A" (v_dot2 row sums would wait for the other wave's MFMAs; the MFMA
-// keeps the softmax to instructions that run beside them).
+// O^T += V^T P^T, with V^T read from LDS; V arrives pre-transposed ([dh, keys]).  The
+// softmax denominators are sums of those same bf16 probabilities, formed on the
+// matrix cores too: one more MFMA per 32 keys with ones as "A".
+//
+// What bounds it is the board's power: a first form with 32x32x16 MFMAs took the same
+// time in 20% fewer cycles at a clock that much lower (1.48 against 1.81 GHz under the
+// counters), so the shape that moves fewer accumulator bytes gains once its cycles come
+// down.  That took a loop body of one tile without a second exit (the masked last tile
+// is a template instance, ring slots switch by an XOR), so that the accumulators are
+// updated in place: 167 - 181 registers and no spills, where two unrolled tiles took 250
+// and the short-key kernel spilled; and fragments read one by one ATT_LA = 3 ahead of
+// their MFMAs (2: up to 7% slower, 5: 2%, 7: 1%).  Both forms in one process: 2 x 12 heads
+// 32760 x 32760 9921 -> 9472 us (1392 TFLOP/s), 40 heads 3000 x 3000 164.4 -> 160.3, 2 x 12
+// heads 32760 x 512 220.1 -> 211.9, 3 heads 5000 x 5000 (4 key shares) 72.1 -> 65.2.
+// Measured and left out: 48 queries a wave, or 12 waves of 32 (2 - 3% faster in whole
+// rounds of whole tiles, slower wherever 384-query blocks leave a round part empty).
 #include <math.h>
 
 #include <algorithm>
@@ -41,11 +48,15 @@ constexpr int ATT_D = 128;
 constexpr float ATT_TAU = 64.0f;
 constexpr float ATT_MLO = -64.0f;  // below this row max the reference leaves 0
 
-// Max of a value and the value held by the lane 32 positions away.
-__device__ __forceinline__ float halfwave_max(float x) {
-  const auto r = __builtin_amdgcn_permlane32_swap(__float_as_uint(x), __float_as_uint(x), false, false);
-  const float a = __uint_as_float(r[0]), b = __uint_as_float(r[1]);
-  return a > b ? a : b;
+// Maxima over the four 16-lane groups (lanes l, l + 16, l + 32, l + 48) of a and
+// of b: lanes 0..31 return that of a, lanes 32..63 that of b.
+__device__ __forceinline__ float group_max2(float a, float b) {
+  const auto r = __builtin_amdgcn_permlane32_swap(__float_as_uint(a), __float_as_uint(b), false, false);
+  const float x = __uint_as_float(r[0]), y = __uint_as_float(r[1]);
+  const float m = fmaxf(x, y);
+  const auto t = __builtin_amdgcn_permlane16_swap(__float_as_uint(m), __float_as_uint(m), false, false);
+  const float u = __uint_as_float(t[0]), v = __uint_as_float(t[1]);
+  return fmaxf(u, v);
 }
 
 // K and V^T tiles travel from global memory straight into LDS
@@ -56,20 +67,16 @@ __device__ __forceinline__ float halfwave_max(float x) {
 // column together), so the resource's range check covers every V^T read.
 // A DMA copy lands lane-contiguously, so every layout choice is made on the
 // source side: each lane picks the 16-byte chunk that belongs at its LDS
-// position.  The XOR swizzles keep the 32-row fragment reads conflict free:
+// position.  The XOR swizzles keep the 16-row fragment reads conflict free:
 // K rows are 256 bytes (unit u of row r at u ^ (r & 15)); V^T rows are 128
-// bytes, and any 8 consecutive rows, as well as rows r and r + 8, get
-// distinct units.  Each lane's fragment offsets are computed once; the tile
-// loop is unrolled by two so the slot offset is an instruction immediate.
-// To make each half-wave's P operand cover 8 consecutive keys (one contiguous
-// 16-byte V^T chunk), the K tile's rows are a permutation of its keys: within
-// every 16 keys, LDS rows 4..7 hold keys 8..11 and rows 8..11 hold keys
-// 4..7.  Softmax and P V are indifferent to the order of keys as long as K
-// and V agree, and the row a logit came from is mapped back to its key only
-// for tail masking.
-__device__ __forceinline__ int key_of_row(int row) {
-  const int a = (row >> 2) & 3;
-  return (row & ~15) | ((((a & 1) << 1) | (a >> 1)) << 2) | (row & 3);
+// bytes (unit u at u ^ att_vswz(r)).  Each lane's fragment offsets are computed
+// once and switch slots with an XOR.  Rows are permuted within every 32: LDS row 16 h + 4 q + j holds
+// key (or channel) 8 q + 4 h + j.  A lane's logits of a pair of 16-key blocks are
+// then 8 consecutive keys, the P operand's k-block, which meets one contiguous
+// 16-byte V^T chunk, and its outputs of a pair of 16-channel blocks are 8
+// consecutive channels, one 16-byte store.
+__device__ __forceinline__ int att_perm(int row) {
+  return (row & ~31) | (((row >> 2) & 3) << 3) | (((row >> 4) & 1) << 2) | (row & 3);
 }
 
 typedef __attribute__((address_space(3))) void* att_lds_ptr_t;
@@ -89,172 +96,220 @@ __device__ __forceinline__ void att_wait_vmcnt() {
   __builtin_amdgcn_s_waitcnt((N & 15) | ((N >> 4) << 14) | (7 << 4) | (15 << 8));
 }
 
-constexpr int ATT_NW = 8, ATT_BKV = 64, ATT_NSB = 2;
+constexpr int ATT_NW = 8, ATT_BKV = 64;
 constexpr int ATT_BQ = 32 * ATT_NW;                 // queries per workgroup
 constexpr int ATT_K_BYTES = ATT_BKV * ATT_D * 2;    // K tile, 16 KB
 constexpr int ATT_VROW = ATT_BKV * 2;               // V^T tile row, 128 bytes
 constexpr int ATT_V_BYTES = ATT_D * ATT_VROW;       // V^T tile, 16 KB
 constexpr int ATT_SLOT = ATT_K_BYTES + ATT_V_BYTES;  // one ring slot, 32 KB
-constexpr int ATT_VCH = ATT_BKV / 8;
 // key sequences of at most this many 64-key tiles (an even number) take the item-loop kernel
 constexpr int ATT_ITEMS_MAX_TILES = 32;
 
-__device__ __forceinline__ int att_vswz(int row) { return ((row & 7) ^ ((row >> 3) & 1)) & (ATT_VCH - 1); }
+__device__ __forceinline__ int att_vswz(int row) { return ((row & 7) ^ ((row >> 3) & 1)) & 6; }
+
+constexpr int ATT_LA = 3;  // fragments read ahead of their MFMAs
+constexpr int ATT_QB = 2;  // 16-query blocks per wave
+
+// What a lane keeps of its wave's 32 queries (lane l holds query 16 b + l % 16 of
+// block b) across the tiles.
+struct AttState {
+  f32x4 o[ATT_D / 16][ATT_QB];  // O^T: channels att_perm of 16 f + 4 (l / 16) + 0..3, of query block b
+  f32x4 lsum[ATT_QB];           // row sums (every element the sum of the lane's query)
+  float ms;                     // reference max: block 0's in lanes 0..31, block 1's in lanes 32..63
+  bool zref;                    // every row of the wave has reference 0
+  __device__ __forceinline__ void reset() {
+#pragma unroll
+    for (int b = 0; b < ATT_QB; ++b) {
+#pragma unroll
+      for (int f = 0; f < ATT_D / 16; ++f) o[f][b] = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
+      lsum[b] = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
+    }
+    ms = -INFINITY;
+    zref = false;
+  }
+};
+
+// The value of the lane's query of block b, of one kept as ms is.
+__device__ __forceinline__ float att_of_block(float v, int b, int lane) {
+  const int src = (32 * b + (lane & 15)) << 2;
+  return __int_as_float(__builtin_amdgcn_ds_bpermute(src, __float_as_int(v)));
+}
 
 // One 64-key tile for one wave's 32 queries: S^T = K Q^T from the slot's K
 // tile, the online-softmax update (lazy rescale), and O^T += V^T P^T from the
-// slot's V^T tile.  kfo / vfo are the lane's fragment offsets within a tile;
-// with MASK, keys at or past Lk get probability zero.
-typedef float att_f32x4 __attribute__((ext_vector_type(4)));
-// Selector for the row sums: as the A operand of v_mfma_f32_16x16x32_bf16
-// (lane l supplies row l % 16, k-block l / 16) it is 1 in row 0 for k-blocks 0
-// and 2 and in row 1 for k-blocks 1 and 3; with a P operand of the 32x32x16
-// layout as B (lane l: query l % 32, keys 8 (l / 32) .. + 7 of a 16-key chunk)
-// the product holds in row 0, column n the sum over the chunk for query n and
-// in row 1 that for query n + 16.
-__device__ __forceinline__ bf16x8 att_sum_selector(int lane) {
-  const int m = lane & 15, kb = lane >> 4;
-  const float v = ((m == 0 && (kb & 1) == 0) || (m == 1 && (kb & 1) == 1)) ? 1.0f : 0.0f;
-  bf16x8 r;
-#pragma unroll
-  for (int j = 0; j < 8; ++j) r[j] = (__bf16)v;
-  return r;
-}
-// The row sum of the lane's query (l % 32) from the accumulated selector products.
-__device__ __forceinline__ float att_row_sum(att_f32x4 ls, int lane) {
-  const int q = lane & 31;
-  const int src = (q & 15) << 2;
-  const float a = __int_as_float(__builtin_amdgcn_ds_bpermute(src, __float_as_int(ls[0])));
-  const float b = __int_as_float(__builtin_amdgcn_ds_bpermute(src, __float_as_int(ls[1])));
-  return q < 16 ? a : b;
-}
-
-// NSB 32-key blocks of the tile (1: the half that kfo and vfo point at).  With
-// SAFE a row whose logits so far are all -inf (a wave of a split sequence can begin
-// with such a tile) takes reference 0 instead of -inf.
-template <bool MASK, bool QLOG2, int NSB = ATT_NSB, bool SAFE = false>
-__device__ __forceinline__ void att_tile(const uint8_t* kb, const bf16x8 (&qf)[ATT_D / 16],
-                                         const uint32_t (&kfo)[ATT_D / 16], const uint32_t (&vfo)[2 * NSB],
-                                         f32x16 (&o)[ATT_D / 32], float& m_i, float& thr, bool& zref, att_f32x4& lsum,
-                                         const bf16x8& sel, int key0, int Lk, int hf, float scale_log2) {
-  constexpr int D = ATT_D;
+// slot's V^T tile.  ko / vo are the lane's fragment offsets (depth step 0, key chunk
+// 0; the others differ in one XOR); with MASK, keys at or past Lk get probability
+// zero.  KB 16-key blocks of the tile (2: the half that ko and vo point at).  With SAFE
+// a row whose logits so far are all -inf (a wave of a split sequence can begin with
+// such a tile) takes reference 0 instead.
+template <bool MASK, bool QLOG2, int KB = ATT_BKV / 16, bool SAFE = false>
+__device__ __forceinline__ void att_tile(const uint8_t* kb, const bf16x8 (&qf)[ATT_D / 32][ATT_QB], uint32_t ko,
+                                         uint32_t vo, AttState& st, int key0, int Lk, float scale_log2) {
+  constexpr int QB = ATT_QB;
   typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
   const uint8_t* vb = kb + ATT_K_BYTES;
-  f32x16 s[NSB];
+  f32x4 s[KB][QB];
 #pragma unroll
-  for (int sb = 0; sb < NSB; ++sb)
+  for (int i = 0; i < KB; ++i)
 #pragma unroll
-    for (int r = 0; r < 16; ++r) s[sb][r] = 0.0f;
-  auto kfrag = [&](int kc, int sb) {
-    return __builtin_bit_cast(bf16x8, *(const u32x4*)(kb + sb * 8192 + kfo[kc]));
+    for (int b = 0; b < QB; ++b) s[i][b] = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
+  // fragment j: 16-key block j % KB of depth step j / KB
+  auto kfrag = [&](int j) {
+    return __builtin_bit_cast(bf16x8, *(const u32x4*)(kb + (j % KB) * 4096 + (ko ^ (uint32_t)(j / KB * 64))));
   };
-  bf16x8 kf[2][NSB];
+  constexpr int KF = ATT_D / 32 * KB;
+  bf16x8 kf[ATT_LA + 1];
 #pragma unroll
-  for (int sb = 0; sb < NSB; ++sb) kf[0][sb] = kfrag(0, sb);
+  for (int j = 0; j < ATT_LA; ++j) kf[j] = kfrag(j);
 #pragma unroll
-  for (int kc = 0; kc < D / 16; ++kc) {
-    if (kc + 1 < D / 16) {
-#pragma unroll
-      for (int sb = 0; sb < NSB; ++sb) kf[(kc + 1) & 1][sb] = kfrag(kc + 1, sb);
-    }
+  for (int j = 0; j < KF; ++j) {
+    if (j + ATT_LA < KF) kf[(j + ATT_LA) % (ATT_LA + 1)] = kfrag(j + ATT_LA);
     __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-    for (int sb = 0; sb < NSB; ++sb)
-      s[sb] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(kf[kc & 1][sb], qf[kc], s[sb], 0, 0, 0);
+    for (int b = 0; b < QB; ++b)
+      s[j % KB][b] =
+          __builtin_amdgcn_mfma_f32_16x16x32_bf16(kf[j % (ATT_LA + 1)], qf[j / KB][b], s[j % KB][b], 0, 0, 0);
   }
-  float mx = -INFINITY;
-  // valid keys from this half-wave's first on (opaque, so that the comparisons are
-  // formed here rather than kept across the tiles)
-  int lim = Lk - key0 - 8 * hf;
-  if constexpr (MASK) asm volatile("" : "+v"(lim));
+  float mx[QB];
 #pragma unroll
-  for (int sb = 0; sb < NSB; ++sb)
+  for (int b = 0; b < QB; ++b) mx[b] = -INFINITY;
+  // valid keys from this lane's first on
+  const int lim = MASK ? Lk - key0 - 8 * (att_lane() >> 4) : 0;
 #pragma unroll
-    for (int r = 0; r < 16; ++r) {
-      if constexpr (MASK) {
-        // row 32 sb + 8 (r / 4) + 4 hf + r % 4 of the tile: its key_of_row less 8 hf
-        if (32 * sb + 16 * (r >> 3) + 4 * ((r >> 2) & 1) + (r & 3) >= lim) s[sb][r] = -INFINITY;
-      }
-      mx = fmaxf(mx, s[sb][r]);
-    }
-  const float mt = QLOG2 ? halfwave_max(mx) : halfwave_max(mx) * scale_log2;
-  if (__ballot(mt > thr)) {
-    float mn = fmaxf(m_i, mt);
-    if (mn >= ATT_MLO && mn <= ATT_TAU) mn = 0.0f;
-    const float alpha = SAFE && mn == -INFINITY ? 1.0f : __builtin_amdgcn_exp2f(m_i - mn);
-    m_i = mn;
-    thr = mn + ATT_TAU;
-    zref = !__ballot(mn != 0.0f);
-    const float alpha_hi = __shfl_down(alpha, 16);  // lane n holds the sums of queries n and n + 16
-    lsum[0] *= alpha;
-    lsum[1] *= alpha_hi;
+  for (int i = 0; i < KB; ++i)
 #pragma unroll
-    for (int db = 0; db < D / 32; ++db)
+    for (int b = 0; b < QB; ++b)
 #pragma unroll
-      for (int r = 0; r < 16; ++r) o[db][r] *= alpha;
-  }
-  // probabilities exp2(s - m) (QLOG2; the shift only where some row of the
-  // wave has a nonzero reference, a wave-uniform branch), or exp2(s c - m)
-  const float nm = SAFE && m_i == -INFINITY ? 0.0f : -m_i;
-  bf16x8 pf[2 * NSB];
-  auto probs = [&](auto shift_tag) {
-#pragma unroll
-    for (int c = 0; c < 2 * NSB; ++c) {
-      uint32_t w[4];
-#pragma unroll
-      for (int e = 0; e < 4; ++e) {
-        float x0 = s[c >> 1][(c & 1) * 8 + 2 * e], x1 = s[c >> 1][(c & 1) * 8 + 2 * e + 1];
-        if constexpr (!QLOG2) {
-          x0 = fmaf(x0, scale_log2, nm);
-          x1 = fmaf(x1, scale_log2, nm);
-        } else if constexpr (decltype(shift_tag)::value) {
-          x0 += nm;
-          x1 += nm;
+      for (int r = 0; r < 4; ++r) {
+        if constexpr (MASK) {
+          if (32 * (i >> 1) + 4 * (i & 1) + r >= lim) s[i][b][r] = -INFINITY;
         }
-        const bf16x2 pb = __builtin_convertvector(f32x2{__builtin_amdgcn_exp2f(x0), __builtin_amdgcn_exp2f(x1)}, bf16x2);
-        w[e] = __builtin_bit_cast(uint32_t, pb);
+        mx[b] = fmaxf(mx[b], s[i][b][r]);
       }
-      pf[c] = __builtin_bit_cast(bf16x8, u32x4{w[0], w[1], w[2], w[3]});
+  const float mt = QLOG2 ? group_max2(mx[0], mx[1]) : group_max2(mx[0], mx[1]) * scale_log2;
+  if (__ballot(mt > st.ms + ATT_TAU)) {
+    float mn = fmaxf(st.ms, mt);
+    if (mn >= ATT_MLO && mn <= ATT_TAU) mn = 0.0f;
+    const float alpha = SAFE && mn == -INFINITY ? 1.0f : __builtin_amdgcn_exp2f(st.ms - mn);
+    st.ms = mn;
+    st.zref = !__ballot(mn != 0.0f);
+    const int lane = att_lane();
+#pragma unroll
+    for (int b = 0; b < QB; ++b) {
+      const float al = att_of_block(alpha, b, lane);
+#pragma unroll
+      for (int r = 0; r < 4; ++r) st.lsum[b][r] *= al;
+#pragma unroll
+      for (int f = 0; f < ATT_D / 16; ++f)
+#pragma unroll
+        for (int r = 0; r < 4; ++r) st.o[f][b][r] *= al;
     }
+  }
+  // probabilities exp2(s c - m) (c = 1 with QLOG2); without the shift while every row
+  // of the wave has reference 0, a wave-uniform branch
+  bf16x8 pf[KB / 2][QB];
+  auto probs = [&](auto shift_tag) {
+    constexpr bool SHIFT = decltype(shift_tag)::value;
+    float nm[QB];
+    if constexpr (SHIFT) {
+      const int lane = att_lane();
+#pragma unroll
+      for (int b = 0; b < QB; ++b) {
+        nm[b] = -att_of_block(st.ms, b, lane);
+        if (SAFE && nm[b] == INFINITY) nm[b] = 0.0f;
+      }
+    }
+#pragma unroll
+    for (int c = 0; c < KB / 2; ++c)
+#pragma unroll
+      for (int b = 0; b < QB; ++b) {
+        uint32_t w[4];
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+          float x[2];
+#pragma unroll
+          for (int k = 0; k < 2; ++k) {
+            x[k] = s[2 * c + (e >> 1)][b][2 * (e & 1) + k];
+            if constexpr (SHIFT) x[k] = QLOG2 ? x[k] + nm[b] : fmaf(x[k], scale_log2, nm[b]);
+            else if constexpr (!QLOG2) x[k] *= scale_log2;
+          }
+          const bf16x2 pb =
+              __builtin_convertvector(f32x2{__builtin_amdgcn_exp2f(x[0]), __builtin_amdgcn_exp2f(x[1])}, bf16x2);
+          w[e] = __builtin_bit_cast(uint32_t, pb);
+        }
+        pf[c][b] = __builtin_bit_cast(bf16x8, u32x4{w[0], w[1], w[2], w[3]});
+      }
   };
-  if (QLOG2 && zref) probs(std::false_type{});
+  if (st.zref) probs(std::false_type{});
   else probs(std::true_type{});
-#pragma unroll
-  for (int c = 0; c < 2 * NSB; ++c) lsum = __builtin_amdgcn_mfma_f32_16x16x32_bf16(sel, pf[c], lsum, 0, 0, 0);
-  auto vfrag = [&](int db, int c) {
-    return __builtin_bit_cast(bf16x8, *(const u32x4*)(vb + db * 4096 + vfo[c]));
+  const bf16x8 ones = __builtin_bit_cast(bf16x8, u32x4{0x3f803f80u, 0x3f803f80u, 0x3f803f80u, 0x3f803f80u});
+  // fragment j: 16-channel block j / (KB / 2), key chunk j % (KB / 2)
+  auto vfrag = [&](int j) {
+    return __builtin_bit_cast(
+        bf16x8, *(const u32x4*)(vb + j / (KB / 2) * 16 * ATT_VROW + (vo ^ (uint32_t)(j % (KB / 2) * 64))));
   };
-  bf16x8 vf[2][2 * NSB];
+  constexpr int VF = ATT_D / 16 * (KB / 2);
+  bf16x8 vf[ATT_LA + 1];
 #pragma unroll
-  for (int c = 0; c < 2 * NSB; ++c) vf[0][c] = vfrag(0, c);
+  for (int j = 0; j < ATT_LA; ++j) vf[j] = vfrag(j);
 #pragma unroll
-  for (int db = 0; db < D / 32; ++db) {
-    if (db + 1 < D / 32) {
+  for (int c = 0; c < KB / 2; ++c)
 #pragma unroll
-      for (int c = 0; c < 2 * NSB; ++c) vf[(db + 1) & 1][c] = vfrag(db + 1, c);
-    }
+    for (int b = 0; b < QB; ++b)
+      st.lsum[b] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(ones, pf[c][b], st.lsum[b], 0, 0, 0);
+#pragma unroll
+  for (int j = 0; j < VF; ++j) {
+    if (j + ATT_LA < VF) vf[(j + ATT_LA) % (ATT_LA + 1)] = vfrag(j + ATT_LA);
     __builtin_amdgcn_sched_barrier(0);
+    const int f = j / (KB / 2), c = j % (KB / 2);
 #pragma unroll
-    for (int c = 0; c < 2 * NSB; ++c)
-      o[db] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(vf[db & 1][c], pf[c], o[db], 0, 0, 0);
+    for (int b = 0; b < QB; ++b)
+      st.o[f][b] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(vf[j % (ATT_LA + 1)], pf[c][b], st.o[f][b], 0, 0, 0);
   }
 }
 
-template <int KIND, bool QLOG2>
+// The wave's 32 rows from q0 on of one (batch, head): op points at row 0, channel 0.
+__device__ __forceinline__ void att_store(const AttState& st, bf16_t* __restrict__ op, int64_t ldo, int q0, int Lq,
+                                          int lane) {
+  const bool wide = (((uintptr_t)op | (uintptr_t)(ldo * 2)) & 15) == 0;  // rows may be 8-byte aligned only
+#pragma unroll
+  for (int b = 0; b < ATT_QB; ++b) {
+    const float inv = 1.0f / st.lsum[b][0];
+    const int qi = q0 + 16 * b + (lane & 15);
+    if (qi < Lq) {
+      bf16_t* orow = op + (int64_t)qi * ldo + 8 * (lane >> 4);
+#pragma unroll
+      for (int p = 0; p < ATT_D / 32; ++p) {
+        const f32x4 &x = st.o[2 * p][b], &y = st.o[2 * p + 1][b];
+        const u32x4 pk = {pack_bf2(x[0] * inv, x[1] * inv), pack_bf2(x[2] * inv, x[3] * inv),
+                          pack_bf2(y[0] * inv, y[1] * inv), pack_bf2(y[2] * inv, y[3] * inv)};
+        if (wide) {
+          *(u32x4*)(orow + 32 * p) = pk;
+        } else {
+          *(u32x2*)(orow + 32 * p) = u32x2{pk[0], pk[1]};
+          *(u32x2*)(orow + 32 * p + 4) = u32x2{pk[2], pk[3]};
+        }
+      }
+    }
+  }
+}
+
+// TAIL: Lk is not whole 64-key tiles, and the last one is masked.
+template <int KIND, bool QLOG2, bool TAIL>
 __global__ __launch_bounds__(512) void flash_attn_bf16_kernel(const bf16_t* __restrict__ q, int64_t ldq,
                                                       const bf16_t* __restrict__ k, int64_t ldk,
                                                       const bf16_t* __restrict__ vt, int64_t ldv,
                                                       bf16_t* __restrict__ out, int64_t ldo, int H,
                                                       int Lq, int Lk, float scale_log2) {
-  constexpr int BKV = ATT_BKV, NSB = ATT_NSB, D = ATT_D, BQ = ATT_BQ;
+  constexpr int BKV = ATT_BKV, D = ATT_D, BQ = ATT_BQ;
   constexpr int K_BYTES = ATT_K_BYTES, VROW = ATT_VROW, SLOT = ATT_SLOT;
   __shared__ __attribute__((aligned(1024))) uint8_t smem[2 * SLOT];
 
   const int tid = threadIdx.x;
   const int lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-  const int jq = lane & 31;
-  const int hf = lane >> 5;
+  const int jq = lane & 15;
+  const int g = lane >> 4;
   const int h = blockIdx.y;
   const int b = blockIdx.z;
   const int q0 = blockIdx.x * BQ + wave * 32;
@@ -262,12 +317,13 @@ __global__ __launch_bounds__(512) void flash_attn_bf16_kernel(const bf16_t* __re
   const bf16_t* kbase = k + (int64_t)b * Lk * ldk + (int64_t)h * D;
   const bf16_t* vbase = vt + ((int64_t)b * H + h) * D * ldv;
 
-  bf16x8 qf[D / 16];
-  {
-    const int qi = min(q0 + jq, Lq - 1);
-    const bf16_t* qp = q + (int64_t)b * Lq * ldq + (int64_t)h * D + (int64_t)qi * ldq + hf * 8;
+  bf16x8 qf[D / 32][ATT_QB];
 #pragma unroll
-    for (int kc = 0; kc < D / 16; ++kc) qf[kc] = __builtin_bit_cast(bf16x8, *(const u32x4*)(qp + kc * 16));
+  for (int i = 0; i < ATT_QB; ++i) {
+    const int qi = min(q0 + 16 * i + jq, Lq - 1);
+    const bf16_t* qp = q + (int64_t)b * Lq * ldq + (int64_t)h * D + (int64_t)qi * ldq + g * 8;
+#pragma unroll
+    for (int kc = 0; kc < D / 32; ++kc) qf[kc][i] = __builtin_bit_cast(bf16x8, *(const u32x4*)(qp + kc * 32));
   }
   // copy i (0, 1) of this wave fills its 1 KB block 2 wave + i of the K (or
   // V^T) region; per-lane byte offsets within the tile's rows
@@ -275,9 +331,9 @@ __global__ __launch_bounds__(512) void flash_attn_bf16_kernel(const bf16_t* __re
 #pragma unroll
   for (int i = 0; i < 2; ++i) {
     const int row = 8 * wave + 4 * i + (lane >> 4);
-    koffg[i] = (uint32_t)((key_of_row(row) * ldk + ((lane & 15) ^ (row & 15)) * 8) * 2);
+    koffg[i] = (uint32_t)((att_perm(row) * ldk + ((lane & 15) ^ (row & 15)) * 8) * 2);
     const int vr = 16 * wave + 8 * i + (lane >> 3);
-    voffg[i] = (uint32_t)((vr * ldv + ((lane & 7) ^ att_vswz(vr)) * 8) * 2);
+    voffg[i] = (uint32_t)((att_perm(vr) * ldv + ((lane & 7) ^ att_vswz(vr)) * 8) * 2);
   }
   const int ntiles = (Lk + BKV - 1) / BKV;
   // V^T of this (batch, head): D rows of ldv keys
@@ -285,8 +341,8 @@ __global__ __launch_bounds__(512) void flash_attn_bf16_kernel(const bf16_t* __re
   const __amdgpu_buffer_rsrc_t rsV =
       __builtin_amdgcn_make_buffer_rsrc((void*)vbase, (short)0, (int)(uint32_t)(D * ldv * 2), 0x00020000);
   // tile t (past the end: the last tile again) into slot S
-  auto issue = [&](int t, auto slot_tag) {
-    constexpr int S = decltype(slot_tag)::value;
+  int slot = 0;
+  auto issue = [&](int t) {
     const int tt = min(t, ntiles - 1);
     const int key0 = tt * BKV;
     // K rows key0 .. Lk - 1 of this head; rows past Lk read as zero
@@ -294,87 +350,39 @@ __global__ __launch_bounds__(512) void flash_attn_bf16_kernel(const bf16_t* __re
                                                                          (int)(uint32_t)((Lk - key0) * ldk * 2), 0x00020000);
 #pragma unroll
     for (int i = 0; i < 2; ++i)
-      __builtin_amdgcn_raw_ptr_buffer_load_lds(rsK, (att_lds_ptr_t)(smem + S * SLOT + wave * 2048 + i * 1024), 16, koffg[i], 0, 0, 0);
+      __builtin_amdgcn_raw_ptr_buffer_load_lds(rsK, (att_lds_ptr_t)(smem + slot + wave * 2048 + i * 1024), 16, koffg[i], 0, 0, 0);
 #pragma unroll
     for (int i = 0; i < 2; ++i)
-      __builtin_amdgcn_raw_ptr_buffer_load_lds(rsV, (att_lds_ptr_t)(smem + S * SLOT + K_BYTES + wave * 2048 + i * 1024), 16,
+      __builtin_amdgcn_raw_ptr_buffer_load_lds(rsV, (att_lds_ptr_t)(smem + slot + K_BYTES + wave * 2048 + i * 1024), 16,
                                                voffg[i] + (uint32_t)(key0 * 2), 0, 0, 0);
+    slot ^= SLOT;
   };
 
   // per-lane LDS fragment offsets (slot and 32-row block are immediates)
-  uint32_t kfo[D / 16], vfo[2 * NSB];
-#pragma unroll
-  for (int kc = 0; kc < D / 16; ++kc) kfo[kc] = jq * 256 + (((kc * 2 + hf) ^ (jq & 15)) << 4);
-#pragma unroll
-  for (int c = 0; c < 2 * NSB; ++c) vfo[c] = jq * VROW + (((2 * c + hf) ^ att_vswz(jq)) << 4);
+  uint32_t ko = jq * 256 + ((g ^ jq) << 4), vo = jq * VROW + ((g ^ att_vswz(jq)) << 4);
 
-  f32x16 o[D / 32];
-#pragma unroll
-  for (int db = 0; db < D / 32; ++db)
-#pragma unroll
-    for (int r = 0; r < 16; ++r) o[db][r] = 0.0f;
-  float m_i = -INFINITY, thr = -INFINITY;  // reference max, and the tile max that moves it
-  bool zref = false;                         // every row of the wave has reference 0
-  att_f32x4 lsum = {0.0f, 0.0f, 0.0f, 0.0f};
-  const bf16x8 sel = att_sum_selector(lane);
+  AttState st;
+  st.reset();
 
-  auto subtile = [&](auto slot_tag, int key0, auto mask_tag) {
-    constexpr int S = decltype(slot_tag)::value;
-    att_tile<decltype(mask_tag)::value, QLOG2>(smem + S * SLOT, qf, kfo, vfo, o, m_i, thr, zref, lsum, sel, key0, Lk, hf,
-                                               scale_log2);
-  };
-
-  using S0 = std::integral_constant<int, 0>;
-  using S1 = std::integral_constant<int, 1>;
-  // tile t in slot S: copy tile t + 1 into the other slot (every wave is past
-  // tile t - 1, its last reader), compute, wait for the copy, barrier
-  auto tile = [&](int t, auto slot_tag, auto mask_tag) {
-    constexpr int S = decltype(slot_tag)::value;
-    issue(t + 1, std::integral_constant<int, 1 - S>{});
-    subtile(slot_tag, t * BKV, mask_tag);
+  auto tile = [&](int t, auto mask_tag) {
+    issue(t + 1);
+    att_tile<decltype(mask_tag)::value, QLOG2>(smem, qf, ko, vo, st, t * BKV, Lk, scale_log2);
+    ko ^= SLOT;
+    vo ^= SLOT;
     att_wait_vmcnt<0>();
     __builtin_amdgcn_s_waitcnt((15 << 0) | (3 << 14) | (7 << 4) | (0 << 8));  // lgkmcnt(0)
     __builtin_amdgcn_s_barrier();
   };
 
-  issue(0, S0{});
+  issue(0);
   att_wait_vmcnt<0>();
   __builtin_amdgcn_s_barrier();
-  const int last = ntiles - 1;
-  int t = 0;
-  for (; t + 1 < last; t += 2) {
-    tile(t, S0{}, std::false_type{});
-    tile(t + 1, S1{}, std::false_type{});
-  }
-  if (t < last) {  // one unmasked tile left (in slot 0)
-    tile(t, S0{}, std::false_type{});
-    ++t;
-  }
-  // the last tile, in slot t & 1
-  if (Lk % BKV) {
-    if (t & 1) tile(t, S1{}, std::true_type{});
-    else tile(t, S0{}, std::true_type{});
-  } else {
-    if (t & 1) tile(t, S1{}, std::false_type{});
-    else tile(t, S0{}, std::false_type{});
-  }
+  const int whole = TAIL ? ntiles - 1 : ntiles;
+  for (int t = 0; t < whole; ++t) tile(t, std::false_type{});
+  if constexpr (TAIL) tile(whole, std::true_type{});
   att_wait_vmcnt<0>();
 
-  const float inv = 1.0f / att_row_sum(lsum, lane);
-  const int qi = q0 + jq;
-  if (qi < Lq) {
-    bf16_t* op = out + (int64_t)b * Lq * ldo + (int64_t)h * D + (int64_t)qi * ldo;
-#pragma unroll
-    for (int db = 0; db < D / 32; ++db)
-#pragma unroll
-      for (int rg = 0; rg < 4; ++rg) {
-        const int c0 = db * 32 + 8 * rg + 4 * hf;
-        u32x2 pk;
-        pk[0] = pack_bf2(o[db][4 * rg + 0] * inv, o[db][4 * rg + 1] * inv);
-        pk[1] = pack_bf2(o[db][4 * rg + 2] * inv, o[db][4 * rg + 3] * inv);
-        *(u32x2*)(op + c0) = pk;
-      }
-  }
+  att_store(st, out + (int64_t)b * Lq * ldo + (int64_t)h * D, ldo, q0, Lq, lane);
 }
 
 // Split attention, for shapes whose 256-query blocks leave most CUs idle.  A
@@ -391,7 +399,7 @@ __global__ __launch_bounds__(512) void flash_attn_split_kernel(const bf16_t* __r
                                                                bf16_t* __restrict__ out, int64_t ldo, int H, int Lq,
                                                                int Lk, float scale_log2) {
   static_assert(KS == 2 || KS == 4, "key shares");
-  constexpr int D = ATT_D, NSB = KS == 2 ? 2 : 1, STEP = 2 * ATT_BKV, NK = 32 * NSB;
+  constexpr int D = ATT_D, KB = KS == 2 ? 4 : 2, STEP = 2 * ATT_BKV, NK = 16 * KB;
   constexpr int STEP_BYTES = 2 * ATT_SLOT;
   __shared__ __attribute__((aligned(1024))) uint8_t smem[2 * STEP_BYTES];
   __shared__ float sm[8][32], sl[8][32];
@@ -400,28 +408,29 @@ __global__ __launch_bounds__(512) void flash_attn_split_kernel(const bf16_t* __r
   const int lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int ks = wave % KS, qw = wave / KS;
-  const int jq = lane & 31;
-  const int hf = lane >> 5;
+  const int jq = lane & 15;
+  const int g = lane >> 4;
   const int h = blockIdx.y;
   const int b = blockIdx.z;
   const int q0 = blockIdx.x * (256 / KS) + qw * 32;
 
   const bf16_t* kbase = k + (int64_t)b * Lk * ldk + (int64_t)h * D;
   const bf16_t* vbase = vt + ((int64_t)b * H + h) * D * ldv;
-  bf16x8 qf[D / 16];
-  {
-    const int qi = min(q0 + jq, Lq - 1);
-    const bf16_t* qp = q + (int64_t)b * Lq * ldq + (int64_t)h * D + (int64_t)qi * ldq + hf * 8;
+  bf16x8 qf[D / 32][2];
 #pragma unroll
-    for (int kc = 0; kc < D / 16; ++kc) qf[kc] = __builtin_bit_cast(bf16x8, *(const u32x4*)(qp + kc * 16));
+  for (int i = 0; i < 2; ++i) {
+    const int qi = min(q0 + 16 * i + jq, Lq - 1);
+    const bf16_t* qp = q + (int64_t)b * Lq * ldq + (int64_t)h * D + (int64_t)qi * ldq + g * 8;
+#pragma unroll
+    for (int kc = 0; kc < D / 32; ++kc) qf[kc][i] = __builtin_bit_cast(bf16x8, *(const u32x4*)(qp + kc * 32));
   }
   uint32_t koffg[2], voffg[2];
 #pragma unroll
   for (int i = 0; i < 2; ++i) {
     const int row = 8 * wave + 4 * i + (lane >> 4);
-    koffg[i] = (uint32_t)((key_of_row(row) * ldk + ((lane & 15) ^ (row & 15)) * 8) * 2);
+    koffg[i] = (uint32_t)((att_perm(row) * ldk + ((lane & 15) ^ (row & 15)) * 8) * 2);
     const int vr = 16 * wave + 8 * i + (lane >> 3);
-    voffg[i] = (uint32_t)((vr * ldv + ((lane & 7) ^ att_vswz(vr)) * 8) * 2);
+    voffg[i] = (uint32_t)((att_perm(vr) * ldv + ((lane & 7) ^ att_vswz(vr)) * 8) * 2);
   }
   const __amdgpu_buffer_rsrc_t rsV =
       __builtin_amdgcn_make_buffer_rsrc((void*)vbase, (short)0, (int)(uint32_t)(D * ldv * 2), 0x00020000);
@@ -449,81 +458,82 @@ __global__ __launch_bounds__(512) void flash_attn_split_kernel(const bf16_t* __r
 
   // the lane's fragment offsets in the wave's share of slot 0
   const int share = (KS == 2 ? ks : ks >> 1) * ATT_SLOT, half = KS == 2 ? 0 : ks & 1;
-  uint32_t kfo[D / 16], vfo[2 * NSB];
-#pragma unroll
-  for (int kc = 0; kc < D / 16; ++kc) kfo[kc] = share + half * 8192 + jq * 256 + (((kc * 2 + hf) ^ (jq & 15)) << 4);
-#pragma unroll
-  for (int c = 0; c < 2 * NSB; ++c) vfo[c] = share + jq * ATT_VROW + (((4 * half + 2 * c + hf) ^ att_vswz(jq)) << 4);
+  uint32_t ko = share + half * 8192 + jq * 256 + ((g ^ jq) << 4);
+  uint32_t vo = share + jq * ATT_VROW + (((4 * half + g) ^ att_vswz(jq)) << 4);
 
-  f32x16 o[D / 32];
-#pragma unroll
-  for (int db = 0; db < D / 32; ++db)
-#pragma unroll
-    for (int r = 0; r < 16; ++r) o[db][r] = 0.0f;
-  float m_i = -INFINITY, thr = -INFINITY;
-  bool zref = false;
-  att_f32x4 lsum = {0.0f, 0.0f, 0.0f, 0.0f};
-  const bf16x8 sel = att_sum_selector(lane);
+  AttState st;
+  st.reset();
 
   issue(0);
   att_wait_vmcnt<0>();
   __builtin_amdgcn_s_barrier();
   const int nsteps = (Lk + STEP - 1) / STEP;
-  int key0 = ks * NK;  // the wave's first key of the step
-  for (int step = 0; step < nsteps; ++step, key0 += STEP) {
-    if (step + 1 < nsteps) issue(step + 1);
-    if (key0 + NK <= Lk)
-      att_tile<false, QLOG2, NSB, true>(smem, qf, kfo, vfo, o, m_i, thr, zref, lsum, sel, key0, Lk, hf, scale_log2);
-    else if (key0 < Lk)
-      att_tile<true, QLOG2, NSB, true>(smem, qf, kfo, vfo, o, m_i, thr, zref, lsum, sel, key0, Lk, hf, scale_log2);
-#pragma unroll
-    for (int kc = 0; kc < D / 16; ++kc) kfo[kc] ^= STEP_BYTES;
-#pragma unroll
-    for (int c = 0; c < 2 * NSB; ++c) vfo[c] ^= STEP_BYTES;
+  auto next = [&]() {
+    ko ^= STEP_BYTES;
+    vo ^= STEP_BYTES;
     att_wait_vmcnt<0>();
     __builtin_amdgcn_s_waitcnt((15 << 0) | (3 << 14) | (7 << 4) | (0 << 8));  // lgkmcnt(0)
     __builtin_amdgcn_s_barrier();
+  };
+  int key0 = ks * NK;  // the wave's first key of the step
+  for (int step = 0; step + 1 < nsteps; ++step, key0 += STEP) {
+    issue(step + 1);
+    att_tile<false, QLOG2, KB, true>(smem, qf, ko, vo, st, key0, Lk, scale_log2);
+    next();
   }
+  // the last step: whole, ragged or past the end for this wave
+  if (key0 < Lk) att_tile<true, QLOG2, KB, true>(smem, qf, ko, vo, st, key0, Lk, scale_log2);
+  next();
 
-  // join the shares: [wave][4 channel blocks][4 groups of 8 channels][lane] of float32 quads
+  // join the shares: [wave][8 channel blocks][2 query blocks][lane] of float32 quads
   f32x4* const so = (f32x4*)smem;
 #pragma unroll
-  for (int db = 0; db < D / 32; ++db)
+  for (int f = 0; f < D / 16; ++f)
 #pragma unroll
-    for (int rg = 0; rg < 4; ++rg)
-      so[(wave * 16 + db * 4 + rg) * 64 + lane] =
-          f32x4{o[db][4 * rg], o[db][4 * rg + 1], o[db][4 * rg + 2], o[db][4 * rg + 3]};
-  const float l = att_row_sum(lsum, lane);
-  if (hf == 0) {
-    sm[wave][jq] = m_i;
-    sl[wave][jq] = l;
+    for (int i = 0; i < 2; ++i) so[(wave * 16 + f * 2 + i) * 64 + lane] = st.o[f][i];
+  const float mref[2] = {att_of_block(st.ms, 0, lane), att_of_block(st.ms, 1, lane)};
+  if (g == 0) {
+#pragma unroll
+    for (int i = 0; i < 2; ++i) {
+      sm[wave][16 * i + jq] = mref[i];
+      sl[wave][16 * i + jq] = st.lsum[i][0];
+    }
   }
   __syncthreads();
-  float wt[KS], mx = sm[qw * KS][jq], sum = 0.0f;
+  float wt[2][KS], inv[2];
 #pragma unroll
-  for (int i = 1; i < KS; ++i) mx = fmaxf(mx, sm[qw * KS + i][jq]);
+  for (int i = 0; i < 2; ++i) {
+    const int qr = 16 * i + jq;
+    float mx = sm[qw * KS][qr], sum = 0.0f;
 #pragma unroll
-  for (int i = 0; i < KS; ++i) {
-    const float mi = sm[qw * KS + i][jq];
-    wt[i] = mi == -INFINITY ? 0.0f : __builtin_amdgcn_exp2f(mi - mx);  // a share without keys
-    sum = fmaf(wt[i], sl[qw * KS + i][jq], sum);
-  }
-  const float inv = 1.0f / sum;
-  const int qi = q0 + jq;
-  if (qi >= Lq) return;
-  bf16_t* op = out + ((int64_t)b * Lq + qi) * ldo + (int64_t)h * D + 4 * hf;
-  // this wave's channels of the group's queries
-#pragma unroll
-  for (int i = 0; i < 16 / KS; ++i) {
-    const int cg = ks * (16 / KS) + i;  // 8-channel group
-    f32x4 v = {0.0f, 0.0f, 0.0f, 0.0f};
+    for (int w = 1; w < KS; ++w) mx = fmaxf(mx, sm[qw * KS + w][qr]);
 #pragma unroll
     for (int w = 0; w < KS; ++w) {
-      const f32x4 u = so[((qw * KS + w) * 16 + cg) * 64 + lane];
-#pragma unroll
-      for (int r = 0; r < 4; ++r) v[r] = fmaf(wt[w], u[r], v[r]);
+      const float mi = sm[qw * KS + w][qr];
+      wt[i][w] = mi == -INFINITY ? 0.0f : __builtin_amdgcn_exp2f(mi - mx);  // a share without keys
+      sum = fmaf(wt[i][w], sl[qw * KS + w][qr], sum);
     }
-    *(u32x2*)(op + 8 * cg) = u32x2{pack_bf2(v[0] * inv, v[1] * inv), pack_bf2(v[2] * inv, v[3] * inv)};
+    inv[i] = 1.0f / sum;
+  }
+  bf16_t* op = out + (int64_t)b * Lq * ldo + (int64_t)h * D + 8 * g;
+  // this wave's channel blocks of the group's queries
+#pragma unroll
+  for (int fi = 0; fi < 8 / KS; ++fi) {
+    const int f = ks * (8 / KS) + fi;
+#pragma unroll
+    for (int i = 0; i < 2; ++i) {
+      const int qi = q0 + 16 * i + jq;
+      f32x4 v = {0.0f, 0.0f, 0.0f, 0.0f};
+#pragma unroll
+      for (int w = 0; w < KS; ++w) {
+        const f32x4 u = so[((qw * KS + w) * 16 + f * 2 + i) * 64 + lane];
+#pragma unroll
+        for (int r = 0; r < 4; ++r) v[r] = fmaf(wt[i][w], u[r], v[r]);
+      }
+      if (qi < Lq)
+        *(u32x2*)(op + (int64_t)qi * ldo + 32 * (f >> 1) + 4 * (f & 1)) =
+            u32x2{pack_bf2(v[0] * inv[i], v[1] * inv[i]), pack_bf2(v[2] * inv[i], v[3] * inv[i])};
+    }
   }
 }
 
@@ -546,16 +556,15 @@ __global__ __launch_bounds__(512) void flash_attn_split_kernel(const bf16_t* __r
 // first tile wait for them.  The next item's first two tiles are therefore
 // copied (and its Q registers read) before the stores are issued, and its first
 // tile waits only for what precedes them; the Q copies, as many bytes again, are
-// spread over an item's last tiles, and the outputs leave through LDS as whole 256-byte
-// rows.  2 x 12 heads, 32760 queries: 240.9 -> 227.4 us at 512 keys (0.91 PFLOP/s; 8 tiles
-// of 1.75 us and 4.3 us at the item's ends), 187 -> 161 at 226.
-template <int KIND, bool QLOG2>
+// spread over an item's last tiles.  2 x 12 heads, 32760 queries: 240.9 -> 229.7 us at 512
+// keys (0.90 PFLOP/s; 8 tiles of 1.75 us and 4.5 us at the item's ends), 187 -> 161 at 226.
+template <int KIND, bool QLOG2, bool TAIL>
 __global__ __launch_bounds__(512) void flash_attn_items_kernel(const bf16_t* __restrict__ q, int64_t ldq,
                                                                const bf16_t* __restrict__ k, int64_t ldk,
                                                                const bf16_t* __restrict__ vt, int64_t ldv,
                                                                bf16_t* __restrict__ out, int64_t ldo, int H, int Lq,
                                                                int Lk, float scale_log2, int nitems) {
-  constexpr int BKV = ATT_BKV, NSB = ATT_NSB, D = ATT_D, BQ = ATT_BQ;
+  constexpr int BKV = ATT_BKV, D = ATT_D, BQ = ATT_BQ;
   constexpr int K_BYTES = ATT_K_BYTES, VROW = ATT_VROW, SLOT = ATT_SLOT;
   constexpr int QROW = D * 2;  // 256-byte Q rows in LDS
   __shared__ __attribute__((aligned(1024))) uint8_t smem[2 * SLOT + BQ * QROW];
@@ -564,8 +573,8 @@ __global__ __launch_bounds__(512) void flash_attn_items_kernel(const bf16_t* __r
   const int tid = threadIdx.x;
   const int lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-  const int jq = lane & 31;
-  const int hf = lane >> 5;
+  const int jq = lane & 15;
+  const int g = lane >> 4;
   const int nqb = (Lq + BQ - 1) / BQ;
   const int ntiles = (Lk + BKV - 1) / BKV;
   const int G = gridDim.x;
@@ -583,19 +592,15 @@ __global__ __launch_bounds__(512) void flash_attn_items_kernel(const bf16_t* __r
 #pragma unroll
   for (int i = 0; i < 2; ++i) {
     const int row = 8 * wave + 4 * i + (lane >> 4);
-    koffg[i] = (uint32_t)((key_of_row(row) * ldk + ((lane & 15) ^ (row & 15)) * 8) * 2);
+    koffg[i] = (uint32_t)((att_perm(row) * ldk + ((lane & 15) ^ (row & 15)) * 8) * 2);
     const int vr = 16 * wave + 8 * i + (lane >> 3);
-    voffg[i] = (uint32_t)((vr * ldv + ((lane & 7) ^ att_vswz(vr)) * 8) * 2);
+    voffg[i] = (uint32_t)((att_perm(vr) * ldv + ((lane & 7) ^ att_vswz(vr)) * 8) * 2);
   }
-  uint32_t kfo[D / 16], vfo[2 * NSB];
-#pragma unroll
-  for (int kc = 0; kc < D / 16; ++kc) kfo[kc] = jq * 256 + (((kc * 2 + hf) ^ (jq & 15)) << 4);
-#pragma unroll
-  for (int c = 0; c < 2 * NSB; ++c) vfo[c] = jq * VROW + (((2 * c + hf) ^ att_vswz(jq)) << 4);
+  uint32_t ko = jq * 256 + ((g ^ jq) << 4), vo = jq * VROW + ((g ^ att_vswz(jq)) << 4);
 
-  // K / V^T tile t of item it into slot S (no copy past the last item)
-  auto issue = [&](int it, int t, auto slot_tag) {
-    constexpr int S = decltype(slot_tag)::value;
+  int slot = 0;  // byte offset of the slot copied into next
+  // K / V^T tile t of item it into the next slot (no copy past the last item)
+  auto issue = [&](int it, int t) {
     if (it >= nitems) return;
     int qb, h, b;
     split(it, qb, h, b);
@@ -607,12 +612,13 @@ __global__ __launch_bounds__(512) void flash_attn_items_kernel(const bf16_t* __r
         (void*)(vt + ((int64_t)b * H + h) * D * ldv), (short)0, (int)(uint32_t)(D * ldv * 2), 0x00020000);
 #pragma unroll
     for (int i = 0; i < 2; ++i)
-      __builtin_amdgcn_raw_ptr_buffer_load_lds(rsK, (att_lds_ptr_t)(smem + S * SLOT + wave * 2048 + i * 1024), 16,
+      __builtin_amdgcn_raw_ptr_buffer_load_lds(rsK, (att_lds_ptr_t)(smem + slot + wave * 2048 + i * 1024), 16,
                                                koffg[i], 0, 0, 0);
 #pragma unroll
     for (int i = 0; i < 2; ++i)
-      __builtin_amdgcn_raw_ptr_buffer_load_lds(rsV, (att_lds_ptr_t)(smem + S * SLOT + K_BYTES + wave * 2048 + i * 1024),
+      __builtin_amdgcn_raw_ptr_buffer_load_lds(rsV, (att_lds_ptr_t)(smem + slot + K_BYTES + wave * 2048 + i * 1024),
                                                16, voffg[i] + (uint32_t)(key0 * 2), 0, 0, 0);
+    slot ^= SLOT;
   };
   // pieces i0 .. i1 - 1 (of 8) of this wave's 32 Q rows of item it into LDS (rows
   // past Lq read as zero)
@@ -635,32 +641,18 @@ __global__ __launch_bounds__(512) void flash_attn_items_kernel(const bf16_t* __r
       __builtin_amdgcn_raw_ptr_buffer_load_lds(rsQ, (att_lds_ptr_t)(qs + wave * 32 * QROW + i * 1024), 16, off, 0, 0, 0);
     }
   };
-  bf16x8 qf[D / 16];
+  bf16x8 qf[D / 32][2];
   auto read_q = [&]() {
 #pragma unroll
-    for (int kc = 0; kc < D / 16; ++kc)
-      // the same row / unit layout as a K tile: kfo doubles as the offset
-      qf[kc] = __builtin_bit_cast(bf16x8, *(const u32x4*)(qs + wave * 32 * QROW + kfo[kc]));
+    for (int kc = 0; kc < D / 32; ++kc)
+#pragma unroll
+      for (int i = 0; i < 2; ++i)
+        // the same row / unit layout as a K tile: ko (in slot 0 between items) doubles as the offset
+        qf[kc][i] = __builtin_bit_cast(bf16x8, *(const u32x4*)(qs + (wave * 32 + 16 * i) * QROW + (ko ^ (uint32_t)(kc * 64))));
     __builtin_amdgcn_s_waitcnt((15 << 0) | (3 << 14) | (7 << 4) | (0 << 8));  // lgkmcnt(0): Q buffer free again
   };
 
-  f32x16 o[D / 32];
-  float m_i, thr;
-  bool zref;
-  att_f32x4 lsum;
-  const bf16x8 sel = att_sum_selector(lane);
-  auto reset = [&]() {
-#pragma unroll
-    for (int db = 0; db < D / 32; ++db)
-#pragma unroll
-      for (int r = 0; r < 16; ++r) o[db][r] = 0.0f;
-    m_i = -INFINITY;
-    thr = -INFINITY;
-    zref = false;
-    lsum = att_f32x4{0.0f, 0.0f, 0.0f, 0.0f};
-  };
-  using S0 = std::integral_constant<int, 0>;
-  using S1 = std::integral_constant<int, 1>;
+  AttState st;
   // 16-byte output stores of an item per wave.  They go through a buffer resource
   // (rows past Lq are dropped there, not masked), so every wave issues as many.
   constexpr int NST = D / 16;
@@ -677,26 +669,21 @@ __global__ __launch_bounds__(512) void flash_attn_items_kernel(const bf16_t* __r
     // the lane index, formed here so that neither it nor the offset is spilled
     // across the tiles (a reload would wait for the copies just issued)
     const int ln = att_lane();
-    const float inv = 1.0f / att_row_sum(lsum, ln);
     // through the wave's Q rows in LDS (free until the next Q pieces; unit u of row r
     // at u ^ (r & 15)), so that a store covers four whole 256-byte rows
     uint8_t* const ob = qs + wave * 32 * QROW;
-    const int orow = ln & 31;
 #pragma unroll
-    for (int db = 0; db < D / 32; ++db)
+    for (int i = 0; i < 2; ++i) {
+      const float inv = 1.0f / st.lsum[i][0];
+      const int r = 16 * i + (ln & 15);
 #pragma unroll
-      for (int rg = 0; rg < 4; rg += 2) {
-        // a lane holds 4 of the 8 channels of groups rg and rg + 1 and its
-        // half-wave partner the other 4: exchanged, each has one whole group
-        const uint32_t a0 = pack_bf2(o[db][4 * rg + 0] * inv, o[db][4 * rg + 1] * inv);
-        const uint32_t a1 = pack_bf2(o[db][4 * rg + 2] * inv, o[db][4 * rg + 3] * inv);
-        const uint32_t b0 = pack_bf2(o[db][4 * rg + 4] * inv, o[db][4 * rg + 5] * inv);
-        const uint32_t b1 = pack_bf2(o[db][4 * rg + 6] * inv, o[db][4 * rg + 7] * inv);
-        const auto x = __builtin_amdgcn_permlane32_swap(a0, b0, false, false);
-        const auto y = __builtin_amdgcn_permlane32_swap(a1, b1, false, false);
-        *(u32x4*)(ob + orow * QROW + (((db * 4 + rg + (ln >> 5)) ^ (orow & 15)) << 4)) =
-            u32x4{(uint32_t)x[0], (uint32_t)y[0], (uint32_t)x[1], (uint32_t)y[1]};
+      for (int p = 0; p < D / 32; ++p) {
+        const f32x4 &x = st.o[2 * p][i], &y = st.o[2 * p + 1][i];
+        *(u32x4*)(ob + r * QROW + (((4 * p + (ln >> 4)) ^ (ln & 15)) << 4)) =
+            u32x4{pack_bf2(x[0] * inv, x[1] * inv), pack_bf2(x[2] * inv, x[3] * inv),
+                  pack_bf2(y[0] * inv, y[1] * inv), pack_bf2(y[2] * inv, y[3] * inv)};
       }
+    }
 #pragma unroll
     for (int i = 0; i < NST; ++i) {
       const int r = 4 * i + (ln >> 4), u = ln & 15;
@@ -704,18 +691,18 @@ __global__ __launch_bounds__(512) void flash_attn_items_kernel(const bf16_t* __r
       __builtin_amdgcn_raw_buffer_store_b128(v, rsO, (uint32_t)(r * ldo * 2 + u * 16), 0, 0);
     }
   };
-  // tile t of item it in slot S, the copy of the tile after it in flight (the
-  // first tile's successor is under way already, before the last item's stores)
-  auto tile = [&](int it, int t, auto slot_tag, auto mask_tag, bool stores_behind) {
-    constexpr int S = decltype(slot_tag)::value;
+  // tile t of item it, the copy of the tile after it in flight (the first tile's
+  // successor is under way already, before the last item's stores)
+  auto tile = [&](int it, int t, auto mask_tag, bool stores_behind) {
     if (t > 0) {
-      if (t + 1 < ntiles) issue(it, t + 1, std::integral_constant<int, 1 - S>{});
-      else issue(it + G, 0, std::integral_constant<int, 1 - S>{});
+      if (t + 1 < ntiles) issue(it, t + 1);
+      else issue(it + G, 0);
       const int i1 = 8 - (ntiles - 1 - t) * qper;  // the last tiles copy the next item's Q
       issue_q(it + G, max(0, i1 - qper), min(i1, 8));
     }
-    att_tile<decltype(mask_tag)::value, QLOG2>(smem + S * SLOT, qf, kfo, vfo, o, m_i, thr, zref, lsum, sel, t * BKV, Lk, hf,
-                                               scale_log2);
+    att_tile<decltype(mask_tag)::value, QLOG2>(smem, qf, ko, vo, st, t * BKV, Lk, scale_log2);
+    ko ^= SLOT;
+    vo ^= SLOT;
     if (stores_behind) att_wait_vmcnt<NST>();
     else att_wait_vmcnt<0>();
     __builtin_amdgcn_s_waitcnt((15 << 0) | (3 << 14) | (7 << 4) | (0 << 8));  // lgkmcnt(0)
@@ -725,26 +712,21 @@ __global__ __launch_bounds__(512) void flash_attn_items_kernel(const bf16_t* __r
   auto begin = [&](int it) {
     if (it >= nitems) return;
     read_q();
-    issue(it, 1, S1{});
+    issue(it, 1);
     __builtin_amdgcn_sched_barrier(0);
   };
 
   int it = blockIdx.x;
   issue_q(it, 0, 8);
-  issue(it, 0, S0{});
+  issue(it, 0);
   att_wait_vmcnt<0>();
   __builtin_amdgcn_s_barrier();
   begin(it);
   for (bool first = true; it < nitems; it += G, first = false) {
-    reset();
-    int t = 0;
-    for (; t + 2 < ntiles; t += 2) {
-      tile(it, t, S0{}, std::false_type{}, t == 0 && !first);
-      tile(it, t + 1, S1{}, std::false_type{}, false);
-    }
-    tile(it, t, S0{}, std::false_type{}, t == 0 && !first);
-    if (Lk % BKV) tile(it, t + 1, S1{}, std::true_type{}, false);
-    else tile(it, t + 1, S1{}, std::false_type{}, false);
+    st.reset();
+    const int whole = TAIL ? ntiles - 1 : ntiles;
+    for (int t = 0; t < whole; ++t) tile(it, t, std::false_type{}, t == 0 && !first);
+    if constexpr (TAIL) tile(it, whole, std::true_type{}, false);
     begin(it + G);
     store_item(it);
   }
@@ -767,14 +749,6 @@ __global__ __launch_bounds__(512) void flash_attn_items_kernel(const bf16_t* __r
 // chain over all keys: 2 x 4 heads of 32, 64 x 64: 35.6 -> 8.2 us; 8 heads of 64, 300 x
 // 300: 303 -> 9.8 us; 2 x 8 heads of 128, 1500 x 1500: 19.9 -> 0.37 ms (50 TFLOP/s, bound by
 // the L2 reads of K and V^T), each with a smaller error against float64.
-// Max over the four 16-lane groups (lanes l, l + 16, l + 32, l + 48).
-__device__ __forceinline__ float group_max(float x) {
-  const float m = halfwave_max(x);
-  const auto t = __builtin_amdgcn_permlane16_swap(__float_as_uint(m), __float_as_uint(m), false, false);
-  const float u = __uint_as_float(t[0]), v = __uint_as_float(t[1]);
-  return u > v ? u : v;
-}
-
 template <bool VEC>
 __device__ __forceinline__ f32x4 att_load4(const float* __restrict__ p) {
   if constexpr (VEC) return *(const f32x4*)p;
@@ -877,7 +851,7 @@ __global__ __launch_bounds__(256) void attn_f32_kernel(const float* __restrict__
 #pragma unroll
     for (int r = 0; r < 4; ++r) x[r] = key0 + 4 * g + r < Lk ? s0[r] + s1[r] : -INFINITY;
     const float t = fmaxf(fmaxf(x[0], x[1]), fmaxf(x[2], x[3]));
-    const float mn = fmaxf(m, group_max(t) * scale_log2);
+    const float mn = fmaxf(m, group_max2(t, t) * scale_log2);
     if (__ballot(mn > m)) {
       const float alpha = __builtin_amdgcn_exp2f(m - mn);
       l *= alpha;
@@ -1036,6 +1010,19 @@ track_status attention(int dtype, int B, int H, int head_dim, int64_t Lq, int64_
     const bf16_t *qq = (const bf16_t*)q, *kk = (const bf16_t*)k, *vv = (const bf16_t*)vt;
     bf16_t* oo = (bf16_t*)out;
     const int64_t ntiles = (Lk + ATT_BKV - 1) / ATT_BKV;
+    // the instance of a kernel for (cross, q_log2, masked last tile)
+#define TRACK_ATT_ALL(LAUNCH)                    \
+  do {                                           \
+    const bool tail = Lk % ATT_BKV != 0;         \
+    if (cross && q_log2 && tail) LAUNCH(1, true, true);        \
+    else if (cross && q_log2) LAUNCH(1, true, false);          \
+    else if (cross && tail) LAUNCH(1, false, true);            \
+    else if (cross) LAUNCH(1, false, false);                   \
+    else if (q_log2 && tail) LAUNCH(0, true, true);            \
+    else if (q_log2) LAUNCH(0, true, false);                   \
+    else if (tail) LAUNCH(0, false, true);                     \
+    else LAUNCH(0, false, false);                              \
+  } while (0)
     // TRACK_ATTN_ITEMS=0 keeps short sequences on the per-block kernel (both
     // give identical bits; the tests compare them)
     const char* items_env = getenv("TRACK_ATTN_ITEMS");
@@ -1063,29 +1050,19 @@ track_status attention(int dtype, int B, int H, int head_dim, int64_t Lq, int64_
       const int64_t nitems = (int64_t)grid.x * H * B;
       if (nitems > INT32_MAX) return fail(TRACK_E_SHAPE, "attention: too many query blocks");
       const int g = (int)std::min<int64_t>(nitems, device_cus());
-#define TRACK_ATT_ITEMS(KIND, QL)                                                                               \
-  flash_attn_items_kernel<KIND, QL><<<g, 512, 0, s>>>(qq, ldq, kk, ldk, vv, ldv, oo, ldo, H, (int)Lq, (int)Lk, \
-                                                      scale_log2, (int)nitems)
-      if (cross) {
-        if (q_log2) TRACK_ATT_ITEMS(1, true);
-        else TRACK_ATT_ITEMS(1, false);
-      } else {
-        if (q_log2) TRACK_ATT_ITEMS(0, true);
-        else TRACK_ATT_ITEMS(0, false);
-      }
+#define TRACK_ATT_ITEMS(KIND, QL, TAIL)                                                                          \
+  flash_attn_items_kernel<KIND, QL, TAIL><<<g, 512, 0, s>>>(qq, ldq, kk, ldk, vv, ldv, oo, ldo, H, (int)Lq, (int)Lk, \
+                                                            scale_log2, (int)nitems)
+      TRACK_ATT_ALL(TRACK_ATT_ITEMS);
 #undef TRACK_ATT_ITEMS
     } else {
-#define TRACK_ATT_BLOCKS(KIND, QL) \
-  flash_attn_bf16_kernel<KIND, QL><<<grid, 512, 0, s>>>(qq, ldq, kk, ldk, vv, ldv, oo, ldo, H, (int)Lq, (int)Lk, scale_log2)
-      if (cross) {
-        if (q_log2) TRACK_ATT_BLOCKS(1, true);
-        else TRACK_ATT_BLOCKS(1, false);
-      } else {
-        if (q_log2) TRACK_ATT_BLOCKS(0, true);
-        else TRACK_ATT_BLOCKS(0, false);
-      }
+#define TRACK_ATT_BLOCKS(KIND, QL, TAIL)                                                                        \
+  flash_attn_bf16_kernel<KIND, QL, TAIL><<<grid, 512, 0, s>>>(qq, ldq, kk, ldk, vv, ldv, oo, ldo, H, (int)Lq, (int)Lk, \
+                                                              scale_log2)
+      TRACK_ATT_ALL(TRACK_ATT_BLOCKS);
 #undef TRACK_ATT_BLOCKS
     }
+#undef TRACK_ATT_ALL
     TRACK_LAUNCH_CHECK();
     return TRACK_OK;
   }
