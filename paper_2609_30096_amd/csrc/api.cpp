@@ -274,6 +274,87 @@ track_status track_dit_forward(track_model mh, const track_latent_shape* shape, 
   return TRACK_OK;
 }
 
+}  // extern "C"
+
+namespace {
+// A second stream with the events that fork it from the caller's stream and join it
+// back, kept for the next call (at most 8 of them).
+struct Side {
+  int dev = -1;
+  hipStream_t st = nullptr;
+  hipEvent_t fork = nullptr, join = nullptr;
+};
+std::mutex g_side_mu;
+std::vector<Side> g_side_free;
+
+void destroy_side(const Side& x) {
+  if (x.fork) (void)hipEventDestroy(x.fork);
+  if (x.join) (void)hipEventDestroy(x.join);
+  if (x.st) (void)hipStreamDestroy(x.st);
+}
+
+class SideStream {
+ public:
+  // (stays without a stream, and unused, if `want` is false or one cannot be made)
+  explicit SideStream(bool want) {
+    int dev = -1;
+    if (!want || hipGetDevice(&dev) != hipSuccess) return;
+    {
+      std::lock_guard<std::mutex> lock(g_side_mu);
+      for (size_t i = 0; i < g_side_free.size(); ++i)
+        if (g_side_free[i].dev == dev) {
+          x_ = g_side_free[i];
+          g_side_free.erase(g_side_free.begin() + i);
+          return;
+        }
+    }
+    Side y;
+    y.dev = dev;
+    if (hipStreamCreateWithFlags(&y.st, hipStreamNonBlocking) != hipSuccess ||
+        hipEventCreateWithFlags(&y.fork, hipEventDisableTiming) != hipSuccess ||
+        hipEventCreateWithFlags(&y.join, hipEventDisableTiming) != hipSuccess) {
+      destroy_side(y);
+      return;
+    }
+    x_ = y;
+  }
+  ~SideStream() {
+    if (!x_.st) return;
+    (void)hipStreamSynchronize(x_.st);  // (work is left only where a call failed between fork and join)
+    {
+      std::lock_guard<std::mutex> lock(g_side_mu);
+      if (g_side_free.size() < 8) {
+        g_side_free.push_back(x_);
+        return;
+      }
+    }
+    destroy_side(x_);
+  }
+  SideStream(const SideStream&) = delete;
+  SideStream& operator=(const SideStream&) = delete;
+  hipStream_t stream() const { return x_.st; }
+  hipError_t fork(hipStream_t s) const {
+    const hipError_t e = hipEventRecord(x_.fork, s);
+    return e != hipSuccess ? e : hipStreamWaitEvent(x_.st, x_.fork, 0);
+  }
+  hipError_t join(hipStream_t s) const {
+    const hipError_t e = hipEventRecord(x_.join, x_.st);
+    return e != hipSuccess ? e : hipStreamWaitEvent(s, x_.join, 0);
+  }
+
+ private:
+  Side x_;
+};
+
+// Activations (rows times width) up to which the two models of a calibration step run
+// side by side: alone, their kernels are a chain of latencies that leaves most of the chip
+// idle (four samples of eight guided steps, 4 + 2 blocks: 64 tokens of width 128 10.05 ->
+// 9.70 ms, bound by the launches; 196 of width 512 27.4 -> 21.2).
+constexpr int64_t SIDE_MAX = (int64_t)1 << 19;
+}  // namespace
+
+extern "C" {
+
 static track_status calibrate_impl(track_model lh, track_model sh, const track_latent_shape* shape, int32_t M,
                                    const float* const* x_T, const void* const* cond, const void* uncond,
                                    const track_sampler_config* scfg, double* r_out, double* q_out, double* band_r_out,
@@ -310,6 +391,10 @@ static track_status calibrate_impl(track_model lh, track_model sh, const track_l
   const Scheduler sched(L, wl, *scfg);
   const std::vector<double>& sig = sched.sig;
   const float w = (float)scfg->guidance;
+  // (a capturing stream fails below at the first copy back; the side stream stays out of it)
+  hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
+  const bool plain = hipStreamIsCapturing(s, &cap) == hipSuccess && cap == hipStreamCaptureStatusNone;
+  const SideStream side(plain && B * wl.L * std::max(c.dim, S.cfg.dim) <= SIDE_MAX);
   std::vector<double> r((size_t)M * N, 0.0), rb(bands ? (size_t)M * N * 6 : 0, 0.0);
   for (int j = 0; j < M; ++j) {
     const void* ctx[2] = {cond[j], uncond};
@@ -321,8 +406,10 @@ static track_status calibrate_impl(track_model lh, track_model sh, const track_l
     TRY(prepare(S, *shape, B, ctx, s));
     for (int k = 0; k < N; ++k) {
       const double t = 1000.0 * sig[k];
+      if (side.stream()) TRACK_HIP(side.fork(s));
       TRY(forward(L, *shape, B, xtok, t, velL, s));
-      TRY(forward(S, *shape, B, xtok, t, velS, s));
+      TRY(forward(S, *shape, B, xtok, t, velS, side.stream() ? side.stream() : s));
+      if (side.stream()) TRACK_HIP(side.join(s));
       // the band kernels read the velocities, which the update leaves intact
       TRY(sched.advance(k, B, w, velL, velS, xtok, partial, scfg->eps, rdev + k, s));
       if (bands)

@@ -530,3 +530,42 @@ def test_sample_with_one_workspace_for_both_models(dtype):
                                                        ctypes.c_size_t(need)))
     got = host(track.sample(pair.L, pair.S, mask, shape, scfg, pair.dx[0], pair.dc[0], pair.du))
     np.testing.assert_array_equal(got, want)
+
+
+@pytest.mark.parametrize("threads", [1, 3])
+def test_calibrate_models_side_by_side(threads):
+    """A small pair's two forward passes of a step run on two streams: the scores and samples are the same bits from
+    the default stream and from streams that are still writing the inputs, in several threads at once."""
+    import threading
+    import torch
+    say(f"calibrate side by side, threads={threads}")
+    scfg = dataclasses.replace(synth.TINY_SAMPLER, steps=5)
+    pairs = [Pair(synth.TINY_LARGE, synth.TINY_SMALL, synth.TINY_LATENT) for _ in range(threads)]
+
+    def run(p, x):
+        r, q, x0 = track.calibrate(p.L, p.S, p.shape, x, p.dc[:2], p.du, scfg, return_x0=True)
+        return r, [host(t) for t in x0]
+
+    want = run(pairs[0], pairs[0].dx[:2])
+    torch.cuda.synchronize()
+    got = [None] * threads
+
+    def work(i):
+        with torch.cuda.stream(torch.cuda.Stream()):
+            x = []
+            for t in pairs[i].dx[:2]:
+                y = torch.zeros_like(t)
+                for _ in range(50):  # keeps the stream busy until after the call begins
+                    y.add_(t, alpha=0.0)
+                x.append(y.copy_(t))
+            got[i] = run(pairs[i], x)
+
+    ts = [threading.Thread(target=work, args=(i,)) for i in range(threads)]
+    for t in ts:
+        t.start()
+    for t in ts:
+        t.join()
+    for r, x0 in got:
+        np.testing.assert_array_equal(r, want[0])
+        for a, b in zip(x0, want[1]):
+            np.testing.assert_array_equal(a, b)
