@@ -74,17 +74,17 @@ def workload_name(cfg, shape, B):
 
 
 def step_flops(cfg, shape, B):
-    """Algorithmic FLOPs of one guided prediction: 2MNK per GEMM, 4 B H Lq Lk dh per attention."""
+    """Algorithmic FLOPs of one guided prediction within a trajectory: 2MNK per GEMM, 4 B H Lq Lk dh per attention
+    (the text MLP and the blocks' text keys and values, formed once per trajectory, are not counted)."""
     L = shape.tokens(cfg.patch)
     Lc, d, f, H, dh, P = shape.text_len, cfg.dim, cfg.ffn_dim, cfg.heads, cfg.head_dim, cfg.patch_elems
     M = B * L
     per_block = (2 * M * d * 3 * d + 2 * M * d * d            # QKV, self O
                  + 2 * M * d * d + 2 * M * d * d               # cross Q, cross O
-                 + 2 * (B * Lc) * d * 2 * d                    # text K, V
                  + 2 * 2 * M * d * f                           # FFN1, FFN2
                  + 4 * B * H * L * L * dh                      # self-attention
                  + 4 * B * H * L * Lc * dh)                    # cross-attention
-    rest = 2 * L * P * d + 2 * M * d * P + 2 * B * Lc * (cfg.text_dim * d + d * d)
+    rest = 2 * L * P * d + 2 * M * d * P
     return cfg.blocks * per_block + rest
 
 
