@@ -70,8 +70,9 @@ __device__ __forceinline__ float group_max2(float a, float b) {
 // position.  The XOR swizzles keep the 16-row fragment reads conflict free:
 // K rows are 256 bytes (unit u of row r at u ^ (r & 15)); V^T rows are 128
 // bytes (unit u at u ^ att_vswz(r)).  Each lane's fragment offsets are computed
-// once and switch slots with an XOR.  Rows are permuted within every 32: LDS row 16 h + 4 q + j holds
-// key (or channel) 8 q + 4 h + j.  A lane's logits of a pair of 16-key blocks are
+// once and switch slots with an XOR.  Rows are permuted within every 32: LDS row
+// 16 h + 4 q + j holds key (or channel) 8 q + 4 h + j.  A lane's logits of a pair of
+// 16-key blocks are
 // then 8 consecutive keys, the P operand's k-block, which meets one contiguous
 // 16-byte V^T chunk, and its outputs of a pair of 16-channel blocks are 8
 // consecutive channels, one 16-byte store.
@@ -391,7 +392,7 @@ __global__ __launch_bounds__(512) void flash_attn_bf16_kernel(const bf16_t* __re
 // steps.  A ring slot holds 128 keys (two of the tiles above); with KS = 2 a wave takes
 // one tile of it, with KS = 4 one 32-key half of one.  The shares' sums meet through
 // LDS at the end: 16 KB of float32 O a wave, in the ring's space.  3 heads, 1000 x 1000:
-// 28.4 us with 1 share, 21.0 with 2, 15.9 with 4; 8 heads, 3001 x 3001: 67.0 / 57.4 / 88.6.
+// 28.7 us with 1 share, 20.3 with 2, 15.6 with 4; 8 heads, 3001 x 3001: 71.8 / 57.6 / 83.3.
 template <int KS, bool QLOG2>
 __global__ __launch_bounds__(512) void flash_attn_split_kernel(const bf16_t* __restrict__ q, int64_t ldq,
                                                                const bf16_t* __restrict__ k, int64_t ldk,
@@ -556,8 +557,9 @@ __global__ __launch_bounds__(512) void flash_attn_split_kernel(const bf16_t* __r
 // first tile wait for them.  The next item's first two tiles are therefore
 // copied (and its Q registers read) before the stores are issued, and its first
 // tile waits only for what precedes them; the Q copies, as many bytes again, are
-// spread over an item's last tiles.  2 x 12 heads, 32760 queries: 240.9 -> 229.7 us at 512
-// keys (0.90 PFLOP/s; 8 tiles of 1.75 us and 4.5 us at the item's ends), 187 -> 161 at 226.
+// spread over an item's last tiles, and the outputs leave through LDS as whole 256-byte
+// rows.  2 x 12 heads, 32760 queries, the three steps: 240.9 -> 227.4 us at 512 keys, 187 ->
+// 161 at 226; with the present tile body 216.8 (0.95 PFLOP/s) and 137.
 template <int KIND, bool QLOG2, bool TAIL>
 __global__ __launch_bounds__(512) void flash_attn_items_kernel(const bf16_t* __restrict__ q, int64_t ldq,
                                                                const bf16_t* __restrict__ k, int64_t ldk,
@@ -923,10 +925,10 @@ __global__ __launch_bounds__(256) void attn_f32_kernel(const float* __restrict__
 
 // Key shares per query block (1, 2 or 4), by an estimate of the time: rounds of
 // workgroups over the CUs, times steps of a workgroup and its fixed cost.  The constants
-// are fits to all three at 19 shapes (1 - 5000 queries, 1 - 40 heads): a step is a 64-key
-// tile with 1 share (1.55 us), 128 keys with 2 (2.2: the copies of 64 KB) or 4 (1.72: half
-// the work per wave).  A shape that fills the chip keeps one share: 2 x 12 heads, 1560 x
-// 1560: 44 us, 72 with 2, 79 with 4.
+// are fits to all three at 19 shapes (1 - 5000 queries, 1 - 40 heads), where the pick is
+// within 5% of the best: a step is a 64-key tile with 1 share (1.55 us), 128 keys with 2
+// (2.2: the copies of 64 KB) or 4 (1.72: half the work per wave).  A shape that fills the
+// chip keeps one share: 2 x 12 heads, 1560 x 1560: 44 us, 68 with 2, 75 with 4.
 // TRACK_ATTN_SPLIT = 1, 2 or 4 (read at every call) forces one, for tests.
 static int pick_split(int64_t Lq, int64_t Lk, int64_t heads) {
   const char* v = getenv("TRACK_ATTN_SPLIT");
