@@ -792,7 +792,7 @@ __global__ __launch_bounds__(256) void gemm_f32_kernel(const float* __restrict__
   }
 }
 
-// Few-tile float32 GEMM on v_mfma_f32_16x16x4_f32 (float32 products and sums): a
+// K-sharing float32 GEMM on v_mfma_f32_16x16x4_f32 (float32 products and sums): a
 // workgroup owns 16 T x 16 T outputs and its four waves share K, every fourth
 // 16-deep chunk each, joined through LDS.  The small float32 models' products (128
 // rows, K 128 - 512) are a latency chain: here one global load and K / 64 short
@@ -1134,15 +1134,18 @@ static void launch_bf16(int tile, int epi, const bf16_t* A, int64_t lda, const b
   }
 }
 
-// Blocks a side of the few-tile kernel's workgroup (0: the LDS-tiled kernel takes
-// the shape): one until the 16 x 16 blocks fill the chip four times over.
+// Blocks a side of the K-sharing kernel's workgroup: one until the 16 x 16 blocks fill
+// the chip four times over, then two, which is the faster one at any size (1000 x 1536 x
+// 512 30 us against 74 of the LDS-tiled kernel, 3120 x 1536 x 512 84 / 126, 2048 x 2048 x 2048
+// 271 / 396, 3120 x 4608 x 1536 749 / 900).  0: the LDS-tiled kernel, for rows that are not
+// 16-byte aligned, or more of them than the grid's second dimension counts.
 static int f32_small_blocks(int64_t M, int64_t N, int64_t K, const void* A, int64_t lda, const void* W, int64_t nb) {
   const int64_t t16 = ((M + 15) / 16) * ((N + 15) / 16) * nb, cus = device_cus();
-  if (K % 4 || lda % 4 || (((uintptr_t)A | (uintptr_t)W) & 15) || t16 > 32 * cus) return 0;
+  if (K % 4 || lda % 4 || (((uintptr_t)A | (uintptr_t)W) & 15) || (M + 31) / 32 > 65535) return 0;
   return t16 > 4 * cus ? 2 : 1;
 }
 
-// ln: the rows of A are LayerNorm inputs (few-tile kernel only, t > 0)
+// ln: the rows of A are LayerNorm inputs (K-sharing kernel only, t > 0)
 static void launch_f32(int t, int epi, const float* A, int64_t lda, const float* W, int64_t M, int N, int K,
                        const EpiArgs& e, int nb, bool ln, const float* scale, const float* shift, hipStream_t s) {
   const int b = t ? 16 * t : 64;
@@ -1238,7 +1241,10 @@ track_status linear_batch(int dtype, int nb, int64_t M, int64_t N, int64_t K, co
 track_status layernorm_linear(int dtype, int epi, int64_t M, int64_t N, int64_t K, const float* X, const float* scale,
                               const float* shift, void* Y, const void* W, const void* bias, const float* gate,
                               void* out, int64_t ldo, hipStream_t s) {
-  const int t = dtype == TRACK_DTYPE_F32 && K <= SF_LN_K && M > 0 && N > 0 && ldo >= N && N <= (1 << 30) && bias && out &&
+  // (up to 32 blocks of 16 x 16 per CU: the rows' sums are formed again for every 32
+  // features, and the registers they take cost a large product its occupancy)
+  const bool few = ((M + 15) / 16) * ((N + 15) / 16) <= 32 * (int64_t)device_cus();
+  const int t = dtype == TRACK_DTYPE_F32 && few && K <= SF_LN_K && M > 0 && N > 0 && ldo >= N && N <= (1 << 30) && bias && out &&
                         (epi != TRACK_EPI_GATE_RESID || gate) && (((uintptr_t)scale | (uintptr_t)shift) & 15) == 0
                     ? f32_small_blocks(M, N, K, X, K, W, 1)
                     : 0;
