@@ -143,7 +143,9 @@ __device__ __forceinline__ float att_of_block(float v, int b, int lane) {
 // zero.  KB 16-key blocks of the tile (2: the half that ko and vo point at).  With SAFE
 // a row whose logits so far are all -inf (a wave of a split sequence can begin with
 // such a tile) takes reference 0 instead.
-template <bool MASK, bool QLOG2, int KB = ATT_BKV / 16, bool SAFE = false>
+// FIRST: the sequence's first tile, which starts O and the sums (no rescale, nothing to
+// zero) and the references: 212.7 -> 207.3 us at 2 x 12 heads, 32760 x 512, 12 times a CU.
+template <bool MASK, bool QLOG2, int KB = ATT_BKV / 16, bool SAFE = false, bool FIRST = false>
 __device__ __forceinline__ void att_tile(const uint8_t* kb, const bf16x8 (&qf)[ATT_D / 32][ATT_QB], uint32_t ko,
                                          uint32_t vo, AttState& st, int key0, int Lk, float scale_log2) {
   constexpr int QB = ATT_QB;
@@ -188,7 +190,11 @@ __device__ __forceinline__ void att_tile(const uint8_t* kb, const bf16x8 (&qf)[A
         mx[b] = fmaxf(mx[b], s[i][b][r]);
       }
   const float mt = QLOG2 ? group_max2(mx[0], mx[1]) : group_max2(mx[0], mx[1]) * scale_log2;
-  if (__ballot(mt > st.ms + ATT_TAU)) {
+  const f32x4 zero = {0.0f, 0.0f, 0.0f, 0.0f};
+  if constexpr (FIRST) {
+    st.ms = mt >= ATT_MLO && mt <= ATT_TAU ? 0.0f : fmaxf(-INFINITY, mt);
+    st.zref = !__ballot(st.ms != 0.0f);
+  } else if (__ballot(mt > st.ms + ATT_TAU)) {
     float mn = fmaxf(st.ms, mt);
     if (mn >= ATT_MLO && mn <= ATT_TAU) mn = 0.0f;
     const float alpha = SAFE && mn == -INFINITY ? 1.0f : __builtin_amdgcn_exp2f(st.ms - mn);
@@ -257,7 +263,7 @@ __device__ __forceinline__ void att_tile(const uint8_t* kb, const bf16x8 (&qf)[A
   for (int c = 0; c < KB / 2; ++c)
 #pragma unroll
     for (int b = 0; b < QB; ++b)
-      st.lsum[b] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(ones, pf[c][b], st.lsum[b], 0, 0, 0);
+      st.lsum[b] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(ones, pf[c][b], FIRST && c == 0 ? zero : st.lsum[b], 0, 0, 0);
 #pragma unroll
   for (int j = 0; j < VF; ++j) {
     if (j + ATT_LA < VF) vf[(j + ATT_LA) % (ATT_LA + 1)] = vfrag(j + ATT_LA);
@@ -265,7 +271,8 @@ __device__ __forceinline__ void att_tile(const uint8_t* kb, const bf16x8 (&qf)[A
     const int f = j / (KB / 2), c = j % (KB / 2);
 #pragma unroll
     for (int b = 0; b < QB; ++b)
-      st.o[f][b] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(vf[j % (ATT_LA + 1)], pf[c][b], st.o[f][b], 0, 0, 0);
+      st.o[f][b] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(vf[j % (ATT_LA + 1)], pf[c][b],
+                                                           FIRST && c == 0 ? zero : st.o[f][b], 0, 0, 0);
   }
 }
 
@@ -295,8 +302,9 @@ __device__ __forceinline__ void att_store(const AttState& st, bf16_t* __restrict
   }
 }
 
-// TAIL: Lk is not whole 64-key tiles, and the last one is masked.
-template <int KIND, bool QLOG2, bool TAIL>
+// TAIL: 16-key blocks computed of a ragged last tile, which is masked: 2 where it holds
+// at most 32 keys, else 4; 0 if Lk is whole tiles.
+template <int KIND, bool QLOG2, int TAIL>
 __global__ __launch_bounds__(512) void flash_attn_bf16_kernel(const bf16_t* __restrict__ q, int64_t ldq,
                                                       const bf16_t* __restrict__ k, int64_t ldk,
                                                       const bf16_t* __restrict__ vt, int64_t ldv,
@@ -363,11 +371,12 @@ __global__ __launch_bounds__(512) void flash_attn_bf16_kernel(const bf16_t* __re
   uint32_t ko = jq * 256 + ((g ^ jq) << 4), vo = jq * VROW + ((g ^ att_vswz(jq)) << 4);
 
   AttState st;
-  st.reset();
 
-  auto tile = [&](int t, auto mask_tag) {
+  auto tile = [&](int t, auto tail_tag, auto first_tag) {
     issue(t + 1);
-    att_tile<decltype(mask_tag)::value, QLOG2>(smem, qf, ko, vo, st, t * BKV, Lk, scale_log2);
+    att_tile<(decltype(tail_tag)::value > 0), QLOG2, decltype(tail_tag)::value ? decltype(tail_tag)::value : BKV / 16, false,
+             decltype(first_tag)::value>(smem, qf, ko, vo, st, t * BKV,
+                                                                                       Lk, scale_log2);
     ko ^= SLOT;
     vo ^= SLOT;
     att_wait_vmcnt<0>();
@@ -378,9 +387,12 @@ __global__ __launch_bounds__(512) void flash_attn_bf16_kernel(const bf16_t* __re
   issue(0);
   att_wait_vmcnt<0>();
   __builtin_amdgcn_s_barrier();
-  const int whole = TAIL ? ntiles - 1 : ntiles;
-  for (int t = 0; t < whole; ++t) tile(t, std::false_type{});
-  if constexpr (TAIL) tile(whole, std::true_type{});
+  const int whole = TAIL > 0 ? ntiles - 1 : ntiles;
+  using Whole = std::integral_constant<int, 0>;
+  if (TAIL == 0 || whole > 0) tile(0, Whole{}, std::true_type{});
+  else st.reset();
+  for (int t = 1; t < whole; ++t) tile(t, Whole{}, std::false_type{});
+  if constexpr (TAIL > 0) tile(whole, std::integral_constant<int, TAIL>{}, std::false_type{});
   att_wait_vmcnt<0>();
 
   att_store(st, out + (int64_t)b * Lq * ldo + (int64_t)h * D, ldo, q0, Lq, lane);
@@ -560,7 +572,7 @@ __global__ __launch_bounds__(512) void flash_attn_split_kernel(const bf16_t* __r
 // spread over an item's last tiles, and the outputs leave through LDS as whole 256-byte
 // rows.  2 x 12 heads, 32760 queries, the three steps: 240.9 -> 227.4 us at 512 keys, 187 ->
 // 161 at 226; with the present tile body 216.8 (0.95 PFLOP/s) and 137.
-template <int KIND, bool QLOG2, bool TAIL>
+template <int KIND, bool QLOG2, int TAIL>
 __global__ __launch_bounds__(512) void flash_attn_items_kernel(const bf16_t* __restrict__ q, int64_t ldq,
                                                                const bf16_t* __restrict__ k, int64_t ldk,
                                                                const bf16_t* __restrict__ vt, int64_t ldv,
@@ -695,14 +707,16 @@ __global__ __launch_bounds__(512) void flash_attn_items_kernel(const bf16_t* __r
   };
   // tile t of item it, the copy of the tile after it in flight (the first tile's
   // successor is under way already, before the last item's stores)
-  auto tile = [&](int it, int t, auto mask_tag, bool stores_behind) {
-    if (t > 0) {
+  auto tile = [&](int it, int t, auto tail_tag, auto first_tag, bool stores_behind) {
+    if constexpr (!decltype(first_tag)::value) {
       if (t + 1 < ntiles) issue(it, t + 1);
       else issue(it + G, 0);
       const int i1 = 8 - (ntiles - 1 - t) * qper;  // the last tiles copy the next item's Q
       issue_q(it + G, max(0, i1 - qper), min(i1, 8));
     }
-    att_tile<decltype(mask_tag)::value, QLOG2>(smem, qf, ko, vo, st, t * BKV, Lk, scale_log2);
+    att_tile<(decltype(tail_tag)::value > 0), QLOG2, decltype(tail_tag)::value ? decltype(tail_tag)::value : BKV / 16, false,
+             decltype(first_tag)::value>(smem, qf, ko, vo, st, t * BKV,
+                                                                                       Lk, scale_log2);
     ko ^= SLOT;
     vo ^= SLOT;
     if (stores_behind) att_wait_vmcnt<NST>();
@@ -725,10 +739,11 @@ __global__ __launch_bounds__(512) void flash_attn_items_kernel(const bf16_t* __r
   __builtin_amdgcn_s_barrier();
   begin(it);
   for (bool first = true; it < nitems; it += G, first = false) {
-    st.reset();
-    const int whole = TAIL ? ntiles - 1 : ntiles;
-    for (int t = 0; t < whole; ++t) tile(it, t, std::false_type{}, t == 0 && !first);
-    if constexpr (TAIL) tile(it, whole, std::true_type{}, false);
+    const int whole = TAIL ? ntiles - 1 : ntiles;  // at least one: ntiles is even
+    using Whole = std::integral_constant<int, 0>;
+    tile(it, 0, Whole{}, std::true_type{}, !first);
+    for (int t = 1; t < whole; ++t) tile(it, t, Whole{}, std::false_type{}, false);
+    if constexpr (TAIL > 0) tile(it, whole, std::integral_constant<int, TAIL>{}, std::false_type{}, false);
     begin(it + G);
     store_item(it);
   }
@@ -1013,17 +1028,19 @@ track_status attention(int dtype, int B, int H, int head_dim, int64_t Lq, int64_
     bf16_t* oo = (bf16_t*)out;
     const int64_t ntiles = (Lk + ATT_BKV - 1) / ATT_BKV;
     // the instance of a kernel for (cross, q_log2, masked last tile)
-#define TRACK_ATT_ALL(LAUNCH)                    \
-  do {                                           \
-    const bool tail = Lk % ATT_BKV != 0;         \
-    if (cross && q_log2 && tail) LAUNCH(1, true, true);        \
-    else if (cross && q_log2) LAUNCH(1, true, false);          \
-    else if (cross && tail) LAUNCH(1, false, true);            \
-    else if (cross) LAUNCH(1, false, false);                   \
-    else if (q_log2 && tail) LAUNCH(0, true, true);            \
-    else if (q_log2) LAUNCH(0, true, false);                   \
-    else if (tail) LAUNCH(0, false, true);                     \
-    else LAUNCH(0, false, false);                              \
+#define TRACK_ATT_TAILS(KIND, QL, LAUNCH)  \
+  do {                                     \
+    if (tail == 0) LAUNCH(KIND, QL, 0);    \
+    else if (tail <= 32) LAUNCH(KIND, QL, 2); \
+    else LAUNCH(KIND, QL, 4);              \
+  } while (0)
+#define TRACK_ATT_ALL(LAUNCH)                               \
+  do {                                                      \
+    const int tail = (int)(Lk % ATT_BKV);                   \
+    if (cross && q_log2) TRACK_ATT_TAILS(1, true, LAUNCH);  \
+    else if (cross) TRACK_ATT_TAILS(1, false, LAUNCH);      \
+    else if (q_log2) TRACK_ATT_TAILS(0, true, LAUNCH);      \
+    else TRACK_ATT_TAILS(0, false, LAUNCH);                 \
   } while (0)
     // TRACK_ATTN_ITEMS=0 keeps short sequences on the per-block kernel (both
     // give identical bits; the tests compare them)
@@ -1065,6 +1082,7 @@ track_status attention(int dtype, int B, int H, int head_dim, int64_t Lq, int64_
 #undef TRACK_ATT_BLOCKS
     }
 #undef TRACK_ATT_ALL
+#undef TRACK_ATT_TAILS
     TRACK_LAUNCH_CHECK();
     return TRACK_OK;
   }

@@ -75,10 +75,11 @@ def test_linear_small(dtype, epi, M, N, K):
 
 # float32: sums of K terms in other orders differ by a few 1e-7 (K up to 640 here)
 @pytest.mark.parametrize("epi", EPIS)
-@pytest.mark.parametrize("M,N,K", [(1, 1, 4), (16, 17, 20), (33, 31, 64), (130, 100, 260), (700, 900, 68), (50, 40, 30)])
+@pytest.mark.parametrize("M,N,K", [(1, 1, 4), (16, 17, 20), (33, 31, 64), (130, 100, 260), (700, 900, 68), (50, 40, 30),
+                                   (1500, 1450, 36)])
 def test_linear_f32_few_tiles(epi, M, N, K):
-    """The K-sharing kernel at one and two 16 x 16 blocks a side, with ragged M, N and K, and (K 30) the
-    kernel it leaves to rows that are not 16-byte aligned."""
+    """The K-sharing kernel at one and two 16 x 16 blocks a side (the last beyond 8192 blocks), with ragged M, N
+    and K, and (K 30) the kernel it leaves to rows that are not 16-byte aligned."""
     say(f"linear f32 few tiles epi={epi} M={M} N={N} K={K}")
     key = 5300 + M + N + K
     A, W, b = normal((key, 1), (M, K)), normal((key, 2), (N, K), 0.05), normal((key, 3), (N,), 0.1)
@@ -246,10 +247,10 @@ def test_attention_f32_forms(dh, B, H, Lq, Lk, pad):
 
 @pytest.mark.parametrize("q_log2", [False, True])
 @pytest.mark.parametrize("B,H,Lq,Lk", [(1, 1, 1, 1), (1, 2, 31, 32), (2, 1, 64, 33), (1, 2, 65, 128), (2, 2, 129, 129),
-                                       (1, 1, 257, 385), (1, 2, 100, 1000)])
+                                       (1, 1, 257, 385), (1, 2, 100, 1000), (1, 1, 40, 96), (1, 1, 40, 97), (1, 1, 40, 160)])
 def test_attention_bf16_split_shares(B, H, Lq, Lk, q_log2, monkeypatch):
-    """1, 2 and 4 key shares per query block (TRACK_ATTN_SPLIT), shares without a key among them: each against
-    the oracle, within the rounding of P and the output to bfloat16 (1e-2, as for the unsplit kernel)."""
+    """1, 2 and 4 key shares per query block (TRACK_ATTN_SPLIT), shares without a key among them, and last tiles
+    of up to 32 keys and of more (both unsplit kernels): each against the oracle, within the rounding of P and the output to bfloat16 (1e-2, as for the unsplit kernel)."""
     for ks in ("1", "2", "4"):
         say(f"attention bf16 split={ks} B={B} H={H} Lq={Lq} Lk={Lk} q_log2={q_log2}")
         monkeypatch.setenv("TRACK_ATTN_SPLIT", ks)
