@@ -60,18 +60,20 @@ __device__ __forceinline__ float dpp_add(float v) {
   return v + __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), CTRL, 0xf, 0xf, true));
 }
 
-// Sum over the wave, the same bits in every lane: pairs, quads, mirrored halves and
-// rows by DPP, then rows and halves by the lane swaps (a chain of register moves; the
-// six LDS permutes of a shuffle butterfly take several times as long).
+// Sum over the wave, the same bits in every lane: lanes 32 apart first, then 16, 8, 4, 2
+// and 1 (other orders give other last bits, which a bfloat16 model carries on).  Halves
+// and rows meet by the lane swaps, the rest by DPP: register moves, where the six LDS
+// permutes of a shuffle butterfly take several times as long.  A rotation by 4 stands for
+// the exchange of lanes 4 apart: lanes 8 apart hold the same value by then.
 __device__ __forceinline__ float wave_sum(float v) {
-  v = dpp_add<0xb1>(v);   // quad_perm [1, 0, 3, 2]
-  v = dpp_add<0x4e>(v);   // quad_perm [2, 3, 0, 1]
-  v = dpp_add<0x141>(v);  // row_half_mirror
-  v = dpp_add<0x140>(v);  // row_mirror
-  const auto a = __builtin_amdgcn_permlane16_swap(__float_as_uint(v), __float_as_uint(v), false, false);
+  const auto a = __builtin_amdgcn_permlane32_swap(__float_as_uint(v), __float_as_uint(v), false, false);
   v = __uint_as_float(a[0]) + __uint_as_float(a[1]);
-  const auto b = __builtin_amdgcn_permlane32_swap(__float_as_uint(v), __float_as_uint(v), false, false);
-  return __uint_as_float(b[0]) + __uint_as_float(b[1]);
+  const auto b = __builtin_amdgcn_permlane16_swap(__float_as_uint(v), __float_as_uint(v), false, false);
+  v = __uint_as_float(b[0]) + __uint_as_float(b[1]);
+  v = dpp_add<0x128>(v);   // row_ror 8
+  v = dpp_add<0x124>(v);   // row_ror 4
+  v = dpp_add<0x4e>(v);    // quad_perm [2, 3, 0, 1]
+  return dpp_add<0xb1>(v);  // quad_perm [1, 0, 3, 2]
 }
 
 __device__ __forceinline__ double wave_sum_d(double v) {

@@ -292,6 +292,31 @@ def test_layernorm(dtype, d, modulated):
     assert rel_l2(host(y), ref) < tol
 
 
+@pytest.mark.parametrize("far", [32, 16, 8, 4, 2, 1])
+def test_layernorm_lane_order(far):
+    """The order in which a wave's 64 lanes are summed (32 apart first, 1 apart last), which the last bits of every
+    norm and so of the bfloat16 models rest on.  Lanes 0 and `far` hold +2^24 and -2^24, the others ones: what is
+    lost to 2^24 before the two meet depends on the order alone.  The ones come out as (1 - mean) / std with the
+    mean of that order's sum, another by at least 1/256 for another sum; 1e-5 bounds the float32 steps after it."""
+    import torch
+    say(f"layernorm lane order, {far} apart")
+    lanes = np.ones(64, np.float32)
+    lanes[0], lanes[far] = 2.0 ** 24, -2.0 ** 24
+    x = np.zeros((3, 256), np.float32)
+    x[:, ::4] = lanes  # one float4 a lane
+    v = lanes.copy()
+    for o in (32, 16, 8, 4, 2, 1):
+        v = v + v[np.arange(64) ^ o]
+    assert np.all(v == v[0])
+    mean = float(v[0]) / 256
+    c = x[0].astype(np.float64) - mean
+    want = (1.0 - mean) / np.sqrt((c * c).mean() + 1e-6)
+    y = torch.empty(3, 256, device="cuda")
+    track.op_layernorm(track.DTYPE_F32, dev(x), y)
+    got = host(y)[:, 4 * (far ^ 3)]  # a lane that holds one
+    np.testing.assert_allclose(got, want, rtol=1e-5)
+
+
 # Widths above 2048 take the kernel that spreads two rows over a workgroup:
 # 40 x 128 (the 14B width); 24 x 96 with B = 1 (ragged last chunk, angles
 # looked up per chunk, an odd row count).
