@@ -124,11 +124,18 @@ track_status track_model_create(const track_dit_config* cfg, const void* dev_wei
 void         track_model_destroy(track_model m);   /* NULL is a no-op */
 
 /* Workspace (activations for one guided prediction of `batch` = 2 with
- * guidance, 1 without, plus trajectory state) for the given latent shape.
+ * guidance, 1 without, the text keys and values of every block, and the
+ * trajectory state) for the given latent shape.  The size belongs to this
+ * build of the library: ask for it anew instead of storing it.
  * Returns 0 when the shape is invalid for the model. */
 size_t       track_workspace_bytes(track_model m, const track_latent_shape* shape, int32_t batch);
 /* Attach a caller-owned, 256-byte aligned device workspace; calls that use
- * the model must not overlap on the GPU while they share it. */
+ * the model must not overlap on the GPU while they share it.  track_sample and
+ * track_calibrate form what depends on the text embeddings alone (every
+ * block's text keys and values) once and keep it there from step to step.
+ * Where the workspaces of a call's two models overlap they are used in turns,
+ * each model forming that part anew; the small model's must leave alone the
+ * end of the large model's, which holds the trajectory state. */
 track_status track_model_set_workspace(track_model m, void* dev_ws, size_t bytes);
 
 /* ---------------------------------------------------------------- the four calls

@@ -189,6 +189,32 @@ static track_status check_pair(const Model& L, const Model& S) {
   return TRACK_OK;
 }
 
+// Which models of a sampling loop have their contexts (text keys and values, constant
+// tables: prepare()) in their workspaces.  Two models whose workspaces overlap take
+// turns: forming one's context, and every forward pass on it, writes over the other's.
+struct Contexts {
+  const Model* m[2];
+  const track_latent_shape& shape;
+  int B;
+  const void* const* ctx;
+  bool shared, have[2] = {false, false};
+
+  Contexts(const Model& L, const Model* S, const track_latent_shape& s, int batch, const void* const* c)
+      : m{&L, S}, shape(s), B(batch), ctx(c) {
+    // (what the layouts need: an attached size may be the rest of a larger allocation)
+    shared = S && L.ws < S->ws + ws_layout(*S, s, batch).total && S->ws < L.ws + ws_layout(L, s, batch).total;
+  }
+  // Before a forward pass of model i (0 large, 1 small).
+  track_status ready(int i, hipStream_t st) {
+    if (have[i]) return TRACK_OK;
+    const track_status e = prepare(*m[i], shape, B, ctx, st);
+    have[i] = e == TRACK_OK;
+    if (shared) have[1 - i] = false;
+    return e;
+  }
+  void reset() { have[0] = have[1] = false; }  // before a new set of contexts
+};
+
 static track_status check_sampler(const track_sampler_config* sc) {
   if (!sc) return fail(TRACK_E_INVALID, "null sampler config");
   if (sc->steps < 1) return fail(TRACK_E_INVALID, "sampler: steps must be >= 1");
@@ -394,20 +420,26 @@ static track_status calibrate_impl(track_model lh, track_model sh, const track_l
   // (a capturing stream fails below at the first copy back; the side stream stays out of it)
   hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
   const bool plain = hipStreamIsCapturing(s, &cap) == hipSuccess && cap == hipStreamCaptureStatusNone;
-  const SideStream side(plain && B * wl.L * std::max(c.dim, S.cfg.dim) <= SIDE_MAX);
+  const void* ctx[2] = {nullptr, uncond};
+  Contexts contexts(L, &S, *shape, B, ctx);
+  const SideStream side(plain && !contexts.shared && B * wl.L * std::max(c.dim, S.cfg.dim) <= SIDE_MAX);
   std::vector<double> r((size_t)M * N, 0.0), rb(bands ? (size_t)M * N * 6 : 0, 0.0);
   for (int j = 0; j < M; ++j) {
-    const void* ctx[2] = {cond[j], uncond};
+    ctx[0] = cond[j];
+    contexts.reset();
     {
       ProfScope prof(TRACK_PROF_OTHER, s);
       TRY(patchify(x_T[j], xtok, c.in_ch, shape->frames, shape->height, shape->width, c.patch_t, c.patch_h, c.patch_w, s));
     }
-    TRY(prepare(L, *shape, B, ctx, s));
-    TRY(prepare(S, *shape, B, ctx, s));
     for (int k = 0; k < N; ++k) {
       const double t = 1000.0 * sig[k];
-      if (side.stream()) TRACK_HIP(side.fork(s));
+      TRY(contexts.ready(0, s));
+      if (side.stream()) {
+        TRY(contexts.ready(1, s));
+        TRACK_HIP(side.fork(s));
+      }
       TRY(forward(L, *shape, B, xtok, t, velL, s));
+      if (!side.stream()) TRY(contexts.ready(1, s));
       TRY(forward(S, *shape, B, xtok, t, velS, side.stream() ? side.stream() : s));
       if (side.stream()) TRACK_HIP(side.join(s));
       // the band kernels read the velocities, which the update leaves intact
@@ -629,18 +661,11 @@ track_status track_sample(track_model lh, track_model sh, const uint8_t* use_sma
     ProfScope prof(TRACK_PROF_OTHER, s);
     TRY(patchify(x_T, xtok, c.in_ch, shape->frames, shape->height, shape->width, c.patch_t, c.patch_h, c.patch_w, s));
   }
-  // each model's text keys and values are formed at its first step (at every change
-  // of model where the two share workspace memory)
-  bool have_ctx[2] = {false, false};
-  const bool shared_ws =
-      any_small && L.ws < sh->m.ws + sh->m.ws_bytes && sh->m.ws < L.ws + L.ws_bytes;
+  Contexts contexts(L, any_small ? &sh->m : nullptr, *shape, B, ctx);
   for (int i = 0; i < N; ++i) {
     const Model& m = use_small[i] ? sh->m : L;
     float* vel = wsp<float>(m, ws_layout(m, *shape, B).vel);
-    if (shared_ws && i > 0 && (use_small[i] != 0) != (use_small[i - 1] != 0)) have_ctx[0] = have_ctx[1] = false;
-    bool& ready = have_ctx[use_small[i] != 0];
-    if (!ready) TRY(prepare(m, *shape, B, ctx, s));
-    ready = true;
+    TRY(contexts.ready(use_small[i] != 0, s));
     TRY(forward(m, *shape, B, xtok, 1000.0 * sig[i], vel, s));
     // UniPC's history is one sequence whichever model produced each entry
     TRY(sched.advance(i, B, w, vel, nullptr, xtok, nullptr, 0.0, nullptr, s));

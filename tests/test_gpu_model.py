@@ -532,21 +532,42 @@ def test_sample_with_one_workspace_for_both_models(dtype):
     np.testing.assert_array_equal(got, want)
 
 
+# a large model whose scratch has room for the tiny small model's whole workspace; side by side with it the two stay
+# below the size up to which a calibration step runs them on two streams
+SIDE_LARGE = dataclasses.replace(synth.TINY_LARGE, dim=512, heads=16, ffn_dim=2048)
+
+
+def _small_workspace_inside_large(pair, batch):
+    """Places the small model's workspace in the large one's scratch, before the trajectory state at its end."""
+    import ctypes
+    pair.L.ensure_workspace(pair.shape, batch)
+    need = pair.S.workspace_bytes(pair.shape, batch)
+    assert need + 256 < pair.L.workspace_bytes(pair.shape, batch) - (1 << 20)
+    pair.S.workspace = pair.L.workspace[256:256 + need]
+    track._check(track.lib().track_model_set_workspace(pair.S.handle, track._ptr(pair.S.workspace),
+                                                       ctypes.c_size_t(need)))
+
+
 @pytest.mark.parametrize("threads", [1, 3])
 def test_calibrate_models_side_by_side(threads):
-    """A small pair's two forward passes of a step run on two streams: the scores and samples are the same bits from
-    the default stream and from streams that are still writing the inputs, in several threads at once."""
+    """A small pair's two forward passes of a step run on two streams: the scores and samples are the same bits as in
+    order on one stream (the small model's workspace inside the large one's scratch, where they must take turns),
+    from the default stream and from streams that are still writing the inputs, in several threads at once."""
     import threading
     import torch
     say(f"calibrate side by side, threads={threads}")
     scfg = dataclasses.replace(synth.TINY_SAMPLER, steps=5)
-    pairs = [Pair(synth.TINY_LARGE, synth.TINY_SMALL, synth.TINY_LATENT) for _ in range(threads)]
+    pairs = [Pair(SIDE_LARGE, synth.TINY_SMALL, synth.TINY_LATENT) for _ in range(threads)]
 
     def run(p, x):
         r, q, x0 = track.calibrate(p.L, p.S, p.shape, x, p.dc[:2], p.du, scfg, return_x0=True)
         return r, [host(t) for t in x0]
 
-    want = run(pairs[0], pairs[0].dx[:2])
+    serial = Pair(SIDE_LARGE, synth.TINY_SMALL, synth.TINY_LATENT)
+    _small_workspace_inside_large(serial, 2)
+    want = run(serial, serial.dx[:2])
+    first = run(pairs[0], pairs[0].dx[:2])
+    np.testing.assert_array_equal(first[0], want[0])
     torch.cuda.synchronize()
     got = [None] * threads
 
