@@ -229,8 +229,12 @@ const char* track_last_error(void);
 /* Progress of the long-running calls.  When a callback is set (process
  * wide), track_calibrate and track_sample synchronise the stream after every
  * denoising step and then call fn(user, sample, step, steps) with the sample
- * index (-1 for track_sample) and the step just completed.  NULL (the
- * default) disables it and the per-step synchronisation. */
+ * index (-1 for track_sample) and the step just completed.  fn may run the
+ * small model (a preview, another prompt) and write the text embeddings, on
+ * work it has waited for or left on the same stream: the step after it reads
+ * the embeddings again.  The large model's workspace holds the trajectory and
+ * is not to be touched.  NULL (the default) disables it and the per-step
+ * synchronisation; the embeddings are then read once per sample and model. */
 typedef void (*track_progress_fn)(void* user, int32_t sample, int32_t step, int32_t steps);
 track_status track_set_progress(track_progress_fn fn, void* user);
 

@@ -37,8 +37,9 @@ static std::mutex g_progress_mu;
 static track_progress_fn g_progress_fn = nullptr;
 static void* g_progress_user = nullptr;
 
-// After a completed step: synchronise and report, if a callback is set.
-static track_status report_progress(hipStream_t s, int sample, int step, int steps) {
+// After a completed step: synchronise and report, if a callback is set (*called then).
+static track_status report_progress(hipStream_t s, int sample, int step, int steps, bool* called) {
+  *called = false;
   track_progress_fn fn;
   void* user;
   {
@@ -49,6 +50,7 @@ static track_status report_progress(hipStream_t s, int sample, int step, int ste
   if (!fn) return TRACK_OK;
   TRACK_HIP(hipStreamSynchronize(s));
   fn(user, sample, step, steps);
+  *called = true;
   return TRACK_OK;
 }
 
@@ -197,12 +199,11 @@ struct Contexts {
   const track_latent_shape& shape;
   int B;
   const void* const* ctx;
-  bool shared, have[2] = {false, false};
+  bool shared = false, have[2] = {false, false};
 
   Contexts(const Model& L, const Model* S, const track_latent_shape& s, int batch, const void* const* c)
       : m{&L, S}, shape(s), B(batch), ctx(c) {
-    // (what the layouts need: an attached size may be the rest of a larger allocation)
-    shared = S && L.ws < S->ws + ws_layout(*S, s, batch).total && S->ws < L.ws + ws_layout(L, s, batch).total;
+    reset();
   }
   // Before a forward pass of model i (0 large, 1 small).
   track_status ready(int i, hipStream_t st) {
@@ -212,7 +213,14 @@ struct Contexts {
     if (shared) have[1 - i] = false;
     return e;
   }
-  void reset() { have[0] = have[1] = false; }  // before a new set of contexts
+  // Before a new set of contexts, and after a progress callback: it may have run a model
+  // on another context, attached another workspace or written the embeddings.
+  void reset() {
+    have[0] = have[1] = false;
+    // (what the layouts need: an attached size may be the rest of a larger allocation)
+    const Model &L = *m[0], *S = m[1];
+    shared = S && L.ws < S->ws + ws_layout(*S, shape, B).total && S->ws < L.ws + ws_layout(L, shape, B).total;
+  }
 };
 
 static track_status check_sampler(const track_sampler_config* sc) {
@@ -433,21 +441,24 @@ static track_status calibrate_impl(track_model lh, track_model sh, const track_l
     }
     for (int k = 0; k < N; ++k) {
       const double t = 1000.0 * sig[k];
+      const bool two = side.stream() && !contexts.shared;
       TRY(contexts.ready(0, s));
-      if (side.stream()) {
+      if (two) {
         TRY(contexts.ready(1, s));
         TRACK_HIP(side.fork(s));
       }
       TRY(forward(L, *shape, B, xtok, t, velL, s));
-      if (!side.stream()) TRY(contexts.ready(1, s));
-      TRY(forward(S, *shape, B, xtok, t, velS, side.stream() ? side.stream() : s));
-      if (side.stream()) TRACK_HIP(side.join(s));
+      if (!two) TRY(contexts.ready(1, s));
+      TRY(forward(S, *shape, B, xtok, t, velS, two ? side.stream() : s));
+      if (two) TRACK_HIP(side.join(s));
       // the band kernels read the velocities, which the update leaves intact
       TRY(sched.advance(k, B, w, velL, velS, xtok, partial, scfg->eps, rdev + k, s));
       if (bands)
         TRY(band_scores(c.in_ch, shape->frames, shape->height, shape->width, c.patch_t, c.patch_h, c.patch_w, B, w,
                         velL, velS, partial, nstep, scfg->eps, wsp<uint8_t>(L, wl.band), nullptr, rbdev + 6 * k, s));
-      TRY(report_progress(s, j, k, N));
+      bool called;
+      TRY(report_progress(s, j, k, N, &called));
+      if (called) contexts.reset();
     }
     if (x0_out && x0_out[j]) {
       ProfScope prof(TRACK_PROF_OTHER, s);
@@ -669,7 +680,9 @@ track_status track_sample(track_model lh, track_model sh, const uint8_t* use_sma
     TRY(forward(m, *shape, B, xtok, 1000.0 * sig[i], vel, s));
     // UniPC's history is one sequence whichever model produced each entry
     TRY(sched.advance(i, B, w, vel, nullptr, xtok, nullptr, 0.0, nullptr, s));
-    TRY(report_progress(s, -1, i, N));
+    bool called;
+    TRY(report_progress(s, -1, i, N, &called));
+    if (called) contexts.reset();
   }
   {
     ProfScope prof(TRACK_PROF_OTHER, s);

@@ -590,3 +590,51 @@ def test_calibrate_models_side_by_side(threads):
         np.testing.assert_array_equal(r, want[0])
         for a, b in zip(x0, want[1]):
             np.testing.assert_array_equal(a, b)
+
+
+@pytest.mark.parametrize("dtype", [synth.F32, synth.BF16])
+def test_progress_callback_previews_and_prompts(dtype):
+    """A progress callback that runs the small model on another prompt leaves sampling and calibration the same bits;
+    one that writes the embeddings changes the steps after it, as a chain of guided predictions does."""
+    say(f"progress callback, dtype={dtype}")
+    bf = dtype == synth.BF16
+    pair = Pair(BF_LARGE, BF_SMALL, BF_LATENT) if bf else Pair(synth.TINY_LARGE, synth.TINY_SMALL, synth.TINY_LATENT)
+    scfg = dataclasses.replace(synth.TINY_SAMPLER, steps=4)
+    mask = np.array([1, 0, 1, 1], bool)
+
+    def both():
+        x = host(track.sample(pair.L, pair.S, mask, pair.shape, scfg, pair.dx[0], pair.dc[0], pair.du))
+        r, _ = track.calibrate(pair.L, pair.S, pair.shape, pair.dx[:1], pair.dc[:1], pair.du, scfg)
+        return x, r
+
+    want = both()
+    track.set_progress(lambda j, k, n: track.dit_forward(pair.S, pair.shape, pair.dx[1], 500.0, pair.dc[2], pair.dc[3],
+                                                         3.0))
+    try:
+        got = both()
+    finally:
+        track.set_progress(None)
+    np.testing.assert_array_equal(got[0], want[0])
+    np.testing.assert_array_equal(got[1], want[1])
+
+    cond = pair.dc[0].clone()
+
+    def prompt(j, k, n):
+        if k == 1:
+            cond.copy_(pair.dc[1])
+
+    track.set_progress(prompt)
+    try:
+        got = host(track.sample(pair.L, pair.S, mask, pair.shape, scfg, pair.dx[0], cond, pair.du))
+    finally:
+        track.set_progress(None)
+    sig = sampler.sigmas(scfg.steps, scfg.shift)
+    x = pair.dx[0].clone()
+    for i in range(scfg.steps):
+        p = track.dit_forward(pair.S if mask[i] else pair.L, pair.shape, x, 1000.0 * sig[i],
+                              pair.dc[0 if i < 2 else 1], pair.du, scfg.guidance)
+        x += float(sig[i + 1] - sig[i]) * p
+    # the chain rounds each update once more; a bfloat16 model turns last-bit inputs into its own rounding
+    err = rel_l2(got, host(x))
+    assert err < (2e-2 if bf else 1e-5), err
+    assert rel_l2(got, want[0]) > 4 * err

@@ -121,3 +121,30 @@ assert streams(lg) == {"77"}
 assert sample(l, s, [1, 0, 0]) == 0, err()
 assert passes(log()) == "PfPff"
 ''')
+
+
+def test_progress_callback_may_use_the_models(fake):
+    """A progress callback can run the small model on another prompt, or write the embeddings: the contexts are formed
+    anew after it, in sampling and calibration."""
+    run(fake, '''
+l, _ = model(LARGE, BASE + (5 << 32))
+s, _ = model(SMALL, BASE + (6 << 32))
+seen = []
+def preview(user, j, k, n):
+    seen.append((j, k))
+    st = L.track_dit_forward(s, ctypes.byref(track.shape_c(shape)), ctypes.c_void_p(BASE), 500.0,
+                             ctypes.c_void_p(BASE + (7 << 32)), None, 1.0, ctypes.c_void_p(BASE + (8 << 32)),
+                             ctypes.c_void_p(0x77))
+    assert st == 0, err()
+track.set_progress(lambda j, k, n: preview(None, j, k, n))
+assert sample(l, s, [1, 1, 0]) == 0, err()
+lg = log()
+assert passes(lg) == 3 * "PfPf", passes(lg)   # a step, the preview
+assert calibrate(l, s) == 0, err()
+lg = log()
+assert passes(lg) == 3 * "PPffPf", passes(lg)
+assert seen == [(-1, 0), (-1, 1), (-1, 2), (0, 0), (0, 1), (0, 2)]
+track.set_progress(None)
+assert sample(l, s, [1, 1, 0]) == 0, err()
+assert passes(log()) == "PffPf"
+''')
