@@ -329,10 +329,15 @@ void destroy_side(const Side& x) {
 
 class SideStream {
  public:
-  // (stays without a stream, and unused, if `want` is false or one cannot be made)
+  // (stays without a stream, and unused, if `want` is false or one cannot be made; a
+  // refused call's status must then not stay behind for the next launch check to find)
   explicit SideStream(bool want) {
     int dev = -1;
-    if (!want || hipGetDevice(&dev) != hipSuccess) return;
+    if (!want) return;
+    if (hipGetDevice(&dev) != hipSuccess) {
+      (void)hipGetLastError();
+      return;
+    }
     {
       std::lock_guard<std::mutex> lock(g_side_mu);
       for (size_t i = 0; i < g_side_free.size(); ++i)
@@ -348,6 +353,7 @@ class SideStream {
         hipEventCreateWithFlags(&y.fork, hipEventDisableTiming) != hipSuccess ||
         hipEventCreateWithFlags(&y.join, hipEventDisableTiming) != hipSuccess) {
       destroy_side(y);
+      (void)hipGetLastError();
       return;
     }
     x_ = y;
@@ -427,7 +433,9 @@ static track_status calibrate_impl(track_model lh, track_model sh, const track_l
   const float w = (float)scfg->guidance;
   // (a capturing stream fails below at the first copy back; the side stream stays out of it)
   hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
-  const bool plain = hipStreamIsCapturing(s, &cap) == hipSuccess && cap == hipStreamCaptureStatusNone;
+  const bool asked = hipStreamIsCapturing(s, &cap) == hipSuccess;
+  if (!asked) (void)hipGetLastError();
+  const bool plain = asked && cap == hipStreamCaptureStatusNone;
   const void* ctx[2] = {nullptr, uncond};
   Contexts contexts(L, &S, *shape, B, ctx);
   const SideStream side(plain && !contexts.shared && B * wl.L * std::max(c.dim, S.cfg.dim) <= SIDE_MAX);

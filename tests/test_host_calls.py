@@ -123,6 +123,21 @@ assert passes(log()) == "PfPff"
 ''')
 
 
+def test_calibrate_without_a_second_stream(fake):
+    """Where the runtime refuses the second stream, its events or the query before them, the call runs on one."""
+    run(fake, '''
+l, _ = model(LARGE, BASE + (5 << 32))
+s, _ = model(SMALL, BASE + (6 << 32))
+for name in (b"hipStreamCreateWithFlags", b"hipEventCreateWithFlags", b"hipStreamIsCapturing"):
+    F.fake_fail(name, 1)
+    assert calibrate(l, s) == 0, (name, err())
+    lg = log()
+    assert passes(lg) == "PfPfffff", (name, passes(lg))
+    assert streams(lg) == {"77"}, name
+assert calibrate(l, s) == 0 and len(streams(log())) == 2
+''')
+
+
 def test_progress_callback_may_use_the_models(fake):
     """A progress callback can run the small model on another prompt, or write the embeddings: the contexts are formed
     anew after it, in sampling and calibration."""
