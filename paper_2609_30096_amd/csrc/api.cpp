@@ -319,7 +319,8 @@ struct Side {
   hipEvent_t fork = nullptr, join = nullptr;
 };
 std::mutex g_side_mu;
-std::vector<Side> g_side_free;
+Side g_side_free[8];
+int g_side_count = 0;
 
 void destroy_side(const Side& x) {
   if (x.fork) (void)hipEventDestroy(x.fork);
@@ -340,10 +341,10 @@ class SideStream {
     }
     {
       std::lock_guard<std::mutex> lock(g_side_mu);
-      for (size_t i = 0; i < g_side_free.size(); ++i)
+      for (int i = 0; i < g_side_count; ++i)
         if (g_side_free[i].dev == dev) {
           x_ = g_side_free[i];
-          g_side_free.erase(g_side_free.begin() + i);
+          g_side_free[i] = g_side_free[--g_side_count];
           return;
         }
     }
@@ -363,8 +364,8 @@ class SideStream {
     (void)hipStreamSynchronize(x_.st);  // (work is left only where a call failed between fork and join)
     {
       std::lock_guard<std::mutex> lock(g_side_mu);
-      if (g_side_free.size() < 8) {
-        g_side_free.push_back(x_);
+      if (g_side_count < 8) {
+        g_side_free[g_side_count++] = x_;
         return;
       }
     }
@@ -525,35 +526,40 @@ size_t track_band_workspace_bytes(const track_latent_shape* shape, int32_t patch
 
 namespace {
 // Six doubles of pinned host memory that a kernel writes and the caller reads after
-// synchronising.  Freed slots are kept for the next call, at most 16 of them.
+// synchronising; none (p null) where the runtime refuses it, for instance while another
+// thread captures a graph.  Freed slots are kept for the next call, at most 16 of them.
 std::mutex g_pinned_mu;
-std::vector<double*> g_pinned_free;
+double* g_pinned_free[16];
+int g_pinned_count = 0;
 
 struct PinnedSlot {
   double* p = nullptr;
   PinnedSlot() {
     {
       std::lock_guard<std::mutex> lock(g_pinned_mu);
-      if (!g_pinned_free.empty()) {
-        p = g_pinned_free.back();
-        g_pinned_free.pop_back();
+      if (g_pinned_count > 0) {
+        p = g_pinned_free[--g_pinned_count];
         return;
       }
     }
     void* q = nullptr;
     if (hipHostMalloc(&q, 6 * sizeof(double), hipHostMallocPortable) == hipSuccess) p = (double*)q;
+    else (void)hipGetLastError();
   }
   ~PinnedSlot() {
     if (!p) return;
     {
       std::lock_guard<std::mutex> lock(g_pinned_mu);
-      if (g_pinned_free.size() < 16) {
-        g_pinned_free.push_back(p);
+      if (g_pinned_count < 16) {
+        g_pinned_free[g_pinned_count++] = p;
         return;
       }
     }
     (void)hipHostFree(p);
   }
+  // The call failed with the kernel perhaps still to run (or recorded into a graph): its
+  // 48 bytes must stay, and no other call may have them.
+  void abandon() { p = nullptr; }
   PinnedSlot(const PinnedSlot&) = delete;
   PinnedSlot& operator=(const PinnedSlot&) = delete;
 };
@@ -575,11 +581,20 @@ track_status track_op_band_energy(const track_latent_shape* shape, int32_t patch
   // the last kernel writes the energies to pinned host memory: a copy back would
   // be one more operation to wait for (60.5 -> 51.3 us a call on the video latent, with the tables below)
   PinnedSlot slot;
-  if (!slot.p) return fail(TRACK_E_DEVICE, "op_band_energy: no pinned host memory");
-  TRY(band_scores(shape->channels, shape->frames, shape->height, shape->width, patch_t, patch_h, patch_w, batch,
-                  guidance, vel_large, vel_small, nullptr, 0, 1.0, workspace, slot.p, nullptr, s));
-  TRACK_HIP(hipStreamSynchronize(s));
-  std::copy(slot.p, slot.p + 6, energy_out);
+  const track_status st =
+      band_scores(shape->channels, shape->frames, shape->height, shape->width, patch_t, patch_h, patch_w, batch,
+                  guidance, vel_large, vel_small, nullptr, 0, 1.0, workspace, slot.p, nullptr, s);
+  hipError_t e = hipSuccess;
+  if (st == TRACK_OK && !slot.p) {
+    const size_t off = band_energy_offset(shape->channels, shape->frames, shape->height, shape->width, patch_t, patch_h,
+                                          patch_w);
+    e = hipMemcpyAsync(energy_out, (const uint8_t*)workspace + off, 6 * sizeof(double), hipMemcpyDeviceToHost, s);
+  }
+  if (st == TRACK_OK && e == hipSuccess) e = hipStreamSynchronize(s);
+  if (st != TRACK_OK || e != hipSuccess) slot.abandon();
+  TRY(st);
+  TRACK_HIP(e);
+  if (slot.p) std::copy(slot.p, slot.p + 6, energy_out);
   return TRACK_OK;
 }
 

@@ -459,6 +459,10 @@ size_t band_workspace_bytes(int C, int F, int H, int W, int pt, int ph, int pw) 
   return band_layout(make_shape(C, F, H, W, pt, ph, pw)).total;
 }
 
+size_t band_energy_offset(int C, int F, int H, int W, int pt, int ph, int pw) {
+  return band_layout(make_shape(C, F, H, W, pt, ph, pw)).energy;
+}
+
 track_status band_scores(int C, int F, int H, int W, int pt, int ph, int pw, int B, float w, const float* vel_L,
                          const float* vel_S, const double* step_partial, int64_t n_step_partials, double eps, void* ws,
                          double* energy_dev, double* score_dev, hipStream_t st) {

@@ -109,6 +109,9 @@ track_status guide_unpatchify(const float* vel, int B, float w, float* out, int 
 // two token-layout velocity buffers (C x F x H x W latent, patch pt x ph x pw).
 track_status band_check(int C, int F, int H, int W, int pt, int ph, int pw);
 size_t band_workspace_bytes(int C, int F, int H, int W, int pt, int ph, int pw);
+// Byte offset in the band workspace of the slot that receives the energies when
+// energy_dev is NULL.
+size_t band_energy_offset(int C, int F, int H, int W, int pt, int ph, int pw);
 // energy_dev (or, if NULL, a slot in ws) receives 6 energies: spatial low,
 // mid, high, temporal low, mid, high.  With step_partial (the calibration step
 // kernel's (sum d^2, sum p_L^2) pairs) score_dev receives the 6 band scores.

@@ -163,3 +163,29 @@ track.set_progress(None)
 assert sample(l, s, [1, 1, 0]) == 0, err()
 assert passes(log()) == "PffPf"
 ''')
+
+
+def test_band_energy_without_pinned_memory(fake):
+    """Refused pinned memory falls back to a copy from the workspace; a slot that a kernel may still write, because the
+    call failed before it was waited for, is not handed to the next call."""
+    run(fake, '''
+w = L.track_band_workspace_bytes(ctypes.byref(track.shape_c(shape)), 1, 2, 2)
+out = (ctypes.c_double * 6)()
+def bands():
+    return L.track_op_band_energy(ctypes.byref(track.shape_c(shape)), 1, 2, 2, 2, 5.0, ctypes.c_void_p(BASE),
+                                  ctypes.c_void_p(BASE + (1 << 32)), ctypes.c_void_p(BASE + (2 << 32)), w, out,
+                                  ctypes.c_void_p(0x77))
+def ops():
+    return [op for op, n, st in log() if op in ("copy", "hostmalloc")]
+F.fake_fail(b"hipHostMalloc", 1)
+assert bands() == 0, err()
+assert ops() == ["hostmalloc", "copy"]
+assert bands() == 0 and ops() == ["hostmalloc"]
+assert bands() == 0 and ops() == []            # the slot is kept
+for name in (b"hipStreamSynchronize", b"hipLaunchKernel"):
+    F.fake_fail(name, 1)
+    assert bands() == track.E_DEVICE
+    ops()
+    F.hipGetLastError()
+    assert bands() == 0 and ops() == ["hostmalloc"]
+''')
