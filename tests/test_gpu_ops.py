@@ -149,21 +149,37 @@ def test_attention_bf16_tight_vt_rows(Lk, ldv):
     assert rel_l2(got, ref) < 1e-2, rel_l2(got, ref)
 
 
+ATTN_FORMS = ["blocks", "items", "2", "4"]
+
+
+def _attn_form(form, monkeypatch):
+    """Keeps attention to one kernel: one key share per query block (per-block kernel, or the item loop where the
+    keys allow it) or 2 or 4."""
+    if form in ("blocks", "items"):
+        monkeypatch.setenv("TRACK_ATTN_ITEMS", "0" if form == "blocks" else "1")
+    else:
+        monkeypatch.setenv("TRACK_ATTN_SPLIT", form)
+
+
+@pytest.mark.parametrize("form", ATTN_FORMS)
 @pytest.mark.parametrize("q_log2", [False, True])
-def test_attention_bf16_large_logits(q_log2):
-    say(f"attention bf16 large logits q_log2={q_log2}")
+def test_attention_bf16_large_logits(q_log2, form, monkeypatch):
+    say(f"attention bf16 large logits q_log2={q_log2} form={form}")
+    _attn_form(form, monkeypatch)
     got, ref = _attn_case(BF16, 1, 2, 128, 200, 333, 6100, scale=3.0, q_log2=q_log2)  # logits ~ N(0, 81)
     assert rel_l2(got, ref) < 2e-2, rel_l2(got, ref)
     assert np.isfinite(got).all()
 
 
+@pytest.mark.parametrize("form", ATTN_FORMS)
 @pytest.mark.parametrize("q_log2", [False, True])
 @pytest.mark.parametrize("growth", [4.0, 60.0])
-def test_attention_bf16_rising_logits(growth, q_log2):
+def test_attention_bf16_rising_logits(growth, q_log2, form, monkeypatch):
     """Keys whose norms grow along the sequence.  With the larger growth the logits climb past several
     multiples of the 64 (log2 units) of headroom, so the reference max moves again and again, tile after
     tile, on both probability paths."""
-    say(f"attention bf16 rising logits growth={growth} q_log2={q_log2}")
+    say(f"attention bf16 rising logits growth={growth} q_log2={q_log2} form={form}")
+    _attn_form(form, monkeypatch)
     import torch
     B, H, dh, Lq, Lk = 1, 2, 128, 150, 1100
     q = normal((6150, 1), (B * Lq, H * dh), 1.0, True)
@@ -183,12 +199,14 @@ def test_attention_bf16_rising_logits(growth, q_log2):
     assert np.isfinite(got).all()
 
 
+@pytest.mark.parametrize("form", ["blocks", "2", "4"])
 @pytest.mark.parametrize("q_log2", [False, True])
 @pytest.mark.parametrize("Lk", [40, 300])
-def test_attention_bf16_offset_logits(Lk, q_log2):
+def test_attention_bf16_offset_logits(Lk, q_log2, form, monkeypatch):
     """Every logit near -100 (head 0) or +100 (head 1): outside the window in which the reference max
     stays 0, on both sides."""
-    say(f"attention bf16 offset logits Lk={Lk} q_log2={q_log2}")
+    say(f"attention bf16 offset logits Lk={Lk} q_log2={q_log2} form={form}")
+    _attn_form(form, monkeypatch)
     import torch
     B, H, dh, Lq = 1, 2, 128, 70
     a = normal((6160, 0), (1, dh), 1.0, False)
@@ -256,6 +274,28 @@ def test_attention_bf16_split_shares(B, H, Lq, Lk, q_log2, monkeypatch):
         monkeypatch.setenv("TRACK_ATTN_SPLIT", ks)
         got, ref = _attn_case(BF16, B, H, 128, Lq, Lk, 6400 + Lq + Lk, q_log2=q_log2)
         assert rel_l2(got, ref) < 1e-2, (ks, rel_l2(got, ref))
+
+
+@pytest.mark.parametrize("form", ATTN_FORMS)
+@pytest.mark.parametrize("Lq,Lk", [(300, 128), (33, 100)])
+def test_attention_bf16_rows_8_byte_aligned(Lq, Lk, form, monkeypatch):
+    """Output rows 8 bytes off a 16-byte boundary (ldo % 8 == 4, the base too): the bits of aligned rows, and nothing
+    written between them."""
+    import torch
+    say(f"attention bf16 8-byte rows Lq={Lq} Lk={Lk} form={form}")
+    _attn_form(form, monkeypatch)
+    B, H, dh = 2, 2, 128
+    w, ldv = H * dh, (Lk + 63) // 64 * 64
+    q, k, v = (dev(normal((6700 + Lq, i), (B * n, w), 1.0, True), BF16) for i, n in ((1, Lq), (2, Lk), (3, Lk)))
+    vt = dev(vt_layout(host(v), B, Lk, H, dh, ldv), BF16)
+    want = torch.empty(B * Lq, w, dtype=torch.bfloat16, device="cuda")
+    track.op_attention(track.DTYPE_BF16, B, H, dh, Lq, Lk, q, w, k, w, vt, ldv, want, w)
+    ldo = w + 12
+    buf = torch.full((4 + B * Lq * ldo,), 7.0, dtype=torch.bfloat16, device="cuda")
+    track.op_attention(track.DTYPE_BF16, B, H, dh, Lq, Lk, q, w, k, w, vt, ldv, buf[4:], ldo)
+    got = buf[4:].view(B * Lq, ldo)
+    assert torch.equal(got[:, :w].view(torch.int16), want.view(torch.int16))
+    assert bool((got[:, w:] == 7.0).all()) and bool((buf[:4] == 7.0).all())
 
 
 def test_attention_errors_and_empty():
@@ -586,6 +626,28 @@ def test_linear_tiles_agree(M, N, K, monkeypatch):
         for i in range(11):
             monkeypatch.setenv("TRACK_GEMM_CFG", str(10 + i))
             assert np.array_equal(_run_linear(BF16, epi, A, W, b, gate, resid), auto), (epi, i)
+
+
+@pytest.mark.parametrize("epi", EPIS)
+def test_linear_large_leading_dimension(epi):
+    """Rows of A 2^22 elements apart, beyond what a buffer resource addresses: the register-staged kernel, at ragged
+    M-tiles and one and several slabs and feature tiles."""
+    import torch
+    say(f"linear large leading dimension epi={epi}")
+    lda = 1 << 22
+    buf = torch.empty(133 * lda, dtype=torch.bfloat16, device="cuda")
+    for M, N, K in ((133, 192, 320), (5, 64, 64)):
+        A = normal((8630, M, K), (M, K), 1.0, True)
+        W = normal((8631, N, K), (N, K), 0.05, True)
+        b = normal((8632, N), (N,), 0.1, True)
+        gate = normal((8633, N), (N,), 1.0)
+        resid = normal((8634, M, N), (M, N), 1.0)
+        buf.view(133, lda)[:M, :K] = dev(A, BF16)
+        f32 = epi in (track.EPI_GATE_RESID, track.EPI_RESID, track.EPI_BIAS_F32)
+        out = dev(resid) if f32 else torch.empty(M, N, dtype=torch.bfloat16, device="cuda")
+        track.op_linear(track.DTYPE_BF16, epi, buf, dev(W, BF16), dev(b, BF16), out, gate=dev(gate), M=M, lda=lda)
+        ref = _linear_ref(epi, A, W, b, gate, resid)
+        assert rel_l2(host(out), ref) < (1e-5 if f32 else 4e-3), (M, rel_l2(host(out), ref))
 
 
 @pytest.mark.parametrize("B,L,N,K", [(1, 128, 256, 64), (3, 136, 512, 128), (2, 1000, 256, 704)])
