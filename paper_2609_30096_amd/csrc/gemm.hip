@@ -291,7 +291,8 @@ constexpr int PK_DPM = 5;   // MFMAs per copy
 // 16-byte bf16 stores without a lane exchange.
 //
 // Epilogue of a tile with bfloat16 output (bias, bias + GELU): the lane holds
-// tokens m_base + 16 y and features n_base + 32 p + 0..7.  Every bias value is
+// tokens m_base + 16 y and features n_base + 32 p + 0..7, one 16-byte store to a row
+// that need only be 8-byte aligned (ldo % 4 == 0).  Every bias value is
 // loaded before the first store (a load issued after a store would wait for
 // it).  Token blocks outermost: the 64-byte pieces of a token row's 128-byte
 // line are stored back to back, so the L2 holds whole lines when it writes
@@ -327,7 +328,7 @@ __device__ __forceinline__ void epilogue_bf16(const EpiArgs& e, const f32x4 (&ac
         pk[2 * h] = pack_bf2(v[0], v[1]);
         pk[2 * h + 1] = pack_bf2(v[2], v[3]);
       }
-      if (m < M) *(u32x4*)(orow + 32 * p) = pk;
+      if (m < M) *(u32x4_a8*)(orow + 32 * p) = pk;
     }
   }
 }

@@ -628,6 +628,24 @@ def test_linear_tiles_agree(M, N, K, monkeypatch):
             assert np.array_equal(_run_linear(BF16, epi, A, W, b, gate, resid), auto), (epi, i)
 
 
+@pytest.mark.parametrize("epi", [track.EPI_BIAS, track.EPI_BIAS_GELU])
+@pytest.mark.parametrize("M,N,K", [(33, 256, 64), (300, 768, 192)])
+def test_linear_rows_8_byte_aligned(epi, M, N, K, monkeypatch):
+    """bfloat16 output rows that are only 8-byte aligned (ldo % 8 == 4), on every tile kernel and the persistent one:
+    the bits of aligned rows, and nothing written between them."""
+    import torch
+    say(f"linear 8-byte rows epi={epi} M={M} N={N} K={K}")
+    A, W, b = (dev(normal((8620, i), s, c, True), BF16) for i, s, c in ((1, (M, K), 1.0), (2, (N, K), 0.05), (3, (N,), 0.1)))
+    for cfg in [0, 4] + list(range(10, 21)):
+        monkeypatch.setenv("TRACK_GEMM_CFG", str(cfg))
+        want = torch.empty(M, N, dtype=torch.bfloat16, device="cuda")
+        track.op_linear(track.DTYPE_BF16, epi, A, W, b, want)
+        got = torch.full((M, N + 4), 7.0, dtype=torch.bfloat16, device="cuda")
+        track.op_linear(track.DTYPE_BF16, epi, A, W, b, got)
+        assert torch.equal(got[:, :N].view(torch.int16), want.view(torch.int16)), cfg
+        assert bool((got[:, N:] == 7.0).all()), cfg
+
+
 @pytest.mark.parametrize("epi", EPIS)
 def test_linear_large_leading_dimension(epi):
     """Rows of A 2^22 elements apart, beyond what a buffer resource addresses: the register-staged kernel, at ragged
