@@ -18,9 +18,10 @@
 //   band_finish   partials summed in a fixed order -> 6 energies (and scores)
 // The DFTs are products with the axis' cosine and sine matrices on
 // v_mfma_f32_16x16x4_f32 (float32 products and sums), whose entries are looked up
-// in LDS tables exp(-2 pi i m / n) (fp64 -> fp32) at (k x) mod n.  The input is
-// real, so k_w (temporal: k_f) runs to n / 2 only, the rest being the conjugates
-// at -k, and row k_h and row H - k_h come from the same four products.
+// in LDS tables exp(-2 pi i m / n) (fp64 -> fp32) at (k x) mod n; each frequency's
+// energy is freed of its entries' rounding (freq_sums).  The input is real, so k_w
+// (temporal: k_f) runs to n / 2 only, the rest being the conjugates at -k, and row
+// k_h and row H - k_h come from the same four products.
 #include <math.h>
 
 #include "common.h"
@@ -103,6 +104,9 @@ __device__ __forceinline__ void block_sum3(double a0, double a1, double a2, doub
   }
 }
 
+// (a + b) mod n for a, b < n
+__device__ __forceinline__ uint32_t add_mod(uint32_t a, uint32_t b, uint32_t n) { return min(a + b, a + b - n); }
+
 __device__ __forceinline__ float2 twiddle(int m, int n) {
   double sn, cs;
   sincospi(2.0 * m / n, &sn, &cs);
@@ -113,20 +117,70 @@ __device__ __forceinline__ void fill_twiddles(float2* __restrict__ tw, int n) {
   for (int m = threadIdx.x; m < n; m += BAND_THREADS) tw[m] = twiddle(m, n);
 }
 
-// n over the energy of the float32 table of length n (one wave): the entries'
-// rounding scales every energy by its inverse on average, the largest error of the
-// transforms (9e-9 of the energies at 21 x 60 x 104, against 2e-9 with it taken out).
-__device__ __forceinline__ double table_correction(int n, int lane) {
-  double e = 0.0;
-  for (int m = lane; m < n; m += 64) {
-    const float2 t = twiddle(m, n);
-    e += (double)t.x * t.x + (double)t.y * t.y;
-  }
-  return n / wave_sum_d(e);
+// |t|^2 - 1
+__device__ __forceinline__ float deviation(float2 t) {
+  return (float)fma((double)t.x, (double)t.x, fma((double)t.y, (double)t.y, -1.0));
 }
 
-// (a + b) mod n for a, b < n
-__device__ __forceinline__ uint32_t add_mod(uint32_t a, uint32_t b, uint32_t n) { return min(a + b, a + b - n); }
+// A frequency's energy is divided by the sum of |t|^2 over the n table entries t that its
+// transform took, n + dsum, in place of n: the entries' float32 rounding scales the energy
+// by their mean |t|^2, which would be the largest error of the transforms (8e-9 to 3e-8 of
+// the energies over latents of 16 - 90 rows, 4e-10 to 8e-9 with it taken out, for 1 of the
+// pass' 52 us on the video latent).  One factor for a whole axis would do as well on
+// average, but put 1e-8 on the mean, whose entries are exact.  Frequency k takes the
+// multiples of g = gcd(k, n), each g times, so one sum per divisor of n serves all.
+__device__ __forceinline__ void freq_sums(float* __restrict__ dsum, float* __restrict__ dev, int n) {
+  __syncthreads();
+  for (int m = threadIdx.x; m < n; m += BAND_THREADS) dev[m] = deviation(twiddle(m, n));
+  __syncthreads();
+  const int lane = threadIdx.x & 63;
+  for (int d = 1 + (threadIdx.x >> 6); d <= n / 2; d += BAND_THREADS / 64) {
+    if (n % d) continue;
+    float e = 0.0f;
+    for (int m = lane * d; m < n; m += 64 * d) e += dev[m];
+    e = (float)d * wave_sum(e);
+    if (lane == 0) dsum[d] = e;
+  }
+  __syncthreads();
+  for (int k = threadIdx.x; k <= n / 2; k += BAND_THREADS) {
+    int g = n, r = k;
+    while (r) {
+      const int t = g % r;
+      g = r;
+      r = t;
+    }
+    if (g != k) dsum[k] = g == n ? 0.0f : dsum[g];
+  }
+}
+
+// The table of the F axis (F <= 64 entries) and the sums of its frequencies: every lane of
+// a 16-lane group takes one frequency and a quarter of its entries.
+__device__ __forceinline__ void fill_temporal(float2* __restrict__ tw, float* __restrict__ dev, float* __restrict__ dsum,
+                                              uint32_t n) {
+  if (threadIdx.x < n) {
+    const float2 t = twiddle(threadIdx.x, n);
+    tw[threadIdx.x] = t;
+    dev[threadIdx.x] = deviation(t);
+  }
+  __syncthreads();
+  const uint32_t k = threadIdx.x >> 6 << 4 | (threadIdx.x & 15), g = (threadIdx.x >> 4) & 3;
+  const uint32_t k1 = min(k, n - 1), k2 = add_mod(k1, k1, n), step = add_mod(k2, k2, n);
+  uint32_t m = (g & 2) ? k2 : 0;
+  if (g & 1) m = add_mod(m, k1, n);
+  float e = 0.0f;
+#pragma unroll 8
+  for (uint32_t x = g; x < n; x += 4) {
+    e += dev[m];
+    m = add_mod(m, step, n);
+  }
+  e += __shfl_xor(e, 16);
+  e += __shfl_xor(e, 32);
+  dsum[k] = e;  // (the same from all four groups)
+  __syncthreads();
+}
+
+// 1 / (n + dsum) for rn = 1 / n; dsum is some 1e-8 of n, so its square is out of reach.
+__device__ __forceinline__ double inv_sum(double rn, float dsum) { return fma(-(double)dsum * rn, rn, rn); }
 
 __device__ __forceinline__ f32x4 guided_diff4(const float* __restrict__ vL, const float* __restrict__ vS, int64_t n,
                                               int B, float w, int64_t o) {
@@ -159,14 +213,18 @@ template <int HB>
 __global__ __launch_bounds__(BAND_THREADS) void band_spatial_kernel(BandShape s, int B, float w,
                                                                     const float* __restrict__ vL,
                                                                     const float* __restrict__ vS, int64_t n,
-                                                                    const f32x4* __restrict__ diff, int kwg,
+                                                                    const f32x4* __restrict__ diff,
+                                                                    const float* __restrict__ dsum, int kwg,
                                                                     double* __restrict__ part) {
   __shared__ __attribute__((aligned(16))) float sd[16 * HB][BAND_XLD];
   __shared__ float2 twW[BAND_MAX_W], twH[BAND_MAX_H];
+  __shared__ float sumH[BAND_MAX_H / 2 + 1];
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   const int jq = lane & 15, g = lane >> 4;
   const int id = xcd_remap(blockIdx.x, gridDim.x);
   const int f = id / (s.C * kwg), c = id / kwg % s.C, kg = id % kwg;
+  // (the W / 2 + 1 sums of the rows' frequencies, then the H / 2 + 1 of the columns')
+  for (int k = threadIdx.x; k <= s.H / 2; k += BAND_THREADS) sumH[k] = dsum[s.W / 2 + 1 + k];
   fill_twiddles(twW, s.W);
   fill_twiddles(twH, s.H);
   const uint32_t W = s.W, H = s.H;
@@ -229,8 +287,9 @@ __global__ __launch_bounds__(BAND_THREADS) void band_spatial_kernel(BandShape s,
       }
     }
   }
+  const double norm = (kw == 0 || 2 * kw == s.W ? 1.0 : 2.0) * inv_sum(1.0 / s.W, dsum[min(kw, s.W / 2)]);
   double acc[3] = {0.0, 0.0, 0.0};
-  const double norm = (kw == 0 || 2 * kw == s.W ? 1.0 : 2.0) / ((double)s.H * s.W);
+  const double rH = 1.0 / s.H;
   for (int kh0 = 0; live && kh0 <= s.H / 2; kh0 += 16) {
     const uint32_t kh = kh0 + jq, steph = (16u * kh) % H;
     uint32_t m[4];
@@ -255,10 +314,18 @@ __global__ __launch_bounds__(BAND_THREADS) void band_spatial_kernel(BandShape s,
       const double re = (double)(p[r] - q[r]), im = (double)(u[r] + v[r]);
       const double re2 = (double)(p[r] + q[r]), im2 = (double)(v[r] - u[r]);  // row H - k
       const double e = re * re + im * im, e2 = k == 0 || 2 * k == s.H ? 0.0 : re2 * re2 + im2 * im2;
-      add_band(acc, spatial_band(k, kw, s.H, s.W), (e + e2) * norm);
+      add_band(acc, spatial_band(k, kw, s.H, s.W), (e + e2) * (norm * inv_sum(rH, sumH[k])));
     }
   }
   block_sum3(acc[0], acc[1], acc[2], part + 3 * (int64_t)blockIdx.x);
+}
+
+// The first block of the temporal pass forms the sums that the spatial pass divides by.
+__device__ __forceinline__ void spatial_sums(const BandShape& s, float* __restrict__ dsum) {
+  __shared__ float dev[BAND_MAX_W];
+  static_assert(BAND_MAX_H <= BAND_MAX_W, "one table's room");
+  freq_sums(dsum, dev, s.W);
+  freq_sums(dsum + s.W / 2 + 1, dev, s.H);
 }
 
 // Temporal block (patch_t 1: a frame's series are contiguous): 64 series a wave,
@@ -268,14 +335,19 @@ __global__ __launch_bounds__(BAND_THREADS) void band_temporal_rows_kernel(BandSh
                                                                           const float* __restrict__ vL,
                                                                           const float* __restrict__ vS, int64_t n,
                                                                           f32x4* __restrict__ diff,
+                                                                          float* __restrict__ dsum,
                                                                           double* __restrict__ part) {
+  if (blockIdx.x == 0) {
+    spatial_sums(s, dsum);
+    return;
+  }
   __shared__ float2 tw[BAND_MAX_F];
-  fill_twiddles(tw, s.F);
-  __syncthreads();
+  __shared__ float dev[BAND_MAX_F], sumF[BAND_MAX_F];
+  fill_temporal(tw, dev, sumF, s.F);
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   const int jq = lane & 15, g = lane >> 4;
   const int64_t total = (int64_t)s.Hp * s.Wp * s.P;  // series, a multiple of 4
-  const int64_t i0 = ((int64_t)xcd_remap(blockIdx.x, gridDim.x) * 4 + wave) * 64 + 4 * jq;
+  const int64_t i0 = ((int64_t)xcd_remap(blockIdx.x - 1, gridDim.x - 1) * 4 + wave) * 64 + 4 * jq;
   const bool in = i0 < total;
   const int64_t base = in ? i0 : 0;
   const uint32_t F = s.F;
@@ -283,6 +355,7 @@ __global__ __launch_bounds__(BAND_THREADS) void band_temporal_rows_kernel(BandSh
   const int64_t T = (int64_t)s.Hp * s.Wp, frame = s.C * T;
   const uint32_t b32 = (uint32_t)base, P = s.P;  // (a latent holds at most 2^31 values)
   f32x4* const dst = diff + (int64_t)(b32 % P / 4) * T + b32 / P;
+  const double rF = 1.0 / s.F;
   double acc[3] = {0.0, 0.0, 0.0};
   for (int kf0 = 0; kf0 <= s.F / 2; kf0 += 16) {
     const uint32_t kf = kf0 + jq, step4 = (4u * kf) % F;
@@ -317,10 +390,10 @@ __global__ __launch_bounds__(BAND_THREADS) void band_temporal_rows_kernel(BandSh
       double e = 0.0;
 #pragma unroll
       for (int i = 0; i < 4; ++i) e += (double)re[i][r] * re[i][r] + (double)im[i][r] * im[i][r];
-      add_band(acc, axis_band(k, s.F), e * ((k == 0 || 2 * k == s.F ? 1.0 : 2.0) / s.F));
+      add_band(acc, axis_band(k, s.F), e * ((k == 0 || 2 * k == s.F ? 1.0 : 2.0) * inv_sum(rF, sumF[k])));
     }
   }
-  block_sum3(acc[0], acc[1], acc[2], part + 3 * (int64_t)blockIdx.x);
+  block_sum3(acc[0], acc[1], acc[2], part + 3 * (int64_t)(blockIdx.x - 1));
 }
 
 // Temporal energies of the other layouts (patch_t > 1, or velocities that are not
@@ -329,11 +402,17 @@ __global__ __launch_bounds__(BAND_THREADS) void band_temporal_rows_kernel(BandSh
 __global__ __launch_bounds__(BAND_THREADS) void band_temporal_kernel(BandShape s, int B, float w,
                                                                     const float* __restrict__ vL,
                                                                     const float* __restrict__ vS, int64_t n,
+                                                                    float* __restrict__ dsum,
                                                                     double* __restrict__ part) {
+  if (blockIdx.x == 0) {
+    spatial_sums(s, dsum);
+    return;
+  }
   __shared__ float ser[BAND_MAX_F][BAND_THREADS];
   __shared__ float2 tw[BAND_MAX_F];
-  fill_twiddles(tw, s.F);
-  const int64_t i = (int64_t)blockIdx.x * BAND_THREADS + threadIdx.x;
+  __shared__ float dev[BAND_MAX_F], sumF[BAND_MAX_F];
+  fill_temporal(tw, dev, sumF, s.F);
+  const int64_t i = (int64_t)(blockIdx.x - 1) * BAND_THREADS + threadIdx.x;
   const int Q = s.C * s.ph * s.pw;
   const int64_t total = (int64_t)s.Hp * s.Wp * Q;
   const bool live = i < total;
@@ -350,7 +429,7 @@ __global__ __launch_bounds__(BAND_THREADS) void band_temporal_kernel(BandShape s
   __syncthreads();
   double acc[3] = {0.0, 0.0, 0.0};
   if (live) {
-    const double norm = 1.0 / s.F;
+    const double rF = 1.0 / s.F;
     for (int kf = 0; kf < s.F; ++kf) {
       float re = 0.0f, im = 0.0f;
       int m = 0;  // kf * f mod F
@@ -362,46 +441,39 @@ __global__ __launch_bounds__(BAND_THREADS) void band_temporal_kernel(BandShape s
         m += kf;
         if (m >= s.F) m -= s.F;
       }
-      const double e = ((double)re * re + (double)im * im) * norm;
+      const double e = ((double)re * re + (double)im * im) * inv_sum(rF, sumF[fold(kf, s.F)]);
       const int b = axis_band(kf, s.F);
       acc[0] += b == 0 ? e : 0.0;
       acc[1] += b == 1 ? e : 0.0;
       acc[2] += b == 2 ? e : 0.0;
     }
   }
-  block_sum3(acc[0], acc[1], acc[2], part + 3 * (int64_t)blockIdx.x);
+  block_sum3(acc[0], acc[1], acc[2], part + 3 * (int64_t)(blockIdx.x - 1));
 }
 
-// Sums the partials in a fixed order, one wave per quantity (the last three: the
-// tables' correction factors).  energy[0..2]
-// spatial, [3..5] temporal.
+// Sums the partials in a fixed order, one wave per quantity.  energy[0..2] spatial,
+// [3..5] temporal.
 // With step partials (pairs (sum d^2, sum p_L^2) of the calibration step
 // kernel) it also writes score[b] = sqrt(energy[b]) / max(||p_L||, eps).
-constexpr int BAND_FINISH_THREADS = 10 * 64;
+constexpr int BAND_FINISH_THREADS = 7 * 64;
 
 __global__ __launch_bounds__(BAND_FINISH_THREADS) void band_finish_kernel(int ns, const double* __restrict__ part_s, int nt,
                                                           const double* __restrict__ part_t, int nstep,
                                                           const double* __restrict__ step_part, double eps,
-                                                          int F, int H, int W, double* __restrict__ energy,
+                                                          double* __restrict__ energy,
                                                           double* __restrict__ score) {
-  __shared__ double tot[7], corr[3];
+  __shared__ double tot[7];
   const int q = threadIdx.x >> 6, lane = threadIdx.x & 63;
   const double* p = q < 3 ? part_s + q : (q < 6 ? part_t + (q - 3) : step_part + 1);
-  const int cnt = q < 3 ? ns : (q < 6 ? nt : (q == 6 && step_part ? nstep : 0));
+  const int cnt = q < 3 ? ns : (q < 6 ? nt : (step_part ? nstep : 0));
   const int stride = q < 6 ? 3 : 2;
   double a = 0.0;
 #pragma unroll 4
   for (int i = lane; i < cnt; i += 64) a += p[(int64_t)i * stride];
-  if (q < 7) {
-    a = wave_sum_d(a);
-    if (lane == 0) tot[q] = a;
-  } else {
-    const double c = table_correction(q == 7 ? W : (q == 8 ? H : F), lane);
-    if (lane == 0) corr[q - 7] = c;
-  }
+  a = wave_sum_d(a);
+  if (lane == 0) tot[q] = a;
   __syncthreads();
   if (threadIdx.x < 6) {
-    tot[threadIdx.x] *= threadIdx.x < 3 ? corr[0] * corr[1] : corr[2];
     energy[threadIdx.x] = tot[threadIdx.x];
     if (step_part && score) {
       const double dn = sqrt(tot[6]);
@@ -411,7 +483,7 @@ __global__ __launch_bounds__(BAND_FINISH_THREADS) void band_finish_kernel(int ns
 }
 
 struct BandLayout {
-  size_t diff, part_s, part_t, energy, total;
+  size_t diff, dsum, part_s, part_t, energy, total;
   int kwg, ns, nt;
 };
 
@@ -430,6 +502,7 @@ BandLayout band_layout(const BandShape& s) {
   b.ns = b.kwg * s.C * s.F;
   b.nt = (int)(((int64_t)s.Hp * s.Wp * s.C * s.ph * s.pw + BAND_THREADS - 1) / BAND_THREADS);
   b.diff = take(planar(s) ? (size_t)s.C * s.F * s.H * s.W * sizeof(float) : 0);
+  b.dsum = take((size_t)(s.W / 2 + s.H / 2 + 2) * sizeof(float));
   b.part_s = take((size_t)b.ns * 3 * 8);
   b.part_t = take((size_t)b.nt * 3 * 8);
   b.energy = take(6 * 8);
@@ -475,6 +548,7 @@ track_status band_scores(int C, int F, int H, int W, int pt, int ph, int pw, int
   const BandShape s = make_shape(C, F, H, W, pt, ph, pw);
   const BandLayout L = band_layout(s);
   uint8_t* base = (uint8_t*)ws;
+  float* dsum = (float*)(base + L.dsum);
   double* part_s = (double*)(base + L.part_s);
   double* part_t = (double*)(base + L.part_t);
   double* energy = energy_dev ? energy_dev : (double*)(base + L.energy);
@@ -483,12 +557,12 @@ track_status band_scores(int C, int F, int H, int W, int pt, int ph, int pw, int
   const bool aligned = (((uintptr_t)vel_L | (uintptr_t)vel_S) & 15) == 0 && n % 4 == 0 && s.P % 4 == 0;
   f32x4* const diff = aligned && planar(s) ? (f32x4*)(base + L.diff) : nullptr;
   if (aligned && pt == 1)
-    band_temporal_rows_kernel<<<L.nt, BAND_THREADS, 0, st>>>(s, B, w, vel_L, vel_S, n, diff, part_t);
+    band_temporal_rows_kernel<<<L.nt + 1, BAND_THREADS, 0, st>>>(s, B, w, vel_L, vel_S, n, diff, dsum, part_t);
   else
-    band_temporal_kernel<<<L.nt, BAND_THREADS, 0, st>>>(s, B, w, vel_L, vel_S, n, part_t);
+    band_temporal_kernel<<<L.nt + 1, BAND_THREADS, 0, st>>>(s, B, w, vel_L, vel_S, n, dsum, part_t);
   TRACK_LAUNCH_CHECK();
 #define TRACK_BAND(HB) \
-  band_spatial_kernel<HB><<<L.ns, BAND_THREADS, 0, st>>>(s, B, w, vel_L, vel_S, n, diff, L.kwg, part_s)
+  band_spatial_kernel<HB><<<L.ns, BAND_THREADS, 0, st>>>(s, B, w, vel_L, vel_S, n, diff, dsum, L.kwg, part_s)
   const int hb = (H + 15) / 16;
   if (hb <= 2) TRACK_BAND(2);
   else if (hb <= 4) TRACK_BAND(4);
@@ -497,7 +571,7 @@ track_status band_scores(int C, int F, int H, int W, int pt, int ph, int pw, int
   else TRACK_BAND(16);
 #undef TRACK_BAND
   TRACK_LAUNCH_CHECK();
-  band_finish_kernel<<<1, BAND_FINISH_THREADS, 0, st>>>(L.ns, part_s, L.nt, part_t, (int)n_step_partials, step_partial, eps, F, H, W,
+  band_finish_kernel<<<1, BAND_FINISH_THREADS, 0, st>>>(L.ns, part_s, L.nt, part_t, (int)n_step_partials, step_partial, eps,
                                                 energy, score_dev);
   TRACK_LAUNCH_CHECK();
   return TRACK_OK;

@@ -89,6 +89,25 @@ def test_band_energy_block_edges(C, F, H, W, patch, offset):
     assert np.all(np.abs(got - ref) <= 2e-6 * tot + 2 * np.sqrt(tot) * 2.0 ** -23 * size), (got, ref)
 
 
+@pytest.mark.parametrize("C,F,H,W,patch,offset", [(2, 21, 60, 104, (1, 2, 2), 0), (1, 5, 12, 20, (1, 2, 2), 0),
+                                                  (2, 5, 12, 20, (1, 2, 2), 1), (2, 6, 10, 6, (2, 1, 1), 0)])
+def test_band_energy_of_a_constant_is_exact(C, F, H, W, patch, offset):
+    """A constant difference of 3 on integer velocities: its transforms at frequency 0 are sums of integers below 2^24,
+    through table entries that are exactly 1, so both low bands hold 9 C F H W but for float64 roundings and the
+    squares of the other frequencies' rounding (below 1e-13 of it).  The rounding of the table's other entries (1e-8
+    and more of an energy) must not reach them."""
+    import torch
+    from paper_2609_30096_amd import track
+    say(f"band energy constant C={C} F={F} H={H} W={W} patch={patch} offset={offset}")
+    shape = synth.LatentShape(C, F, H, W, 16)
+    n = C * F * H * W
+    vL = np.rint(100 * normal((7200, F, H), (n + offset,))).astype(np.float32)
+    ws = torch.empty(track.band_workspace_bytes(shape, patch), dtype=torch.uint8, device="cuda")
+    got = track.op_band_energy(shape, 1, 1.0, dev(vL)[offset:], dev(vL + 3)[offset:], ws, patch)
+    want = np.array([9.0 * n, 0, 0] * 2)
+    assert np.all(np.abs(got - want) <= 1e-12 * 9.0 * n), got / (9.0 * n) - [1, 0, 0] * 2
+
+
 def test_band_energy_argument_checks():
     import torch
     from paper_2609_30096_amd import track
