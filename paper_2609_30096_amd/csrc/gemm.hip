@@ -1146,7 +1146,7 @@ static int f32_small_blocks(int64_t M, int64_t N, int64_t K, const void* A, int6
   return t16 > 4 * cus ? 2 : 1;
 }
 
-// ln: the rows of A are LayerNorm inputs (K-sharing kernel only, t > 0)
+// ln: the rows of A are LayerNorm inputs (t 1, an epilogue without a residual)
 static void launch_f32(int t, int epi, const float* A, int64_t lda, const float* W, int64_t M, int N, int K,
                        const EpiArgs& e, int nb, bool ln, const float* scale, const float* shift, hipStream_t s) {
   const int b = t ? 16 * t : 64;
@@ -1154,12 +1154,16 @@ static void launch_f32(int t, int epi, const float* A, int64_t lda, const float*
 #define TRACK_F32_S(E, T, LN) gemm_f32_small_kernel<E, T, LN><<<grid, block, 0, s>>>(A, lda, W, M, N, K, e, scale, shift)
 #define TRACK_F32(E)                                                \
   do {                                                              \
-    if (t == 1 && ln) TRACK_F32_S(E, 1, true);                      \
-    else if (t == 2 && ln) TRACK_F32_S(E, 2, true);                 \
-    else if (t == 1) TRACK_F32_S(E, 1, false);                      \
+    if (t == 1) TRACK_F32_S(E, 1, false);                           \
     else if (t == 2) TRACK_F32_S(E, 2, false);                      \
     else gemm_f32_kernel<E><<<grid, block, 0, s>>>(A, lda, W, M, N, K, e); \
   } while (0)
+  if (ln) {
+    if (epi == TRACK_EPI_BIAS) TRACK_F32_S(TRACK_EPI_BIAS, 1, true);
+    else if (epi == TRACK_EPI_BIAS_GELU) TRACK_F32_S(TRACK_EPI_BIAS_GELU, 1, true);
+    else TRACK_F32_S(TRACK_EPI_BIAS_F32, 1, true);
+    return;
+  }
   switch (epi) {
     case TRACK_EPI_BIAS: TRACK_F32(TRACK_EPI_BIAS); break;
     case TRACK_EPI_BIAS_GELU: TRACK_F32(TRACK_EPI_BIAS_GELU); break;
@@ -1242,20 +1246,22 @@ track_status linear_batch(int dtype, int nb, int64_t M, int64_t N, int64_t K, co
 track_status layernorm_linear(int dtype, int epi, int64_t M, int64_t N, int64_t K, const float* X, const float* scale,
                               const float* shift, void* Y, const void* W, const void* bias, const float* gate,
                               void* out, int64_t ldo, hipStream_t s) {
-  // (up to 32 blocks of 16 x 16 per CU: the rows' sums are formed again for every 32
-  // features, and the registers they take cost a large product its occupancy)
-  const bool few = ((M + 15) / 16) * ((N + 15) / 16) <= 32 * (int64_t)device_cus();
-  const int t = dtype == TRACK_DTYPE_F32 && few && K <= SF_LN_K && M > 0 && N > 0 && ldo >= N && N <= (1 << 30) && bias && out &&
-                        (epi != TRACK_EPI_GATE_RESID || gate) && (((uintptr_t)scale | (uintptr_t)shift) & 15) == 0
-                    ? f32_small_blocks(M, N, K, X, K, W, 1)
-                    : 0;
-  if (!t) {
+  // (only where one 16 x 16 block a workgroup covers the product: the rows' sums are formed
+  // again for every 16 features.  8 blocks of a float32 model, LayerNorm inside all products
+  // against in launches of its own: width 128, 64 tokens 330 / 421 us, 512 tokens 482 / 486;
+  // width 512, 64 tokens 522 / 541, but 256 tokens (1536 - 2048 such blocks) 793 / 767 and
+  // 1024 tokens 2391 / 2311)
+  const bool takes = dtype == TRACK_DTYPE_F32 && K <= SF_LN_K && M > 0 && N > 0 && ldo >= N && N <= (1 << 30) && bias &&
+                     out && (epi == TRACK_EPI_BIAS || epi == TRACK_EPI_BIAS_GELU || epi == TRACK_EPI_BIAS_F32) &&
+                     (((uintptr_t)scale | (uintptr_t)shift) & 15) == 0;
+  const int t = takes ? f32_small_blocks(M, N, K, X, K, W, 1) : 0;
+  if (t != 1) {
     const track_status st = layernorm(dtype, M, (int)K, X, scale, shift, Y, s);
     if (st != TRACK_OK) return st;
     return linear(dtype, epi, M, N, K, Y, K, W, bias, gate, out, ldo, s);
   }
   ProfScope prof(TRACK_PROF_GEMM, s);
-  launch_f32(t, epi, X, K, (const float*)W, M, (int)N, (int)K, EpiArgs{bias, gate, out, ldo}, 1, true, scale, shift, s);
+  launch_f32(1, epi, X, K, (const float*)W, M, (int)N, (int)K, EpiArgs{bias, gate, out, ldo}, 1, true, scale, shift, s);
   TRACK_LAUNCH_CHECK();
   return TRACK_OK;
 }
