@@ -374,9 +374,9 @@ __global__ __launch_bounds__(512) void flash_attn_bf16_kernel(const bf16_t* __re
 
   auto tile = [&](int t, auto tail_tag, auto first_tag) {
     issue(t + 1);
-    att_tile<(decltype(tail_tag)::value > 0), QLOG2, decltype(tail_tag)::value ? decltype(tail_tag)::value : BKV / 16, false,
-             decltype(first_tag)::value>(smem, qf, ko, vo, st, t * BKV,
-                                                                                       Lk, scale_log2);
+    constexpr int NB = decltype(tail_tag)::value;
+    att_tile<(NB > 0), QLOG2, NB ? NB : BKV / 16, false, decltype(first_tag)::value>(smem, qf, ko, vo, st, t * BKV, Lk,
+                                                                                     scale_log2);
     ko ^= SLOT;
     vo ^= SLOT;
     att_wait_vmcnt<0>();
@@ -714,9 +714,9 @@ __global__ __launch_bounds__(512) void flash_attn_items_kernel(const bf16_t* __r
       const int i1 = 8 - (ntiles - 1 - t) * qper;  // the last tiles copy the next item's Q
       issue_q(it + G, max(0, i1 - qper), min(i1, 8));
     }
-    att_tile<(decltype(tail_tag)::value > 0), QLOG2, decltype(tail_tag)::value ? decltype(tail_tag)::value : BKV / 16, false,
-             decltype(first_tag)::value>(smem, qf, ko, vo, st, t * BKV,
-                                                                                       Lk, scale_log2);
+    constexpr int NB = decltype(tail_tag)::value;
+    att_tile<(NB > 0), QLOG2, NB ? NB : BKV / 16, false, decltype(first_tag)::value>(smem, qf, ko, vo, st, t * BKV, Lk,
+                                                                                     scale_log2);
     ko ^= SLOT;
     vo ^= SLOT;
     if (stores_behind) att_wait_vmcnt<NST>();
@@ -975,15 +975,14 @@ static track_status attention_f32(int B, int H, int head_dim, int64_t Lq, int64_
   const bool split = nqb * H * B < 4 * (int64_t)device_cus();
   const bool vec = ((ldq | ldk | ldv | ldo) & 3) == 0 &&
                    (((uintptr_t)q | (uintptr_t)k | (uintptr_t)v | (uintptr_t)out | (uintptr_t)q_gain) & 15) == 0;
+  if (vrows && !vec) return fail(TRACK_E_INVALID, "attention_f32_vrows: needs 16-byte aligned rows");
   dim3 grid((unsigned)(split ? nqb : (nqb + 3) / 4), H, B);
 #define TRACK_ATT_F32_K(DH, KS, VEC, VR) \
   attn_f32_kernel<DH, KS, VEC, VR><<<grid, 256, 0, s>>>(q, ldq, k, ldk, v, ldv, out, ldo, H, Lq, Lk, scale_log2, q_gain)
-#define TRACK_ATT_F32(DH)                                     \
-  do {                                                        \
-    if (vrows && split && vec) TRACK_ATT_F32_K(DH, 4, true, true); \
-    else if (vrows && split) TRACK_ATT_F32_K(DH, 4, false, true);  \
-    else if (vrows && vec) TRACK_ATT_F32_K(DH, 1, true, true);     \
-    else if (vrows) TRACK_ATT_F32_K(DH, 1, false, true);           \
+#define TRACK_ATT_F32(DH)                                          \
+  do {                                                             \
+    if (vrows && split) TRACK_ATT_F32_K(DH, 4, true, true);        \
+    else if (vrows) TRACK_ATT_F32_K(DH, 1, true, true);            \
     else if (split && vec) TRACK_ATT_F32_K(DH, 4, true, false);    \
     else if (split) TRACK_ATT_F32_K(DH, 4, false, false);          \
     else if (vec) TRACK_ATT_F32_K(DH, 1, true, false);             \

@@ -658,10 +658,10 @@ track_status zero_cols_bf16(void* p, int64_t rows, int64_t ld, int64_t c0, int64
 
 // ------------------------------------------------------------------ V transpose
 // Tile of 64 keys x 32 channels through LDS; coalesced on both sides.
-template <typename T>
-__global__ __launch_bounds__(256) void v_transpose_kernel(int H, int dh, int64_t Lk, const T* __restrict__ src,
-                                                          int64_t ld, int64_t col0, T* __restrict__ vt, int64_t ldv) {
-  __shared__ T tile[64][33];
+__global__ __launch_bounds__(256) void v_transpose_kernel(int H, int dh, int64_t Lk, const bf16_t* __restrict__ src,
+                                                          int64_t ld, int64_t col0, bf16_t* __restrict__ vt,
+                                                          int64_t ldv) {
+  __shared__ bf16_t tile[64][33];
   const int64_t key0 = (int64_t)blockIdx.x * 64;
   const int cblocks = dh / 32;
   const int h = blockIdx.y / cblocks;
@@ -672,7 +672,7 @@ __global__ __launch_bounds__(256) void v_transpose_kernel(int H, int dh, int64_t
   for (int i = tid; i < 64 * 32; i += 256) {
     const int kr = i / 32, cc = i % 32;
     const int64_t key = key0 + kr;
-    T v = T(0);
+    bf16_t v = 0;
     if (key < Lk) v = src[((int64_t)b * Lk + key) * ld + col0 + (int64_t)h * dh + c0 + cc];
     tile[kr][cc] = v;
   }
@@ -684,15 +684,12 @@ __global__ __launch_bounds__(256) void v_transpose_kernel(int H, int dh, int64_t
   }
 }
 
-track_status v_transpose(int dtype, int B, int H, int head_dim, int64_t Lk, const void* src, int64_t ld, int64_t col0,
-                         void* vt, int64_t ldv, hipStream_t s) {
+track_status v_transpose(int B, int H, int head_dim, int64_t Lk, const bf16_t* src, int64_t ld, int64_t col0, bf16_t* vt,
+                         int64_t ldv, hipStream_t s) {
   if (head_dim % 32) return fail(TRACK_E_UNSUPPORTED, "v_transpose: head_dim %% 32 != 0");
   if (ldv < Lk) return fail(TRACK_E_SHAPE, "v_transpose: ldv < Lk");
   dim3 grid(cdiv(ldv, 64), H * (head_dim / 32), B);
-  if (dtype == TRACK_DTYPE_BF16)
-    v_transpose_kernel<bf16_t><<<grid, 256, 0, s>>>(H, head_dim, Lk, (const bf16_t*)src, ld, col0, (bf16_t*)vt, ldv);
-  else
-    v_transpose_kernel<float><<<grid, 256, 0, s>>>(H, head_dim, Lk, (const float*)src, ld, col0, (float*)vt, ldv);
+  v_transpose_kernel<<<grid, 256, 0, s>>>(H, head_dim, Lk, src, ld, col0, vt, ldv);
   TRACK_LAUNCH_CHECK();
   return TRACK_OK;
 }

@@ -14,13 +14,14 @@ namespace track {
 // gemm.hip
 track_status linear(int dtype, int epi, int64_t M, int64_t N, int64_t K, const void* A, int64_t lda, const void* W,
                     const void* bias, const float* gate, void* out, int64_t ldo, hipStream_t s);
-// `nb` products over one A: W, bias and out advance by wstride, wstride_b and
-// ostride elements from one to the next (bias epilogue only).
+// `nb` products over one A: W and bias advance by wstride elements, out by ostride,
+// from one to the next (bias epilogue only).
 track_status linear_batch(int dtype, int nb, int64_t M, int64_t N, int64_t K, const void* A, int64_t lda, const void* W,
                           const void* bias, int64_t wstride, void* out, int64_t ldo, int64_t ostride, hipStream_t s);
 // linear() on the modulated LayerNorm of float32 rows X [M, K] (scale and shift
 // both null: plain LayerNorm).  One launch where the float32 kernel that holds its
-// rows applies; otherwise layernorm() into Y, then linear().
+// rows applies (few rows, an epilogue without a residual); otherwise layernorm() into
+// Y, then linear().
 track_status layernorm_linear(int dtype, int epi, int64_t M, int64_t N, int64_t K, const float* X, const float* scale,
                               const float* shift, void* Y, const void* W, const void* bias, const float* gate,
                               void* out, int64_t ldo, hipStream_t s);
@@ -40,7 +41,7 @@ track_status attention(int dtype, int B, int H, int head_dim, int64_t Lq, int64_
                        const void* k, int64_t ldk, const void* vt, int64_t ldv, void* out, int64_t ldo,
                        hipStream_t s, int prof_kind, bool q_log2 = false);
 // attention() in float32 with V in rows of stride ldv (key j of head h at
-// v[(b Lk + j) ldv + h head_dim]) in place of V^T.  With q_gain [H head_dim] the
+// v[(b Lk + j) ldv + h head_dim]) in place of V^T, all rows 16-byte aligned.  With q_gain [H head_dim] the
 // rows of q are RMS-normalised and multiplied by it first.
 track_status attention_f32_vrows(int B, int H, int head_dim, int64_t Lq, int64_t Lk, const float* q, int64_t ldq,
                                  const float* k, int64_t ldk, const float* v, int64_t ldv, float* out, int64_t ldo,
@@ -76,9 +77,9 @@ track_status layernorm(int dtype, int64_t rows, int d, const float* x, const flo
 track_status rmsnorm_rope(int dtype, int64_t rows, int heads, int head_dim, void* buf, int64_t ld, int64_t col0,
                           const void* g, const void* g2, const float* cos_t, const float* sin_t, Grid3 grid, int64_t L,
                           hipStream_t s, float qscale = 1.0f, int64_t gain_rows = 0, int64_t gain_stride = 0);
-// vt[(b*H + h)*head_dim + c][key] = src[(b*Lk + key)*ld + col0 + h*head_dim + c]; zeros for Lk <= key < ldv
-track_status v_transpose(int dtype, int B, int H, int head_dim, int64_t Lk, const void* src, int64_t ld, int64_t col0,
-                         void* vt, int64_t ldv, hipStream_t s);
+// vt[(b*H + h)*head_dim + c][key] = src[(b*Lk + key)*ld + col0 + h*head_dim + c] (bfloat16); zeros for Lk <= key < ldv
+track_status v_transpose(int B, int H, int head_dim, int64_t Lk, const bf16_t* src, int64_t ld, int64_t col0, bf16_t* vt,
+                         int64_t ldv, hipStream_t s);
 // Step kernels (see track_op_step).
 int64_t step_partial_count(int64_t n);
 track_status step(int64_t n, int B, float w, float dsigma, const float* vel_L, const float* vel_S, float* x,

@@ -225,7 +225,7 @@ track_status prepare(const Model& m, const track_latent_shape& s, int B, const v
                    w.grid, Lc, st, 1.0f, B * Lc, stride));
   if (dt == TRACK_DTYPE_BF16) {
     ProfScope prof(TRACK_PROF_NORM, st);
-    TRY(v_transpose(dt, c.blocks * B, (int)H, (int)dh, Lc, kvc, 2 * d, d, wsp<void>(m, w.vct), w.Lcpad, st));
+    TRY(v_transpose(c.blocks * B, (int)H, (int)dh, Lc, (const bf16_t*)kvc, 2 * d, d, wsp<bf16_t>(m, w.vct), w.Lcpad, st));
   }
   return TRACK_OK;
 }
@@ -299,7 +299,7 @@ track_status forward(const Model& m, const track_latent_shape& s, int B, const f
                            nullptr, QKV, 3 * d, st));
       if (dt == TRACK_DTYPE_BF16) {
         ProfScope prof(TRACK_PROF_NORM, st);
-        TRY(v_transpose(dt, B, (int)H, (int)dh, L, QKV, 3 * d, 2 * d, Vt, w.Lpad, st));
+        TRY(v_transpose(B, (int)H, (int)dh, L, (const bf16_t*)QKV, 3 * d, 2 * d, (bf16_t*)Vt, w.Lpad, st));
       }
     }
     // q and k of each row in one pass
