@@ -487,7 +487,7 @@ class BoardSampler:
 
 def sustained_mfma(launches=24, iters=250000):
     """The sustained matrix-core rate on this board right after the timed steps: the library's MFMA stream
-    (independent 32x32x16 bf16 chains on every CU, no memory traffic) on N(0,1) bf16 operands, back to
+    (independent 16x16x32 bf16 chains on every CU, no memory traffic) on N(0,1) bf16 operands, back to
     back for about 1.7 s.  The clock under matrix work follows the operand bits, not only the power
     limit, so this is the ceiling an MFMA-bound kernel of this data can reach here; `peak` stays the
     published 2.5 PFLOP/s."""

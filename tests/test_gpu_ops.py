@@ -801,7 +801,7 @@ def test_mfma_stream_kernel():
     flop = track.mfma_stream(ops, 20000, sink)
     e1.record()
     torch.cuda.synchronize()
-    assert flop == cus * 4 * 20000 * 8 * 32768
+    assert flop == cus * 4 * 20000 * 16 * 16384
     assert bool((sink == 7.0).all())
     tflops = flop / e0.elapsed_time(e1) / 1e9
     print(f"mfma_stream: {tflops:.0f} TFLOP/s on {cus} CUs")
