@@ -50,7 +50,7 @@ WORKLOADS = {
 # --pmc FETCH_SIZE and WRITE_SIZE runs, each scaled by the factor the same
 # counter shows for the library's 1 GiB copy stream (2.0 and 1.0).  It
 # describes the kernel source it was measured on; any other source gives null.
-_ATTN_SRC = "6a09a230978a881e12704092fb2e949806a07af82f214e37c933d95451411488"
+_ATTN_SRC = "3faf39eaf08a8839ee4f70935c8ba0e3062004095520e68d5d8fa847bf33d603"
 ATTN_TRAFFIC = {"large": {"source_sha256": _ATTN_SRC, "bytes": 1.2096e10},
                 "small": {"source_sha256": _ATTN_SRC, "bytes": 3.6240e9}}
 

@@ -389,8 +389,10 @@ class SideStream {
 
 // Activations (rows times width) up to which the two models of a calibration step run
 // side by side: alone, their kernels are a chain of latencies that leaves most of the chip
-// idle (four samples of eight guided steps, 4 + 2 blocks: 64 tokens of width 128 10.05 ->
-// 9.70 ms, bound by the launches; 196 of width 512 27.4 -> 21.2).
+// idle.  One sample of eight guided steps, 4 + 2 blocks, in order and side by side: float32
+// width 128, 256 tokens 3.06 / 2.61 ms, 2048 tokens 15.5 / 11.8; width 512, 16 tokens 3.39 /
+// 2.72, 512 tokens 12.0 / 10.7; bfloat16 width 1536, 64 tokens 7.12 / 5.43.  No size up to 2^22
+// was found at which it loses; the line is a cautious one.
 constexpr int64_t SIDE_MAX = (int64_t)1 << 19;
 }  // namespace
 

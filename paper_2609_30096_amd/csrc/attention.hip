@@ -18,16 +18,20 @@
 // softmax denominators are sums of those same bf16 probabilities, formed on the
 // matrix cores too: one more MFMA per 32 keys with ones as "A".
 //
-// What bounds it is the board's power: a first form with 32x32x16 MFMAs took the same
-// time in 20% fewer cycles at a clock that much lower (1.48 against 1.81 GHz under the
-// counters), so the shape that moves fewer accumulator bytes gains once its cycles come
-// down.  That took a loop body of one tile without a second exit (the masked last tile
-// is a template instance, ring slots switch by an XOR), so that the accumulators are
-// updated in place: 167 - 181 registers and no spills, where two unrolled tiles took 250
-// and the short-key kernel spilled; and fragments read one by one ATT_LA = 3 ahead of
-// their MFMAs (2: up to 7% slower, 5: 2%, 7: 1%).  Both forms in one process: 2 x 12 heads
-// 32760 x 32760 9921 -> 9472 us (1392 TFLOP/s), 40 heads 3000 x 3000 164.4 -> 160.3, 2 x 12
-// heads 32760 x 512 220.1 -> 211.9, 3 heads 5000 x 5000 (4 key shares) 72.1 -> 65.2.
+// What bounds it: the matrix pipe is busy 68% of the cycles (12 heads, 16384 x 16384:
+// 1.711e9 of 1024 SIMDs x 2.44e6), the softmax between the two products takes most of the
+// rest, and the clock under this work is 1.95 - 2.0 GHz of 2.4 (1310 - 1350 W of 1400).
+// A first form with 32x32x16 MFMAs took 9% fewer cycles at a clock that was lower by as
+// much or more (1.48 against 1.61 GHz under the counters): the 16x16x32 shape moves half
+// the accumulator bytes per FLOP, so it gains where its cycles can be kept down.  That
+// took a loop body of one tile without a second exit (the masked last tile is a template
+// instance, ring slots switch by an XOR), so that the accumulators are updated in place:
+// 153 - 189 registers and no VGPR spilled (the item loop's TAIL 4 instances keep 7 SGPRs in
+// vector lanes), where two unrolled tiles took 250 and the short-key kernel spilled; and
+// fragments read one by one ATT_LA = 3 ahead of their MFMAs (2: up to 7% slower, 5: 2%,
+// 7: 1%).  Both forms in turn on seven cards, 2 x 12 heads 32760 x 32760: 0.98, 1.01, 1.01,
+// 1.03, 1.04, 1.05 and 1.05 times as fast (9.83 - 10.32 ms, 1280 - 1342 TFLOP/s); one card,
+// 40 heads 8190 x 8190 1101 -> 1063 us, 2 x 12 heads 3000 x 3000 145.0 -> 143.8.
 // Measured and left out: 48 queries a wave, or 12 waves of 32 (2 - 3% faster in whole
 // rounds of whole tiles, slower wherever 384-query blocks leave a round part empty).
 #include <math.h>

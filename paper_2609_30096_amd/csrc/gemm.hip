@@ -258,13 +258,15 @@ __global__ __launch_bounds__(256) void gemm_bf16_kernel(const bf16_t* __restrict
 // row, which the load path coalesces better than a 16-byte permutation (3% slower).
 //
 // The 16x16x32 shape moves half the accumulator bytes of 32x32x16 per FLOP, and
-// the chip's clock under matrix work is set by its power: a stream of it holds
-// 2040-2060 TFLOP/s on N(0,1) operands where 32x32x16 holds 1830, and this
-// kernel ran 7-9% faster with it at every Wan projection (14B q/k 5.02 -> 4.57
-// ms, 1378 -> 1505 TFLOP/s; 1.3B q/k 0.541 -> 0.493).  What bounds it now
-// (s_memtime copy, 14B q/k): 2470 of the 2048 cycles per slab the MFMAs need,
-// 140 of the excess the copies' issue waiting on L2 misses, 10 k cycles of
-// output stores per tile (220 k).
+// the chip's clock under matrix work follows that: a stream of it
+// (mfma_stream_kernel) holds 1950-1995 TFLOP/s on N(0,1) operands where 32x32x16
+// holds 1720-1835, and this kernel ran 6-9% faster with it at every Wan projection
+// (14B FFN1 6994 -> 6468 us, 1.3B O 393 -> 371; on another card q/k 5.02 -> 4.57
+// ms, 1378 -> 1505 TFLOP/s).  What bounds it now (s_memtime copy, 14B q/k): 2470 of
+// the 2048 cycles per slab the MFMAs need, 140 of the excess the copies' issue
+// waiting on L2 misses, 10 k cycles of output stores per tile (220 k).  The
+// accumulators fill the 256 AGPRs; 3-4 VGPRs (10 in the transposed form) are
+// spilled, and reloaded once a tile, outside the slab loop.
 __device__ __forceinline__ int lds_swz16(int row) { return ((row & 7) ^ ((row >> 3) & 1)) & ~1; }
 
 typedef __attribute__((address_space(3))) void* lds_ptr_t;
@@ -1136,10 +1138,11 @@ static void launch_bf16(int tile, int epi, const bf16_t* A, int64_t lda, const b
 }
 
 // Blocks a side of the K-sharing kernel's workgroup: one until the 16 x 16 blocks fill
-// the chip four times over, then two, which is the faster one at any size (1000 x 1536 x
-// 512 30 us against 74 of the LDS-tiled kernel, 3120 x 1536 x 512 84 / 126, 2048 x 2048 x 2048
-// 271 / 396, 3120 x 4608 x 1536 749 / 900).  0: the LDS-tiled kernel, for rows that are not
-// 16-byte aligned, or more of them than the grid's second dimension counts.
+// the chip four times over, then two, which was the faster one at all of 15 shapes up to
+// 2e12 FLOP (1000 x 1536 x 512 30 us against 74 of the LDS-tiled kernel, 3120 x 4608 x 1536
+// 756 / 896, 8192 x 8192 x 2048 4515 / 5132, 200000 x 64 x 512 248 / 334, 65520 x 1536 x 8960
+// 30.4 / 33.9 ms).  0: the LDS-tiled kernel, for rows that are not 16-byte aligned, or more
+// of them than the grid's second dimension counts.
 static int f32_small_blocks(int64_t M, int64_t N, int64_t K, const void* A, int64_t lda, const void* W, int64_t nb) {
   const int64_t t16 = ((M + 15) / 16) * ((N + 15) / 16) * nb, cus = device_cus();
   if (K % 4 || lda % 4 || (((uintptr_t)A | (uintptr_t)W) & 15) || (M + 31) / 32 > 65535) return 0;

@@ -163,13 +163,13 @@ def main():
     cases["mfma_stream_zeros"] = (lambda: track.mfma_stream(mf_zero, mf_iters, sink), mf_flop, None)
     if L == 32760:
         # band decomposition of the calibration difference on the 16 x 21 x 60 x 104
-        # latent (synchronous op: includes the 48-byte copy of the result)
+        # latent (synchronous op)
         bshape = synth.LatentShape(16, 21, 60, 104, Lc)
         bws = torch.empty(track.band_workspace_bytes(bshape), device=dev, dtype=torch.uint8)
-        # both passes read both models' branches; the row pass writes and the
-        # column pass reads the complex intermediate
+        # the temporal pass reads both models' branches and writes the guided
+        # difference, which the spatial pass reads
         cases["band_energy"] = (lambda: track.op_band_energy(bshape, B, 5.0, vel, velS, bws), None,
-                                2 * (2 * B * n_step * 4) + 2 * n_step * 8)
+                                2 * B * n_step * 4 + 2 * n_step * 4)
     # a mid-trajectory order-2 UniPC step (corrector with one history term,
     # predictor with one): reads x, x_last, two stored predictions and the
     # velocities, writes x, x_last and the new prediction

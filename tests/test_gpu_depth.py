@@ -9,8 +9,8 @@ the V projection writes V^T from its epilogue), and their guided velocity
 oracle on the same float32 latent.  Each case runs twice on the device: with
 the automatic kernel choice, and with every projection whose width the
 256-wide tiles divide forced onto the persistent GEMM kernel that the
-full-size step uses (at 512 rows the automatic choice takes the
-register-staged kernel).
+full-size step uses (at 512 rows the automatic choice takes
+one-tile-per-workgroup kernels).
 
 The oracle evaluates the network block by block through ``oracle.dit``,
 with each block's parameters regenerated from the seeded recipe just before
