@@ -688,9 +688,13 @@ track_status v_transpose(int B, int H, int head_dim, int64_t Lk, const bf16_t* s
                          int64_t ldv, hipStream_t s) {
   if (head_dim % 32) return fail(TRACK_E_UNSUPPORTED, "v_transpose: head_dim %% 32 != 0");
   if (ldv < Lk) return fail(TRACK_E_SHAPE, "v_transpose: ldv < Lk");
-  dim3 grid(cdiv(ldv, 64), H * (head_dim / 32), B);
-  v_transpose_kernel<<<grid, 256, 0, s>>>(H, head_dim, Lk, src, ld, col0, vt, ldv);
-  TRACK_LAUNCH_CHECK();
+  constexpr int ZMAX = 65535;  // (the text values of all blocks at once can be more)
+  for (int b = 0; b < B; b += ZMAX) {
+    dim3 grid(cdiv(ldv, 64), H * (head_dim / 32), B - b < ZMAX ? B - b : ZMAX);
+    v_transpose_kernel<<<grid, 256, 0, s>>>(H, head_dim, Lk, src + b * Lk * ld, ld, col0,
+                                            vt + (int64_t)b * H * head_dim * ldv, ldv);
+    TRACK_LAUNCH_CHECK();
+  }
   return TRACK_OK;
 }
 

@@ -72,6 +72,7 @@ hipError_t hipLaunchKernel(const void* fn, dim3_t g, dim3_t b, void** args, size
   for (int i = 0; i < g_nfns; ++i)
     if (g_fns[i].fn == fn) name = g_fns[i].name;
   say("launch", name, st);
+  if (g.x > 0x7fffffffu || g.y > 65535 || g.z > 65535 || (uint64_t)g.x * b.x > 0xffffffffu) return g_last = 9;
   return status("hipLaunchKernel");
 }
 hipError_t hipGetDevice(int* d) {

@@ -189,3 +189,16 @@ for name in (b"hipStreamSynchronize", b"hipLaunchKernel"):
     F.hipGetLastError()
     assert bands() == 0 and ops() == ["hostmalloc"]
 ''')
+
+
+def test_forward_of_very_many_blocks(fake):
+    """The text values of all blocks are transposed together: more blocks than a grid's third dimension holds (65535)
+    take more than one launch."""
+    run(fake, '''
+shape = synth.LatentShape(16, 1, 4, 4, 3)
+many = synth.DiTConfig(blocks=33000, dim=128, heads=1, head_dim=128, ffn_dim=64, text_dim=64, dtype=synth.BF16)
+m, _ = model(many, BASE + (5 << 32))
+st = L.track_dit_forward(m, ctypes.byref(track.shape_c(shape)), ctypes.c_void_p(BASE), 500.0, ctypes.c_void_p(BASE),
+                         ctypes.c_void_p(BASE), 2.0, ctypes.c_void_p(BASE), ctypes.c_void_p(0x77))
+assert st == 0, err()
+''')
