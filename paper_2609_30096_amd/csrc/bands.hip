@@ -38,6 +38,8 @@ constexpr int BAND_XLD = BAND_XCH + 4;  // LDS row stride: 4 mod 8 floats, so 16
 constexpr int BAND_MAX_W = 1024;  // twiddle table bound
 constexpr int BAND_MAX_H = 256;   // LDS bound of a staged chunk, and the accumulators of 16 row blocks
 constexpr int BAND_MAX_F = 64;    // temporal kernel LDS bound
+constexpr int BAND_MAX_DIVS = 32;  // divisors of a length up to 1024 (840 has 32, itself among them)
+constexpr int BAND_EXTRA = 2;      // first blocks of the temporal pass, which do the spatial axes' sums
 
 inline unsigned blocks_for(int64_t n, int64_t per) { return (unsigned)((n + per - 1) / per); }
 inline size_t align_256(size_t v) { return (v + 255) & ~(size_t)255; }
@@ -127,15 +129,20 @@ __device__ __forceinline__ float deviation(float2 t) {
 // by their mean |t|^2, which would be the largest error of the transforms (8e-9 to 3e-8 of
 // the energies over latents of 16 - 90 rows, 4e-10 to 8e-9 with it taken out, for 1 of the
 // pass' 52 us on the video latent).  One factor for a whole axis would do as well on
-// average, but put 1e-8 on the mean, whose entries are exact.  Frequency k takes the
+// average, but puts 1e-8 on the mean, whose entries are exact.  Frequency k takes the
 // multiples of g = gcd(k, n), each g times, so one sum per divisor of n serves all.
-__device__ __forceinline__ void freq_sums(float* __restrict__ dsum, float* __restrict__ dev, int n) {
+__device__ __forceinline__ void freq_sums(float* __restrict__ dsum, int n) {
+  __shared__ float dev[BAND_MAX_W];
+  __shared__ int divs[BAND_MAX_DIVS], ndivs;
+  if (threadIdx.x == 0) ndivs = 0;
   __syncthreads();
   for (int m = threadIdx.x; m < n; m += BAND_THREADS) dev[m] = deviation(twiddle(m, n));
+  for (int d = 1 + threadIdx.x; d <= n / 2; d += BAND_THREADS)
+    if (n % d == 0) divs[atomicAdd(&ndivs, 1)] = d;
   __syncthreads();
   const int lane = threadIdx.x & 63;
-  for (int d = 1 + (threadIdx.x >> 6); d <= n / 2; d += BAND_THREADS / 64) {
-    if (n % d) continue;
+  for (int i = threadIdx.x >> 6; i < ndivs; i += BAND_THREADS / 64) {
+    const int d = divs[i];
     float e = 0.0f;
     for (int m = lane * d; m < n; m += 64 * d) e += dev[m];
     e = (float)d * wave_sum(e);
@@ -230,6 +237,7 @@ __global__ __launch_bounds__(BAND_THREADS) void band_spatial_kernel(BandShape s,
   const uint32_t W = s.W, H = s.H;
   const int kw0 = (kg * 4 + wave) * 16, kw = kw0 + jq;
   const bool live = kw0 <= s.W / 2;  // wave-uniform
+  const float sumW = dsum[min(kw, s.W / 2)];
   f32x4 yr[HB], yi[HB];
 #pragma unroll
   for (int b = 0; b < HB; ++b) yr[b] = yi[b] = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
@@ -287,7 +295,7 @@ __global__ __launch_bounds__(BAND_THREADS) void band_spatial_kernel(BandShape s,
       }
     }
   }
-  const double norm = (kw == 0 || 2 * kw == s.W ? 1.0 : 2.0) * inv_sum(1.0 / s.W, dsum[min(kw, s.W / 2)]);
+  const double norm = (kw == 0 || 2 * kw == s.W ? 1.0 : 2.0) * inv_sum(1.0 / s.W, sumW);
   double acc[3] = {0.0, 0.0, 0.0};
   const double rH = 1.0 / s.H;
   for (int kh0 = 0; live && kh0 <= s.H / 2; kh0 += 16) {
@@ -320,12 +328,12 @@ __global__ __launch_bounds__(BAND_THREADS) void band_spatial_kernel(BandShape s,
   block_sum3(acc[0], acc[1], acc[2], part + 3 * (int64_t)blockIdx.x);
 }
 
-// The first block of the temporal pass forms the sums that the spatial pass divides by.
+// Block 0 of the temporal pass forms the sums of the rows' frequencies (W), block 1 those
+// of the columns' (H), which the spatial pass divides by.
 __device__ __forceinline__ void spatial_sums(const BandShape& s, float* __restrict__ dsum) {
-  __shared__ float dev[BAND_MAX_W];
   static_assert(BAND_MAX_H <= BAND_MAX_W, "one table's room");
-  freq_sums(dsum, dev, s.W);
-  freq_sums(dsum + s.W / 2 + 1, dev, s.H);
+  if (blockIdx.x == 0) freq_sums(dsum, s.W);
+  else freq_sums(dsum + s.W / 2 + 1, s.H);
 }
 
 // Temporal block (patch_t 1: a frame's series are contiguous): 64 series a wave,
@@ -337,7 +345,7 @@ __global__ __launch_bounds__(BAND_THREADS) void band_temporal_rows_kernel(BandSh
                                                                           f32x4* __restrict__ diff,
                                                                           float* __restrict__ dsum,
                                                                           double* __restrict__ part) {
-  if (blockIdx.x == 0) {
+  if (blockIdx.x < BAND_EXTRA) {
     spatial_sums(s, dsum);
     return;
   }
@@ -347,7 +355,7 @@ __global__ __launch_bounds__(BAND_THREADS) void band_temporal_rows_kernel(BandSh
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   const int jq = lane & 15, g = lane >> 4;
   const int64_t total = (int64_t)s.Hp * s.Wp * s.P;  // series, a multiple of 4
-  const int64_t i0 = ((int64_t)xcd_remap(blockIdx.x - 1, gridDim.x - 1) * 4 + wave) * 64 + 4 * jq;
+  const int64_t i0 = ((int64_t)xcd_remap(blockIdx.x - BAND_EXTRA, gridDim.x - BAND_EXTRA) * 4 + wave) * 64 + 4 * jq;
   const bool in = i0 < total;
   const int64_t base = in ? i0 : 0;
   const uint32_t F = s.F;
@@ -393,7 +401,7 @@ __global__ __launch_bounds__(BAND_THREADS) void band_temporal_rows_kernel(BandSh
       add_band(acc, axis_band(k, s.F), e * ((k == 0 || 2 * k == s.F ? 1.0 : 2.0) * inv_sum(rF, sumF[k])));
     }
   }
-  block_sum3(acc[0], acc[1], acc[2], part + 3 * (int64_t)(blockIdx.x - 1));
+  block_sum3(acc[0], acc[1], acc[2], part + 3 * (int64_t)(blockIdx.x - BAND_EXTRA));
 }
 
 // Temporal energies of the other layouts (patch_t > 1, or velocities that are not
@@ -404,7 +412,7 @@ __global__ __launch_bounds__(BAND_THREADS) void band_temporal_kernel(BandShape s
                                                                     const float* __restrict__ vS, int64_t n,
                                                                     float* __restrict__ dsum,
                                                                     double* __restrict__ part) {
-  if (blockIdx.x == 0) {
+  if (blockIdx.x < BAND_EXTRA) {
     spatial_sums(s, dsum);
     return;
   }
@@ -412,7 +420,7 @@ __global__ __launch_bounds__(BAND_THREADS) void band_temporal_kernel(BandShape s
   __shared__ float2 tw[BAND_MAX_F];
   __shared__ float dev[BAND_MAX_F], sumF[BAND_MAX_F];
   fill_temporal(tw, dev, sumF, s.F);
-  const int64_t i = (int64_t)(blockIdx.x - 1) * BAND_THREADS + threadIdx.x;
+  const int64_t i = (int64_t)(blockIdx.x - BAND_EXTRA) * BAND_THREADS + threadIdx.x;
   const int Q = s.C * s.ph * s.pw;
   const int64_t total = (int64_t)s.Hp * s.Wp * Q;
   const bool live = i < total;
@@ -448,7 +456,7 @@ __global__ __launch_bounds__(BAND_THREADS) void band_temporal_kernel(BandShape s
       acc[2] += b == 2 ? e : 0.0;
     }
   }
-  block_sum3(acc[0], acc[1], acc[2], part + 3 * (int64_t)(blockIdx.x - 1));
+  block_sum3(acc[0], acc[1], acc[2], part + 3 * (int64_t)(blockIdx.x - BAND_EXTRA));
 }
 
 // Sums the partials in a fixed order, one wave per quantity.  energy[0..2] spatial,
@@ -557,9 +565,9 @@ track_status band_scores(int C, int F, int H, int W, int pt, int ph, int pw, int
   const bool aligned = (((uintptr_t)vel_L | (uintptr_t)vel_S) & 15) == 0 && n % 4 == 0 && s.P % 4 == 0;
   f32x4* const diff = aligned && planar(s) ? (f32x4*)(base + L.diff) : nullptr;
   if (aligned && pt == 1)
-    band_temporal_rows_kernel<<<L.nt + 1, BAND_THREADS, 0, st>>>(s, B, w, vel_L, vel_S, n, diff, dsum, part_t);
+    band_temporal_rows_kernel<<<L.nt + BAND_EXTRA, BAND_THREADS, 0, st>>>(s, B, w, vel_L, vel_S, n, diff, dsum, part_t);
   else
-    band_temporal_kernel<<<L.nt + 1, BAND_THREADS, 0, st>>>(s, B, w, vel_L, vel_S, n, dsum, part_t);
+    band_temporal_kernel<<<L.nt + BAND_EXTRA, BAND_THREADS, 0, st>>>(s, B, w, vel_L, vel_S, n, dsum, part_t);
   TRACK_LAUNCH_CHECK();
 #define TRACK_BAND(HB) \
   band_spatial_kernel<HB><<<L.ns, BAND_THREADS, 0, st>>>(s, B, w, vel_L, vel_S, n, diff, dsum, L.kwg, part_s)

@@ -58,6 +58,7 @@ def test_band_energy_matches_oracle(C, F, H, W, patch, B):
     (1, 33, 98, 6, (1, 2, 2), 0),     # k_f beyond one block of 16, k_h beyond 48
     (1, 64, 256, 4, (1, 2, 2), 0),    # the largest F and H
     (1, 2, 2, 1024, (1, 2, 2), 0),    # the largest W
+    (1, 1, 2, 840, (1, 2, 2), 0),     # the W with the most divisors
     (3, 5, 17, 33, (1, 1, 1), 0),     # odd sizes, element-wise staging
     (4, 5, 12, 20, (1, 2, 2), 1),     # velocities that are not 16-byte aligned
 ])
