@@ -259,7 +259,7 @@ __global__ __launch_bounds__(256) void gemm_bf16_kernel(const bf16_t* __restrict
 //
 // The 16x16x32 shape moves half the accumulator bytes of 32x32x16 per FLOP, and
 // the chip's clock under matrix work follows that: a stream of it
-// (mfma_stream_kernel) holds 1950-1995 TFLOP/s on N(0,1) operands where 32x32x16
+// (mfma_stream_kernel) holds 1950-2020 TFLOP/s on N(0,1) operands where 32x32x16
 // holds 1720-1835, and this kernel ran 6-9% faster with it at every Wan projection
 // (14B FFN1 6994 -> 6468 us, 1.3B O 393 -> 371; on another card q/k 5.02 -> 4.57
 // ms, 1378 -> 1505 TFLOP/s).  What bounds it now (s_memtime copy, 14B q/k): 2470 of
